@@ -328,18 +328,18 @@ int lbrmt_kernel_time(lbrmt_ctx* ctx, const char* name, double* avg_ms, int64_t*
  *                         leaves HBM bandwidth to the reference-map chain
  *                         running beside it; 0: one workgroup per tile.
  *                         Results do not depend on it.
- *   LBRMT_OPT_FUSED_FIT   1024, 512 or 256: one solid on walled axes
- *                         with at most 11 layers fits all layers of the
- *                         extrapolation (Sec. 3.2) in one launch of blocks of
- *                         that many threads, each taking a tile of the window
+ *   LBRMT_OPT_FUSED_FIT   1024, 512 or 256: one solid with at most 11 layers
+ *                         (and periodic axes of at least 76 nodes) fits all
+ *                         layers of the extrapolation (Sec. 3.2) in one launch
+ *                         of blocks of that many threads (1024: 512, which
+ *                         leaves the registers), each taking a tile of the window
  *                         with the margin its later layers read; tiles whose
  *                         targets need wider scan windows than the margin
  *                         holds are finished by a second, one-block launch.
- *                         0: one launch per layer; 1: 1024 threads with the
+ *                         0: one launch per layer; 1: 512 threads with the
  *                         margin check one node tighter, so that the second
  *                         launch finishes most tiles (a check of that
- *                         launch); -1 (default): 512 in FP64 and 1024
- *                         in FP32, or 0 when LBRMT_OPT_BULK_BLOCKS caps
+ *                         launch); -1 (default): 512, or 0 when LBRMT_OPT_BULK_BLOCKS caps
  *                         the bulk update.  With
  *                         overlap and no cap, the bulk lattice update then
  *                         starts when the advection pass has finished, so

@@ -27,6 +27,7 @@
 // well-posedness test (exact sums of powers of two on a few nodes), and the
 // inversion of grad xi where det < kappa_J.
 #include "lb_node.h"
+#include "fit_window.h"
 
 namespace lbrmt {
 
@@ -721,114 +722,6 @@ hipError_t launch_layers(const GridP& g, const BandBufs& bb, int wslot, hipStrea
 
 // ---------------------------------------------------------------- extrapolation
 
-__device__ __forceinline__ double det3(double a00, double a01, double a02, double a10,
-                                       double a11, double a12, double a20, double a21,
-                                       double a22)
-{
-    return a00 * (a11 * a22 - a12 * a21) - a01 * (a10 * a22 - a12 * a20) +
-           a02 * (a10 * a21 - a11 * a20);
-}
-
-// Weighted least-squares fit of Sec. 3.2 step (ii) in coordinates centred at
-// the target.  The normal matrix and its well-posedness test are kept in
-// double (sums of w dx dy with w a power of two, or the normal weight of the
-// first two layers); the right-hand sides are accumulated in the storage
-// precision C of the reference map.  MT = float is exact where the weights
-// are the powers of two alone and r <= FIT_EXACT_R: every term w a b (w =
-// 2^-(|a|+|b|) >= 2^-16, |a|, |b| <= 8) is a multiple of 2^-16, and every
-// partial sum of them stays below 2^6 in magnitude, so 22 bits hold it: the
-// float sums equal the double ones bit for bit, at half the cost.
-constexpr int FIT_EXACT_R = 8;
-// layers from 3 on weigh by powers of two alone: their sums can run in float
-__host__ __device__ __forceinline__ bool float_sums(const GridP& g, int l)
-{
-    return l >= 3 && g.r_max <= FIT_EXACT_R;
-}
-template <typename C, typename MT = double>
-struct Fit {
-    MT M00, M01, M02, M11, M12, M22;
-    C bX0, bX1, bX2, bY0, bY1, bY2;
-    __device__ __forceinline__ void zero()
-    {
-        M00 = M01 = M02 = M11 = M12 = M22 = MT(0);
-        bX0 = bX1 = bX2 = bY0 = bY1 = bY2 = C(0);
-    }
-    // one valid node at offset (a, b) from the target, weight of Eq. (3_2_extrap_weight)
-    __device__ __forceinline__ void add(int a, int b, bool use_n, double nxh, double nyh, C xv,
-                                        C yv)
-    {
-        double wt = ldexp(1.0, -(abs(a) + abs(b)));
-        if (use_n) {
-            const double ddx = -(double)a, ddy = -(double)b;  // d = x_target - x_valid
-            const double dn = (ddx * nxh + ddy * nyh) / sqrt(ddx * ddx + ddy * ddy);
-            wt = dn * wt > 0.0 ? dn * wt : 0.0;
-        }
-        const MT w = MT(wt), dx = MT(a), dy = MT(b);
-        M00 += w * dx * dx;
-        M01 += w * dx * dy;
-        M02 += w * dx;
-        M11 += w * dy * dy;
-        M12 += w * dy;
-        M22 += w;
-        const C wc = C(wt), cx = C(a), cy = C(b);
-        bX0 += wc * cx * xv;
-        bX1 += wc * cy * xv;
-        bX2 += wc * xv;
-        bY0 += wc * cx * yv;
-        bY1 += wc * cy * yv;
-        bY2 += wc * yv;
-    }
-    // add() for a node that may not be valid (v false: every sum gets a
-    // signed zero, which leaves its bits as skipping the node does, since no
-    // sum that starts at +0 ever holds -0)
-    __device__ __forceinline__ void add_if(bool v, int a, int b, bool use_n, double nxh,
-                                           double nyh, C xv, C yv)
-    {
-        double wt = v ? ldexp(1.0, -(abs(a) + abs(b))) : 0.0;
-        if (use_n) {
-            const double ddx = -(double)a, ddy = -(double)b;
-            // (a valid node is never the target itself, so d2 > 0 for it)
-            const double d2 = ddx * ddx + ddy * ddy;
-            const double dn = (ddx * nxh + ddy * nyh) / sqrt(d2 > 0.0 ? d2 : 1.0);
-            wt = dn * wt > 0.0 ? dn * wt : 0.0;
-        }
-        const MT w = MT(wt), dx = MT(a), dy = MT(b);
-        M00 += w * dx * dx;
-        M01 += w * dx * dy;
-        M02 += w * dx;
-        M11 += w * dy * dy;
-        M12 += w * dy;
-        M22 += w;
-        const C wc = C(wt), cx = C(a), cy = C(b);
-        const C xs = v ? xv : C(0), ys = v ? yv : C(0);
-        bX0 += wc * cx * xs;
-        bX1 += wc * cy * xs;
-        bX2 += wc * xs;
-        bY0 += wc * cx * ys;
-        bY1 += wc * cy * ys;
-        bY2 += wc * ys;
-    }
-    // intercept of the weighted linear fit, if well posed
-    __device__ __forceinline__ bool solve(double det_rel, C& x, C& y) const
-    {
-        const double m00 = M00, m01 = M01, m02 = M02, m11 = M11, m12 = M12, m22 = M22;
-        const double det = det3(m00, m01, m02, m01, m11, m12, m02, m12, m22);
-        if (!(det > det_rel * m22 * m22 * m22)) return false;
-        if (sizeof(C) == 8) {
-            x = C(det3(m00, m01, bX0, m01, m11, bX1, m02, m12, bX2) / det);
-            y = C(det3(m00, m01, bY0, m01, m11, bY1, m02, m12, bY2) / det);
-        } else {
-            // Cramer in float: the cofactors of the third column weigh the
-            // right-hand sides
-            const C c0 = C(m01 * m12 - m11 * m02), c1 = C(m01 * m02 - m00 * m12);
-            const C c2 = C(m00 * m11 - m01 * m01), id = C(1.0 / det);
-            x = (c0 * bX0 + c1 * bX1 + c2 * bX2) * id;
-            y = (c0 * bY0 + c1 * bY1 + c2 * bY2) * id;
-        }
-        return true;
-    }
-};
-
 // outward normal of phi^n at a target from its four neighbours (e, w, n, s),
 // used by the weights of layers 1 and 2
 __device__ __forceinline__ bool normal_from(double pe, double pw, double pn, double ps,
@@ -844,51 +737,18 @@ __device__ __forceinline__ bool normal_from(double pe, double pw, double pn, dou
     return true;
 }
 
-// a lane's partner value by a DPP move within its row (no LDS round trip;
-// 64-bit values move as two halves)
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int v)
-{
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(dpp_move<CTRL>(__float_as_int(v)));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v)
-{
-    return __hiloint2double(dpp_move<CTRL>(__double2hiint(v)), dpp_move<CTRL>(__double2loint(v)));
-}
-
-// sum over the FIT_LANES = 8 lanes of a group (8 aligned lanes, all active
-// together): lane i adds lane i ^ 1 (quad_perm 1,0,3,2), then lane i ^ 2
-// (quad_perm 2,3,0,1), then the other quad's sum from lane 7 - i (row half
-// mirror).  Every lane ends with the same bits, since each addition sees the
-// same two operands in either order.
-static_assert(FIT_LANES == 8, "group_sum pairs the lanes of an 8-lane group");
-template <typename V>
-__device__ __forceinline__ V group_sum(V v)
-{
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    return v;
-}
-
 // Sums of the normal equations over the nodes of the scan window of
 // half-width r (side 2r + 1, nodes q = 0 .. side^2 - 1 row by row) that fall
 // to this lane: node q goes to lane q mod FIT_LANES; each lane issues the
 // loads of PER nodes before adding them.  The offsets (a, b) of node q are
 // stepped along instead of divided out.
-template <typename T, typename MT>
+template <typename T>
 __device__ __forceinline__ void fit_window(const GridP& g, const Rect& W, int l, int i, int j,
                                            int kt, int r, int sub, bool use_n, double nxh,
                                            double nyh, const int8_t* tag, const T* X1,
-                                           const T* Y1, Fit<T, MT>& f, int& count)
+                                           const T* Y1, Fit<T>& f, int& count)
 {
-    constexpr int PER = 4;  // window nodes per lane and pass: 25 of r = 2 in one pass
+    constexpr int PER = 4;
     const int side = 2 * r + 1, nq = side * side;
     // offsets of this lane's first node
     int a = sub % side - r, b = sub / side - r;
@@ -926,85 +786,46 @@ __device__ __forceinline__ void fit_window(const GridP& g, const Rect& W, int l,
     }
 }
 
-// the group's sums reduced across its lanes, then the intercept, if the
-// window held three valid nodes and the fit is well posed
-template <typename T, typename MT>
-__device__ __forceinline__ bool fit_finish(const GridP& g, Fit<T, MT>& f, int count, T& xo,
-                                           T& yo)
+// scan window of half-width 2 around target kt = (i, j) read from the maps
+// (lane sub of an 8-lane group)
+template <typename T, bool N>
+__device__ __forceinline__ bool fit2_global(const GridP& g, const Rect& W,
+                                            int l, int i, int j, int kt, int sub, bool use_n,
+                                            double nxh, double nyh, const int8_t* tag,
+                                            const T* X1, const T* Y1, T& xo, T& yo)
 {
-    count = group_sum(count);
-    if (count < 3) return false;
-    f.M00 = group_sum(f.M00);
-    f.M01 = group_sum(f.M01);
-    f.M02 = group_sum(f.M02);
-    f.M11 = group_sum(f.M11);
-    f.M12 = group_sum(f.M12);
-    f.M22 = group_sum(f.M22);
-    f.bX0 = group_sum(f.bX0);
-    f.bX1 = group_sum(f.bX1);
-    f.bX2 = group_sum(f.bX2);
-    f.bY0 = group_sum(f.bY0);
-    f.bY1 = group_sum(f.bY1);
-    f.bY2 = group_sum(f.bY2);
-    return f.solve(g.det_rel, xo, yo);
-}
-
-// scan window of half-width r = side / 2: reduced normal equations and the
-// intercept, if the window holds three valid nodes and the fit is well posed
-template <typename T, typename MT>
-__device__ __forceinline__ bool fit_at(const GridP& g, const Rect& W, int l, int i, int j, int kt,
-                                       int r, int sub, bool use_n, double nxh, double nyh,
-                                       const int8_t* tag, const T* X1, const T* Y1, T& xo, T& yo)
-{
-    int count = 0;
-    Fit<T, MT> f;
-    f.zero();
-    fit_window<T, MT>(g, W, l, i, j, kt, r, sub, use_n, nxh, nyh, tag, X1, Y1, f, count);
-    return fit_finish<T, MT>(g, f, count, xo, yo);
-}
-
-// fit_window over the block's staged copy of the zone (tags st, values sx,
-// sy on a row-major region of rw columns; (li, lj) the target's place in it)
-// for the window of half-width 2 (side 5, 25 nodes), the only one the copy is
-// searched with: the same nodes in the same lanes and the same order of
-// additions as fit_window (lane sub takes nodes sub + 8 u, u = 0 .. 3, below
-// 25), every slot added through add_if, so the same bits without a branch
-// per node
-template <typename T, typename MT>
-__device__ __forceinline__ void fit_window_lds_r2(int l, int li, int lj, int sub, bool use_n,
-                                                  double nxh, double nyh, const int8_t* st,
-                                                  const T* sx, const T* sy, int rw,
-                                                  Fit<T, MT>& f, int& count)
-{
-    constexpr int PER = 4, SIDE = 5, NQ = SIDE * SIDE;
-    static_assert(PER * FIT_LANES >= NQ && (PER - 1) * FIT_LANES < NQ,
-                  "one pass of PER nodes per lane covers the window");
-    const int base = lj * rw + li;
-    int tk[PER];
-    T xv[PER], yv[PER];
+    using C2 = Win2<T, 1>;
+    bool v[C2::NS];
+    T xs[C2::NS], ys[C2::NS];
+    int tk[C2::NS];
 #pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int q = sub + u * FIT_LANES;
-        // (a slot past the window reads the target's own place, never used)
-        const int k = q < NQ ? base + (q / SIDE - 2) * rw + q % SIDE - 2 : base;
-        tk[u] = st[k];
-        xv[u] = sx[k];
-        yv[u] = sy[k];
+    for (int u = 0; u < C2::NS; u++) {
+        int ci = i + C2::off_a(sub, u), cj = j + C2::off_b(sub, u);
+        v[u] = C2::in(sub, u) && canon(g, ci, cj) && W.has(ci, cj);
+        const long long k = v[u] ? pidx(g, ci, cj) : kt;
+        tk[u] = tag[k];
+        xs[u] = X1[k];
+        ys[u] = Y1[k];
     }
 #pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int q = sub + u * FIT_LANES;
-        const bool v = q < NQ && tag_valid_before(tk[u], l);
-        count += v ? 1 : 0;
-        f.add_if(v, q % SIDE - 2, q / SIDE - 2, use_n, nxh, nyh, xv[u], yv[u]);
+    for (int u = 0; u < C2::NS; u++) {
+        v[u] = v[u] && tag_valid_before(tk[u], l);
+        xs[u] = v[u] ? xs[u] : T(0);
+        ys[u] = v[u] ? ys[u] : T(0);
     }
+    const unsigned mask = C2::mask_of(sub, v);
+    if (N && use_n) {
+        typename C2::NW w;
+        if (!C2::weights_n(sub, __popc(mask), v, nxh, nyh, g.det_rel, w)) return false;
+        C2::value_n(sub, w, xs, ys, xo, yo);
+    } else {
+        const Geo2 G = geo2(mask, g.det_rel);
+        if (!G.ok) return false;
+        C2::value(sub, G, xs, ys, xo, yo);
+    }
+    return true;
 }
 
-// Fit of one target kt = (i, j) of layer l by the FIT_LANES lanes of a group
-// (every lane of the group calls it with the same target): the outward normal
-// of phi^n for layers 1 and 2, then scan windows of half-width r = 2 .. r_max
-// until one holds three valid nodes and a well-posed fit.  Windows wider than
-// rlim are not tried: if the fit needs one, the result is false with cut set.
 // outward normal of phi^n at target (i, j) for the weights of layers 1 and 2:
 // lanes 0..3 of the group load the four neighbours
 template <typename T>
@@ -1026,48 +847,29 @@ __device__ __forceinline__ bool target_normal(const GridP& g, const Rect& D, int
     return normal_from(pe, pw, pn, ps, nxh, nyh);
 }
 
-template <typename T, typename MT>
-__device__ __forceinline__ bool fit_target(const GridP& g, const Rect& W, const Rect& D, int l,
-                                           int kt, int i, int j, int sub, int rlim,
-                                           const int8_t* tag, const T* __restrict__ phin,
-                                           const T* X1, const T* Y1, T& xo, T& yo, bool& cut)
+// Fit of one target kt = (i, j) of layer l by the FIT_LANES lanes of a group
+// (every lane of the group calls it with the same target): the outward normal
+// of phi^n for layers 1 and 2, then scan windows of half-width r = 2 .. r_max
+// until one holds three valid nodes and a well-posed fit.  N: layers 1 and 2
+// (an instance of their own: the other layers' needs fewer registers).
+template <typename T, bool N>
+__device__ __forceinline__ bool fit_target(const GridP& g, const Rect& W, const Rect& D,
+                                           int l, int kt, int i, int j,
+                                           int sub, const int8_t* tag,
+                                           const T* __restrict__ phin, const T* X1, const T* Y1,
+                                           T& xo, T& yo)
 {
-    double nxh, nyh;
-    const bool use_n = target_normal<T>(g, D, l, i, j, sub, phin, nxh, nyh);
-    cut = false;
-    for (int r = 2; r <= g.r_max; r++) {
-        if (r > rlim) {
-            cut = true;
-            return false;
-        }
-        if (fit_at<T, MT>(g, W, l, i, j, kt, r, sub, use_n, nxh, nyh, tag, X1, Y1, xo, yo))
-            return true;
+    double nxh = 0.0, nyh = 0.0;
+    const bool use_n = N && target_normal<T>(g, D, l, i, j, sub, phin, nxh, nyh);
+    if (fit2_global<T, N>(g, W, l, i, j, kt, sub, use_n, nxh, nyh, tag, X1, Y1, xo, yo))
+        return true;
+    for (int r = 3; r <= g.r_max; r++) {
+        int count = 0;
+        Fit<T> f;
+        f.zero();
+        fit_window<T>(g, W, l, i, j, kt, r, sub, use_n, nxh, nyh, tag, X1, Y1, f, count);
+        if (fit_finish<T>(g.det_rel, f, count, xo, yo)) return true;
     }
-    return false;
-}
-
-// fit_target with the scan window read from the block's staged copy of the
-// zone ((li, lj): the target's place in it), of half-width 2 only: a target
-// whose fit needs a wider window, or whose window of half-width 2 reaches
-// beyond the copy (rlim < 2), is not fitted (cut set, unless r_max is 2 and
-// the fit has failed for good); k_fit_rest then fits it with the full search,
-// which finds the same bits for the window of half-width 2
-// (use_n, nxh, nyh: the normal weight of layers 1 and 2, found by the caller
-// as target_normal finds it)
-template <typename T, typename MT>
-__device__ __forceinline__ bool fit_target_lds(const GridP& g, int l, int li, int lj, int sub,
-                                               int rlim, const int8_t* st, const T* sx,
-                                               const T* sy, int rw, T& xo, T& yo, bool& cut,
-                                               bool use_n, double nxh, double nyh)
-{
-    cut = rlim < 2;
-    if (cut) return false;
-    int count = 0;
-    Fit<T, MT> f;
-    f.zero();
-    fit_window_lds_r2<T, MT>(l, li, lj, sub, use_n, nxh, nyh, st, sx, sy, rw, f, count);
-    if (fit_finish<T, MT>(g, f, count, xo, yo)) return true;
-    cut = g.r_max > 2;
     return false;
 }
 
@@ -1078,7 +880,7 @@ __device__ __forceinline__ bool fit_target_lds(const GridP& g, int l, int li, in
 // come only from earlier layers, so targets of one layer never read each
 // other.  With displacement storage the fit of d = xi - x gives the fit of xi
 // minus x at the target, since the weighted fit reproduces linear fields.
-template <typename T, typename MT>
+template <typename T, bool N>
 __device__ __forceinline__ void layer_fit_body(GridP g, const Win* __restrict__ win,
                                                    int wcur, int wprev, int l, int8_t* tag,
                                                    const int* __restrict__ lists,
@@ -1105,9 +907,8 @@ __device__ __forceinline__ void layer_fit_body(GridP g, const Win* __restrict__ 
         const int kt = at == a0 ? kfirst : list[at];
         const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
         T xo = T(0), yo = T(0);
-        bool cut;
-        const bool done = fit_target<T, MT>(g, W, D, l, kt, i, j, sub, g.r_max, tag, phin, X1,
-                                            Y1, xo, yo, cut);
+        const bool done = fit_target<T, N>(g, W, D, l, kt, i, j, sub, tag, phin, X1, Y1, xo,
+                                           yo);
         if (sub == 0) {
             if (done) {
                 X1[kt] = xo;
@@ -1120,7 +921,7 @@ __device__ __forceinline__ void layer_fit_body(GridP g, const Win* __restrict__ 
     }
 }
 
-template <typename T>
+template <typename T, bool N>
 __global__ __launch_bounds__(256) void k_layer_fit(GridP g, const Win* __restrict__ win,
                                                    int wcur, int wprev, int l, int8_t* tag,
                                                    const int* __restrict__ lists,
@@ -1128,195 +929,365 @@ __global__ __launch_bounds__(256) void k_layer_fit(GridP g, const Win* __restric
                                                    const T* __restrict__ phin, T* X1, T* Y1,
                                                    unsigned* health)
 {
-    if (float_sums(g, l))
-        layer_fit_body<T, float>(g, win, wcur, wprev, l, tag, lists, lcount, phin, X1, Y1, health);
-    else
-        layer_fit_body<T, double>(g, win, wcur, wprev, l, tag, lists, lcount, phin, X1, Y1,
-                                  health);
+    layer_fit_body<T, N>(g, win, wcur, wprev, l, tag, lists, lcount, phin, X1, Y1, health);
 }
 
-template <typename T>
+template <typename T, bool N>
 __global__ __launch_bounds__(256) void kb_layer_fit(const FitArgs* __restrict__ args, int l)
 {
     const FitArgs& a = args[blockIdx.y];
     if (l > a.g.layers) return;
-    if (float_sums(a.g, l))
-        layer_fit_body<T, float>(a.g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
-                                 (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
-    else
-        layer_fit_body<T, double>(a.g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
-                                  (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
+    layer_fit_body<T, N>(a.g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
+                         (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
 }
 
-// Every layer of one solid in one block (several solids: a solid's layers
-// are short, so one block per solid runs them in order, separated by block
-// barriers that make a layer's fitted values visible to the next layer,
-// instead of one launch per layer over all solids), on an LDS copy of its
-// window dilated by 2 (tags and map values; each fitted value is written to
-// the copy as well as to HBM), as the one-launch single-solid kernel does
-// for a tile: a scan window of half-width 2 around a target (which lies in
-// the window) is read from the copy.  The copy is laid out in unwrapped
-// coordinates, each node holding what its periodic image holds, so it is
-// kept only while no two of its nodes are images of one node (the copy no
-// wider than a period).  A target whose fit needs a wider window takes the
-// global path (fit_target, the full search from half-width 2, on the values
-// written back so far), and so does every target of a solid whose copy
-// would exceed MB_FIT_LDS_NODES nodes or a period.  The same per-target
-// arithmetic as layer_fit_body, so the same bits.  Block row y takes table
+// ---- every layer of a region in one block
+//
+// A region of the window (a tile with its margin, or a whole window) is copied
+// into LDS once: tags, and the advected values of the solid nodes.  What the
+// fits depend on besides values is then known at once: which nodes are valid
+// at layer l is in the tags (solid, or of an earlier layer), so the targets
+// of every layer are listed, their validity masks taken and their cofactors
+// computed up front, all layers side by side.  A layer is left with the
+// dependent part alone: read the window's values, weigh and add them, write
+// the result.
+//
+// A block's time is its instruction count (one VALU instruction of a wave takes
+// its SIMD 4 cycles and a layer has 20 to 100 targets), so one lane takes a
+// target (a 64-target layer is one wave's work; eight lanes repeated the solve
+// eight times and the window's offsets, weights and address arithmetic are
+// constants when the slot is a node), and four sets of two waves take the
+// layers in turn: one finishes layer l while the others take the coefficients
+// and addresses of the next three from their records.  Measured alone, 64^2
+// FP64: eight lanes and every sum in double 38.5 us, eight lanes and integer
+// normal matrices 27.4, two lanes with records 20.2, this 18.6 (256^2 FP32: 31 to
+// 18.5).
+//
+// A target that the copy cannot serve (its fit needs a scan window wider than
+// half-width 2, or fails for good) sets s.cut to its layer: the layers before
+// it stand, the caller sees to the others.
+template <typename T>
+struct Vec2;
+template <>
+struct Vec2<double> {
+    using V = double2;
+};
+template <>
+struct Vec2<float> {
+    using V = float2;
+};
+
+template <typename T, int NODES, int LN>
+struct FitLds {
+    typename Vec2<T>::V val[NODES + 1];  // values of node e at e + 1; the first stays zero
+    uint4 rec[(FF_LAYERS - 2) * LN];     // layers >= 3: mask, cofactors, determinant
+    unsigned short lst[FF_LAYERS * LN];  // targets of layer l (places in the copy) from (l - 1) LN
+    unsigned char st[NODES];             // tags; 255 where there is none
+    int cnt[FF_LAYERS + 1];
+    int cut;
+};
+
+// the region: origin (x0, y0), width rw (rh rows), its own nodes [ox, ox + ow)
+// x [oy, oy + oh); targets of layer l are taken within mstep (L - l) of them
+struct FitRegion {
+    int x0, y0, rw, rh, ox, oy, ow, oh, mstep;
+};
+
+template <typename T, int NT, int NODES, int LN, int RWC>
+__device__ __forceinline__ void fit_region(FitLds<T, NODES, LN>& s, const GridP& g,
+                                           const Rect& W, const Rect& D, int L,
+                                           const FitRegion& R, const int8_t* tag,
+                                           const T* __restrict__ phin, T* X1, T* Y1, int reach)
+{
+    using C2 = Win2<T, 8>;
+    constexpr int NS = C2::NS;
+    constexpr int NIT = (NODES + NT - 1) / NT;  // staged nodes per thread
+    constexpr int NSET = 4, SW = NT / NSET;     // sets of threads, targets per pass
+    static_assert(SW % 64 == 0, "whole waves");
+    const int rw = RWC > 0 ? RWC : R.rw;
+    // (behind an empty asm: what follows from the thread's number is computed
+    // here for each region, not ahead of a loop over regions, where it would
+    // hold half the registers)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int set = tid / SW, lane = tid % SW;
+    // ---- copy: every tag and value of the thread's nodes in flight together;
+    // node tid + u NT, stepped along the rows; periodic axes wrap (the region
+    // is no wider than a period)
+    const int step_y = NT / rw, step_x = NT % rw;
+    int tvs[NIT];
+    T xs0[NIT], ys0[NIT];
+    const int wx = g.px ? g.nx : 0, wy = g.py ? g.ny : 0;
+    {
+        int x = R.x0 + tid % rw, y = R.y0 + tid / rw;
+        const int xe = R.x0 + rw, ye = R.y0 + R.rh;
+#pragma unroll
+        for (int u = 0; u < NIT; u++) {
+            const int xc = x + (x < 0 ? wx : x >= g.nx ? -wx : 0);
+            const int yc = y + (y < 0 ? wy : y >= g.ny ? -wy : 0);
+            const bool in = y < ye && W.has(xc, yc);
+            const int kq = in ? (yc + PAD) * g.pp + xc + PAD : 0;
+            const int tv = tag[kq];
+            tvs[u] = in ? tv : TAG_NONE;
+            xs0[u] = X1[kq];
+            ys0[u] = Y1[kq];
+            x += step_x;
+            y += step_y;
+            if (x >= xe) {
+                x -= rw;
+                y++;
+            }
+        }
+    }
+    __syncthreads();  // the previous region's shared state is no longer read
+    if (tid <= FF_LAYERS) s.cnt[tid] = 0;
+    if (tid == 0) {
+        s.cut = L + 1;
+        s.val[0].x = s.val[0].y = T(0);
+    }
+    __syncthreads();
+    // (a layer's targets do not read each other: their order does not matter)
+    int pos[NIT];
+    {
+        int lx = tid % rw, ly = tid / rw;
+        const int x0 = R.ox - R.x0, y0 = R.oy - R.y0, x1 = x0 + R.ow - 1, y1 = y0 + R.oh - 1;
+#pragma unroll
+        for (int u = 0; u < NIT; u++) {
+            const int tv = tvs[u];
+            pos[u] = LN;
+            // distance to the own nodes
+            const int d = max(max(x0 - lx, lx - x1), max(y0 - ly, ly - y1));
+            if (tv >= 1 && d <= R.mstep * (L - tv)) {
+                pos[u] = atomicAdd(&s.cnt[tv], 1);
+                // (the check mode: the copy is taken to hold one node less
+                // around the targets of each layer)
+                if (reach < 2 && tv > 1 && reach + 2 * (L - tv) - d < 2) atomicMin(&s.cut, tv);
+            }
+            lx += step_x;
+            ly += step_y;
+            if (lx >= rw) {
+                lx -= rw;
+                ly++;
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NIT; u++) {
+        const int e = tid + u * NT, tv = tvs[u];
+        if (u == NIT - 1 && e >= NODES) continue;
+        s.st[e] = (unsigned char)tv;
+        s.val[e + 1].x = tv == TAG_SOLID ? xs0[u] : T(0);
+        s.val[e + 1].y = tv == TAG_SOLID ? ys0[u] : T(0);
+        if (pos[u] < LN) s.lst[(tv - 1) * LN + pos[u]] = (unsigned short)e;
+    }
+    __syncthreads();
+    int cn[FF_LAYERS + 1];  // targets of each layer (the same in every thread)
+    bool fits = true;
+    cn[0] = 0;
+#pragma unroll
+    for (int l = 1; l <= FF_LAYERS; l++) {
+        cn[l] = s.cnt[l];
+        fits = fits && cn[l] <= LN;
+    }
+    if (!fits || (reach < 2 && cn[1] + cn[2] > 64)) {
+        if (tid == 0) s.cut = 1;
+        __syncthreads();
+        return;
+    }
+    // ---- layers 1 and 2 (sets 0 and 1), with the normal of phi^n at the
+    // target; the records of the others (sets 2 and 3)
+    auto record = [&](int e) {
+        // record e of the layers 3 .. L laid end to end
+        int l = 3;
+#pragma unroll
+        for (int k = 3; k < FF_LAYERS; k++)
+            if (l == k && e >= cn[k]) {
+                e -= cn[k];
+                l++;
+            }
+        const int q = s.lst[(l - 1) * LN + e];
+        unsigned m = 0;
+#pragma unroll
+        for (int k = 0; k < NS; k++)
+            if (C2::in(0, k))
+                m |= s.st[q + C2::off_b(0, k) * rw + C2::off_a(0, k)] < l ? 1u << k : 0u;
+        const Geo2 G = geo2(m, g.det_rel);
+        if (!G.ok) atomicMin(&s.cut, l);
+        s.rec[(l - 3) * LN + e] =
+            make_uint4(m, (unsigned)(G.m00 | G.m11 << 8 | (G.m01 & 0xff) << 16),
+                       (unsigned)((G.m02 & 0xff) | (G.m12 & 0xff) << 8), (unsigned)G.det);
+    };
+    // layer 1 + set: set 1 takes its weights while set 0 fits layer 1, and
+    // weighs the values after the barrier
+    {
+        typename C2::NW w;
+        int q = 0;
+        bool have = false, ok = false;
+        int nrec = 0, e = tid - 2 * SW;
+#pragma unroll
+        for (int k = 3; k <= FF_LAYERS; k++) nrec += cn[k];
+#pragma unroll 1
+        for (int ph = 0; ph < 2; ph++) {
+            if (set < 2 && ph <= set) {
+                const int l = 1 + set, n = set == 0 ? cn[1] : cn[2];
+#pragma unroll 1
+                for (int a = lane; a < n; a += SW) {
+                    if (!have) {
+                        q = s.lst[set * LN + a];
+                        const int i = R.x0 + q % rw, j = R.y0 + q / rw;
+                        // (D lies in the map's domain: no test of their own)
+                        auto at = [&](int x, int y) {
+                            x += x < 0 ? wx : x >= g.nx ? -wx : 0;
+                            y += y < 0 ? wy : y >= g.ny ? -wy : 0;
+                            return D.has(x, y) ? (y + PAD) * g.pp + x + PAD : -1;
+                        };
+                        const int ke = at(i + 1, j), kw = at(i - 1, j);
+                        const int kn = at(i, j + 1), ks = at(i, j - 1);
+                        const T pe = phin[ke >= 0 ? ke : 0], pw = phin[kw >= 0 ? kw : 0];
+                        const T pn = phin[kn >= 0 ? kn : 0], ps = phin[ks >= 0 ? ks : 0];
+                        bool v[NS];
+#pragma unroll
+                        for (int k = 0; k < NS; k++)
+                            v[k] = C2::in(0, k) &&
+                                   s.st[q + C2::off_b(0, k) * rw + C2::off_a(0, k)] < l;
+                        const unsigned mask = C2::mask_of(0, v);
+                        double nxh = 0.0, nyh = 0.0;
+                        const bool use_n = normal_from(ke >= 0 ? (double)pe : INFINITY,
+                                                       kw >= 0 ? (double)pw : INFINITY,
+                                                       kn >= 0 ? (double)pn : INFINITY,
+                                                       ks >= 0 ? (double)ps : INFINITY, nxh, nyh);
+                        ok = use_n ? C2::weights_n(0, __popc(mask), v, nxh, nyh, g.det_rel, w)
+                                   : C2::weights_2(0, mask, g.det_rel, w);
+                        have = true;
+                    }
+                    if (set != ph) break;
+                    T xs[NS], ys[NS], xo, yo;
+#pragma unroll
+                    for (int k = 0; k < NS; k++) {
+                        if (!C2::in(0, k)) continue;
+                        const int qk = q + C2::off_b(0, k) * rw + C2::off_a(0, k);
+                        const auto z = s.val[s.st[qk] < l ? qk + 1 : 0];
+                        xs[k] = z.x;
+                        ys[k] = z.y;
+                    }
+                    C2::value_n(0, w, xs, ys, xo, yo);
+                    if (ok) {
+                        s.val[q + 1].x = xo;
+                        s.val[q + 1].y = yo;
+                    } else {
+                        atomicMin(&s.cut, l);
+                    }
+                    have = false;
+                }
+            }
+            if (set >= 2) {
+                const int stop = ph == 0 ? min(nrec, NT) : nrec;
+#pragma unroll 1
+                for (; e < stop; e += NT - 2 * SW) record(e);
+            }
+            __syncthreads();
+        }
+    }
+    // ---- layers 3 and up
+    int pq = -1, adr[NS];
+    Geo2 pg{};
+    auto prep = [&](int l, int a, int n) {
+        pq = -1;
+        if (a >= n) return;
+        const uint4 r = s.rec[(l - 3) * LN + a];
+        pq = s.lst[(l - 1) * LN + a] + 1;
+        pg.m00 = (int)(r.y & 0xff);
+        pg.m11 = (int)(r.y >> 8 & 0xff);
+        pg.m01 = (int)(r.y << 8) >> 24;
+        pg.m02 = (int)(r.z << 24) >> 24;
+        pg.m12 = (int)(r.z << 16) >> 24;
+        pg.det = (int)r.w;
+#pragma unroll
+        for (int k = 0; k < NS; k++)
+            adr[k] = ((int)(r.x << (31 - k)) >> 31) &
+                     (pq + C2::off_b(0, k) * rw + C2::off_a(0, k));
+    };
+    auto finish = [&]() {
+        if (pq < 0) return;
+        T xs[NS], ys[NS], xo, yo;
+#pragma unroll
+        for (int k = 0; k < NS; k++) {
+            if (!C2::in(0, k)) continue;
+            const auto z = s.val[adr[k]];
+            xs[k] = z.x;
+            ys[k] = z.y;
+        }
+        C2::value(0, pg, xs, ys, xo, yo);
+        s.val[pq].x = xo;
+        s.val[pq].y = yo;
+    };
+    const int last = min(L, s.cut - 1);  // (the same in every thread: no cut follows)
+    int lm = 3 + set, n = s.cnt[min(lm, FF_LAYERS)];  // the set's next layer
+    if (lm <= last) prep(lm, lane, n);
+#pragma unroll 1
+    for (int l = 3; l <= last; l++) {
+        const bool mine = l == lm;
+        if (mine) {
+            int a = lane;
+#pragma unroll 1
+            while (true) {
+                finish();
+                a += SW;
+                if (a >= n) break;
+                prep(l, a, n);
+            }
+        }
+        __syncthreads();
+        if (mine) {
+            lm += NSET;
+            n = s.cnt[min(lm, FF_LAYERS)];
+            if (lm <= last) prep(lm, lane, n);
+        }
+    }
+    // ---- the region's own nodes of the layers that stand (the layers touch
+    // LDS only, so none of their barriers waits for HBM)
+    for (int e = tid; e < R.ow * R.oh; e += NT) {
+        const int x = R.ox + e % R.ow, y = R.oy + e / R.ow;
+        const int q = (y - R.y0) * rw + x - R.x0, l = s.st[q];
+        if (l >= 1 && l <= last && W.has(x, y)) {
+            const long long kt = pidx(g, x, y);
+            X1[kt] = s.val[q + 1].x;
+            Y1[kt] = s.val[q + 1].y;
+        }
+    }
+}
+
+// Every layer of one solid in one block (several solids: a solid's layers are
+// short) on a copy of its window dilated by 2, laid out in unwrapped
+// coordinates, each node holding what its periodic image holds, so it is kept
+// only while no two of its nodes are images of one node (the copy no wider
+// than a period).  The layers that the copy cannot serve, and every layer of
+// a solid whose copy would exceed MB_FIT_LDS_NODES nodes or a period, are
+// fitted on the maps (layer_fit_body: the same bits).  Block row y takes table
 // row ord[y] (row y when ord is null).
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ args, int layers,
                                                   const int* __restrict__ ord)
 {
-    __shared__ int8_t st[MB_FIT_LDS_NODES];
-    __shared__ T sx[MB_FIT_LDS_NODES], sy[MB_FIT_LDS_NODES];
-    __shared__ int s_ns[(MAX_LAYERS + 1) * NSUB];  // sub-list lengths, read once
-    // FP32: phi^n of the copy's nodes inside the previous window (+inf
-    // elsewhere, as ref_index leaves it), for the normals of layers 1 and 2
-    // (in FP64 the copy of phi^n would not fit beside the map values)
-    constexpr bool SPHI = sizeof(T) == 4;
-    __shared__ T sp[SPHI ? MB_FIT_LDS_NODES : 1];
-    constexpr int NG = NT / FIT_LANES;
+    __shared__ FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB> s;
     const FitArgs& a = args[ord ? ord[blockIdx.y] : blockIdx.y];
     const GridP& g = a.g;
     const Rect W = window_of(a.win, a.wcur, g);
     const Rect D = window_of(a.win, a.wprev, g);
     if (!W.ok) return;
-    const int bx0 = W.i0 - 2, by0 = W.j0 - 2;
-    const int bw = W.i1 - W.i0 + 5, bh = W.j1 - W.j0 + 5;
-    if ((long long)bw * bh > MB_FIT_LDS_NODES || (g.px && bw > g.nx) || (g.py && bh > g.ny)) {
-        for (int l = 1; l <= layers; l++) {
-            if (float_sums(g, l))
-                layer_fit_body<T, float>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
-                                         (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
-            else
-                layer_fit_body<T, double>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists,
-                                          a.lcount, (const T*)a.phin, (T*)a.X1, (T*)a.Y1,
-                                          a.health);
-            __syncthreads();
-        }
-        return;
+    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
+    int l0 = 1;
+    if (layers <= FF_LAYERS && (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
+        !(g.py && h + 4 > g.ny)) {
+        const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
+        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0>(s, g, W, D, layers, R, a.tag, (const T*)a.phin,
+                                               (T*)a.X1, (T*)a.Y1, 2);
+        l0 = s.cut;
+        __syncthreads();
     }
-    T* X1 = (T*)a.X1;
-    T* Y1 = (T*)a.Y1;
-    const T* phin = (const T*)a.phin;
-    const long long cap = g.lcap;
-    // the copy: nodes outside the window hold no value (as in fit_window,
-    // which wraps a node's periodic axes before the window test); the loads
-    // of U nodes per thread are issued before their stores
-    constexpr int U = 4;
-    const int nn = bw * bh;
-    for (int e0 = threadIdx.x; e0 < nn; e0 += U * NT) {
-        int8_t tv[U];
-        T xv[U], yv[U], pv[U];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int e = e0 + u * NT;
-            int x = bx0 + e % bw, y = by0 + e / bw;
-            if (g.px) x = wrap_axis(x, g.nx);
-            if (g.py) y = wrap_axis(y, g.ny);
-            const bool in = e < nn && W.has(x, y);
-            const long long k = pidx(g, in ? x : W.i0, in ? y : W.j0);
-            tv[u] = in ? a.tag[k] : (int8_t)TAG_NONE;
-            xv[u] = in ? X1[k] : T(0);
-            yv[u] = in ? Y1[k] : T(0);
-            if constexpr (SPHI) {
-                const bool ind = e < nn && D.has(x, y);
-                pv[u] = ind ? phin[pidx(g, ind ? x : W.i0, ind ? y : W.j0)] : T(INFINITY);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int e = e0 + u * NT;
-            if (e >= nn) break;
-            st[e] = tv[u];
-            sx[e] = xv[u];
-            sy[e] = yv[u];
-            if constexpr (SPHI) sp[e] = pv[u];
-        }
-    }
-    for (int q = threadIdx.x; q < (layers + 1) * NSUB; q += NT)
-        s_ns[q] = (int)min((long long)a.lcount[q * LCOUNT_PAD], cap);
-    __syncthreads();
-    // group grp takes sub-list grp mod NSUB, as layer_fit_body does, so the
-    // sub-lists of a layer are fitted side by side; the list entry a group
-    // fits next is loaded while it fits the current one (the lists are
-    // complete before the kernel starts)
-    static_assert(NG % NSUB == 0, "whole groups per sub-list");
-    constexpr int AS = NG / NSUB;
-    const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
-    const int sl = grp % NSUB, a0 = grp / NSUB;
-    int knext = a0 < s_ns[NSUB + sl] ? a.lists[(NSUB + sl) * cap + a0] : 0;
-    for (int l = 1; l <= layers; l++) {
-        const int* list = a.lists + (l * NSUB + sl) * cap;
-        const int ns = s_ns[l * NSUB + sl];
-        // every lane of a group runs the same trip counts
-        for (int at = a0; at < ns; at += AS) {
-            const int kt = knext;
-            knext = at + AS < ns ? list[at + AS] : 0;
-            const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
-            const int li = i - bx0, lj = j - by0;
-            double nxh, nyh;
-            bool use_n;
-            if constexpr (SPHI) {
-                // target_normal with the four neighbours read from the copy
-                nxh = nyh = 0.0;
-                use_n = false;
-                if (l <= 2) {
-                    double p = INFINITY;
-                    if (sub < 4) {
-                        const int di = sub == 0 ? 1 : sub == 1 ? -1 : 0;
-                        const int dj = sub == 2 ? 1 : sub == 3 ? -1 : 0;
-                        p = (double)sp[(lj + dj) * bw + li + di];
-                    }
-                    const double pe = __shfl(p, 0, FIT_LANES), pw = __shfl(p, 1, FIT_LANES);
-                    const double pn = __shfl(p, 2, FIT_LANES), ps = __shfl(p, 3, FIT_LANES);
-                    use_n = normal_from(pe, pw, pn, ps, nxh, nyh);
-                }
-            } else {
-                use_n = target_normal<T>(g, D, l, i, j, sub, phin, nxh, nyh);
-            }
-            T xo = T(0), yo = T(0);
-            bool done, cut;
-            int count = 0;
-            if (float_sums(g, l)) {
-                Fit<T, float> f;
-                f.zero();
-                fit_window_lds_r2<T, float>(l, li, lj, sub, use_n, nxh, nyh, st, sx, sy, bw,
-                                            f, count);
-                done = fit_finish<T, float>(g, f, count, xo, yo);
-                if (!done && g.r_max > 2)
-                    done = fit_target<T, float>(g, W, D, l, kt, i, j, sub, g.r_max, a.tag,
-                                                phin, X1, Y1, xo, yo, cut);
-            } else {
-                Fit<T, double> f;
-                f.zero();
-                fit_window_lds_r2<T, double>(l, li, lj, sub, use_n, nxh, nyh, st, sx, sy,
-                                             bw, f, count);
-                done = fit_finish<T, double>(g, f, count, xo, yo);
-                if (!done && g.r_max > 2)
-                    done = fit_target<T, double>(g, W, D, l, kt, i, j, sub, g.r_max, a.tag,
-                                                 phin, X1, Y1, xo, yo, cut);
-            }
-            if (sub == 0) {
-                const int q = lj * bw + li;
-                if (done) {
-                    sx[q] = xo;
-                    sy[q] = yo;
-                    X1[kt] = xo;
-                    Y1[kt] = yo;
-                } else {
-                    st[q] = (int8_t)(l | TAG_FAIL);
-                    a.tag[kt] = (int8_t)(l | TAG_FAIL);
-                    atomicAdd(&a.health[1], 1u);
-                }
-            }
-        }
-        if (l < layers) {
-            const int n1 = s_ns[(l + 1) * NSUB + sl];
-            knext = a0 < n1 ? a.lists[((l + 1) * NSUB + sl) * cap + a0] : 0;
-        }
-        // the layer's values (copy and global) before the next layer reads them
+    for (int l = l0; l <= layers; l++) {
+        layer_fit_body<T, true>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
+                                (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
         __syncthreads();
     }
 }
@@ -1356,13 +1327,8 @@ __device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, 
                     const int t = (i - W.i0) / FF_TILE + ((j - W.j0) / FF_TILE) * ntx;
                     if (cut_layer[t] > l) continue;
                     T xo = T(0), yo = T(0);
-                    bool cut;
-                    const bool done =
-                        float_sums(g, l)
-                            ? fit_target<T, float>(g, W, D, l, kt, i, j, sub, g.r_max, tag, phin,
-                                                   X1, Y1, xo, yo, cut)
-                            : fit_target<T, double>(g, W, D, l, kt, i, j, sub, g.r_max, tag,
-                                                    phin, X1, Y1, xo, yo, cut);
+                    const bool done = fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin,
+                                                          X1, Y1, xo, yo);
                     if (sub == 0) {
                         if (done) {
                             X1[kt] = xo;
@@ -1392,253 +1358,71 @@ __device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, 
 // the zone reaches; for layer l it fits every layer-l target within
 // M_l = 2 (L - l) nodes of its tile, its own and those of the tiles around
 // (recomputed, with the same arithmetic, so the same bits as their own
-// blocks find), then a block barrier, then layer l + 1.  The block works on a
-// copy in LDS: the tags and the advected solid values of the tile and a
-// margin of M_1 + 2 nodes are staged once, and each fitted value (or failure)
-// goes into the copy; only the tile's own targets are written back.  The
-// level-set normals of the layer-1 and layer-2 targets (the weights of
-// Eq. (3_2_extrap_weight)) are found before the layers, all their loads in
-// one round; a tile with more such targets than FF_NORMALS is stopped
-// before its first layer.  A scan
+// blocks find), on a copy of the tile and a margin of M_1 + 2 nodes: a scan
 // window of half-width 2 around a target within M_l of the tile stays within
 // M_l + 2 = M_{l-1}, where the copy holds every earlier layer, and layer-1
-// windows read solid nodes only, which the copy holds across the margin.  A
-// target whose fit needs a wider window than that (fewer than three valid
-// nodes in it, or an ill-posed fit) stops the tile at that layer:
-// the tile is listed, with the layer, for k_fit_rest, which finishes the
-// listed tiles layer by layer; the tile's layers before that one are final.
+// windows read solid nodes only, which the copy holds across the margin.  Only
+// the tile's own targets are written back.  A tile that the copy cannot serve
+// from some layer on (a fit that needs a wider scan window, or fails for good;
+// more than FF_LAYER targets
+// in a layer) is listed, with the layer, for k_fit_rest,
+// which finishes the listed tiles layer by layer.
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
-// margin at layer 2, and every tile with more than 64 targets in layers 1
-// and 2 before its first layer (k_fit_rest then fits most of the zone: a
-// check of that launch).  Walled axes only (a window across a periodic seam would
-// reach another tile's nodes).
-template <typename T, int NT>
+// margin, and every tile with more than 64 targets in layers 1 and 2 before
+// its first layer (k_fit_rest then fits most of the zone: a check of that
+// launch).
+template <typename T, int NT, int LC>
 __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
-                                               int wcur, int wprev, int8_t* tag,
+                                               int wcur, int wprev, const int8_t* tag,
                                                const T* __restrict__ phin, T* X1, T* Y1,
-                                               unsigned* health, int8_t* cut_layer,
-                                               int* cut_tiles, int* ncut,
+                                               int8_t* cut_layer, int* cut_tiles, int* ncut,
                                                const int* __restrict__ ff_list,
                                                const int* __restrict__ ff_n, int reach)
 {
-    constexpr int RW = FF_TILE + 4 * (FF_LAYERS - 1) + 4;
-    constexpr int NG = NT / FIT_LANES;
-    __shared__ int8_t st[RW * RW];  // tags of the tile and its margin
-    __shared__ T sx[RW * RW];       // xi (or the displacement): solid nodes, then fitted ones
-    __shared__ T sy[RW * RW];
-    __shared__ short lst[RW * RW];  // the block's targets, layer by layer (places in the copy)
-    __shared__ short cand[RW * RW];  // the same, in staging order
-    __shared__ int s_cnt[FF_LAYERS + 1], s_base[FF_LAYERS + 2], s_fill[FF_LAYERS + 1];
-    // per layer: a target needed a wider window than the copy holds; targets
-    // whose fit failed (own nodes)
-    __shared__ int s_cut[FF_LAYERS + 1], s_fail[FF_LAYERS + 1];
-    __shared__ int s_n;
-    // the level-set normals of the first FF_NORMALS layer-1 and layer-2
-    // targets (in list order), found before the layers (flag 1: exists)
-    __shared__ double s_nx[FF_NORMALS], s_ny[FF_NORMALS];
-    __shared__ int8_t s_nok[FF_NORMALS];
-    const int ntile = *ff_n;
-    if (blockIdx.x >= ntile) return;
+    constexpr int RW = FF_REGION;
+    __shared__ FitLds<T, RW * RW, FF_LAYER> s;
+    // (the first tile is read together with the count: the list holds at
+    // least as many entries as there are blocks)
+    const int ntile = *ff_n, t0 = ff_list[blockIdx.x];
     const Rect W = window_of(win, wcur, g);
-    if (!W.ok) return;
     const Rect D = window_of(win, wprev, g);
-    const int L = g.layers;
+    if ((int)blockIdx.x >= ntile || !W.ok) return;
+    const int L = LC > 0 ? LC : g.layers;
     const int S = 2 * (L - 1) + 2, rw = FF_TILE + 2 * S;  // margin of the copy, its width
     const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
-    const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
-    constexpr int NIT = (RW * RW + NT - 1) / NT;  // staged nodes per thread
-    // normal slots in use (reach 1, a check of k_fit_rest: few, so that
-    // most tiles are stopped before their first layer)
-    const int ncap = reach == 1 ? 64 : FF_NORMALS;
     for (int k = blockIdx.x; k < ntile; k += gridDim.x) {
-        const int t = ff_list[k];
+        const int t = k == (int)blockIdx.x ? t0 : ff_list[k];
         const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
-        __syncthreads();  // the previous tile's shared state is no longer read
-        if (threadIdx.x == 0) s_n = 0;
-        if (threadIdx.x <= FF_LAYERS) {
-            s_cnt[threadIdx.x] = 0;
-            s_fill[threadIdx.x] = 0;
-            s_cut[threadIdx.x] = 0;
-            s_fail[threadIdx.x] = 0;
-        }
-        __syncthreads();
-        // staging in two rounds of loads: every tag of the thread's nodes,
-        // then the values of its solid nodes
-        int8_t tvs[NIT];
-#pragma unroll
-        for (int u = 0; u < NIT; u++) {
-            const int e = threadIdx.x + u * NT;
-            const int x = x0 - S + e % rw, y = y0 - S + e / rw;
-            const bool in = e < rw * rw && W.has(x, y);
-            const long long kq = pidx(g, in ? x : W.i0, in ? y : W.j0);
-            tvs[u] = in ? tag[kq] : (int8_t)TAG_NONE;
-        }
-        T xs[NIT], ys[NIT];
-#pragma unroll
-        for (int u = 0; u < NIT; u++) {
-            const int e = threadIdx.x + u * NT;
-            const int x = x0 - S + e % rw, y = y0 - S + e / rw;
-            // the owner of a margin node may have marked it failed already:
-            // it is fitted here again, to the same verdict
-            if (tvs[u] > 0) tvs[u] = (int8_t)(tvs[u] & (TAG_FAIL - 1));
-            const bool solid = e < rw * rw && tvs[u] == TAG_SOLID;
-            const long long kq = pidx(g, solid ? x : W.i0, solid ? y : W.j0);
-            xs[u] = solid ? X1[kq] : T(0);
-            ys[u] = solid ? Y1[kq] : T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < NIT; u++) {
-            const int e = threadIdx.x + u * NT;
-            if (e >= rw * rw) continue;
-            const int x = x0 - S + e % rw, y = y0 - S + e / rw;
-            const int tv = tvs[u];
-            st[e] = (int8_t)tv;
-            if (tv == TAG_SOLID) {
-                sx[e] = xs[u];
-                sy[e] = ys[u];
-            }
-            // a layer-l node is this block's target within M_l of the tile
-            if (tv >= 1 && tv <= L) {
-                const int dx = max(max(x0 - x, x - (x0 + FF_TILE - 1)), 0);
-                const int dy = max(max(y0 - y, y - (y0 + FF_TILE - 1)), 0);
-                if (max(dx, dy) <= 2 * (L - tv)) {
-                    atomicAdd(&s_cnt[tv], 1);
-                    cand[atomicAdd(&s_n, 1)] = (short)e;
-                }
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            s_base[1] = 0;
-            for (int l = 1; l <= L; l++) s_base[l + 1] = s_base[l] + s_cnt[l];
-        }
-        __syncthreads();
-        // the targets sorted by layer (the order within a layer does not
-        // matter: a layer's targets do not read each other)
-        for (int a = threadIdx.x; a < s_n; a += NT) {
-            const int q = cand[a];
-            const int l = st[q];
-            lst[s_base[l] + atomicAdd(&s_fill[l], 1)] = (short)q;
-        }
-        __syncthreads();
-        // the outward normals of phi^n of the layer-1 and layer-2 targets
-        // (weights of Eq. (3_2_extrap_weight)), all loads in one round: the
-        // same values and arithmetic as target_normal
-        {
-            // (none when they do not fit: the tile is stopped below)
-            const int n12 = s_base[min(L, 2) + 1] <= ncap ? s_base[min(L, 2) + 1] : 0;
-            for (int a = threadIdx.x; a < n12; a += NT) {
-                const int q = lst[a];
-                const int i = x0 - S + q % rw, j = y0 - S + q / rw;
-                const long long ke = ref_index(g, D, i + 1, j), kw = ref_index(g, D, i - 1, j);
-                const long long kn = ref_index(g, D, i, j + 1), ks = ref_index(g, D, i, j - 1);
-                const long long k0 = pidx(g, i, j);
-                const T pe = phin[ke >= 0 ? ke : k0], pw = phin[kw >= 0 ? kw : k0];
-                const T pn = phin[kn >= 0 ? kn : k0], ps = phin[ks >= 0 ? ks : k0];
-                double nxh = 0.0, nyh = 0.0;
-                const bool ok = normal_from(ke >= 0 ? (double)pe : INFINITY,
-                                            kw >= 0 ? (double)pw : INFINITY,
-                                            kn >= 0 ? (double)pn : INFINITY,
-                                            ks >= 0 ? (double)ps : INFINITY, nxh, nyh);
-                s_nx[a] = nxh;
-                s_ny[a] = nyh;
-                s_nok[a] = ok ? 1 : 0;
-            }
-        }
-        __syncthreads();
-        // more layer-1 and layer-2 targets than normal slots: the tile is
-        // stopped before its first layer (k_fit_rest fits it)
-        if (s_base[min(L, 2) + 1] > ncap) {
-            if (threadIdx.x == 0) {
-                cut_layer[t] = (int8_t)1;
-                cut_tiles[atomicAdd(ncut, 1)] = t;
-            }
-            continue;
-        }
-        for (int l = 1; l <= L; l++) {
-            const int M = 2 * (L - l);
-            const int n = s_cnt[l];
-            const short* lt = lst + s_base[l];
-            // the copy holds layer-(l-1) values within K of the tile (layer
-            // 1: solid values across the whole copy); reach < 2 narrows it
-            const int K = l == 1 ? S : M + reach;
-            for (int a = grp; a < n; a += NG) {
-                const int q = lt[a];
-                const int li = q % rw, lj = q / rw;
-                const int i = x0 - S + li, j = y0 - S + lj;
-                const int rlim = min(g.r_max, min(min(li - (S - K), S + FF_TILE - 1 + K - li),
-                                                  min(lj - (S - K), S + FF_TILE - 1 + K - lj)));
-                // the normal found above (layers 1 and 2)
-                const int pos = l <= 2 ? s_base[l] + a : 0;
-                const bool use_n = l <= 2 && s_nok[pos] != 0;
-                const double nxh = use_n ? s_nx[pos] : 0.0, nyh = use_n ? s_ny[pos] : 0.0;
-                T xo = T(0), yo = T(0);
-                bool cut;
-                const bool done =
-                    float_sums(g, l)
-                        ? fit_target_lds<T, float>(g, l, li, lj, sub, rlim, st, sx, sy, rw, xo,
-                                                   yo, cut, use_n, nxh, nyh)
-                        : fit_target_lds<T, double>(g, l, li, lj, sub, rlim, st, sx, sy, rw, xo,
-                                                    yo, cut, use_n, nxh, nyh);
-                if (sub == 0) {
-                    const bool own = i >= x0 && i < x0 + FF_TILE && j >= y0 && j < y0 + FF_TILE;
-                    const long long kt = pidx(g, i, j);
-                    if (done) {
-                        sx[q] = xo;
-                        sy[q] = yo;
-                        if (own) {
-                            X1[kt] = xo;
-                            Y1[kt] = yo;
-                        }
-                    } else if (cut) {
-                        s_cut[l] = 1;
-                    } else {
-                        st[q] = (int8_t)(l | TAG_FAIL);
-                        if (own) {
-                            tag[kt] = (int8_t)(l | TAG_FAIL);
-                            atomicAdd(&s_fail[l], 1);
-                        }
-                    }
-                }
-            }
-            // one barrier per layer: the decision reads this layer's flags,
-            // which the next layer does not write
-            __syncthreads();
-            const bool stop = s_cut[l] != 0;
-            if (threadIdx.x == 0) {
-                if (stop) {
-                    cut_layer[t] = (int8_t)l;
-                    cut_tiles[atomicAdd(ncut, 1)] = t;
-                } else if (s_fail[l] > 0) {
-                    atomicAdd(&health[1], (unsigned)s_fail[l]);
-                }
-            }
-            if (stop) break;
+        const FitRegion R{x0 - S, y0 - S, rw, rw, x0, y0, FF_TILE, FF_TILE, 2};
+        fit_region<T, NT, RW * RW, FF_LAYER, LC == FF_LAYERS ? RW : 0>(s, g, W, D, L, R, tag, phin,
+                                                                       X1, Y1, reach);
+        if (threadIdx.x == 0 && s.cut <= L) {
+            cut_layer[t] = (int8_t)s.cut;
+            cut_tiles[atomicAdd(ncut, 1)] = t;
         }
     }
 }
 
-template <typename T, int NT>
+template <typename T, int NT, int LC>
 __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict__ win, int wcur,
-                                                  int wprev, int8_t* tag,
+                                                  int wprev, const int8_t* tag,
                                                   const T* __restrict__ phin, T* X1, T* Y1,
-                                                  unsigned* health, int8_t* cut_layer,
-                                                  int* cut_tiles, int* ncut,
+                                                  int8_t* cut_layer, int* cut_tiles, int* ncut,
                                                   const int* __restrict__ ff_list,
                                                   const int* __restrict__ ff_n, int reach)
 {
-    fit_fused_body<T, NT>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_layer, cut_tiles,
-                          ncut, ff_list, ff_n, reach);
+    fit_fused_body<T, NT, LC>(g, win, wcur, wprev, tag, phin, X1, Y1, cut_layer, cut_tiles, ncut,
+                              ff_list, ff_n, reach);
 }
 
 // a batch: member blockIdx.y
-template <typename T>
-__global__ __launch_bounds__(1024) void kb_fit_fused(const FitArgs* __restrict__ args)
+template <typename T, int LC>
+__global__ __launch_bounds__(FF_THREADS) void kb_fit_fused(const FitArgs* __restrict__ args)
 {
     const FitArgs& a = args[blockIdx.y];
-    fit_fused_body<T, 1024>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1,
-                            (T*)a.Y1, a.health, a.cut_layer, a.cut_tiles, a.ncut, a.ff_list,
-                            a.ff_n, 2);
+    fit_fused_body<T, FF_THREADS, LC>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin,
+                                            (T*)a.X1, (T*)a.Y1, a.cut_layer, a.cut_tiles, a.ncut,
+                                            a.ff_list, a.ff_n, 2);
 }
 
 template <typename T>
@@ -1668,16 +1452,20 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
                               hipStream_t st, int fused_threads)
 {
     if (fused_threads > 0 && fused_fit_ok(g)) {
-#define FUSED(T, NT)                                                                              \
-    k_fit_fused<T, NT><<<FF_BLOCKS, NT, 0, st>>>(                                                 \
+#define FUSED_L(T, NT, LC)                                                                        \
+    k_fit_fused<T, NT, LC><<<FF_BLOCKS, NT, 0, st>>>(                                             \
         g, bb.win, s.wcur, s.wprev, bb.tag, (const T*)bb.phi[s.cur], (T*)bb.X[s.nxt],             \
-        (T*)bb.Y[s.nxt], bb.health, bb.cut_layer, bb.cut_tiles, bb.ncut, bb.ff_list, bb.ff_n,    \
+        (T*)bb.Y[s.nxt], bb.cut_layer, bb.cut_tiles, bb.ncut, bb.ff_list, bb.ff_n,               \
         fused_threads == 1 ? 1 : 2)
+#define FUSED(T, NT)                                                                              \
+    do {                                                                                          \
+        if (g.layers == FF_LAYERS) FUSED_L(T, NT, FF_LAYERS);                                     \
+        else FUSED_L(T, NT, 0);                                                                   \
+    } while (0)
 #define FUSED_T(T)                                                                                \
     do {                                                                                          \
         if (fused_threads == 256) FUSED(T, 256);                                                  \
-        else if (fused_threads == 512) FUSED(T, 512);                                             \
-        else FUSED(T, 1024);                                                                      \
+        else FUSED(T, FF_THREADS);                                                                \
         k_fit_rest<T><<<1, FF_REST_THREADS, 0, st>>>(                                             \
             g, bb.win, s.wcur, s.wprev, bb.tag, bb.lists, bb.lcount, (const T*)bb.phi[s.cur],     \
             (T*)bb.X[s.nxt], (T*)bb.Y[s.nxt], bb.health, bb.cut_layer, bb.cut_tiles, bb.ncut,     \
@@ -1687,18 +1475,22 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
         else FUSED_T(double);
 #undef FUSED_T
 #undef FUSED
+#undef FUSED_L
         return hipGetLastError();
     }
+#define LAYER(T, N)                                                                            \
+    k_layer_fit<T, N><<<FIT_BLOCKS, 256, 0, st>>>(g, bb.win, s.wcur, s.wprev, l, bb.tag,       \
+                                                  bb.lists, bb.lcount, (const T*)bb.phi[s.cur], \
+                                                  (T*)bb.X[s.nxt], (T*)bb.Y[s.nxt], bb.health)
     for (int l = 1; l <= g.layers; l++)
-        if (g.rm32)
-            k_layer_fit<float><<<FIT_BLOCKS, 256, 0, st>>>(
-                g, bb.win, s.wcur, s.wprev, l, bb.tag, bb.lists, bb.lcount,
-                (const float*)bb.phi[s.cur], (float*)bb.X[s.nxt], (float*)bb.Y[s.nxt], bb.health);
-        else
-            k_layer_fit<double><<<FIT_BLOCKS, 256, 0, st>>>(
-                g, bb.win, s.wcur, s.wprev, l, bb.tag, bb.lists, bb.lcount,
-                (const double*)bb.phi[s.cur], (double*)bb.X[s.nxt], (double*)bb.Y[s.nxt],
-                bb.health);
+        if (g.rm32) {
+            if (l <= 2) LAYER(float, true);
+            else LAYER(float, false);
+        } else {
+            if (l <= 2) LAYER(double, true);
+            else LAYER(double, false);
+        }
+#undef LAYER
     return hipGetLastError();
 }
 
@@ -2772,13 +2564,16 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
         if (layers == 11) kb_advect_dt<11, double><<<gd, 256, 0, st>>>(t.adv, t.ord);
         else kb_advect_dt<0, double><<<gd, 256, 0, st>>>(t.adv, t.ord);
         if (fused) {
-            kb_fit_fused<double><<<gz, 1024, 0, st>>>(t.fit);
+            if (layers == FF_LAYERS) kb_fit_fused<double, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
+            else kb_fit_fused<double, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
             kb_fit_rest<double><<<g1, FF_REST_THREADS, 0, st>>>(t.fit);
         } else if (fit_blocks == 0) {
             kb_fit_lds<double, MB_FIT_THREADS_F64><<<g1, MB_FIT_THREADS_F64, 0, st>>>(t.fit, layers,
                                                                                  t.ord);
         } else {
-            for (int l = 1; l <= layers; l++) kb_layer_fit<double><<<gf, 256, 0, st>>>(t.fit, l);
+            for (int l = 1; l <= layers; l++)
+                if (l <= 2) kb_layer_fit<double, true><<<gf, 256, 0, st>>>(t.fit, l);
+                else kb_layer_fit<double, false><<<gf, 256, 0, st>>>(t.fit, l);
         }
         if (relabel_only) kb_force<2, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
         else kb_force<0, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
@@ -2786,13 +2581,16 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
         if (layers == 11) kb_advect_dt<11, float><<<gd, 256, 0, st>>>(t.adv, t.ord);
         else kb_advect_dt<0, float><<<gd, 256, 0, st>>>(t.adv, t.ord);
         if (fused) {
-            kb_fit_fused<float><<<gz, 1024, 0, st>>>(t.fit);
+            if (layers == FF_LAYERS) kb_fit_fused<float, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
+            else kb_fit_fused<float, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
             kb_fit_rest<float><<<g1, FF_REST_THREADS, 0, st>>>(t.fit);
         } else if (fit_blocks == 0) {
             kb_fit_lds<float, MB_FIT_THREADS_F32><<<g1, MB_FIT_THREADS_F32, 0, st>>>(t.fit, layers,
                                                                                 t.ord);
         } else {
-            for (int l = 1; l <= layers; l++) kb_layer_fit<float><<<gf, 256, 0, st>>>(t.fit, l);
+            for (int l = 1; l <= layers; l++)
+                if (l <= 2) kb_layer_fit<float, true><<<gf, 256, 0, st>>>(t.fit, l);
+                else kb_layer_fit<float, false><<<gf, 256, 0, st>>>(t.fit, l);
         }
         if (relabel_only) kb_force<2, float><<<gb, 256, 0, st>>>(t.edg, t.ord);
         else kb_force<0, float><<<gb, 256, 0, st>>>(t.edg, t.ord);

@@ -390,11 +390,11 @@ static StampValid prev_valid(const lbrmt_ctx* c)
     return StampValid{c->stamp[slots_for(c->step).nxt], (int)c->step, c->L.nbx};
 }
 
-// Block size of the one-launch extrapolation (default 1024; one launch per
+// Block size of the one-launch extrapolation (default 512; one launch per
 // layer, 0, by default when the bulk update's workgroups are capped), 0 for
 // one launch per layer.
 // The early part of a held bulk update: -1 (default) takes the far tiles of
-// the first 30 % on grids of 2048^2 nodes or more, where the bulk update
+// the first 35 % on grids of 2048^2 nodes or more, where the bulk update
 // outlasts the chain's latency-bound head (MI355X, cavity with a disc,
 // ms/step without -> with: 2048^2 FP64 0.1732 -> 0.1624, FP32 0.1124 ->
 // 0.1072), and none on smaller ones, where it only slows the advection pass
@@ -402,17 +402,14 @@ static StampValid prev_valid(const lbrmt_ctx* c)
 static int bulk_early(const lbrmt_ctx* c)
 {
     if (c->bulk_early >= 0) return c->bulk_early;
-    return (long long)c->d.nx * c->d.ny >= 2048ll * 2048 ? 300 : 0;
+    return (long long)c->d.nx * c->d.ny >= 2048ll * 2048 ? 350 : 0;
 }
 
 static int fused_threads(const lbrmt_ctx* c)
 {
     if (c->fused_fit >= 0) return c->fused_fit;
     if (c->bulk_blocks > 0) return 0;
-    // FP64: blocks of 512 (198 registers, none spilled, two waves per SIMD)
-    // beside the bulk update, 0.1613 -> 0.1595 ms per 2048^2 step against
-    // 1024; FP32 keeps 1024 (0.1070 against 0.1091 at 512)
-    return c->d.precision == 0 ? 512 : 1024;
+    return 512;
 }
 
 // Step n on stream main_s.  With overlap the reference-map chain runs on the
@@ -2001,7 +1998,10 @@ struct lbrmt_batch {
     int lb_variant = 3;
     long long nodes = 0;  // interior nodes of all members (the autotune key)
     bool graph = true;
-    int fused_fit = 0;  // 1024: one extrapolation launch if every member can; 0 (-1): per layer
+    // the option as set: 1024, 0 (one launch per layer) or -1; not set or -1:
+    // one extrapolation launch if every member can
+    int fused_fit = 0;
+    bool fused_set = false;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t gsrc = nullptr;  // the captured graph of gexec
     long long step = 0;
@@ -2068,21 +2068,20 @@ int bfail(lbrmt_batch* b, const char* what, hipError_t e)
         if (e_ != hipSuccess) return bfail(b, #expr, e_); \
     } while (0)
 
-// argument tables of phase p (p = n mod 6 for n >= 1; p = 6 for n = 0)
-// with LBRMT_OPT_FUSED_FIT = 1024 the batch fits every member's layers in one
-// launch when every member can (one solid on walled axes, at most FF_LAYERS
-// layers).  Not the default: with many members the one launch holds thousands
-// of long 1024-thread blocks for a few hundred slots, where eleven launches
-// over all members keep the GPU fuller (96-member ensemble, FP32: 1.077
-// against 0.844 ms per step).
+// One extrapolation launch over every member's zone tiles, unless the option
+// asks for one launch per layer, or a member cannot (no solid, more than
+// FF_LAYERS layers, a short periodic axis): 96 cavities in FP32
+// 763 us per step layer by layer, 723 in one launch; 8 cavities in FP64 132
+// and 93
 bool batch_fused(const lbrmt_batch* b)
 {
-    if (b->fused_fit != 1024) return false;
+    if (b->fused_set && b->fused_fit == 0) return false;
     for (const lbrmt_ctx* c : b->m)
         if (c->nsolid == 0 || !fused_fit_ok(c->g)) return false;
     return true;
 }
 
+// argument tables of phase p (p = n mod 6 for n >= 1; p = 6 for n = 0)
 int batch_tables(lbrmt_batch* b)
 {
     const int n = b->n;
@@ -2336,6 +2335,7 @@ int lbrmt_batch_set_option(lbrmt_batch* b, int32_t option, int64_t value)
     case LBRMT_OPT_FUSED_FIT:
         if (value != -1 && value != 0 && value != 1024) return LBRMT_EINVAL;
         b->fused_fit = (int)value;
+        b->fused_set = value != -1;
         break;
     default:
         return LBRMT_EINVAL;

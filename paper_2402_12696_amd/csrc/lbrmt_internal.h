@@ -35,7 +35,15 @@ constexpr int FF_LAYERS = 11;         // fused extrapolation: most layers
 constexpr int FF_BLOCKS = 256;        // fused extrapolation: blocks striding over its tile list
 constexpr int FF_NO_CUT = 127;        // tile not stopped (cut_layer)
 constexpr int FF_REST_THREADS = 256;  // fused extrapolation: the one-block pass
-constexpr int FF_NORMALS = 1024;      // fused extrapolation: layer-1/2 normals found up front
+// side of a tile with its margin (2 (FF_LAYERS - 1) + 2 nodes around it)
+constexpr int FF_REGION = FF_TILE + 4 * (FF_LAYERS - 1) + 4;
+// most targets of a layer in a block's copy (a tile: typically 50 to 90; a
+// whole solid: up to 220 for a disc that fits the copy)
+constexpr int FF_LAYER = 192;
+constexpr int FF_LAYER_MB = 224;
+// fused extrapolation: threads of a block (two halves of 128 targets a pass;
+// up to 256 registers a lane, where 1024 threads would leave 128 and spill)
+constexpr int FF_THREADS = 512;
 constexpr int FF_BATCH_BLOCKS = 64;   // fused extrapolation of a batch: blocks per member
 
 // Several solids: the lattice is cut into force blocks of FB x FB nodes;
@@ -51,12 +59,11 @@ constexpr int MB_DT_BLOCKS = 8;
 // solid (4096^2 suspension of 400 solids: FP32 step 0.6157 -> 0.6120 ms
 // against 16, 0.637 at 32; 4 as fast as 8)
 constexpr int MB_BAND_BLOCKS = 8;
-// one block per solid runs all its layers; 768 threads leave 170 registers a
-// lane (1024 would leave 128, and both precisions would spill)
-constexpr int MB_FIT_THREADS_F64 = 768;
-constexpr int MB_FIT_THREADS_F32 = 768;
+// one block per solid runs all its layers
+constexpr int MB_FIT_THREADS_F64 = 512;
+constexpr int MB_FIT_THREADS_F32 = 512;
 // nodes of a several-solid fit block's LDS copy (its window dilated by 2)
-constexpr int MB_FIT_LDS_NODES = 8192;
+constexpr int MB_FIT_LDS_NODES = 7168;
 constexpr int MB_MAX_PER_BLOCK = 32;  // solids overlapping one force block
 // force combine of several solids: blocks striding over the stamped force
 // blocks (4096: suspension FP32 step 0.5416 -> 0.5370 ms against 2048)
@@ -551,7 +558,12 @@ hipError_t launch_layers(const GridP& g, const BandBufs& bb, int wslot, hipStrea
 // node, so that the one-block pass over stopped tiles takes most of them
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
                               hipStream_t st, int fused_threads);
-inline bool fused_fit_ok(const GridP& g) { return !g.px && !g.py && g.layers <= FF_LAYERS; }
+// (a periodic axis wraps inside a block's copy, which holds no node twice when
+// the period is at least as wide)
+inline bool fused_fit_ok(const GridP& g)
+{
+    return g.layers <= FF_LAYERS && (!g.px || g.nx >= FF_REGION) && (!g.py || g.ny >= FF_REGION);
+}
 __host__ __device__ inline long long fused_tiles(int nx, int ny)
 {
     return (long long)((nx + 2 * PAD + FF_TILE - 1) / FF_TILE) *
