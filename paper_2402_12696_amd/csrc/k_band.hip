@@ -443,27 +443,57 @@ __device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict_
 
 // Layers of Sec. 3.2: layer 1 = non-solid nodes 4-adjacent to the solid,
 // layer l = unmarked nodes 4-adjacent to layer l-1.  Inside a rectangle this
-// is the Manhattan distance to the solid set, computed here exactly in two
-// separable passes: per column, the distance to the nearest solid node of the
-// column (capped at layers + 1); per row, min over |e| of |e| + that distance.
-// One block takes a DTX x DTY tile of the window at a time: it stages the
-// solid flags of the tile plus a halo of `layers` nodes in LDS, runs both
-// passes there, writes the layer numbers and lists the zone nodes of each
-// layer (split into NSUB sub-lists by block so that few blocks share a
-// counter; the order inside a list does not matter since targets of one layer
-// are independent).  The layer counters were cleared by the kernel before.
+// is the Manhattan distance to the solid set, computed here exactly on tiles
+// of DTX x TH nodes with a halo of `layers` nodes.
+//
+// Up to DT_MASK_LAYERS layers (LC = 11, the count as a compile-time constant,
+// or LC = 0) a row of the region is one 64-bit word of solid flags: a wave
+// reads a row with one node per lane, coalesced, and ballots the signs; then
+// lane r holds row r, and a layer is one dilation of the region, d | d << 1 |
+// d >> 1 | the rows above and below (a lane to either side), whose new bits are
+// added to the planes of a bit-sliced layer number.  Every wave runs all of
+// it (14 instructions a layer), which spares the barriers between layers.
+// Bound by its chain of loads (window, level set) and, for a large solid, by
+// the advection's loads in flight (MI355X, pass over the solid of a 64^2
+// cavity 12.4 -> 8.9 us against scans of 38 x 54 flags in LDS with 16-row
+// tiles; 96 members of 96^2 .. 768^2, FP32, 107 -> 96 us).
+// More layers (LC = -1, the region wider than a word): two separable passes
+// over flags in LDS, per column the distance to the nearest solid node of the
+// column (capped at layers + 1), per row the minimum over |e| of |e| + that.
+//
+// Then the tile's tags are written and its zone nodes listed: for the
+// extrapolation in one launch the tile alone (ff_list), else the nodes of
+// each layer (lists, split into NSUB sub-lists by block so that few blocks
+// share a counter; the order inside a list does not matter since targets of
+// one layer are independent).  The counters were cleared by the kernels
+// before.
 constexpr int DTX = 32, DTY = 16;
-static_assert(DTX == FF_TILE && FF_TILE % DTY == 0, "a distance-transform tile lies in one fused-fit tile");
+// rows of a tile when no layer lists are made: fewer halo rows read per node,
+// and a tile is listed by its own block
+constexpr int DTY_FF = FF_TILE;
+static_assert(DTX == FF_TILE, "a fused-fit tile");
+constexpr int DT_MASK_LAYERS = 16;
+static_assert(DTX + 2 * DT_MASK_LAYERS <= 64 && DTY_FF + 2 * DT_MASK_LAYERS <= 64,
+              "a region's row is one word, its rows one wave's lanes");
+static_assert(FF_LAYERS <= DT_MASK_LAYERS, "DTY_FF tiles use the words");
 constexpr int DRW = DTX + 2 * MAX_LAYERS, DRH = DTY + 2 * MAX_LAYERS;
 
-// LC > 0: the layer count as a compile-time constant (scans unrolled);
-// LC = 0: the count of the grid.  ADV = false (initialisation): the solid set
-// is read from the tags.  ADV = true (a step): the solid set S^n = {interior,
-// phi^n < 0, inside the previous window} is read from the level set, the
-// tile's solid nodes are tagged and advected (Sec. 3.1) in the same pass, and
-// the tags of the window are all written here.
-template <int LC, bool ADV, typename S, bool PRE = false, bool LATCHK = false,
-          bool SPLIT = false>
+// the word of the lane below (r - 1) or above (r + 1), 0 beyond the wave
+template <int CTRL>
+__device__ __forceinline__ unsigned long long row_shift(unsigned long long v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, true);
+    return (unsigned long long)(unsigned)hi << 32 | (unsigned)lo;
+}
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
+
+// ADV = false (initialisation): the solid set is read from the tags.  ADV =
+// true (a step): the solid set S^n = {interior, phi^n < 0, inside the
+// previous window} is read from the level set, the tile's solid nodes are
+// tagged and advected (Sec. 3.1) in the same pass, and the tags of the window
+// are all written here.
+template <int LC, int TH, bool ADV, typename S, bool LATCHK = false, bool SPLIT = false>
 __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ win, int wslot,
                                              int wprev, int8_t* tag, int* lists, int* lcount,
                                              unsigned* health, const S* __restrict__ A,
@@ -471,23 +501,16 @@ __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ wi
                                              const double* __restrict__ fpy,
                                              const S* __restrict__ X, const S* __restrict__ Y,
                                              const S* __restrict__ phi, S* X1, S* Y1,
-                                             int* ff_flag = nullptr, int* ff_list = nullptr,
-                                             int* ff_n = nullptr)
+                                             int* ff_list = nullptr, int* ff_n = nullptr)
 {
-    __shared__ int8_t sol[DRH * DRW];   // solid flags of the tile and its halo
-    __shared__ int8_t gc[DTY * DRW];    // column distances of the tile rows
-    __shared__ int cnt[MAX_LAYERS + 1];
-    __shared__ int base[MAX_LAYERS + 1];
+    constexpr bool MASK = LC >= 0;
+    static_assert(MASK || TH == DTY, "the scans' region");
     const Rect W = window_of(win, wslot, g);
     if (!W.ok) return;
     const Rect D = window_of(win, wprev, g);
     const int L = LC > 0 ? LC : g.layers;
-    const long long cap = g.lcap;
-    const int sub = blockIdx.x % NSUB;
     const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
-    const int ntx = (w + DTX - 1) / DTX, nty = (h + DTY - 1) / DTY;
-    const int rw = DTX + 2 * L, rh = DTY + 2 * L;  // region in use
-    const int lane = __lane_id();
+    const int ntx = (w + DTX - 1) / DTX, nty = (h + TH - 1) / TH;
     // SPLIT (one solid): when the grid has at least ADV_MIN_WORKERS blocks
     // beyond the tiles, block t < ntile takes tile t without its advection,
     // and the blocks beyond advect the solid nodes of the window, 256 nodes
@@ -515,129 +538,190 @@ __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ wi
             return;
         }
     }
+    __shared__ int cnt[MAX_LAYERS + 1];
+    __shared__ int base[MAX_LAYERS + 1];
+    const long long cap = g.lcap;
+    const int sub = blockIdx.x % NSUB;
+    const int rw = DTX + 2 * L, rh = TH + 2 * L;  // region in use
+    const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    constexpr int NPT = DTX * TH / 256;  // nodes per thread, row-major in waves
+    // the nodes whose flag is read: the rest holds no solid
+    Rect Z = W;
+    if (ADV) {
+        Z.i0 = max(max(W.i0, D.i0), 0);
+        Z.i1 = min(min(W.i1, D.i1), g.nx - 1);
+        Z.j0 = max(max(W.j0, D.j0), 0);
+        Z.j1 = min(min(W.j1, D.j1), g.ny - 1);
+        Z.ok = D.ok && Z.i0 <= Z.i1 && Z.j0 <= Z.j1;
+    }
     for (int t = blockIdx.x; t < ntile; t += gridDim.x) {
-        const int x0 = W.i0 + (t % ntx) * DTX, y0 = W.j0 + (t / ntx) * DTY;
-        if (threadIdx.x <= MAX_LAYERS) cnt[threadIdx.x] = 0;
-        // solid flags of the region (nodes outside the window hold none).
-        // With PRE, FP32 steps with a compile-time layer count issue all of a
-        // thread's level-set loads before using any (one solid: advection
-        // pass 25.0 -> 23.1 us at 2048^2; with FP64 values the extra
-        // registers cost as much, and the several-solid pass at 4096^2 slows
-        // from 139 to 154 us)
-        constexpr bool PRELOAD = PRE && ADV && LC > 0 && sizeof(S) == 4;
-        if (PRELOAD) {
-            constexpr int NE = (DTX + 2 * LC) * (DTY + 2 * LC);
-            constexpr int NS = (NE + 255) / 256;  // 256 threads per block
-            S pv[NS];
-            bool inv[NS];
+        const int x0 = W.i0 + (t % ntx) * DTX, y0 = W.j0 + (t / ntx) * TH;
+        // (behind an empty asm: what follows from the thread's number is
+        // computed here, not held over the loop)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        int lay[NPT];       // layer number, 0: none
+        unsigned solid = 0; // bit u: node u is solid
+        bool zone = false;  // the zone reaches the tile
+        if constexpr (MASK) {
+            constexpr int NP = LC == 11 ? 4 : 5;  // planes of a layer number
+            __shared__ unsigned long long rows[64];
+            const int x = x0 - L + lane;
+            const bool xin = lane < rw && x >= Z.i0 && x <= Z.i1;
+            const int xc = xin ? x + PAD : W.i0 + PAD;
+            auto flag = [&](int r) {
+                const int y = y0 - L + r;
+                const bool in = Z.ok && r < rh && y >= Z.j0 && y <= Z.j1;  // (wave-uniform)
+                const int k = (in ? y + PAD : W.j0 + PAD) * g.pp + xc;
+                if (ADV) {
+                    const S p = phi[k];
+                    return in && xin && p < S(0);
+                }
+                return in && xin && tag[k] == TAG_SOLID;
+            };
+            if constexpr (LC > 0) {
+                // all of a wave's rows in flight together
+                constexpr int NR = (TH + 2 * LC + 3) / 4;
+                bool f[NR];
 #pragma unroll
-            for (int u = 0; u < NS; u++) {
-                const int e = threadIdx.x + u * 256;
-                const int x = x0 - L + e % rw, y = y0 - L + e / rw;
-                inv[u] = e < NE && W.has(x, y) && x >= 0 && x < g.nx && y >= 0 && y < g.ny &&
-                         D.has(x, y);
-                pv[u] = phi[inv[u] ? pidx(g, x, y) : pidx(g, W.i0, W.j0)];
-            }
+                for (int u = 0; u < NR; u++) f[u] = flag(wv + 4 * u);
+                __syncthreads();  // the previous tile's words are no longer read
 #pragma unroll
-            for (int u = 0; u < NS; u++) {
-                const int e = threadIdx.x + u * 256;
-                if (e < NE) sol[(e / rw) * DRW + e % rw] = inv[u] && pv[u] < S(0) ? 1 : 0;
-            }
-        }
-        for (int e = threadIdx.x; !PRELOAD && e < rw * rh; e += blockDim.x) {
-            const int x = x0 - L + e % rw, y = y0 - L + e / rw;
-            bool s = false;
-            if (ADV) {
-                const bool in = W.has(x, y) && x >= 0 && x < g.nx && y >= 0 && y < g.ny &&
-                                D.has(x, y);
-                const S p = phi[in ? pidx(g, x, y) : pidx(g, W.i0, W.j0)];
-                s = in && p < S(0);
+                for (int u = 0; u < NR; u++) {
+                    const unsigned long long b = __ballot(f[u]);
+                    if (lane == u) rows[wv + 4 * u] = b;
+                }
             } else {
-                const bool in = W.has(x, y);
-                const int8_t tv = tag[in ? pidx(g, x, y) : pidx(g, W.i0, W.j0)];
-                s = in && tv == TAG_SOLID;
+                __syncthreads();
+                for (int r = wv; r < rh; r += 4) {
+                    const unsigned long long b = __ballot(flag(r));
+                    if (lane == 0) rows[r] = b;
+                }
             }
-            sol[(e / rw) * DRW + e % rw] = s ? 1 : 0;
-        }
-        __syncthreads();
-        // column pass over the tile rows, the whole region width
-        for (int e = threadIdx.x; e < rw * DTY; e += blockDim.x) {
-            const int cx = e % rw, cy = e / rw;
-            int best = L + 1;
+            if (tid <= MAX_LAYERS) cnt[tid] = 0;
+            __syncthreads();
+            unsigned long long d = lane < rh ? rows[lane] : 0ull;
+            const unsigned ps = (unsigned)(d >> L);
+            unsigned pl[NP] = {}, any = 0;
 #pragma unroll
-            for (int d = -L; d <= L; d++)
-                if (sol[(cy + L + d) * DRW + cx]) best = min(best, abs(d));
-            gc[cy * DRW + cx] = (int8_t)best;
-        }
-        __syncthreads();
-        // row pass: DTX x DTY nodes, NPT per thread, row-major in waves; each
-        // node's slot in the block's share of its layer list comes from one
-        // LDS atomic per wave and layer present
-        constexpr int NPT = DTX * DTY / 256;
-        int lay[NPT], kk[NPT], slot[NPT];
+            for (int l = 1; l <= (LC > 0 ? LC : DT_MASK_LAYERS); l++) {
+                if (LC == 0 && l > L) break;
+                const unsigned long long n = d | d << 1 | d >> 1 | row_shift<DPP_WAVE_SHL1>(d) |
+                                             row_shift<DPP_WAVE_SHR1>(d);
+                const unsigned fresh = (unsigned)((n & ~d) >> L);
+                any |= fresh;
 #pragma unroll
-        for (int u = 0; u < NPT; u++) {
-            const int e = u * blockDim.x + threadIdx.x;
-            const int cx = e % DTX, cy = e / DTX;
-            const int x = x0 + cx, y = y0 + cy;
-            lay[u] = 0;
-            kk[u] = 0;
-            slot[u] = 0;
-            const bool solid = sol[(cy + L) * DRW + cx + L];
-            if (ADV && W.has(x, y) && solid) tag[pidx(g, x, y)] = TAG_SOLID;
-            if (W.has(x, y) && !solid) {
+                for (int b = 0; b < NP; b++)
+                    if (l >> b & 1) pl[b] |= fresh;
+                d = n;
+            }
+            const unsigned cols = W.i1 - x0 >= 31 ? ~0u : (2u << (W.i1 - x0)) - 1u;
+            zone = __ballot(lane >= L && lane < L + TH && y0 + lane - L <= W.j1 &&
+                            (any & cols) != 0) != 0ull;
+#pragma unroll
+            for (int u = 0; u < NPT; u++) {
+                const int e = u * 256 + tid, cx = e % DTX, src = L + e / DTX;
+                int l = 0;
+#pragma unroll
+                for (int b = 0; b < NP; b++) l |= ((unsigned)__shfl((int)pl[b], src) >> cx & 1u) << b;
+                lay[u] = l;
+                solid |= ((unsigned)__shfl((int)ps, src) >> cx & 1u) << u;
+            }
+        } else {
+            __shared__ int8_t sol[DRH * DRW];  // solid flags of the tile and its halo
+            __shared__ int8_t gc[DTY * DRW];   // column distances of the tile rows
+            __syncthreads();
+            if (tid <= MAX_LAYERS) cnt[tid] = 0;
+            for (int e = tid; e < rw * rh; e += blockDim.x) {
+                const int x = x0 - L + e % rw, y = y0 - L + e / rw;
+                const bool in = Z.ok && x >= Z.i0 && x <= Z.i1 && y >= Z.j0 && y <= Z.j1;
+                const long long k = in ? pidx(g, x, y) : pidx(g, W.i0, W.j0);
+                bool s;
+                if (ADV) s = in && phi[k] < S(0);
+                else s = in && tag[k] == TAG_SOLID;
+                sol[(e / rw) * DRW + e % rw] = s ? 1 : 0;
+            }
+            __syncthreads();
+            // column pass over the tile rows, the whole region width
+            for (int e = tid; e < rw * DTY; e += blockDim.x) {
+                const int cx = e % rw, cy = e / rw;
+                int best = L + 1;
+                for (int d = -L; d <= L; d++)
+                    if (sol[(cy + L + d) * DRW + cx]) best = min(best, abs(d));
+                gc[cy * DRW + cx] = (int8_t)best;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NPT; u++) {
+                const int e = u * 256 + tid;
+                const int cx = e % DTX, cy = e / DTX;
+                if (sol[(cy + L) * DRW + cx + L]) solid |= 1u << u;
                 int best = 2 * L + 2;
-#pragma unroll
                 for (int d = -L; d <= L; d++) best = min(best, abs(d) + gc[cy * DRW + cx + L + d]);
-                kk[u] = (int)pidx(g, x, y);
-                if (best <= L) lay[u] = best;
-                tag[kk[u]] = lay[u] > 0 ? (int8_t)lay[u] : TAG_NONE;
-            }
-            for (int l = 1; l <= L; l++) {
-                const unsigned long long mask = __ballot(lay[u] == l);
-                if (mask == 0ull) continue;
-                const int leader = __ffsll((long long)mask) - 1;
-                int wb = 0;
-                if (lane == leader) wb = atomicAdd(&cnt[l], __popcll(mask));
-                wb = __shfl(wb, leader);
-                if (lay[u] == l) slot[u] = wb + __popcll(mask & ((1ull << lane) - 1ull));
+                lay[u] = best <= L && !(solid >> u & 1) ? best : 0;
             }
         }
-        __syncthreads();
-        // one reservation per layer present in the tile
-        if (threadIdx.x >= 1 && threadIdx.x <= L && cnt[threadIdx.x] > 0)
-            base[threadIdx.x] =
-                atomicAdd(&lcount[(threadIdx.x * NSUB + sub) * LCOUNT_PAD], cnt[threadIdx.x]);
-        // the fused extrapolation's tile (FF_TILE square, same origin) holding
-        // this one is listed once if the zone reaches it
-        if (ff_list && threadIdx.x == 0) {
-            bool zone = false;
-            for (int l = 1; l <= L; l++) zone = zone || cnt[l] > 0;
-            if (zone) {
-                const int ft = (x0 - W.i0) / FF_TILE +
-                               ((y0 - W.j0) / FF_TILE) * ((w + FF_TILE - 1) / FF_TILE);
-                if (atomicExch(&ff_flag[ft], 1) == 0) ff_list[atomicAdd(ff_n, 1)] = ft;
-            }
-        }
-        __syncthreads();
+        // tags (a wave covers two rows of the tile)
 #pragma unroll
         for (int u = 0; u < NPT; u++) {
-            if (lay[u] > 0) {
-                const long long at = (long long)base[lay[u]] + slot[u];
-                if (at < cap) lists[(lay[u] * NSUB + sub) * cap + at] = kk[u];
-                else atomicAdd(&health[7], 1u);  // beyond the sub-list capacity
+            const int e = u * 256 + tid;
+            const int x = x0 + e % DTX, y = y0 + e / DTX;
+            const bool in = x <= W.i1 && y <= W.j1, s = solid >> u & 1;
+            if (!in) {
+                lay[u] = 0;
+                solid &= ~(1u << u);
+            } else if (ADV || !s) {
+                tag[pidx(g, x, y)] = s ? TAG_SOLID : lay[u] > 0 ? (int8_t)lay[u] : TAG_NONE;
+            }
+        }
+        if (ff_list) {
+            // the tile is the fused extrapolation's (TH = FF_TILE)
+            if (zone && tid == 0) ff_list[atomicAdd(ff_n, 1)] = t;
+        } else {
+            // each node's slot in the block's share of its layer list comes
+            // from one LDS atomic per wave and layer present
+            int slot[NPT];
+#pragma unroll
+            for (int u = 0; u < NPT; u++) {
+                slot[u] = 0;
+                for (int l = 1; l <= L; l++) {
+                    const unsigned long long mask = __ballot(lay[u] == l);
+                    if (mask == 0ull) continue;
+                    const int leader = __ffsll((long long)mask) - 1;
+                    int wb = 0;
+                    if (lane == leader) wb = atomicAdd(&cnt[l], __popcll(mask));
+                    wb = __shfl(wb, leader);
+                    if (lay[u] == l) slot[u] = wb + __popcll(mask & ((1ull << lane) - 1ull));
+                }
+            }
+            __syncthreads();
+            // one reservation per layer present in the tile
+            if (tid >= 1 && tid <= L && cnt[tid] > 0)
+                base[tid] =
+                    atomicAdd(&lcount[(tid * NSUB + sub) * LCOUNT_PAD], cnt[tid]);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NPT; u++) {
+                if (lay[u] > 0) {
+                    const int e = u * 256 + tid;
+                    const long long at = (long long)base[lay[u]] + slot[u];
+                    if (at < cap)
+                        lists[(lay[u] * NSUB + sub) * cap + at] =
+                            (int)pidx(g, x0 + e % DTX, y0 + e / DTX);
+                    else atomicAdd(&health[7], 1u);  // beyond the sub-list capacity
+                }
             }
         }
         if (adv_here) {
             // advection of the tile's solid nodes
-            for (int e = threadIdx.x; e < DTX * DTY; e += blockDim.x) {
-                const int cx = e % DTX, cy = e / DTX;
-                const int x = x0 + cx, y = y0 + cy;
-                if (W.has(x, y) && sol[(cy + L) * DRW + cx + L])
-                    advect_node<S, LATCHK>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, x, y, health);
+#pragma unroll 1
+            for (int u = 0; u < NPT; u++) {
+                const int e = u * 256 + tid;
+                if (solid >> u & 1)
+                    advect_node<S, LATCHK>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, x0 + e % DTX,
+                                           y0 + e / DTX, health);
             }
         }
-        __syncthreads();
     }
 }
 
@@ -647,15 +731,15 @@ __global__ __launch_bounds__(256) void k_dt_tile(GridP g, const Win* __restrict_
                                                  int8_t* tag, int* lists, int* lcount,
                                                  unsigned* health)
 {
-    dt_tile_body<LC, false, double>(g, win, wslot, 0, tag, lists, lcount, health, nullptr,
-                                    nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    dt_tile_body<LC, DTY, false, double>(g, win, wslot, 0, tag, lists, lcount, health, nullptr,
+                                         nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                         nullptr);
 }
 
 // a step: advection of xi plus the layers of the extrapolation zone
-// FP64: five waves per SIMD (96 registers, a few spilled) run the 2048
-// blocks in fewer rounds (2048^2 step 0.1626 -> 0.1614 ms); FP32 spills more
-// at five and is left as the compiler sizes it
-template <int LC, typename S>
+// FP64: five waves per SIMD (96 registers) run the 2048 blocks in fewer
+// rounds (2048^2 step 0.1626 -> 0.1614 ms); FP32 needs 73 and runs six
+template <int LC, int TH, typename S>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 5 : 1, 8))) void k_advect_dt(
     GridP g, const S* __restrict__ A,
@@ -666,57 +750,74 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 5 : 1, 8))) void k_advect_dt
                                                    const S* __restrict__ phi, S* X1, S* Y1,
                                                    int8_t* tag, const Win* __restrict__ win,
                                                    int wprev, int wcur, int* lists, int* lcount,
-                                                   unsigned* health, int* ff_flag, int* ff_list,
-                                                   int* ff_n)
+                                                   unsigned* health, int* ff_list, int* ff_n)
 {
-    dt_tile_body<LC, true, S, true, true, true>(g, win, wcur, wprev, tag, lists, lcount, health,
-                                                A, fpx, fpy, X, Y, phi, X1, Y1, ff_flag, ff_list,
-                                                ff_n);
+    dt_tile_body<LC, TH, true, S, true, true>(g, win, wcur, wprev, tag, lists, lcount, health, A,
+                                              fpx, fpy, X, Y, phi, X1, Y1, ff_list, ff_n);
 }
 
 // five waves per SIMD: the suspension's 6400 blocks (400 solids) run in
 // fewer rounds (FP32 step 0.634 -> 0.619 ms; FP64 0.998 -> 0.994)
-template <int LC, typename S>
+template <int LC, int TH, typename S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void kb_advect_dt(
     const AdvectArgs* __restrict__ args, const int* __restrict__ ord)
 {
     const AdvectArgs& a = args[ord ? ord[blockIdx.y] : blockIdx.y];
-    dt_tile_body<LC, true, S>(a.g, a.win, a.wcur, a.wprev, a.tag, a.lists, a.lcount, a.health,
-                              (const S*)a.A, a.fpx, a.fpy, (const S*)a.X, (const S*)a.Y,
-                              (const S*)a.phi, (S*)a.X1, (S*)a.Y1, a.ff_flag, a.ff_list, a.ff_n);
+    dt_tile_body<LC, TH, true, S>(a.g, a.win, a.wcur, a.wprev, a.tag, a.lists, a.lcount, a.health,
+                                  (const S*)a.A, a.fpx, a.fpy, (const S*)a.X, (const S*)a.Y,
+                                  (const S*)a.phi, (S*)a.X1, (S*)a.Y1, a.ff_list, a.ff_n);
 }
+
+// the kernel of a layer count and of the tile rows: KERN(LC, TH)
+#define DT_DISPATCH(LAYERS, FUSED, KERN)            \
+    do {                                            \
+        if (FUSED) {                                \
+            if ((LAYERS) == 11) KERN(11, DTY_FF);   \
+            else KERN(0, DTY_FF);                   \
+        } else if ((LAYERS) == 11) {                \
+            KERN(11, DTY);                          \
+        } else if ((LAYERS) <= DT_MASK_LAYERS) {    \
+            KERN(0, DTY);                           \
+        } else {                                    \
+            KERN(-1, DTY);                          \
+        }                                           \
+    } while (0)
 
 hipError_t launch_advect_layers(const GridP& g, int precision, const BandBufs& bb,
                                 const StepSlots& s, const void* A, const double* fpx,
                                 const double* fpy, hipStream_t st, bool fused)
 {
-    int* ffl = fused ? bb.ff_flag : nullptr;
     int* ffs = fused ? bb.ff_list : nullptr;
     int* ffn = fused ? bb.ff_n : nullptr;
-#define ADT(LC, S)                                                                                \
-    k_advect_dt<LC, S><<<DT_BLOCKS, 256, 0, st>>>(                                              \
+    // blocks beyond the tiles of the largest window and one advection thread
+    // per node of it find nothing to do
+    const long long ths = fused ? DTY_FF : DTY;
+    const long long tiles = ((g.nx + 2 * PAD + DTX - 1) / DTX) * ((g.ny + 2 * PAD + ths - 1) / ths);
+    const long long nodes = ((long long)g.nx * g.ny + 255) / 256;
+    const long long want = tiles + std::max<long long>(nodes, ADV_MIN_WORKERS);
+    const int blocks = (int)std::min<long long>(DT_BLOCKS, want);
+#define ADT(S, LC, TH)                                                                            \
+    k_advect_dt<LC, TH, S><<<blocks, 256, 0, st>>>(                                             \
         g, (const S*)A, fpx, fpy, (const S*)bb.X[s.cur], (const S*)bb.Y[s.cur],                   \
         (const S*)bb.phi[s.cur], (S*)bb.X[s.nxt], (S*)bb.Y[s.nxt], bb.tag, bb.win, s.wprev,      \
-        s.wcur, bb.lists, bb.lcount, bb.health, ffl, ffs, ffn)
-    if (precision == 0) {
-        if (g.layers == 11) ADT(11, double);
-        else ADT(0, double);
-    } else {
-        if (g.layers == 11) ADT(11, float);
-        else ADT(0, float);
-    }
+        s.wcur, bb.lists, bb.lcount, bb.health, ffs, ffn)
+#define ADT_D(LC, TH) ADT(double, LC, TH)
+#define ADT_F(LC, TH) ADT(float, LC, TH)
+    if (precision == 0) DT_DISPATCH(g.layers, fused, ADT_D);
+    else DT_DISPATCH(g.layers, fused, ADT_F);
+#undef ADT_F
+#undef ADT_D
 #undef ADT
     return hipGetLastError();
 }
 
 hipError_t launch_layers(const GridP& g, const BandBufs& bb, int wslot, hipStream_t st)
 {
-    if (g.layers == 11)
-        k_dt_tile<11><<<DT_BLOCKS, 256, 0, st>>>(g, bb.win, wslot, bb.tag, bb.lists, bb.lcount,
-                                                 bb.health);
-    else
-        k_dt_tile<0><<<DT_BLOCKS, 256, 0, st>>>(g, bb.win, wslot, bb.tag, bb.lists, bb.lcount,
-                                                bb.health);
+#define KDT(LC, TH)                                                                              \
+    k_dt_tile<LC><<<DT_BLOCKS, 256, 0, st>>>(g, bb.win, wslot, bb.tag, bb.lists, bb.lcount,      \
+                                             bb.health)
+    DT_DISPATCH(g.layers, false, KDT);
+#undef KDT
     return hipGetLastError();
 }
 
@@ -1293,39 +1394,42 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
 }
 
 // The tiles k_fit_fused stopped (k_fit_rest, one block): fits, layer by
-// layer from the first to the last, every target of the layer lists that
-// lies in a stopped tile at or after the layer where that tile stopped (full
-// scan windows up to r_max, the per-layer path's fit), then clears that list
-// and the list of zone tiles.  With no tile stopped it only clears the lists.
+// layer from the first to the last, every target that lies in a stopped tile
+// at or after the layer where that tile stopped (found by the tile's tags;
+// full scan windows up to r_max, the per-layer path's fit), then clears that
+// list and the list of zone tiles.  With no tile stopped it only clears the
+// lists.
 template <typename T, int NT>
 __device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, int wprev,
-                         int8_t* tag, const int* __restrict__ lists,
-                         const int* __restrict__ lcount, const T* __restrict__ phin, T* X1,
-                         T* Y1, unsigned* health, int8_t* cut_layer, const int* cut_tiles,
-                         int* ncut, int* ff_flag, const int* ff_list, int* ff_n)
+                         int8_t* tag, const T* __restrict__ phin, T* X1, T* Y1,
+                         unsigned* health, int8_t* cut_layer, const int* cut_tiles, int* ncut,
+                         int* ff_n)
 {
-    constexpr int NG = NT / FIT_LANES;
-    // this thread's first list entry is loaded together with the two counters
-    // (the list holds one entry per fused-extrapolation tile of the grid, at
-    // least one); the windows are read only when a tile was stopped
-    const int a0 = threadIdx.x;
-    const int e0 = ff_list[min((long long)a0, fused_tiles(g.nx, g.ny) - 1)];
-    const int nt = *ff_n, nc = *ncut;
-    const long long cap = g.lcap;
+    constexpr int NG = NT / FIT_LANES, NN = FF_TILE * FF_TILE;
+    __shared__ int lst[NN], cn;
+    const int nc = *ncut;
     const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
     if (nc > 0) {
         const Rect W = window_of(win, wcur, g);
         const Rect D = window_of(win, wprev, g);
         const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
         for (int l = 1; l <= g.layers; l++) {
-            for (int s = 0; s < NSUB; s++) {
-                const int* list = lists + (l * NSUB + s) * cap;
-                const int ns = (int)min((long long)lcount[(l * NSUB + s) * LCOUNT_PAD], cap);
-                for (int a = grp; a < ns; a += NG) {
-                    const int kt = list[a];
+            for (int c = 0; c < nc; c++) {
+                const int t = cut_tiles[c];
+                if (cut_layer[t] > l) continue;
+                const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
+                if (threadIdx.x == 0) cn = 0;
+                __syncthreads();
+                for (int e = threadIdx.x; e < NN; e += NT) {
+                    const int x = x0 + e % FF_TILE, y = y0 + e / FF_TILE;
+                    const int kt = (int)pidx(g, min(x, W.i1), min(y, W.j1));
+                    if (tag[kt] == l && W.has(x, y)) lst[atomicAdd(&cn, 1)] = kt;
+                }
+                __syncthreads();
+                const int n = cn;
+                for (int a = grp; a < n; a += NG) {
+                    const int kt = lst[a];
                     const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
-                    const int t = (i - W.i0) / FF_TILE + ((j - W.j0) / FF_TILE) * ntx;
-                    if (cut_layer[t] > l) continue;
                     T xo = T(0), yo = T(0);
                     const bool done = fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin,
                                                           X1, Y1, xo, yo);
@@ -1339,12 +1443,11 @@ __device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, 
                         }
                     }
                 }
+                __syncthreads();
             }
-            __syncthreads();
         }
     }
     // the lists of the next step start empty
-    for (int a = threadIdx.x; a < nt; a += NT) ff_flag[a == a0 ? e0 : ff_list[a]] = 0;
     for (int a = threadIdx.x; a < nc; a += NT) cut_layer[cut_tiles[a]] = FF_NO_CUT;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1429,10 +1532,8 @@ template <typename T>
 __global__ __launch_bounds__(FF_REST_THREADS) void kb_fit_rest(const FitArgs* __restrict__ args)
 {
     const FitArgs& a = args[blockIdx.y];
-    fit_rest<T, FF_REST_THREADS>(a.g, a.win, a.wcur, a.wprev, a.tag, a.lists, a.lcount,
-                                 (const T*)a.phin,
-                                 (T*)a.X1, (T*)a.Y1, a.health, a.cut_layer, a.cut_tiles, a.ncut,
-                                 a.ff_flag, a.ff_list, a.ff_n);
+    fit_rest<T, FF_REST_THREADS>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1,
+                                 (T*)a.Y1, a.health, a.cut_layer, a.cut_tiles, a.ncut, a.ff_n);
 }
 
 // fit_rest in a block of FF_REST_THREADS threads, which finds a free slot
@@ -1440,12 +1541,11 @@ __global__ __launch_bounds__(FF_REST_THREADS) void kb_fit_rest(const FitArgs* __
 template <typename T>
 __global__ __launch_bounds__(FF_REST_THREADS) void k_fit_rest(
     GridP g, const Win* __restrict__ win, int wcur, int wprev, int8_t* tag,
-    const int* __restrict__ lists, const int* __restrict__ lcount, const T* __restrict__ phin,
-    T* X1, T* Y1, unsigned* health, int8_t* cut_layer, const int* cut_tiles, int* ncut,
-    int* ff_flag, const int* ff_list, int* ff_n)
+    const T* __restrict__ phin, T* X1, T* Y1, unsigned* health, int8_t* cut_layer,
+    const int* cut_tiles, int* ncut, int* ff_n)
 {
-    fit_rest<T, FF_REST_THREADS>(g, win, wcur, wprev, tag, lists, lcount, phin, X1, Y1, health,
-                                 cut_layer, cut_tiles, ncut, ff_flag, ff_list, ff_n);
+    fit_rest<T, FF_REST_THREADS>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_layer,
+                                 cut_tiles, ncut, ff_n);
 }
 
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
@@ -1467,9 +1567,8 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
         if (fused_threads == 256) FUSED(T, 256);                                                  \
         else FUSED(T, FF_THREADS);                                                                \
         k_fit_rest<T><<<1, FF_REST_THREADS, 0, st>>>(                                             \
-            g, bb.win, s.wcur, s.wprev, bb.tag, bb.lists, bb.lcount, (const T*)bb.phi[s.cur],     \
-            (T*)bb.X[s.nxt], (T*)bb.Y[s.nxt], bb.health, bb.cut_layer, bb.cut_tiles, bb.ncut,     \
-            bb.ff_flag, bb.ff_list, bb.ff_n);                                                     \
+            g, bb.win, s.wcur, s.wprev, bb.tag, (const T*)bb.phi[s.cur], (T*)bb.X[s.nxt],         \
+            (T*)bb.Y[s.nxt], bb.health, bb.cut_layer, bb.cut_tiles, bb.ncut, bb.ff_n);            \
     } while (0)
         if (g.rm32) FUSED_T(float);
         else FUSED_T(double);
@@ -2561,8 +2660,9 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
     // members' advection pass lists those tiles)
     const dim3 g1(1, nsim), gz(FF_BATCH_BLOCKS, nsim);
     if (precision == 0) {
-        if (layers == 11) kb_advect_dt<11, double><<<gd, 256, 0, st>>>(t.adv, t.ord);
-        else kb_advect_dt<0, double><<<gd, 256, 0, st>>>(t.adv, t.ord);
+#define ADB(LC, TH) kb_advect_dt<LC, TH, double><<<gd, 256, 0, st>>>(t.adv, t.ord)
+        DT_DISPATCH(layers, fused, ADB);
+#undef ADB
         if (fused) {
             if (layers == FF_LAYERS) kb_fit_fused<double, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
             else kb_fit_fused<double, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
@@ -2578,8 +2678,9 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
         if (relabel_only) kb_force<2, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
         else kb_force<0, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
     } else {
-        if (layers == 11) kb_advect_dt<11, float><<<gd, 256, 0, st>>>(t.adv, t.ord);
-        else kb_advect_dt<0, float><<<gd, 256, 0, st>>>(t.adv, t.ord);
+#define ADB(LC, TH) kb_advect_dt<LC, TH, float><<<gd, 256, 0, st>>>(t.adv, t.ord)
+        DT_DISPATCH(layers, fused, ADB);
+#undef ADB
         if (fused) {
             if (layers == FF_LAYERS) kb_fit_fused<float, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
             else kb_fit_fused<float, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);

@@ -110,7 +110,7 @@ struct Layout {
     size_t rm_es;  // bytes per reference-map value: 8 (FP64 xi) or 4 (FP32 displacement)
     size_t off_lat[2], off_fx[2], off_fy[2], off_drho, off_X[2], off_Y[2], off_phi[2], off_tag,
         off_win, off_health, off_dpart, off_dout, off_gcol, off_lists, off_lcount, off_boxpart,
-        off_ticket, off_cut_layer, off_cut_tiles, off_ncut, off_ff_flag, off_ff_list, off_ff_n,
+        off_ticket, off_cut_layer, off_cut_tiles, off_ncut, off_ff_list, off_ff_n,
         total;
     size_t lat_bytes;
     // several solids
@@ -160,7 +160,6 @@ Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
     L.off_cut_layer = take(ntile);
     L.off_cut_tiles = take(ntile * 4);
     L.off_ncut = take(4);
-    L.off_ff_flag = take(ntile * 4);
     L.off_ff_list = take(ntile * 4);
     L.off_ff_n = take(4);
     L.off_win = take(3 * sizeof(Win));
@@ -721,7 +720,6 @@ static int create_impl(const lbrmt_grid_desc* d, int32_t max_solids, void* ws, s
     c->bb.cut_layer = (int8_t*)(c->ws + L.off_cut_layer);
     c->bb.cut_tiles = (int*)(c->ws + L.off_cut_tiles);
     c->bb.ncut = (int*)(c->ws + L.off_ncut);
-    c->bb.ff_flag = (int*)(c->ws + L.off_ff_flag);
     c->bb.ff_list = (int*)(c->ws + L.off_ff_list);
     c->bb.ff_n = (int*)(c->ws + L.off_ff_n);
     c->bb.win = (Win*)(c->ws + L.off_win);
@@ -890,7 +888,6 @@ static BandBufs mb_bufs(const lbrmt_ctx* c, int k)
     b.cut_layer = nullptr;  // one launch per layer for several solids
     b.cut_tiles = nullptr;
     b.ncut = nullptr;
-    b.ff_flag = nullptr;
     b.ff_list = nullptr;
     b.ff_n = nullptr;
     return b;
@@ -1025,7 +1022,6 @@ static hipError_t clear_cut_tiles(lbrmt_ctx* c, hipStream_t st)
     const size_t nt = (size_t)fused_tiles(c->d.nx, c->d.ny);
     hipError_t e = hipMemsetAsync(c->bb.cut_layer, FF_NO_CUT, nt, st);
     if (e == hipSuccess) e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_flag, 0, nt * 4, st);
     if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_n, 0, 4, st);
     return e;
 }
@@ -2109,14 +2105,14 @@ int batch_tables(lbrmt_batch* b)
             adv[k] = AdvectArgs{g, c->lat[s.cur], c->Fx[s.nxt], c->Fy[s.nxt], c->bb.X[s.cur],
                                 c->bb.Y[s.cur], c->bb.phi[s.cur], c->bb.X[s.nxt], c->bb.Y[s.nxt],
                                 c->bb.tag, c->bb.win, s.wprev, s.wcur, c->bb.lists,
-                                c->bb.lcount, c->bb.health, ff ? c->bb.ff_flag : nullptr,
-                                ff ? c->bb.ff_list : nullptr, ff ? c->bb.ff_n : nullptr};
+                                c->bb.lcount, c->bb.health, ff ? c->bb.ff_list : nullptr,
+                                ff ? c->bb.ff_n : nullptr};
             lay[k] = LayersArgs{g, c->bb.win, s.wcur, c->bb.tag, c->bb.gcol, c->bb.lists,
                                 c->bb.lcount, c->bb.health};
             fit[k] = FitArgs{g, c->bb.win, s.wcur, s.wprev, c->bb.tag, c->bb.lists, c->bb.lcount,
                              c->bb.phi[s.cur], c->bb.X[s.nxt], c->bb.Y[s.nxt], c->bb.health,
-                             c->bb.cut_layer, c->bb.cut_tiles, c->bb.ncut, c->bb.ff_flag,
-                             c->bb.ff_list, c->bb.ff_n};
+                             c->bb.cut_layer, c->bb.cut_tiles, c->bb.ncut, c->bb.ff_list,
+                             c->bb.ff_n};
             edg[k] = EdgesArgs{g, c->body, c->bb.win, s.wcur, c->bb.boxpart, c->bb.X[s.nxt],
                                c->bb.Y[s.nxt], c->bb.tag, c->bb.phi[s.nxt], c->Fx[s.cur],
                                c->Fy[s.cur], c->drho, c->bb.lcount, c->bb.health};

@@ -144,8 +144,7 @@ struct BandBufs {
     int* cut_tiles;
     int* ncut;
     // fused extrapolation: the tiles the zone reaches, listed once each by
-    // the distance transform (flag per tile, list, count; cleared each step)
-    int* ff_flag;
+    // the distance transform (list and count; cleared each step)
     int* ff_list;
     int* ff_n;
 };
@@ -264,7 +263,7 @@ struct AdvectArgs {
     int* lcount;
     unsigned* health;
     // the fused extrapolation's zone-tile list (null: not built)
-    int *ff_flag, *ff_list, *ff_n;
+    int *ff_list, *ff_n;
 };
 struct LayersArgs {
     GridP g;
@@ -288,7 +287,7 @@ struct FitArgs {
     unsigned* health;
     // the fused extrapolation's buffers (batches of single-solid members)
     int8_t* cut_layer;
-    int *cut_tiles, *ncut, *ff_flag, *ff_list, *ff_n;
+    int *cut_tiles, *ncut, *ff_list, *ff_n;
 };
 struct EdgesArgs {
     GridP g;
