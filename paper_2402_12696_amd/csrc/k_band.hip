@@ -127,6 +127,50 @@ __device__ __forceinline__ bool tag_set(int t)
 
 // ---------------------------------------------------------------- block helpers
 
+// true in exactly one block: the last to arrive (all blocks must call it)
+__device__ bool last_block(unsigned* ticket)
+{
+    __shared__ bool last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (last) __threadfence();
+    return last;
+}
+
+// The same among n blocks in the passes of a step, without the fences: a
+// release writes back all that an XCD's L2 holds dirty, which beside a
+// lattice update of 2048^2 nodes costs more than the launch it saves (force
+// pass 64 -> 141 us, FP64).  What the last block reads of the others goes
+// through that cache by itself (through()), and every thread waits for its
+// stores before its block arrives; the last block reads it by seen() or after
+// a fence.  It leaves the ticket 0.
+template <typename V>
+__device__ __forceinline__ void through(V* p, V v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename V>
+__device__ __forceinline__ V seen(const V* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool last_arrival(unsigned* ticket, int n)
+{
+    __shared__ bool last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = atomicAdd(ticket, 1u) == (unsigned)n - 1u;
+        if (last) *ticket = 0u;
+    }
+    __syncthreads();
+    return last;
+}
+
 // box of the block's flagged nodes, stored as one partial per block
 __device__ void block_box(int i0, int i1, int j0, int j1, int* out4)
 {
@@ -151,29 +195,16 @@ __device__ void block_box(int i0, int i1, int j0, int j1, int* out4)
             j0 = min(j0, sb[2][w]);
             j1 = max(j1, sb[3][w]);
         }
-        out4[0] = i0;
-        out4[1] = i1;
-        out4[2] = j0;
-        out4[3] = j1;
+        // (through the cache: the last block of a pass may read them)
+        through(&out4[0], i0);
+        through(&out4[1], i1);
+        through(&out4[2], j0);
+        through(&out4[3], j1);
     }
     __syncthreads();
 }
 
 // reduce n partial boxes into one window slot (called by a whole block)
-
-// true in exactly one block: the last to arrive (all blocks must call it)
-__device__ bool last_block(unsigned* ticket)
-{
-    __shared__ bool last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (last) __threadfence();
-    return last;
-}
 
 // ---------------------------------------------------------------- window ring
 
@@ -1352,8 +1383,8 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN>& s, const GridP&
         const int q = (y - R.y0) * rw + x - R.x0, l = s.st[q];
         if (l >= 1 && l <= last && W.has(x, y)) {
             const long long kt = pidx(g, x, y);
-            X1[kt] = s.val[q + 1].x;
-            Y1[kt] = s.val[q + 1].y;
+            through(&X1[kt], T(s.val[q + 1].x));  // (read by fit_rest, if it runs)
+            through(&Y1[kt], T(s.val[q + 1].y));
         }
     }
 }
@@ -1393,66 +1424,51 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
     }
 }
 
-// The tiles k_fit_fused stopped (k_fit_rest, one block): fits, layer by
-// layer from the first to the last, every target that lies in a stopped tile
-// at or after the layer where that tile stopped (found by the tile's tags;
-// full scan windows up to r_max, the per-layer path's fit), then clears that
-// list and the list of zone tiles.  With no tile stopped it only clears the
-// lists.
+// The stopped tiles of a fused extrapolation (one block, the last to end):
+// fits, layer by layer from the first to the last, every target that lies in
+// a stopped tile at or after the layer where that tile stopped (found by the
+// tile's tags; full scan windows up to r_max, the per-layer path's fit).
+// lst: FF_TILE^2 entries of LDS, cn one
 template <typename T, int NT>
-__device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, int wprev,
-                         int8_t* tag, const T* __restrict__ phin, T* X1, T* Y1,
-                         unsigned* health, int8_t* cut_layer, const int* cut_tiles, int* ncut,
-                         int* ff_n)
+__device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* tag,
+                         const T* __restrict__ phin, T* X1, T* Y1, unsigned* health,
+                         const int* cut_tiles, int nc, int* lst, int* cn)
 {
-    constexpr int NG = NT / FIT_LANES, NN = FF_TILE * FF_TILE;
-    __shared__ int lst[NN], cn;
-    const int nc = *ncut;
+    constexpr int NG = NT / FIT_LANES;
     const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
-    if (nc > 0) {
-        const Rect W = window_of(win, wcur, g);
-        const Rect D = window_of(win, wprev, g);
-        const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
-        for (int l = 1; l <= g.layers; l++) {
-            for (int c = 0; c < nc; c++) {
-                const int t = cut_tiles[c];
-                if (cut_layer[t] > l) continue;
-                const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
-                if (threadIdx.x == 0) cn = 0;
-                __syncthreads();
-                for (int e = threadIdx.x; e < NN; e += NT) {
-                    const int x = x0 + e % FF_TILE, y = y0 + e / FF_TILE;
-                    const int kt = (int)pidx(g, min(x, W.i1), min(y, W.j1));
-                    if (tag[kt] == l && W.has(x, y)) lst[atomicAdd(&cn, 1)] = kt;
-                }
-                __syncthreads();
-                const int n = cn;
-                for (int a = grp; a < n; a += NG) {
-                    const int kt = lst[a];
-                    const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
-                    T xo = T(0), yo = T(0);
-                    const bool done = fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin,
-                                                          X1, Y1, xo, yo);
-                    if (sub == 0) {
-                        if (done) {
-                            X1[kt] = xo;
-                            Y1[kt] = yo;
-                        } else {
-                            tag[kt] = (int8_t)(l | TAG_FAIL);
-                            atomicAdd(&health[1], 1u);
-                        }
+    const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
+    for (int l = 1; l <= g.layers; l++) {
+        for (int c = 0; c < nc; c++) {
+            const int t = cut_tiles[c] & FF_CUT_TILE;
+            if (cut_tiles[c] >> FF_CUT_SHIFT > l) continue;
+            const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
+            if (threadIdx.x == 0) *cn = 0;
+            __syncthreads();
+            for (int e = threadIdx.x; e < FF_TILE * FF_TILE; e += NT) {
+                const int x = x0 + e % FF_TILE, y = y0 + e / FF_TILE;
+                const int kt = (int)pidx(g, min(x, W.i1), min(y, W.j1));
+                if (tag[kt] == l && W.has(x, y)) lst[atomicAdd(cn, 1)] = kt;
+            }
+            __syncthreads();
+            const int n = *cn;
+            for (int a = grp; a < n; a += NG) {
+                const int kt = lst[a];
+                const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
+                T xo = T(0), yo = T(0);
+                const bool done =
+                    fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin, X1, Y1, xo, yo);
+                if (sub == 0) {
+                    if (done) {
+                        X1[kt] = xo;
+                        Y1[kt] = yo;
+                    } else {
+                        tag[kt] = (int8_t)(l | TAG_FAIL);
+                        atomicAdd(&health[1], 1u);
                     }
                 }
-                __syncthreads();
             }
+            __syncthreads();
         }
-    }
-    // the lists of the next step start empty
-    for (int a = threadIdx.x; a < nc; a += NT) cut_layer[cut_tiles[a]] = FF_NO_CUT;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        *ncut = 0;
-        *ff_n = 0;
     }
 }
 
@@ -1468,19 +1484,20 @@ __device__ void fit_rest(const GridP& g, const Win* __restrict__ win, int wcur, 
 // the tile's own targets are written back.  A tile that the copy cannot serve
 // from some layer on (a fit that needs a wider scan window, or fails for good;
 // more than FF_LAYER targets
-// in a layer) is listed, with the layer, for k_fit_rest,
-// which finishes the listed tiles layer by layer.
+// in a layer) is listed, with the layer; the block that ends last finishes
+// the listed tiles layer by layer (fit_rest) and empties both lists.  (A
+// launch of its own for that took 4 us a step, with nothing to do but at rare
+// steps; the ticket of the blocks takes ~1 us.)
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
 // margin, and every tile with more than 64 targets in layers 1 and 2 before
-// its first layer (k_fit_rest then fits most of the zone: a check of that
-// launch).
+// its first layer (fit_rest then fits most of the zone: a check of it).
 template <typename T, int NT, int LC>
 __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
-                                               int wcur, int wprev, const int8_t* tag,
+                                               int wcur, int wprev, int8_t* tag,
                                                const T* __restrict__ phin, T* X1, T* Y1,
-                                               int8_t* cut_layer, int* cut_tiles, int* ncut,
-                                               const int* __restrict__ ff_list,
-                                               const int* __restrict__ ff_n, int reach)
+                                               unsigned* health, int* cut_tiles, int* ncut,
+                                               const int* __restrict__ ff_list, int* ff_n,
+                                               unsigned* ticket, int reach)
 {
     constexpr int RW = FF_REGION;
     __shared__ FitLds<T, RW * RW, FF_LAYER> s;
@@ -1499,23 +1516,32 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
         const FitRegion R{x0 - S, y0 - S, rw, rw, x0, y0, FF_TILE, FF_TILE, 2};
         fit_region<T, NT, RW * RW, FF_LAYER, LC == FF_LAYERS ? RW : 0>(s, g, W, D, L, R, tag, phin,
                                                                        X1, Y1, reach);
-        if (threadIdx.x == 0 && s.cut <= L) {
-            cut_layer[t] = (int8_t)s.cut;
-            cut_tiles[atomicAdd(ncut, 1)] = t;
-        }
+        if (threadIdx.x == 0 && s.cut <= L)
+            through(&cut_tiles[atomicAdd(ncut, 1)], t | s.cut << FF_CUT_SHIFT);
+    }
+    if (!last_arrival(ticket, min(ntile, (int)gridDim.x))) return;
+    const int nc = seen(ncut);
+    if (nc > 0) {
+        __threadfence();
+        static_assert(sizeof(s.rec) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
+        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, (int*)s.rec, s.cnt);
+    }
+    if (threadIdx.x == 0) {
+        *ncut = 0;
+        *ff_n = 0;
     }
 }
 
 template <typename T, int NT, int LC>
 __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict__ win, int wcur,
-                                                  int wprev, const int8_t* tag,
+                                                  int wprev, int8_t* tag,
                                                   const T* __restrict__ phin, T* X1, T* Y1,
-                                                  int8_t* cut_layer, int* cut_tiles, int* ncut,
-                                                  const int* __restrict__ ff_list,
-                                                  const int* __restrict__ ff_n, int reach)
+                                                  unsigned* health, int* cut_tiles, int* ncut,
+                                                  const int* __restrict__ ff_list, int* ff_n,
+                                                  unsigned* ticket, int reach)
 {
-    fit_fused_body<T, NT, LC>(g, win, wcur, wprev, tag, phin, X1, Y1, cut_layer, cut_tiles, ncut,
-                              ff_list, ff_n, reach);
+    fit_fused_body<T, NT, LC>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_tiles, ncut,
+                              ff_list, ff_n, ticket, reach);
 }
 
 // a batch: member blockIdx.y
@@ -1524,28 +1550,8 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_fused(const FitArgs* __rest
 {
     const FitArgs& a = args[blockIdx.y];
     fit_fused_body<T, FF_THREADS, LC>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin,
-                                            (T*)a.X1, (T*)a.Y1, a.cut_layer, a.cut_tiles, a.ncut,
-                                            a.ff_list, a.ff_n, 2);
-}
-
-template <typename T>
-__global__ __launch_bounds__(FF_REST_THREADS) void kb_fit_rest(const FitArgs* __restrict__ args)
-{
-    const FitArgs& a = args[blockIdx.y];
-    fit_rest<T, FF_REST_THREADS>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1,
-                                 (T*)a.Y1, a.health, a.cut_layer, a.cut_tiles, a.ncut, a.ff_n);
-}
-
-// fit_rest in a block of FF_REST_THREADS threads, which finds a free slot
-// beside the bulk update sooner than one that needs a whole compute unit
-template <typename T>
-__global__ __launch_bounds__(FF_REST_THREADS) void k_fit_rest(
-    GridP g, const Win* __restrict__ win, int wcur, int wprev, int8_t* tag,
-    const T* __restrict__ phin, T* X1, T* Y1, unsigned* health, int8_t* cut_layer,
-    const int* cut_tiles, int* ncut, int* ff_n)
-{
-    fit_rest<T, FF_REST_THREADS>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_layer,
-                                 cut_tiles, ncut, ff_n);
+                                      (T*)a.X1, (T*)a.Y1, a.health, a.cut_tiles, a.ncut,
+                                      a.ff_list, a.ff_n, a.ticket, 2);
 }
 
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
@@ -1555,7 +1561,7 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
 #define FUSED_L(T, NT, LC)                                                                        \
     k_fit_fused<T, NT, LC><<<FF_BLOCKS, NT, 0, st>>>(                                             \
         g, bb.win, s.wcur, s.wprev, bb.tag, (const T*)bb.phi[s.cur], (T*)bb.X[s.nxt],             \
-        (T*)bb.Y[s.nxt], bb.cut_layer, bb.cut_tiles, bb.ncut, bb.ff_list, bb.ff_n,               \
+        (T*)bb.Y[s.nxt], bb.health, bb.cut_tiles, bb.ncut, bb.ff_list, bb.ff_n, bb.ticket,       \
         fused_threads == 1 ? 1 : 2)
 #define FUSED(T, NT)                                                                              \
     do {                                                                                          \
@@ -1566,9 +1572,6 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
     do {                                                                                          \
         if (fused_threads == 256) FUSED(T, 256);                                                  \
         else FUSED(T, FF_THREADS);                                                                \
-        k_fit_rest<T><<<1, FF_REST_THREADS, 0, st>>>(                                             \
-            g, bb.win, s.wcur, s.wprev, bb.tag, (const T*)bb.phi[s.cur], (T*)bb.X[s.nxt],         \
-            (T*)bb.Y[s.nxt], bb.health, bb.cut_layer, bb.cut_tiles, bb.ncut, bb.ff_n);            \
     } while (0)
         if (g.rm32) FUSED_T(float);
         else FUSED_T(double);
@@ -1712,7 +1715,7 @@ __device__ __forceinline__ double relabel_phi(const GridP& g, const BodyP& b, in
 // tile's own nodes (with the map cleared where none is held), and for the
 // window's nodes outside the interior by a strided pass; each block writes
 // the partial box of the new interior solid set it saw, which the next
-// lattice update reduces into the next ring slot.  MODE 2 is MODE 0 without
+// lattice update (MODE 3: the last block) reduces into the next ring slot.  MODE 2 is MODE 0 without
 // the stresses (one solid of several: the forces are combined over all
 // solids afterwards).  MODE 3 is MODE 0 followed, for each of the tile's own
 // nodes, by its lattice Boltzmann update with the force just computed (the
@@ -1898,6 +1901,26 @@ __device__ __forceinline__ void edges_body(GridP g, BodyP b, Win* win, int wvali
                 }
             }
         }
+        if (MODE == 3) {
+            // the last of the blocks that took a tile (block 0 if none did)
+            // reduces the boxes into ring slot wnext, checks the new window's
+            // zone, and counts a box whose lower edge moved down by more than
+            // BULK_EARLY_GAP rows from the current one (the early part of the
+            // next step's bulk update assumes it does not).  (A launch of its
+            // own for that took 4 to 7 us a step.)
+            const int nb = max(1, min(ntx * nty, (int)gridDim.x));
+            if ((int)blockIdx.x >= nb) return;
+            block_box(bi0, bi1, bj0, bj1, boxpart + 4 * blockIdx.x);
+            if (!last_arrival(lf.ticket, nb)) return;
+            const Win r = reduce_boxes<true>(boxpart, nb, &win[lf.wnext], nullptr);
+            if (threadIdx.x == 0) {
+                const Win cur = win[wvalid];
+                check_zone(g, r, health);
+                if (r.i0 <= r.i1 && cur.i0 <= cur.i1 && r.j0 < cur.j0 - BULK_EARLY_GAP)
+                    atomicAdd(&health[6], 1u);
+            }
+            return;
+        }
         block_box(bi0, bi1, bj0, bj1, boxpart + 4 * blockIdx.x);
         if (MODE == 2) block_box(ei0, ei1, ej0, ej1, boxpart + 4 * (gridDim.x + blockIdx.x));
     }
@@ -1942,32 +1965,6 @@ hipError_t launch_force(const GridP& g, const BodyP& b, const BandBufs& bb, cons
         else KE(0, double, LbFuse{});
     }
 #undef KE
-    return hipGetLastError();
-}
-
-// one block: the force pass's partial boxes into ring slot wnext, and the
-// zone check of the new window (what the band lattice launch does otherwise)
-// (also counts a box whose lower edge moved down by more than
-// BULK_EARLY_GAP rows from the current one: the early part of the next
-// step's bulk update assumes it does not)
-__global__ __launch_bounds__(256) void k_reduce_window(GridP g, const int* __restrict__ boxpart,
-                                                       int nbox, Win* win, int wcur, int wnext,
-                                                       unsigned* health)
-{
-    const Win cur = win[wcur];
-    const Win r = reduce_boxes(boxpart, nbox, &win[wnext], nullptr);
-    if (threadIdx.x == 0) {
-        check_zone(g, r, health);
-        if (r.i0 <= r.i1 && cur.i0 <= cur.i1 && r.j0 < cur.j0 - BULK_EARLY_GAP)
-            atomicAdd(&health[6], 1u);
-    }
-}
-
-hipError_t launch_reduce_window(const GridP& g, const BandBufs& bb, int wcur, int wnext,
-                                hipStream_t st)
-{
-    k_reduce_window<<<1, 256, 0, st>>>(g, bb.boxpart, RELABEL_BLOCKS, bb.win, wcur, wnext,
-                                       bb.health);
     return hipGetLastError();
 }
 
@@ -2666,7 +2663,6 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
         if (fused) {
             if (layers == FF_LAYERS) kb_fit_fused<double, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
             else kb_fit_fused<double, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
-            kb_fit_rest<double><<<g1, FF_REST_THREADS, 0, st>>>(t.fit);
         } else if (fit_blocks == 0) {
             kb_fit_lds<double, MB_FIT_THREADS_F64><<<g1, MB_FIT_THREADS_F64, 0, st>>>(t.fit, layers,
                                                                                  t.ord);
@@ -2684,7 +2680,6 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
         if (fused) {
             if (layers == FF_LAYERS) kb_fit_fused<float, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
             else kb_fit_fused<float, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
-            kb_fit_rest<float><<<g1, FF_REST_THREADS, 0, st>>>(t.fit);
         } else if (fit_blocks == 0) {
             kb_fit_lds<float, MB_FIT_THREADS_F32><<<g1, MB_FIT_THREADS_F32, 0, st>>>(t.fit, layers,
                                                                                 t.ord);

@@ -110,7 +110,7 @@ struct Layout {
     size_t rm_es;  // bytes per reference-map value: 8 (FP64 xi) or 4 (FP32 displacement)
     size_t off_lat[2], off_fx[2], off_fy[2], off_drho, off_X[2], off_Y[2], off_phi[2], off_tag,
         off_win, off_health, off_dpart, off_dout, off_gcol, off_lists, off_lcount, off_boxpart,
-        off_ticket, off_cut_layer, off_cut_tiles, off_ncut, off_ff_list, off_ff_n,
+        off_ticket, off_cut_tiles, off_ncut, off_ff_list, off_ff_n,
         total;
     size_t lat_bytes;
     // several solids
@@ -157,7 +157,6 @@ Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
     L.off_boxpart = take((size_t)std::max(RELABEL_BLOCKS, BOX_BLOCKS) * 4 * 4);
     L.off_ticket = take(4);
     const size_t ntile = multi ? 0 : (size_t)fused_tiles(d->nx, d->ny);
-    L.off_cut_layer = take(ntile);
     L.off_cut_tiles = take(ntile * 4);
     L.off_ncut = take(4);
     L.off_ff_list = take(ntile * 4);
@@ -478,12 +477,9 @@ static int enqueue_step(lbrmt_ctx* c, long long n, hipStream_t main_s, bool firs
             // the lattice update of the window's nodes
             Bracket b(c, 3, band);
             const LbFuse lf{c->lat[s.cur], c->lat[s.nxt], c->Fx[s.nxt], c->Fy[s.nxt], s.wprev,
-                            ox, oy};
+                            ox, oy, c->bb.ticket, s.wnext};
             HIPCHK(c, launch_force(g, c->body, c->bb, s, c->Fx[s.cur], c->Fy[s.cur], c->drho,
                                    band, c->overlap ? &lf : nullptr));
-            // the new solid box into the next ring slot (the band lattice
-            // launch does this when the force pass leaves the lattice to it)
-            if (c->overlap) HIPCHK(c, launch_reduce_window(g, c->bb, s.wcur, s.wnext, band));
             b.done();
         }
         if (c->overlap) {
@@ -717,7 +713,6 @@ static int create_impl(const lbrmt_grid_desc* d, int32_t max_solids, void* ws, s
     c->bb.lcount = (int*)(c->ws + L.off_lcount);
     c->bb.boxpart = (int*)(c->ws + L.off_boxpart);
     c->bb.ticket = (unsigned*)(c->ws + L.off_ticket);
-    c->bb.cut_layer = (int8_t*)(c->ws + L.off_cut_layer);
     c->bb.cut_tiles = (int*)(c->ws + L.off_cut_tiles);
     c->bb.ncut = (int*)(c->ws + L.off_ncut);
     c->bb.ff_list = (int*)(c->ws + L.off_ff_list);
@@ -885,8 +880,7 @@ static BandBufs mb_bufs(const lbrmt_ctx* c, int k)
     b.ticket = (unsigned*)(base + c->BL.off_ticket);
     b.win = m.win;
     b.health = c->bb.health;
-    b.cut_layer = nullptr;  // one launch per layer for several solids
-    b.cut_tiles = nullptr;
+    b.cut_tiles = nullptr;  // no tiles: a solid's layers in one block
     b.ncut = nullptr;
     b.ff_list = nullptr;
     b.ff_n = nullptr;
@@ -1015,13 +1009,11 @@ static int init_mb(lbrmt_ctx* c, const double* d_u0)
     return LBRMT_OK;
 }
 
-// the fused extrapolation's tile lists start empty (k_fit_rest leaves them so)
+// the fused extrapolation's tile lists start empty (each launch leaves them so)
 static hipError_t clear_cut_tiles(lbrmt_ctx* c, hipStream_t st)
 {
     if (c->multi) return hipSuccess;  // several solids: no fused extrapolation
-    const size_t nt = (size_t)fused_tiles(c->d.nx, c->d.ny);
-    hipError_t e = hipMemsetAsync(c->bb.cut_layer, FF_NO_CUT, nt, st);
-    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
+    hipError_t e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
     if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_n, 0, 4, st);
     return e;
 }
@@ -2111,8 +2103,8 @@ int batch_tables(lbrmt_batch* b)
                                 c->bb.lcount, c->bb.health};
             fit[k] = FitArgs{g, c->bb.win, s.wcur, s.wprev, c->bb.tag, c->bb.lists, c->bb.lcount,
                              c->bb.phi[s.cur], c->bb.X[s.nxt], c->bb.Y[s.nxt], c->bb.health,
-                             c->bb.cut_layer, c->bb.cut_tiles, c->bb.ncut, c->bb.ff_list,
-                             c->bb.ff_n};
+                             c->bb.cut_tiles, c->bb.ncut, c->bb.ff_list, c->bb.ff_n,
+                             c->bb.ticket};
             edg[k] = EdgesArgs{g, c->body, c->bb.win, s.wcur, c->bb.boxpart, c->bb.X[s.nxt],
                                c->bb.Y[s.nxt], c->bb.tag, c->bb.phi[s.nxt], c->Fx[s.cur],
                                c->Fy[s.cur], c->drho, c->bb.lcount, c->bb.health};

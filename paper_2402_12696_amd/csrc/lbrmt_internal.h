@@ -33,8 +33,9 @@ constexpr int NSUB = 8;               // sub-lists per layer (distance-transform
 constexpr int FF_TILE = 32;           // fused extrapolation: tile side
 constexpr int FF_LAYERS = 11;         // fused extrapolation: most layers
 constexpr int FF_BLOCKS = 256;        // fused extrapolation: blocks striding over its tile list
-constexpr int FF_NO_CUT = 127;        // tile not stopped (cut_layer)
-constexpr int FF_REST_THREADS = 256;  // fused extrapolation: the one-block pass
+// a stopped tile of the fused extrapolation: its number (a grid has fewer than
+// 2^26 nodes), and from this bit on the layer where it stopped
+constexpr int FF_CUT_SHIFT = 26, FF_CUT_TILE = (1 << FF_CUT_SHIFT) - 1;
 // side of a tile with its margin (2 (FF_LAYERS - 1) + 2 nodes around it)
 constexpr int FF_REGION = FF_TILE + 4 * (FF_LAYERS - 1) + 4;
 // most targets of a layer in a block's copy (a tile: typically 50 to 90; a
@@ -138,9 +139,7 @@ struct BandBufs {
     unsigned* ticket;     // arrival counter of last-block reductions
     Win* win;             // ring of 3 boxes
     unsigned* health;
-    // fused extrapolation: per window tile the layer where it stopped
-    // (FF_NO_CUT between steps), the stopped tiles and their count
-    int8_t* cut_layer;
+    // fused extrapolation: the stopped tiles and their count (0 between steps)
     int* cut_tiles;
     int* ncut;
     // fused extrapolation: the tiles the zone reaches, listed once each by
@@ -166,41 +165,38 @@ __device__ __forceinline__ int wave_max(int v)
 // into *dst0 (and *dst1 when not null), and returns it in thread 0; an empty
 // result is the empty box.
 // SAME_KERNEL: the partials were written by other blocks of the running
-// kernel (read through volatile loads after the last-block handshake);
-// otherwise by an earlier kernel (plain loads, all issued at once).
+// kernel (read past the XCD's own cache, after the last-block handshake);
+// otherwise by an earlier kernel (plain loads).
 template <bool SAME_KERNEL = false>
 __device__ inline Win reduce_boxes(const int* part, int n, Win* dst0, Win* dst1)
 {
     Win r{};
     __shared__ int sb[4][16];
     int a0 = 0x3fffffff, a1 = -0x3fffffff, a2 = 0x3fffffff, a3 = -0x3fffffff;
-    if (SAME_KERNEL) {
-        for (int k = threadIdx.x; k < n; k += blockDim.x) {
-            const volatile int* q = part + 4 * k;
-            a0 = min(a0, q[0]);
-            a1 = max(a1, q[1]);
-            a2 = min(a2, q[2]);
-            a3 = max(a3, q[3]);
+    // several partials per thread in flight at a time
+    constexpr int NB = SAME_KERNEL ? 4 : 8;
+    for (int k0 = threadIdx.x; k0 < n; k0 += NB * blockDim.x) {
+        int4 q[NB];
+#pragma unroll
+        for (int u = 0; u < NB; u++) {
+            const int k = k0 + u * blockDim.x;
+            const int* p = part + 4 * (k < n ? k : 0);
+            if (SAME_KERNEL) {
+                q[u].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                q[u].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                q[u].z = __hip_atomic_load(p + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                q[u].w = __hip_atomic_load(p + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                q[u] = *reinterpret_cast<const int4*>(p);
+            }
         }
-    } else {
-        // eight partials per thread in flight at a time
-        constexpr int NB = 8;
-        const int4* p4 = reinterpret_cast<const int4*>(part);
-        for (int k0 = threadIdx.x; k0 < n; k0 += NB * blockDim.x) {
-            int4 q[NB];
 #pragma unroll
-            for (int u = 0; u < NB; u++) {
-                const int k = k0 + u * blockDim.x;
-                q[u] = p4[k < n ? k : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < NB; u++) {
-                if (k0 + u * (int)blockDim.x >= n) continue;
-                a0 = min(a0, q[u].x);
-                a1 = max(a1, q[u].y);
-                a2 = min(a2, q[u].z);
-                a3 = max(a3, q[u].w);
-            }
+        for (int u = 0; u < NB; u++) {
+            if (k0 + u * (int)blockDim.x >= n) continue;
+            a0 = min(a0, q[u].x);
+            a1 = max(a1, q[u].y);
+            a2 = min(a2, q[u].z);
+            a3 = max(a3, q[u].w);
         }
     }
     a0 = wave_min(a0);
@@ -286,8 +282,8 @@ struct FitArgs {
     void *X1, *Y1;
     unsigned* health;
     // the fused extrapolation's buffers (batches of single-solid members)
-    int8_t* cut_layer;
     int *cut_tiles, *ncut, *ff_list, *ff_n;
+    unsigned* ticket;
 };
 struct EdgesArgs {
     GridP g;
@@ -583,16 +579,15 @@ struct LbFuse {
     const double *fpx, *fpy;
     int wprev;
     double fpo_x, fpo_y;
+    unsigned* ticket;  // arrival counter of the blocks, 0 between launches
+    int wnext;         // ring slot of the new solid box
 };
 // lf null: relabel and force only (the lattice update of the window follows
-// in a lattice kernel).  Either way the new solid box is left as partial
-// boxes in bb.boxpart (RELABEL_BLOCKS of them).
+// in a lattice kernel), the new solid box left as partial boxes in bb.boxpart
+// (RELABEL_BLOCKS of them); else it goes into ring slot lf->wnext.
 hipError_t launch_force(const GridP& g, const BodyP& b, const BandBufs& bb, const StepSlots& s,
                         double* fx, double* fy, double* drho, hipStream_t st,
                         const LbFuse* lf = nullptr);
-// the force pass's partial boxes into ring slot wnext, with the zone check
-hipError_t launch_reduce_window(const GridP& g, const BandBufs& bb, int wcur, int wnext,
-                                hipStream_t st);
 hipError_t launch_read_stress(const GridP& g, const BodyP& b, const BandBufs& bb, int buf,
                               int wvalid, double* sxx, double* sxy, double* syy, hipStream_t st);
 hipError_t launch_read_refmap(const GridP& g, const BodyP& b, const BandBufs& bb, int buf, int wvalid, double* X,
