@@ -363,141 +363,336 @@ __global__ __launch_bounds__(256) void k_adj_relabel(GridP g, BodyP b, AdjSnap s
 }
 
 // ---------------------------------------------------------------- extrapolation
-// Targets of layer l backwards (one thread per target): the fitted intercept
-// c = e3^T M^{-1} b with M = sum w a a^T, b = sum w a xi (a = (dx, dy, 1) in
-// target-centred coordinates) sends dL/dc to every valid node k with weight
-// w_k (a_k . s), s = M^{-1} e3; with the normal weights of layers 1 and 2 the
-// weights themselves depend on phi^n at the target's four neighbours:
+// One target of layer l backwards: the fitted intercept c = e3^T M^{-1} b with
+// M = sum w a a^T, b = sum w a xi (a = (dx, dy, 1) in target-centred
+// coordinates) sends dL/dc to every valid node k with weight w_k (a_k . s),
+// s = M^{-1} e3; with the normal weights of layers 1 and 2 the weights
+// themselves depend on phi^n at the target's four neighbours:
 // dc/dw_k = (a_k . s)(xi_k - a_k . p), p = M^{-1} b.
-__global__ __launch_bounds__(256) void k_adj_fit(GridP g, AdjSnap s, AdjBufs a, int l)
+// Scan windows of half-width 2 .. rmax (RMAX > 0: at compile time).
+// node(aa, bb): the handle of the scan node at that offset, -1 if it is not
+// valid (no map, or of layer l or later); val(h, x, y): xi^{n+1} there;
+// add(h, vx, vy): adds to its adjoint.  own: the target's normal is this
+// call's to pass on (to pbar0).
+template <int RMAX, typename Node, typename Val, typename Add>
+__device__ __forceinline__ void adj_fit_target(const GridP& g, const Rect& D, const AdjSnap& s,
+                                               const AdjBufs& a, int l, int i, int j, double Xb,
+                                               double Yb, bool own, Node node, Val val, Add add)
 {
-    const Rect W = window_of(s.win, 1, g);
-    const Rect D = window_of(s.win, 0, g);
-    if (!W.ok) return;
+    // outward normal of phi^n at the target (layers 1, 2)
+    bool use_n = false;
+    double nxh = 0.0, nyh = 0.0, gx = 0.0, gy = 0.0, gn = 0.0;
+    long long kn[4] = {-1, -1, -1, -1};
+    if (l <= 2) {
+        const int di[4] = {1, -1, 0, 0}, dj[4] = {0, 0, 1, -1};
+        double pv[4];
+        bool ok = true;
+        for (int q = 0; q < 4; q++) {
+            int x = i + di[q], y = j + dj[q];
+            kn[q] = (canon(g, x, y) && D.has(x, y)) ? pidx(g, x, y) : -1;
+            pv[q] = kn[q] >= 0 ? s.P0[kn[q]] : INFINITY;
+            ok = ok && pv[q] < INFINITY;
+        }
+        if (ok) {
+            gx = (pv[0] - pv[1]) / 2.0;
+            gy = (pv[2] - pv[3]) / 2.0;
+            gn = sqrt(gx * gx + gy * gy);
+            if (gn > 0.0) {
+                nxh = gx / gn;
+                nyh = gy / gn;
+                use_n = true;
+            }
+        }
+    }
+    auto weight = [&](int aa, int bb, double& dn, double& ddx, double& ddy, double& dl) {
+        const double w0 = ldexp(1.0, -(abs(aa) + abs(bb)));
+        if (!use_n) return w0;
+        ddx = -(double)aa;
+        ddy = -(double)bb;
+        dl = sqrt(ddx * ddx + ddy * ddy);
+        dn = (ddx * nxh + ddy * nyh) / dl;
+        return dn * w0 > 0.0 ? dn * w0 : 0.0;
+    };
+    const int rmax = RMAX > 0 ? RMAX : g.r_max;
+#pragma unroll 1
+    for (int rr = 2; rr <= rmax; rr++) {
+        const int r = RMAX == 2 ? 2 : rr;
+        double M00 = 0, M01 = 0, M02 = 0, M11 = 0, M12 = 0, M22 = 0;
+        double bX0 = 0, bX1 = 0, bX2 = 0, bY0 = 0, bY1 = 0, bY2 = 0;
+        int count = 0;
+#pragma unroll(RMAX == 2 ? 5 : 1)
+        for (int bb = -r; bb <= r; bb++)
+#pragma unroll(RMAX == 2 ? 5 : 1)
+            for (int aa = -r; aa <= r; aa++) {
+                if (aa == 0 && bb == 0) continue;  // (the target is of layer l)
+                const auto k = node(aa, bb);
+                if (k < 0) continue;
+                count++;
+                double dn = 0.0, ddx, ddy, dl;
+                const double wt = weight(aa, bb, dn, ddx, ddy, dl);
+                const double dx = aa, dy = bb;
+                M00 += wt * dx * dx; M01 += wt * dx * dy; M02 += wt * dx;
+                M11 += wt * dy * dy; M12 += wt * dy; M22 += wt;
+                if (use_n) {
+                    double xv, yv;
+                    val(k, aa, bb, xv, yv);
+                    bX0 += wt * dx * xv; bX1 += wt * dy * xv; bX2 += wt * xv;
+                    bY0 += wt * dx * yv; bY1 += wt * dy * yv; bY2 += wt * yv;
+                }
+            }
+        if (count < 3) continue;
+        const double det = M00 * (M11 * M22 - M12 * M12) - M01 * (M01 * M22 - M12 * M02) +
+                           M02 * (M01 * M12 - M11 * M02);
+        if (!(det > g.det_rel * M22 * M22 * M22)) continue;
+        // inverse of the symmetric normal matrix
+        const double i02 = (M01 * M12 - M11 * M02) / det;
+        const double i12 = (M01 * M02 - M00 * M12) / det, i22 = (M00 * M11 - M01 * M01) / det;
+        // s = M^{-1} e3, plane coefficients p = M^{-1} b
+        const double s0 = i02, s1 = i12, s2 = i22;
+        double pX0 = 0, pX1 = 0, pX2 = 0, pY0 = 0, pY1 = 0, pY2 = 0;
+        if (use_n) {
+            const double i00 = (M11 * M22 - M12 * M12) / det, i01 = (M02 * M12 - M01 * M22) / det;
+            const double i11 = (M00 * M22 - M02 * M02) / det;
+            pX0 = i00 * bX0 + i01 * bX1 + i02 * bX2;
+            pX1 = i01 * bX0 + i11 * bX1 + i12 * bX2;
+            pX2 = i02 * bX0 + i12 * bX1 + i22 * bX2;
+            pY0 = i00 * bY0 + i01 * bY1 + i02 * bY2;
+            pY1 = i01 * bY0 + i11 * bY1 + i12 * bY2;
+            pY2 = i02 * bY0 + i12 * bY1 + i22 * bY2;
+        }
+        double nbx = 0.0, nby = 0.0;  // dL/d(normal)
+#pragma unroll(RMAX == 2 ? 5 : 1)
+        for (int bb = -r; bb <= r; bb++)
+#pragma unroll(RMAX == 2 ? 5 : 1)
+            for (int aa = -r; aa <= r; aa++) {
+                if (aa == 0 && bb == 0) continue;
+                const auto k = node(aa, bb);
+                if (k < 0) continue;
+                double dn = 0.0, ddx = 0.0, ddy = 0.0, dl = 0.0;
+                const double wt = weight(aa, bb, dn, ddx, ddy, dl);
+                const double w0 = ldexp(1.0, -(abs(aa) + abs(bb)));
+                const double as = s0 * aa + s1 * bb + s2;
+                if (wt != 0.0) add(k, Xb * wt * as, Yb * wt * as);
+                if (use_n && own && dn * w0 > 0.0) {
+                    double xv, yv;
+                    val(k, aa, bb, xv, yv);
+                    const double rX = xv - (pX0 * aa + pX1 * bb + pX2);
+                    const double rY = yv - (pY0 * aa + pY1 * bb + pY2);
+                    const double wb = as * (Xb * rX + Yb * rY);
+                    const double dnb = wb * w0;
+                    nbx += dnb * ddx / dl;
+                    nby += dnb * ddy / dl;
+                }
+            }
+        if (use_n && own && (nbx != 0.0 || nby != 0.0)) {
+            // n = g / |g|, g = ((phi_e - phi_w) / 2, (phi_n - phi_s) / 2)
+            const double dotp = nbx * nxh + nby * nyh;
+            const double gbx = (nbx - dotp * nxh) / gn, gby = (nby - dotp * nyh) / gn;
+            atomicAdd(&a.pbar0[kn[0]], gbx / 2.0);
+            atomicAdd(&a.pbar0[kn[1]], -gbx / 2.0);
+            atomicAdd(&a.pbar0[kn[2]], gby / 2.0);
+            atomicAdd(&a.pbar0[kn[3]], -gby / 2.0);
+        }
+        break;
+    }
+}
+
+// relabel backwards at one node (see k_adj_relabel), into x and y
+__device__ __forceinline__ void adj_relabel_node(const BodyP& b, const AdjSnap& s, long long k,
+                                                 double pb, double& x, double& y)
+{
+    if (pb == 0.0 || !(s.P1[k] < INFINITY)) return;
+    double gx, gy;
+    grad_phi0(b, s.X1[k], s.Y1[k], gx, gy);
+    x += pb * gx;
+    y += pb * gy;
+}
+
+// The targets of layer l of the window, nt threads of which this is number t,
+// on the adjoint fields in memory.  RELABEL: each target's relabel first (only
+// its own thread touches a node of layer l in this pass).
+template <bool RELABEL>
+__device__ __forceinline__ void adj_fit_layer(const GridP& g, const BodyP& b, const AdjSnap& s,
+                                              const AdjBufs& a, const Rect& W, const Rect& D,
+                                              int l, long long t, long long nt)
+{
     const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < (long long)w * h;
-         e += (long long)gridDim.x * blockDim.x) {
+    for (long long e = t; e < (long long)w * h; e += nt) {
         int i = W.i0 + (int)(e % w), j = W.j0 + (int)(e / w);
         if (!canon(g, i, j)) continue;
         const long long kt = pidx(g, i, j);
         if (s.tag[kt] != l) continue;  // not this layer, or its fit failed
-        const double Xb = a.xbar1[kt], Yb = a.ybar1[kt];
+        // (past the CU's own cache: the block may have added to it)
+        double Xb = __hip_atomic_load(&a.xbar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        double Yb = __hip_atomic_load(&a.ybar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (RELABEL) adj_relabel_node(b, s, kt, a.pbar1[kt], Xb, Yb);
         if (Xb == 0.0 && Yb == 0.0) continue;
-        // outward normal of phi^n at the target (layers 1, 2)
-        bool use_n = false;
-        double nxh = 0.0, nyh = 0.0, gx = 0.0, gy = 0.0, gn = 0.0;
-        long long kn[4] = {-1, -1, -1, -1};
-        if (l <= 2) {
-            const int di[4] = {1, -1, 0, 0}, dj[4] = {0, 0, 1, -1};
-            double pv[4];
-            bool ok = true;
-            for (int q = 0; q < 4; q++) {
-                int x = i + di[q], y = j + dj[q];
-                kn[q] = (canon(g, x, y) && D.has(x, y)) ? pidx(g, x, y) : -1;
-                pv[q] = kn[q] >= 0 ? s.P0[kn[q]] : INFINITY;
-                ok = ok && pv[q] < INFINITY;
-            }
-            if (ok) {
-                gx = (pv[0] - pv[1]) / 2.0;
-                gy = (pv[2] - pv[3]) / 2.0;
-                gn = sqrt(gx * gx + gy * gy);
-                if (gn > 0.0) {
-                    nxh = gx / gn;
-                    nyh = gy / gn;
-                    use_n = true;
-                }
+        adj_fit_target<0>(
+            g, D, s, a, l, i, j, Xb, Yb, true,
+            [&](int aa, int bb) -> long long {
+                int x = i + aa, y = j + bb;
+                if (!canon(g, x, y) || !W.has(x, y)) return -1;
+                const long long k = pidx(g, x, y);
+                const int t = s.tag[k];
+                return t == TAG_SOLID || (t > 0 && t < l) ? k : -1;
+            },
+            [&](long long k, int, int, double& xv, double& yv) {
+                xv = s.X1[k];
+                yv = s.Y1[k];
+            },
+            [&](long long k, double vx, double vy) {
+                atomicAdd(&a.xbar1[k], vx);
+                atomicAdd(&a.ybar1[k], vy);
+            });
+    }
+}
+
+// one launch per layer, last layer first
+__global__ __launch_bounds__(256) void k_adj_fit(GridP g, BodyP b, AdjSnap s, AdjBufs a, int l)
+{
+    const Rect W = window_of(s.win, 1, g);
+    const Rect D = window_of(s.win, 0, g);
+    if (!W.ok) return;
+    adj_fit_layer<false>(g, b, s, a, W, D, l, blockIdx.x * (long long)blockDim.x + threadIdx.x,
+                         (long long)gridDim.x * blockDim.x);
+}
+
+// Relabel and every layer backwards in one launch (up to FF_LAYERS layers).
+// A block takes AT x AT tiles of the window: what reaches a solid node comes
+// from targets within 2 nodes of it, to which targets of later layers within
+// 2 nodes of them send, so that a target of layer l is taken within 2 l nodes
+// of the tile, on a copy of the tags and adjoints of the tile and a margin of
+// 2 L + 2 nodes (a margin's targets are recomputed by each block that needs
+// them).  Only the tile's solid nodes are written: what the zone's nodes hold
+// is spent after this, and k_adj_advect clears it, so no block reads what
+// another writes.  Bound by a chain of L dependent layers in LDS; launches of
+// their own each scanned the window's tags again (gradient of 100 steps at
+// 256^2: 12 launches, ~75 us a step -> one, ~20 us).
+// s.wide: some target of the step has a wider scan window (or none): then one
+// block runs the layers on the fields in memory.
+constexpr int AT = FF_TILE, AT_THREADS = 512;
+constexpr int AT_R = AT + 4 * FF_LAYERS + 4;  // side of the copy at FF_LAYERS layers
+__global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSnap s, AdjBufs a)
+{
+    constexpr int NN = AT_R * AT_R;
+    __shared__ double xb[NN], yb[NN];
+    __shared__ unsigned char st[NN];
+    __shared__ unsigned short lst[NN];
+    __shared__ int cnt[FF_LAYERS + 2], at[FF_LAYERS + 2], near;
+    const Rect W = window_of(s.win, 1, g);
+    const Rect D = window_of(s.win, 0, g);
+    if (!W.ok) return;
+    const int L = g.layers;
+    if (*s.wide != 0) {
+        if (blockIdx.x != 0) return;
+        for (int l = L; l >= 1; l--) {
+            adj_fit_layer<true>(g, b, s, a, W, D, l, threadIdx.x, blockDim.x);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        return;
+    }
+    const int m = 2 * L + 2, rw = AT + 2 * m;
+    const int ntx = (W.i1 - W.i0 + AT) / AT, nty = (W.j1 - W.j0 + AT) / AT;
+    for (int t = blockIdx.x; t < ntx * nty; t += gridDim.x) {
+        const int x0 = W.i0 + (t % ntx) * AT - m, y0 = W.j0 + (t / ntx) * AT - m;
+        if (threadIdx.x <= FF_LAYERS + 1) cnt[threadIdx.x] = 0;
+        if (threadIdx.x == 0) near = 0;
+        __syncthreads();
+        // node of the copy (unwrapped; a periodic axis wraps)
+        auto global_of = [&](int q) -> long long {
+            int x = x0 + q % rw, y = y0 + q / rw;
+            if (!canon(g, x, y) || !W.has(x, y)) return -1;
+            return pidx(g, x, y);
+        };
+        auto dist = [&](int q) {
+            const int lx = q % rw - m, ly = q / rw - m;
+            return max(max(-lx, lx - (AT - 1)), max(-ly, ly - (AT - 1)));
+        };
+        for (int q = threadIdx.x; q < rw * rw; q += blockDim.x) {
+            const long long k = global_of(q);
+            const int tv = k >= 0 ? s.tag[k] : TAG_NONE;
+            st[q] = (unsigned char)tv;
+            xb[q] = 0.0;
+            yb[q] = 0.0;
+            if (tv >= 1 && tv <= L) {
+                const int d = dist(q);
+                if (d <= 2 * tv) atomicAdd(&cnt[tv], 1);
+                if (d <= 2) near = 1;
             }
         }
-        for (int r = 2; r <= g.r_max; r++) {
-            double M00 = 0, M01 = 0, M02 = 0, M11 = 0, M12 = 0, M22 = 0;
-            double bX0 = 0, bX1 = 0, bX2 = 0, bY0 = 0, bY1 = 0, bY2 = 0;
-            int count = 0;
-            for (int bb = -r; bb <= r; bb++)
-                for (int aa = -r; aa <= r; aa++) {
-                    int x = i + aa, y = j + bb;
-                    if (!canon(g, x, y) || !W.has(x, y)) continue;
-                    const long long k = pidx(g, x, y);
-                    const int t = s.tag[k];
-                    if (!(t == TAG_SOLID || (t > 0 && t < l))) continue;
-                    count++;
-                    double wt = ldexp(1.0, -(abs(aa) + abs(bb)));
-                    if (use_n) {
-                        const double ddx = -(double)aa, ddy = -(double)bb;
-                        const double dn = (ddx * nxh + ddy * nyh) / sqrt(ddx * ddx + ddy * ddy);
-                        wt = dn * wt > 0.0 ? dn * wt : 0.0;
-                    }
-                    const double dx = aa, dy = bb, xv = s.X1[k], yv = s.Y1[k];
-                    M00 += wt * dx * dx; M01 += wt * dx * dy; M02 += wt * dx;
-                    M11 += wt * dy * dy; M12 += wt * dy; M22 += wt;
-                    bX0 += wt * dx * xv; bX1 += wt * dy * xv; bX2 += wt * xv;
-                    bY0 += wt * dx * yv; bY1 += wt * dy * yv; bY2 += wt * yv;
-                }
-            if (count < 3) continue;
-            const double det = M00 * (M11 * M22 - M12 * M12) - M01 * (M01 * M22 - M12 * M02) +
-                               M02 * (M01 * M12 - M11 * M02);
-            if (!(det > g.det_rel * M22 * M22 * M22)) continue;
-            // inverse of the symmetric normal matrix
-            const double i00 = (M11 * M22 - M12 * M12) / det, i01 = (M02 * M12 - M01 * M22) / det;
-            const double i02 = (M01 * M12 - M11 * M02) / det, i11 = (M00 * M22 - M02 * M02) / det;
-            const double i12 = (M01 * M02 - M00 * M12) / det, i22 = (M00 * M11 - M01 * M01) / det;
-            // s = M^{-1} e3, plane coefficients p = M^{-1} b
-            const double s0 = i02, s1 = i12, s2 = i22;
-            const double pX0 = i00 * bX0 + i01 * bX1 + i02 * bX2;
-            const double pX1 = i01 * bX0 + i11 * bX1 + i12 * bX2;
-            const double pX2 = i02 * bX0 + i12 * bX1 + i22 * bX2;
-            const double pY0 = i00 * bY0 + i01 * bY1 + i02 * bY2;
-            const double pY1 = i01 * bY0 + i11 * bY1 + i12 * bY2;
-            const double pY2 = i02 * bY0 + i12 * bY1 + i22 * bY2;
-            double nbx = 0.0, nby = 0.0;  // dL/d(normal)
-            for (int bb = -r; bb <= r; bb++)
-                for (int aa = -r; aa <= r; aa++) {
-                    int x = i + aa, y = j + bb;
-                    if (!canon(g, x, y) || !W.has(x, y)) continue;
-                    const long long k = pidx(g, x, y);
-                    const int t = s.tag[k];
-                    if (!(t == TAG_SOLID || (t > 0 && t < l))) continue;
-                    const double w0 = ldexp(1.0, -(abs(aa) + abs(bb)));
-                    double wt = w0, dn = 0.0, ddx = 0.0, ddy = 0.0, dl = 0.0;
-                    if (use_n) {
-                        ddx = -(double)aa;
-                        ddy = -(double)bb;
-                        dl = sqrt(ddx * ddx + ddy * ddy);
-                        dn = (ddx * nxh + ddy * nyh) / dl;
-                        wt = dn * w0 > 0.0 ? dn * w0 : 0.0;
-                    }
-                    const double as = s0 * aa + s1 * bb + s2;
-                    if (wt != 0.0) {
-                        atomicAdd(&a.xbar1[k], Xb * wt * as);
-                        atomicAdd(&a.ybar1[k], Yb * wt * as);
-                    }
-                    if (use_n && dn * w0 > 0.0) {
-                        const double rX = s.X1[k] - (pX0 * aa + pX1 * bb + pX2);
-                        const double rY = s.Y1[k] - (pY0 * aa + pY1 * bb + pY2);
-                        const double wb = as * (Xb * rX + Yb * rY);
-                        const double dnb = wb * w0;
-                        nbx += dnb * ddx / dl;
-                        nby += dnb * ddy / dl;
-                    }
-                }
-            if (use_n && (nbx != 0.0 || nby != 0.0)) {
-                // n = g / |g|, g = ((phi_e - phi_w) / 2, (phi_n - phi_s) / 2)
-                const double dotp = nbx * nxh + nby * nyh;
-                const double gbx = (nbx - dotp * nxh) / gn, gby = (nby - dotp * nyh) / gn;
-                atomicAdd(&a.pbar0[kn[0]], gbx / 2.0);
-                atomicAdd(&a.pbar0[kn[1]], -gbx / 2.0);
-                atomicAdd(&a.pbar0[kn[2]], gby / 2.0);
-                atomicAdd(&a.pbar0[kn[3]], -gby / 2.0);
+        __syncthreads();
+        if (!near) continue;  // (uniform; the loop's next barrier follows the reads)
+        if (threadIdx.x == 0) {
+            int o = 0;
+            for (int l = 1; l <= L; l++) {
+                at[l] = o;
+                o += cnt[l];
+                cnt[l] = 0;
             }
-            break;
+            at[L + 1] = o;
         }
+        __syncthreads();
+        for (int q = threadIdx.x; q < rw * rw; q += blockDim.x) {
+            const int tv = st[q];
+            if (tv >= 1 && tv <= L && dist(q) <= 2 * tv) {
+                lst[at[tv] + atomicAdd(&cnt[tv], 1)] = (unsigned short)q;
+                const long long k = global_of(q);
+                double x = a.xbar1[k], y = a.ybar1[k];
+                adj_relabel_node(b, s, k, a.pbar1[k], x, y);
+                xb[q] = x;
+                yb[q] = y;
+            }
+        }
+        __syncthreads();
+        for (int l = L; l >= 1; l--) {
+            for (int e = at[l] + threadIdx.x; e < at[l + 1]; e += blockDim.x) {
+                const int q = lst[e];
+                const double Xb = xb[q], Yb = yb[q];
+                if (Xb == 0.0 && Yb == 0.0) continue;
+                int i = x0 + q % rw, j = y0 + q / rw;
+                canon(g, i, j);
+                adj_fit_target<2>(
+                    g, D, s, a, l, i, j, Xb, Yb, dist(q) <= 0,
+                    [&](int aa, int bb) {
+                        const int k = q + bb * rw + aa;
+                        return st[k] < l ? k : -1;
+                    },
+                    [&](int, int aa, int bb, double& xv, double& yv) {
+                        int x = i + aa, y = j + bb;
+                        canon(g, x, y);
+                        const long long k = pidx(g, x, y);
+                        xv = s.X1[k];
+                        yv = s.Y1[k];
+                    },
+                    [&](int k, double vx, double vy) {
+                        atomicAdd(&xb[k], vx);
+                        atomicAdd(&yb[k], vy);
+                    });
+            }
+            __syncthreads();
+        }
+        for (int e = threadIdx.x; e < AT * AT; e += blockDim.x) {
+            const int q = (m + e / AT) * rw + m + e % AT;
+            if (st[q] != TAG_SOLID) continue;
+            const double x = xb[q], y = yb[q];
+            if (x == 0.0 && y == 0.0) continue;
+            const long long k = global_of(q);
+            a.xbar1[k] += x;
+            a.ybar1[k] += y;
+        }
+        __syncthreads();
     }
 }
 
 // ---------------------------------------------------------------- advection
 // Solid nodes of S^n backwards: xi~ = xi - (u d/dx + v d/dy) xi with the
-// upwind side of the forward step.  dL/dxi~ (held in xbar1 at solid nodes) ->
-// xbar0 at the node and its stencil nodes, and u^n -> f^n, F^{n-1}.
-__global__ __launch_bounds__(256) void k_adj_advect(GridP g, AdjSnap s, AdjBufs a)
+// upwind side of the forward step.  dL/dxi~ (held in xbar1 at solid nodes,
+// after their relabel backwards) -> xbar0 at the node and its stencil nodes,
+// and u^n -> f^n, F^{n-1}.  The adjoints of state n + 1 are spent: every node
+// of their window (nothing outside it was added to) is cleared here, the next
+// step's xbar0, ybar0, pbar0 to be.
+__global__ __launch_bounds__(256) void k_adj_advect(GridP g, BodyP b, AdjSnap s, AdjBufs a)
 {
     const Rect W = window_of(s.win, 1, g);
     const Rect D = window_of(s.win, 0, g);
@@ -507,10 +702,15 @@ __global__ __launch_bounds__(256) void k_adj_advect(GridP g, AdjSnap s, AdjBufs 
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < (long long)w * h;
          e += (long long)gridDim.x * blockDim.x) {
         const int i = W.i0 + (int)(e % w), j = W.j0 + (int)(e / w);
-        if (i < 0 || i >= g.nx || j < 0 || j >= g.ny) continue;
         const long long k0 = pidx(g, i, j);
-        if (s.tag[k0] != TAG_SOLID) continue;
-        const double Xb = a.xbar1[k0], Yb = a.ybar1[k0];
+        double Xb = a.xbar1[k0], Yb = a.ybar1[k0];
+        const double pb = a.pbar1[k0];
+        const bool solid = s.tag[k0] == TAG_SOLID;
+        a.xbar1[k0] = 0.0;
+        a.ybar1[k0] = 0.0;
+        a.pbar1[k0] = 0.0;
+        if (i < 0 || i >= g.nx || j < 0 || j >= g.ny || !solid) continue;
+        adj_relabel_node(b, s, k0, pb, Xb, Yb);
         if (Xb == 0.0 && Yb == 0.0) continue;
         // u^n at the node
         double f[NQ];
@@ -661,16 +861,21 @@ __global__ __launch_bounds__(256) void k_adj_init(GridP g, BodyP b, AdjSnap s, A
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_adjoint_step(const GridP& g, const BodyP& b, const AdjSnap& s,
-                               const AdjBufs& a, hipStream_t st)
+                               const AdjBufs& a, bool fused, hipStream_t st)
 {
     const long long N = (long long)g.nx * g.ny;
     const int blocks = (int)((N + 255) / 256 < 4096 ? (N + 255) / 256 : 4096);
     k_adj_lattice<<<blocks, 256, 0, st>>>(g, b, s, a);
     k_adj_force<<<blocks, 256, 0, st>>>(g, b, s, a);
     if (b.present) {
-        k_adj_relabel<<<blocks, 256, 0, st>>>(g, b, s, a);
-        for (int l = g.layers; l >= 1; l--) k_adj_fit<<<blocks, 256, 0, st>>>(g, s, a, l);
-        k_adj_advect<<<blocks, 256, 0, st>>>(g, s, a);
+        if (fused) {
+            const long long tiles = fused_tiles(g.nx, g.ny);
+            k_adj_fits<<<(int)(tiles < 1024 ? tiles : 1024), AT_THREADS, 0, st>>>(g, b, s, a);
+        } else {
+            k_adj_relabel<<<blocks, 256, 0, st>>>(g, b, s, a);
+            for (int l = g.layers; l >= 1; l--) k_adj_fit<<<blocks, 256, 0, st>>>(g, b, s, a, l);
+        }
+        k_adj_advect<<<blocks, 256, 0, st>>>(g, b, s, a);
     }
     return hipGetLastError();
 }
@@ -693,17 +898,46 @@ hipError_t launch_adjoint_init(const GridP& g, const BodyP& b, const AdjSnap& s,
     return hipGetLastError();
 }
 
-__global__ void k_set2(double* dst, double x, double y)
+// ---------------------------------------------------------------- snapshot
+
+// Every piece of a snapshot in one launch (block row y copies piece y, 8 bytes
+// a thread and access; twelve copies and a fill of their own, each a few us,
+// took longer than the step), with the two windows, the uniform force
+// F^{n-1} and the wide-window flag of the step's extrapolation
+__global__ __launch_bounds__(256) void k_snapshot(SnapCopy c)
 {
-    if (threadIdx.x == 0) {
-        dst[0] = x;
-        dst[1] = y;
+    const SnapPiece p = c.piece[blockIdx.y];
+    const unsigned long long* src = (const unsigned long long*)p.src;
+    unsigned long long* dst = (unsigned long long*)p.dst;
+    const long long n = p.bytes / 8, st = (long long)gridDim.x * blockDim.x;
+    const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    constexpr int U = 4;
+    for (long long e = t; e < n; e += U * st) {
+        unsigned long long v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) v[u] = src[e + u * st < n ? e + u * st : e];
+#pragma unroll
+        for (int u = 0; u < U; u++)
+            if (e + u * st < n) dst[e + u * st] = v[u];
+    }
+    if (blockIdx.x == 0 && (long long)threadIdx.x < p.bytes % 8)
+        ((char*)p.dst)[n * 8 + threadIdx.x] = ((const char*)p.src)[n * 8 + threadIdx.x];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        c.win[0] = *c.wprev;
+        c.win[1] = *c.wcur;
+        c.fpo[0] = c.fpo_x;
+        c.fpo[1] = c.fpo_y;
+        *c.wide = c.wide_src ? *c.wide_src : 1;
     }
 }
 
-hipError_t launch_set2(double* dst, double x, double y, hipStream_t st)
+hipError_t launch_snapshot(const SnapCopy& c, int pieces, hipStream_t st)
 {
-    k_set2<<<1, 64, 0, st>>>(dst, x, y);
+    long long most = 0;
+    for (int k = 0; k < pieces; k++) most = most < c.piece[k].bytes ? c.piece[k].bytes : most;
+    const long long want = (most / 8 + 1023) / 1024;  // four accesses per thread
+    const dim3 grid((unsigned)(want < 1 ? 1 : want < 1024 ? want : 1024), pieces);
+    k_snapshot<<<grid, 256, 0, st>>>(c);
     return hipGetLastError();
 }
 

@@ -1497,7 +1497,7 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
                                                const T* __restrict__ phin, T* X1, T* Y1,
                                                unsigned* health, int* cut_tiles, int* ncut,
                                                const int* __restrict__ ff_list, int* ff_n,
-                                               unsigned* ticket, int reach)
+                                               unsigned* ticket, int* wide, int reach)
 {
     constexpr int RW = FF_REGION;
     __shared__ FitLds<T, RW * RW, FF_LAYER> s;
@@ -1529,6 +1529,7 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     if (threadIdx.x == 0) {
         *ncut = 0;
         *ff_n = 0;
+        *wide = nc;
     }
 }
 
@@ -1538,10 +1539,10 @@ __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict
                                                   const T* __restrict__ phin, T* X1, T* Y1,
                                                   unsigned* health, int* cut_tiles, int* ncut,
                                                   const int* __restrict__ ff_list, int* ff_n,
-                                                  unsigned* ticket, int reach)
+                                                  unsigned* ticket, int* wide, int reach)
 {
     fit_fused_body<T, NT, LC>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_tiles, ncut,
-                              ff_list, ff_n, ticket, reach);
+                              ff_list, ff_n, ticket, wide, reach);
 }
 
 // a batch: member blockIdx.y
@@ -1551,7 +1552,7 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_fused(const FitArgs* __rest
     const FitArgs& a = args[blockIdx.y];
     fit_fused_body<T, FF_THREADS, LC>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin,
                                       (T*)a.X1, (T*)a.Y1, a.health, a.cut_tiles, a.ncut,
-                                      a.ff_list, a.ff_n, a.ticket, 2);
+                                      a.ff_list, a.ff_n, a.ticket, a.ff_wide, 2);
 }
 
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
@@ -1562,7 +1563,7 @@ hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlot
     k_fit_fused<T, NT, LC><<<FF_BLOCKS, NT, 0, st>>>(                                             \
         g, bb.win, s.wcur, s.wprev, bb.tag, (const T*)bb.phi[s.cur], (T*)bb.X[s.nxt],             \
         (T*)bb.Y[s.nxt], bb.health, bb.cut_tiles, bb.ncut, bb.ff_list, bb.ff_n, bb.ticket,       \
-        fused_threads == 1 ? 1 : 2)
+        bb.ff_wide, fused_threads == 1 ? 1 : 2)
 #define FUSED(T, NT)                                                                              \
     do {                                                                                          \
         if (g.layers == FF_LAYERS) FUSED_L(T, NT, FF_LAYERS);                                     \

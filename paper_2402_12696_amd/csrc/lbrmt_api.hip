@@ -110,7 +110,7 @@ struct Layout {
     size_t rm_es;  // bytes per reference-map value: 8 (FP64 xi) or 4 (FP32 displacement)
     size_t off_lat[2], off_fx[2], off_fy[2], off_drho, off_X[2], off_Y[2], off_phi[2], off_tag,
         off_win, off_health, off_dpart, off_dout, off_gcol, off_lists, off_lcount, off_boxpart,
-        off_ticket, off_cut_tiles, off_ncut, off_ff_list, off_ff_n,
+        off_ticket, off_cut_tiles, off_ncut, off_ff_list, off_ff_n, off_ff_wide,
         total;
     size_t lat_bytes;
     // several solids
@@ -161,6 +161,7 @@ Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
     L.off_ncut = take(4);
     L.off_ff_list = take(ntile * 4);
     L.off_ff_n = take(4);
+    L.off_ff_wide = take(4);
     L.off_win = take(3 * sizeof(Win));
     L.off_health = take(LBRMT_H_COUNT * sizeof(unsigned));
     L.off_dpart = take(diag_partial_doubles() * 8);
@@ -717,6 +718,7 @@ static int create_impl(const lbrmt_grid_desc* d, int32_t max_solids, void* ws, s
     c->bb.ncut = (int*)(c->ws + L.off_ncut);
     c->bb.ff_list = (int*)(c->ws + L.off_ff_list);
     c->bb.ff_n = (int*)(c->ws + L.off_ff_n);
+    c->bb.ff_wide = (int*)(c->ws + L.off_ff_wide);
     c->bb.win = (Win*)(c->ws + L.off_win);
     c->bb.health = (unsigned*)(c->ws + L.off_health);
     c->dpart = (double*)(c->ws + L.off_dpart);
@@ -884,6 +886,7 @@ static BandBufs mb_bufs(const lbrmt_ctx* c, int k)
     b.ncut = nullptr;
     b.ff_list = nullptr;
     b.ff_n = nullptr;
+    b.ff_wide = nullptr;
     return b;
 }
 
@@ -1015,6 +1018,7 @@ static hipError_t clear_cut_tiles(lbrmt_ctx* c, hipStream_t st)
     if (c->multi) return hipSuccess;  // several solids: no fused extrapolation
     hipError_t e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
     if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_n, 0, 4, st);
+    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_wide, 0, 4, st);
     return e;
 }
 
@@ -1315,7 +1319,7 @@ int lbrmt_diag_solid(lbrmt_ctx* c, int32_t solid, double* out)
 namespace {
 
 struct SnapLayout {
-    size_t A, fpx, fpy, fcx, fcy, X0, Y0, P0, X1, Y1, P1, tag, win, fpo, total;
+    size_t A, fpx, fpy, fcx, fcy, X0, Y0, P0, X1, Y1, P1, tag, win, fpo, wide, total;
 };
 
 SnapLayout snap_layout(const lbrmt_ctx* c)
@@ -1342,6 +1346,7 @@ SnapLayout snap_layout(const lbrmt_ctx* c)
     S.tag = take(c->L.pplane);
     S.win = take(2 * sizeof(Win));
     S.fpo = take(2 * 8);
+    S.wide = take(4);
     S.total = o;
     return S;
 }
@@ -1365,6 +1370,7 @@ AdjSnap adj_snap(const lbrmt_ctx* c, const void* snap)
     a.tag = (const int8_t*)(b + S.tag);
     a.win = (const Win*)(b + S.win);
     a.fpo = (const double*)(b + S.fpo);
+    a.wide = (const int*)(b + S.wide);
     return a;
 }
 
@@ -1445,26 +1451,35 @@ int lbrmt_step_snapshot(lbrmt_ctx* c, void* snap)
     c->step = n + 1;
     const SnapLayout S = snap_layout(c);
     char* b = (char*)snap;
-    const hipMemcpyKind D2D = hipMemcpyDeviceToDevice;
-    const size_t pl = c->L.plane * 8, rp = c->L.pplane * 8;
-    hipStream_t st = c->st;
-    HIPCHK(c, hipMemcpyAsync(b + S.A, c->lat[s.cur], c->L.lat_bytes, D2D, st));
-    HIPCHK(c, hipMemcpyAsync(b + S.fpx, c->Fx[s.nxt], pl, D2D, st));
-    HIPCHK(c, hipMemcpyAsync(b + S.fpy, c->Fy[s.nxt], pl, D2D, st));
-    HIPCHK(c, hipMemcpyAsync(b + S.fcx, c->Fx[s.cur], pl, D2D, st));
-    HIPCHK(c, hipMemcpyAsync(b + S.fcy, c->Fy[s.cur], pl, D2D, st));
+    const long long pl = c->L.plane * 8, rp = c->L.pplane * 8;
+    SnapCopy q{};
+    int np = 0;
+    auto piece = [&](size_t at, const void* src, long long bytes) {
+        q.piece[np++] = SnapPiece{src, b + at, bytes};
+    };
+    piece(S.A, c->lat[s.cur], (long long)c->L.lat_bytes);
+    piece(S.fpx, c->Fx[s.nxt], pl);
+    piece(S.fpy, c->Fy[s.nxt], pl);
+    piece(S.fcx, c->Fx[s.cur], pl);
+    piece(S.fcy, c->Fy[s.cur], pl);
     if (c->nsolid > 0) {
-        HIPCHK(c, hipMemcpyAsync(b + S.X0, c->bb.X[s.cur], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.Y0, c->bb.Y[s.cur], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.P0, c->bb.phi[s.cur], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.X1, c->bb.X[s.nxt], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.Y1, c->bb.Y[s.nxt], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.P1, c->bb.phi[s.nxt], rp, D2D, st));
-        HIPCHK(c, hipMemcpyAsync(b + S.tag, c->bb.tag, c->L.pplane, D2D, st));
+        piece(S.X0, c->bb.X[s.cur], rp);
+        piece(S.Y0, c->bb.Y[s.cur], rp);
+        piece(S.P0, c->bb.phi[s.cur], rp);
+        piece(S.X1, c->bb.X[s.nxt], rp);
+        piece(S.Y1, c->bb.Y[s.nxt], rp);
+        piece(S.P1, c->bb.phi[s.nxt], rp);
+        piece(S.tag, c->bb.tag, c->L.pplane);
     }
-    HIPCHK(c, hipMemcpyAsync(b + S.win, c->bb.win + s.wprev, sizeof(Win), D2D, st));
-    HIPCHK(c, hipMemcpyAsync(b + S.win + sizeof(Win), c->bb.win + s.wcur, sizeof(Win), D2D, st));
-    HIPCHK(c, launch_set2((double*)(b + S.fpo), fpo_x(c, n), fpo_y(c, n), st));
+    q.wprev = c->bb.win + s.wprev;
+    q.wcur = c->bb.win + s.wcur;
+    q.win = (Win*)(b + S.win);
+    q.fpo = (double*)(b + S.fpo);
+    q.fpo_x = fpo_x(c, n);
+    q.fpo_y = fpo_y(c, n);
+    q.wide_src = fused_threads(c) > 0 && fused_fit_ok(c->g) ? c->bb.ff_wide : nullptr;
+    q.wide = (int*)(b + S.wide);
+    HIPCHK(c, launch_snapshot(q, np, c->st));
     return LBRMT_OK;
 }
 
@@ -1508,16 +1523,11 @@ int lbrmt_adjoint_step(lbrmt_ctx* c, void* adj, const void* snap)
 {
     if (!c || !adj || !snap) return LBRMT_EINVAL;
     if (!adj_ok(c)) return LBRMT_ESTATE;
-    HIPCHK(c, launch_adjoint_step(c->g, c->body, adj_snap(c, snap), adj_bufs(c, adj), c->st));
-    // state n becomes the next step's state n + 1; the spent half is cleared
+    HIPCHK(c, launch_adjoint_step(c->g, c->body, adj_snap(c, snap), adj_bufs(c, adj),
+                                  fused_threads(c) > 0 && fused_fit_ok(c->g), c->st));
+    // state n becomes the next step's state n + 1 (the step cleared the spent
+    // half)
     c->adj_flip = 1 - c->adj_flip;
-    const AdjLayout L = adj_layout(c);
-    const int h = 1 - c->adj_flip;
-    char* b = (char*)adj;
-    const size_t rp = c->L.pplane * 8;
-    HIPCHK(c, hipMemsetAsync(b + L.x[h], 0, rp, c->st));
-    HIPCHK(c, hipMemsetAsync(b + L.y[h], 0, rp, c->st));
-    HIPCHK(c, hipMemsetAsync(b + L.p[h], 0, rp, c->st));
     return LBRMT_OK;
 }
 
@@ -2104,7 +2114,7 @@ int batch_tables(lbrmt_batch* b)
             fit[k] = FitArgs{g, c->bb.win, s.wcur, s.wprev, c->bb.tag, c->bb.lists, c->bb.lcount,
                              c->bb.phi[s.cur], c->bb.X[s.nxt], c->bb.Y[s.nxt], c->bb.health,
                              c->bb.cut_tiles, c->bb.ncut, c->bb.ff_list, c->bb.ff_n,
-                             c->bb.ticket};
+                             c->bb.ticket, c->bb.ff_wide};
             edg[k] = EdgesArgs{g, c->body, c->bb.win, s.wcur, c->bb.boxpart, c->bb.X[s.nxt],
                                c->bb.Y[s.nxt], c->bb.tag, c->bb.phi[s.nxt], c->Fx[s.cur],
                                c->Fy[s.cur], c->drho, c->bb.lcount, c->bb.health};

@@ -146,6 +146,7 @@ struct BandBufs {
     // the distance transform (list and count; cleared each step)
     int* ff_list;
     int* ff_n;
+    int* ff_wide;  // stopped tiles of the last step
 };
 
 // ---- box reductions (wave64 shuffles + LDS)
@@ -284,6 +285,7 @@ struct FitArgs {
     // the fused extrapolation's buffers (batches of single-solid members)
     int *cut_tiles, *ncut, *ff_list, *ff_n;
     unsigned* ticket;
+    int* ff_wide;
 };
 struct EdgesArgs {
     GridP g;
@@ -462,6 +464,22 @@ struct AdjSnap {
     const int8_t* tag;           // solid / layer tags of step n
     const Win* win;              // [0] = wprev, [1] = wcur
     const double* fpo;           // F^{n-1} outside the window (x, y)
+    const int* wide;             // not 0: some fit's scan window was wider than 2
+};
+
+// one launch's copies of a snapshot
+struct SnapPiece {
+    const void* src;
+    void* dst;
+    long long bytes;
+};
+struct SnapCopy {
+    SnapPiece piece[12];
+    const Win *wprev, *wcur;
+    Win* win;
+    double *fpo, fpo_x, fpo_y;
+    const int* wide_src;  // null: unknown (taken as wide)
+    int* wide;
 };
 
 // Adjoint fields of one reverse step: *1 belong to state n+1 (read), *0 to
@@ -650,13 +668,13 @@ hipError_t launch_mb_diag(int precision, const MbBody* bodies, int nb, int buf, 
 // layers from last to first, advection); the loss of one state (which = 0:
 // the step's input state, 1: its output); the initial velocity
 hipError_t launch_adjoint_step(const GridP& g, const BodyP& b, const AdjSnap& s,
-                               const AdjBufs& a, hipStream_t st);
+                               const AdjBufs& a, bool fused, hipStream_t st);
 hipError_t launch_adjoint_loss(const GridP& g, const BodyP& b, const AdjSnap& s,
                                const AdjBufs& a, int which, const LossCoef& c, hipStream_t st);
 hipError_t launch_adjoint_init(const GridP& g, const BodyP& b, const AdjSnap& s,
                                const AdjBufs& a, double* u0bar, hipStream_t st);
 // dst[0] = x, dst[1] = y (device, stream-ordered)
-hipError_t launch_set2(double* dst, double x, double y, hipStream_t st);
+hipError_t launch_snapshot(const SnapCopy& c, int pieces, hipStream_t st);
 
 // reductions (k_diag.hip); partial: scratch of diag_partial_doubles() doubles
 int diag_blocks();
