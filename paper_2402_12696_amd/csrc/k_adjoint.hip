@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lbrmt_internal.h"
+#include "fit_window.h"
 
 namespace lbrmt {
 
@@ -420,9 +421,9 @@ __device__ __forceinline__ void adj_fit_target(const GridP& g, const Rect& D, co
         double M00 = 0, M01 = 0, M02 = 0, M11 = 0, M12 = 0, M22 = 0;
         double bX0 = 0, bX1 = 0, bX2 = 0, bY0 = 0, bY1 = 0, bY2 = 0;
         int count = 0;
-#pragma unroll(RMAX == 2 ? 5 : 1)
+#pragma unroll RMAX == 2 ? 5 : 1
         for (int bb = -r; bb <= r; bb++)
-#pragma unroll(RMAX == 2 ? 5 : 1)
+#pragma unroll RMAX == 2 ? 5 : 1
             for (int aa = -r; aa <= r; aa++) {
                 if (aa == 0 && bb == 0) continue;  // (the target is of layer l)
                 const auto k = node(aa, bb);
@@ -433,7 +434,7 @@ __device__ __forceinline__ void adj_fit_target(const GridP& g, const Rect& D, co
                 const double dx = aa, dy = bb;
                 M00 += wt * dx * dx; M01 += wt * dx * dy; M02 += wt * dx;
                 M11 += wt * dy * dy; M12 += wt * dy; M22 += wt;
-                if (use_n) {
+                if (use_n && own) {
                     double xv, yv;
                     val(k, aa, bb, xv, yv);
                     bX0 += wt * dx * xv; bX1 += wt * dy * xv; bX2 += wt * xv;
@@ -450,7 +451,7 @@ __device__ __forceinline__ void adj_fit_target(const GridP& g, const Rect& D, co
         // s = M^{-1} e3, plane coefficients p = M^{-1} b
         const double s0 = i02, s1 = i12, s2 = i22;
         double pX0 = 0, pX1 = 0, pX2 = 0, pY0 = 0, pY1 = 0, pY2 = 0;
-        if (use_n) {
+        if (use_n && own) {
             const double i00 = (M11 * M22 - M12 * M12) / det, i01 = (M02 * M12 - M01 * M22) / det;
             const double i11 = (M00 * M22 - M02 * M02) / det;
             pX0 = i00 * bX0 + i01 * bX1 + i02 * bX2;
@@ -461,9 +462,9 @@ __device__ __forceinline__ void adj_fit_target(const GridP& g, const Rect& D, co
             pY2 = i02 * bY0 + i12 * bY1 + i22 * bY2;
         }
         double nbx = 0.0, nby = 0.0;  // dL/d(normal)
-#pragma unroll(RMAX == 2 ? 5 : 1)
+#pragma unroll RMAX == 2 ? 5 : 1
         for (int bb = -r; bb <= r; bb++)
-#pragma unroll(RMAX == 2 ? 5 : 1)
+#pragma unroll RMAX == 2 ? 5 : 1
             for (int aa = -r; aa <= r; aa++) {
                 if (aa == 0 && bb == 0) continue;
                 const auto k = node(aa, bb);
@@ -566,15 +567,18 @@ __global__ __launch_bounds__(256) void k_adj_fit(GridP g, BodyP b, AdjSnap s, Ad
 // them).  Only the tile's solid nodes are written: what the zone's nodes hold
 // is spent after this, and k_adj_advect clears it, so no block reads what
 // another writes.  Bound by a chain of L dependent layers in LDS; launches of
-// their own each scanned the window's tags again (gradient of 100 steps at
-// 256^2: 12 launches, ~75 us a step -> one, ~20 us).
+// their own each scanned the window's tags again (256^2, solid of radius 40:
+// 12 launches, ~75 us a step -> one, 43 us).
 // s.wide: some target of the step has a wider scan window (or none): then one
 // block runs the layers on the fields in memory.
 constexpr int AT = FF_TILE, AT_THREADS = 512;
 constexpr int AT_R = AT + 4 * FF_LAYERS + 4;  // side of the copy at FF_LAYERS layers
+// LC: the layer count (FF_LAYERS), or 0 (the grid's)
+template <int LC>
 __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSnap s, AdjBufs a)
 {
-    constexpr int NN = AT_R * AT_R;
+    constexpr int NN = AT_R * AT_R, NIT = (NN + AT_THREADS - 1) / AT_THREADS;
+    constexpr int NSET = 4, SW = AT_THREADS / NSET;  // sets of threads, targets per pass
     __shared__ double xb[NN], yb[NN];
     __shared__ unsigned char st[NN];
     __shared__ unsigned short lst[NN];
@@ -582,7 +586,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
     const Rect W = window_of(s.win, 1, g);
     const Rect D = window_of(s.win, 0, g);
     if (!W.ok) return;
-    const int L = g.layers;
+    const int L = LC > 0 ? LC : g.layers;
     if (*s.wide != 0) {
         if (blockIdx.x != 0) return;
         for (int l = L; l >= 1; l--) {
@@ -592,13 +596,14 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
         }
         return;
     }
-    const int m = 2 * L + 2, rw = AT + 2 * m;
+    const int m = 2 * L + 2, rw = LC == FF_LAYERS ? AT_R : AT + 2 * m;
     const int ntx = (W.i1 - W.i0 + AT) / AT, nty = (W.j1 - W.j0 + AT) / AT;
     for (int t = blockIdx.x; t < ntx * nty; t += gridDim.x) {
         const int x0 = W.i0 + (t % ntx) * AT - m, y0 = W.j0 + (t / ntx) * AT - m;
-        if (threadIdx.x <= FF_LAYERS + 1) cnt[threadIdx.x] = 0;
-        if (threadIdx.x == 0) near = 0;
-        __syncthreads();
+        // (behind an empty asm: what follows from the thread's number is
+        // computed here, not held over the loop)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
         // node of the copy (unwrapped; a periodic axis wraps)
         auto global_of = [&](int q) -> long long {
             int x = x0 + q % rw, y = y0 + q / rw;
@@ -609,21 +614,34 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
             const int lx = q % rw - m, ly = q / rw - m;
             return max(max(-lx, lx - (AT - 1)), max(-ly, ly - (AT - 1)));
         };
-        for (int q = threadIdx.x; q < rw * rw; q += blockDim.x) {
-            const long long k = global_of(q);
-            const int tv = k >= 0 ? s.tag[k] : TAG_NONE;
+        int tvs[NIT];  // the thread's tags, all in flight together
+#pragma unroll
+        for (int u = 0; u < NIT; u++) {
+            const int q = tid + u * AT_THREADS;
+            const long long k = q < rw * rw ? global_of(q) : -1;
+            const int tv = s.tag[k >= 0 ? k : 0];
+            tvs[u] = k >= 0 ? tv : TAG_NONE;
+        }
+        if (tid <= FF_LAYERS + 1) cnt[tid] = 0;
+        if (tid == 0) near = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NIT; u++) {
+            const int q = tid + u * AT_THREADS, tv = tvs[u];
+            if (q >= rw * rw) continue;
             st[q] = (unsigned char)tv;
             xb[q] = 0.0;
             yb[q] = 0.0;
             if (tv >= 1 && tv <= L) {
                 const int d = dist(q);
                 if (d <= 2 * tv) atomicAdd(&cnt[tv], 1);
+                else tvs[u] = TAG_NONE;  // no target of this block
                 if (d <= 2) near = 1;
             }
         }
         __syncthreads();
-        if (!near) continue;  // (uniform; the loop's next barrier follows the reads)
-        if (threadIdx.x == 0) {
+        if (!near) continue;  // (uniform; nothing of the tile hears from the zone)
+        if (tid == 0) {
             int o = 0;
             for (int l = 1; l <= L; l++) {
                 at[l] = o;
@@ -633,37 +651,130 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
             at[L + 1] = o;
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < rw * rw; q += blockDim.x) {
-            const int tv = st[q];
-            if (tv >= 1 && tv <= L && dist(q) <= 2 * tv) {
-                lst[at[tv] + atomicAdd(&cnt[tv], 1)] = (unsigned short)q;
-                const long long k = global_of(q);
-                double x = a.xbar1[k], y = a.ybar1[k];
-                adj_relabel_node(b, s, k, a.pbar1[k], x, y);
-                xb[q] = x;
-                yb[q] = y;
-            }
+#pragma unroll
+        for (int u = 0; u < NIT; u++) {
+            const int q = tid + u * AT_THREADS, tv = tvs[u];
+            if (tv < 1 || tv > L) continue;
+            lst[at[tv] + atomicAdd(&cnt[tv], 1)] = (unsigned short)q;
         }
         __syncthreads();
-        for (int l = L; l >= 1; l--) {
-            for (int e = at[l] + threadIdx.x; e < at[l + 1]; e += blockDim.x) {
+        // the targets' adjoints, relabelled (every load in flight together)
+#pragma unroll 1
+        for (int e = tid; e < at[L + 1]; e += AT_THREADS) {
+            const int q = lst[e];
+            const long long k = global_of(q);
+            double x = a.xbar1[k], y = a.ybar1[k];
+            const double pb = a.pbar1[k], P = s.P1[k], X = s.X1[k], Y = s.Y1[k];
+            if (pb != 0.0 && P < INFINITY) {
+                double gx, gy;
+                grad_phi0(b, X, Y, gx, gy);
+                x += pb * gx;
+                y += pb * gy;
+            }
+            xb[q] = x;
+            yb[q] = y;
+        }
+        __syncthreads();
+        // layers 3 and up, a set of threads to each layer in turn: a set
+        // finds its targets' valid nodes and s while the others add.  The
+        // matrix is counted from the mask (its entries times 16 are whole),
+        // so s has the bits of sums in double.
+        const int set = tid / SW, lane = tid % SW;
+        int pq = -1;
+        unsigned pm = 0;
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        auto prep = [&](int l, int e, int end) {
+            pq = -1;
+            if (e >= end) return;
+            const int q = lst[e];
+            unsigned mk = 0;
+#pragma unroll
+            for (int n = 0; n < 25; n++)
+                if (n != 12) mk |= st[q + (n / 5 - 2) * rw + n % 5 - 2] < l ? 1u << n : 0u;
+            const Geo2 G = geo2(mk, g.det_rel);
+            if (!G.ok) return;
+            const double det = (double)G.det * 0x1p-12;
+            s0 = (double)G.c0() * 0x1p-8 / det;
+            s1 = (double)G.c1() * 0x1p-8 / det;
+            s2 = (double)G.c2() * 0x1p-8 / det;
+            pq = q;
+            pm = mk;
+        };
+        auto send = [&]() {
+            if (pq < 0) return;
+            const double Xb = xb[pq], Yb = yb[pq];
+            if (Xb == 0.0 && Yb == 0.0) return;
+#pragma unroll
+            for (int n = 0; n < 25; n++) {
+                if (n == 12 || !(pm >> n & 1)) continue;
+                const int aa = n % 5 - 2, bb = n / 5 - 2;
+                const double wt = 1.0 / (1 << ((aa < 0 ? -aa : aa) + (bb < 0 ? -bb : bb)));
+                const double as = s0 * aa + s1 * bb + s2;
+                const int k = pq + bb * rw + aa;
+                atomicAdd(&xb[k], Xb * wt * as);
+                atomicAdd(&yb[k], Yb * wt * as);
+            }
+        };
+        int lm = L - set;  // the set's next layer
+        if (lm >= 3) prep(lm, at[lm] + lane, at[lm + 1]);
+#pragma unroll 1
+        for (int l = L; l >= 3; l--) {
+            if (l == lm) {
+                const int end = at[l + 1];
+                int e = at[l] + lane;
+#pragma unroll 1
+                while (true) {
+                    send();
+                    e += SW;
+                    if (e >= end) break;
+                    prep(l, e, end);
+                }
+            }
+            __syncthreads();
+            if (l == lm) {
+                lm -= NSET;
+                if (lm >= 3) prep(lm, at[lm] + lane, at[lm + 1]);
+            }
+        }
+        // layers 2 and 1: normal weights
+#pragma unroll 1
+        for (int l = min(L, 2); l >= 1; l--) {
+#pragma unroll 1
+            for (int e = at[l] + tid; e < at[l + 1]; e += AT_THREADS) {
                 const int q = lst[e];
                 const double Xb = xb[q], Yb = yb[q];
                 if (Xb == 0.0 && Yb == 0.0) continue;
-                int i = x0 + q % rw, j = y0 + q / rw;
+                const int i0 = x0 + q % rw, j0 = y0 + q / rw;
+                const bool own = dist(q) <= 0;
+                int i = i0, j = j0;
                 canon(g, i, j);
+                // xi^{n+1} of the scan nodes, all in flight together
+                double xs[25], ys[25];
+                if (own) {
+                    int kx[5], ky[5];
+#pragma unroll
+                    for (int n = 0; n < 5; n++) {
+                        int x = i0 + n - 2, y = j0 + n - 2;
+                        if (g.px) x = wrap_axis(x, g.nx);
+                        if (g.py) y = wrap_axis(y, g.ny);
+                        kx[n] = min(max(x, W.i0), W.i1) + PAD;
+                        ky[n] = (min(max(y, W.j0), W.j1) + PAD) * g.pp;
+                    }
+#pragma unroll
+                    for (int n = 0; n < 25; n++) {
+                        xs[n] = s.X1[ky[n / 5] + kx[n % 5]];
+                        ys[n] = s.Y1[ky[n / 5] + kx[n % 5]];
+                    }
+                }
                 adj_fit_target<2>(
-                    g, D, s, a, l, i, j, Xb, Yb, dist(q) <= 0,
+                    g, D, s, a, l, i, j, Xb, Yb, own,
                     [&](int aa, int bb) {
                         const int k = q + bb * rw + aa;
                         return st[k] < l ? k : -1;
                     },
                     [&](int, int aa, int bb, double& xv, double& yv) {
-                        int x = i + aa, y = j + bb;
-                        canon(g, x, y);
-                        const long long k = pidx(g, x, y);
-                        xv = s.X1[k];
-                        yv = s.Y1[k];
+                        xv = xs[(bb + 2) * 5 + aa + 2];
+                        yv = ys[(bb + 2) * 5 + aa + 2];
                     },
                     [&](int k, double vx, double vy) {
                         atomicAdd(&xb[k], vx);
@@ -672,7 +783,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
             }
             __syncthreads();
         }
-        for (int e = threadIdx.x; e < AT * AT; e += blockDim.x) {
+        for (int e = tid; e < AT * AT; e += AT_THREADS) {
             const int q = (m + e / AT) * rw + m + e % AT;
             if (st[q] != TAG_SOLID) continue;
             const double x = xb[q], y = yb[q];
@@ -870,7 +981,9 @@ hipError_t launch_adjoint_step(const GridP& g, const BodyP& b, const AdjSnap& s,
     if (b.present) {
         if (fused) {
             const long long tiles = fused_tiles(g.nx, g.ny);
-            k_adj_fits<<<(int)(tiles < 1024 ? tiles : 1024), AT_THREADS, 0, st>>>(g, b, s, a);
+            const int nb = (int)(tiles < 1024 ? tiles : 1024);
+            if (g.layers == FF_LAYERS) k_adj_fits<FF_LAYERS><<<nb, AT_THREADS, 0, st>>>(g, b, s, a);
+            else k_adj_fits<0><<<nb, AT_THREADS, 0, st>>>(g, b, s, a);
         } else {
             k_adj_relabel<<<blocks, 256, 0, st>>>(g, b, s, a);
             for (int l = g.layers; l >= 1; l--) k_adj_fit<<<blocks, 256, 0, st>>>(g, b, s, a, l);
