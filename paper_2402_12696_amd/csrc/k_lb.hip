@@ -20,13 +20,6 @@
 
 namespace lbrmt {
 
-__device__ __forceinline__ int xcd_remap(int b, int nb)
-{
-    const int per = nb / 8, rem = nb % 8;
-    const int x = b % 8, k = b / 8;
-    return x * per + min(x, rem) + k;
-}
-
 // Band region of a step: every interior node where the force of this step or
 // of the previous one may differ from the uniform fluid force.
 __device__ __forceinline__ Rect band_region(const GridP& g, const Rect& a, const Rect& b)
@@ -44,61 +37,6 @@ __device__ __forceinline__ Rect band_region(const GridP& g, const Rect& a, const
     u.j1 = min(u.j1, g.ny - 1);
     u.ok = u.i0 <= u.i1 && u.j0 <= u.j1;
     return u;
-}
-
-// Update of one tile of LB_TX x (LB_TY * R) nodes: each thread updates R
-// nodes of one column, issuing all their gathers before any arithmetic so
-// that more loads are in flight per wave.  PART 1 tiles (outside the band
-// region) use the uniform fluid force; otherwise the force planes are read
-// inside the windows of this and the previous step.
-// VP, VC: where the force planes of the previous and of this step are held
-// (Rect: a solid's window; StampValid: force-block stamps of several solids)
-template <typename S, int PART, int LB_TX, int LB_TY, int R, bool NT, typename VP = Rect,
-          typename VC = Rect>
-__device__ __forceinline__ void lb_tile(const GridP& g, const S* __restrict__ A, S* __restrict__ B,
-                                        const double* __restrict__ fpx,
-                                        const double* __restrict__ fpy,
-                                        const double* __restrict__ fcx,
-                                        const double* __restrict__ fcy,
-                                        const double* __restrict__ drho, const VP& wp,
-                                        const VC& wc, double fpo_x, double fpo_y,
-                                        unsigned* __restrict__ health, int tile_x, int tile_y)
-{
-    using C = typename Prec<S>::C;
-    constexpr int TH = LB_TY * R;  // tile height
-    const int tx = threadIdx.x % LB_TX, ty = threadIdx.x / LB_TX;
-    const int i = tile_x * LB_TX + tx;
-    if (i >= g.nx) return;
-    Neigh q[R];
-    bool ok[R];
-    C f[R][NQ];
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int j = tile_y * TH + ty + r * LB_TY;
-        // PART 3 leaves the nodes of the current window to the force pass
-        ok[r] = j < g.ny && !(PART == 3 && wc.has(i, j));
-        q[r] = neigh(g, i, j < g.ny ? j : g.ny - 1);
-        if (PART != 3 || ok[r]) gather<S>(g, q[r], A, f[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        if (!ok[r]) continue;
-        const int j = tile_y * TH + ty + r * LB_TY;
-        C Fpx = C(fpo_x), Fpy = C(fpo_y);
-        C Fx = C(g.fext_x), Fy = C(g.fext_y), dr = C(0);
-        if (PART != 1) {
-            if (wp.has(i, j)) {
-                Fpx = C(fpx[q[r].n]);
-                Fpy = C(fpy[q[r].n]);
-            }
-            if (PART != 3 && wc.has(i, j)) {
-                Fx = C(fcx[q[r].n]);
-                Fy = C(fcy[q[r].n]);
-                dr = C(drho[q[r].n]);
-            }
-        }
-        lb_finish_node<S, NT>(g, B, q[r], f[r], Fpx, Fpy, Fx, Fy, dr, health);
-    }
 }
 
 // PART 0: every tile, per-node window tests.  PART 1: tiles outside the band

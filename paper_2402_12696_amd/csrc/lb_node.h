@@ -170,4 +170,94 @@ __device__ __forceinline__ void lb_finish_node(const GridP& g, S* __restrict__ B
     }
 }
 
+__device__ __forceinline__ int xcd_remap(int b, int nb)
+{
+    const int per = nb / 8, rem = nb % 8;
+    const int x = b % 8, k = b / 8;
+    return x * per + min(x, rem) + k;
+}
+
+// Update of one tile of LB_TX x (LB_TY * R) nodes: each thread updates R
+// nodes of one column, issuing all their gathers before any arithmetic so
+// that more loads are in flight per wave.  PART 1 tiles (outside the band
+// region) use the uniform fluid force; otherwise the force planes are read
+// inside the windows of this and the previous step.
+// VP, VC: where the force planes of the previous and of this step are held
+// (Rect: a solid's window; StampValid: force-block stamps of several solids)
+template <typename S, int PART, int LB_TX, int LB_TY, int R, bool NT, typename VP = Rect,
+          typename VC = Rect>
+__device__ __forceinline__ void lb_tile(const GridP& g, const S* __restrict__ A, S* __restrict__ B,
+                                        const double* __restrict__ fpx,
+                                        const double* __restrict__ fpy,
+                                        const double* __restrict__ fcx,
+                                        const double* __restrict__ fcy,
+                                        const double* __restrict__ drho, const VP& wp,
+                                        const VC& wc, double fpo_x, double fpo_y,
+                                        unsigned* __restrict__ health, int tile_x, int tile_y)
+{
+    using C = typename Prec<S>::C;
+    constexpr int TH = LB_TY * R;  // tile height
+    const int tx = threadIdx.x % LB_TX, ty = threadIdx.x / LB_TX;
+    const int i = tile_x * LB_TX + tx;
+    if (i >= g.nx) return;
+    Neigh q[R];
+    bool ok[R];
+    C f[R][NQ];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int j = tile_y * TH + ty + r * LB_TY;
+        // PART 3 leaves the nodes of the current window to the force pass
+        ok[r] = j < g.ny && !(PART == 3 && wc.has(i, j));
+        q[r] = neigh(g, i, j < g.ny ? j : g.ny - 1);
+        if (PART != 3 || ok[r]) gather<S>(g, q[r], A, f[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if (!ok[r]) continue;
+        const int j = tile_y * TH + ty + r * LB_TY;
+        C Fpx = C(fpo_x), Fpy = C(fpo_y);
+        C Fx = C(g.fext_x), Fy = C(g.fext_y), dr = C(0);
+        if (PART != 1) {
+            if (wp.has(i, j)) {
+                Fpx = C(fpx[q[r].n]);
+                Fpy = C(fpy[q[r].n]);
+            }
+            if (PART != 3 && wc.has(i, j)) {
+                Fx = C(fcx[q[r].n]);
+                Fy = C(fcy[q[r].n]);
+                dr = C(drho[q[r].n]);
+            }
+        }
+        lb_finish_node<S, NT>(g, B, q[r], f[r], Fpx, Fpy, Fx, Fy, dr, health);
+    }
+}
+
+// The lattice update outside the current window (lb_tile PART 3, tiles of
+// LbTile) as block b of nb blocks of 256 threads that the force pass takes
+// along
+template <typename S>
+struct LbTile {
+    static constexpr int TX = sizeof(S) == 8 ? 64 : 256, TY = 256 / TX;
+};
+template <typename S>
+__device__ __forceinline__ void lb_along(const GridP& g, const LbFuse& lf, const Win* win,
+                                         int wcur, int b, int nb, unsigned* health)
+{
+    constexpr int TX = LbTile<S>::TX, TY = LbTile<S>::TY;
+    const int ntx = (g.nx + TX - 1) / TX, nt = ntx * ((g.ny + TY - 1) / TY);
+    const Rect wp = window_of(win, lf.wprev, g), wc = window_of(win, wcur, g);
+    for (int t = xcd_remap(b, nb); t < nt; t += nb) {
+        const int tile_x = t % ntx, tile_y = t / ntx;
+        if (wc.ok) {
+            // a tile inside the window is the force pass's
+            const int x0 = tile_x * TX, y0 = tile_y * TY;
+            const int x1 = min(x0 + TX, g.nx) - 1, y1 = min(y0 + TY, g.ny) - 1;
+            if (x0 >= wc.i0 && x1 <= wc.i1 && y0 >= wc.j0 && y1 <= wc.j1) continue;
+        }
+        lb_tile<S, 3, TX, TY, 1, true>(g, (const S*)lf.A, (S*)lf.B, lf.fpx, lf.fpy, nullptr,
+                                       nullptr, nullptr, wp, wc, lf.fpo_x, lf.fpo_y, health,
+                                       tile_x, tile_y);
+    }
+}
+
 }  // namespace lbrmt

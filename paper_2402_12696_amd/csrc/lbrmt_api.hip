@@ -389,21 +389,35 @@ static StampValid prev_valid(const lbrmt_ctx* c)
     return StampValid{c->stamp[slots_for(c->step).nxt], (int)c->step, c->L.nbx};
 }
 
+// The early part of a held bulk update, thousandths of its tiles: none by
+// default (-1).  Since the chain's waves go first on a SIMD, the part that
+// ran beside the advection pass costs that pass more than it gains (MI355X,
+// cavity with a disc, 2048^2, us/step with 35 % -> with none: FP64 153 -> 151,
+// FP32 99 -> 93).
+static int bulk_early(const lbrmt_ctx* c) { return c->bulk_early >= 0 ? c->bulk_early : 0; }
+
+// Does the force pass take the bulk update along, in blocks beyond its own,
+// instead of a launch beside the chain?  Then a step is three launches on one
+// stream: the two dependencies between streams cost the chain 6 us, more
+// than the update of a small grid's nodes takes when the chain leaves the
+// chip idle anyway.  MI355X, cavity with a disc, us/step beside -> along:
+// FP64 64^2 50.6 -> 44.4, 256^2 52.3 -> 45.9, 640^2 55.4 -> 51.9, 768^2 55.0
+// -> 55.8, 1024^2 62.7 -> 69.6; FP32 64^2 46.5 -> 40.4, 768^2 49.6 -> 46.1,
+// 1024^2 53.8 -> 53.5, 1300^2 59.5 -> 65.8: the lines cross near 75 MB read
+// and written.  An option that shapes the launch beside the chain keeps that
+// launch, as timing does.
+static bool bulk_along(const lbrmt_ctx* c, bool fused)
+{
+    if (!c->overlap || !fused || c->timing || c->bulk_blocks > 0 || c->hold_bulk == 0 ||
+        c->bulk_early >= 0)
+        return false;
+    const long long bytes = (long long)c->d.nx * c->d.ny * 18 * (c->d.precision == 0 ? 8 : 4);
+    return bytes <= BULK_ALONG_BYTES;
+}
+
 // Block size of the one-launch extrapolation (default 512; one launch per
 // layer, 0, by default when the bulk update's workgroups are capped), 0 for
 // one launch per layer.
-// The early part of a held bulk update: -1 (default) takes the far tiles of
-// the first 35 % on grids of 2048^2 nodes or more, where the bulk update
-// outlasts the chain's latency-bound head (MI355X, cavity with a disc,
-// ms/step without -> with: 2048^2 FP64 0.1732 -> 0.1624, FP32 0.1124 ->
-// 0.1072), and none on smaller ones, where it only slows the advection pass
-// beside it (1024^2 FP64 0.0796 -> 0.0854 with half the tiles)
-static int bulk_early(const lbrmt_ctx* c)
-{
-    if (c->bulk_early >= 0) return c->bulk_early;
-    return (long long)c->d.nx * c->d.ny >= 2048ll * 2048 ? 350 : 0;
-}
-
 static int fused_threads(const lbrmt_ctx* c)
 {
     if (c->fused_fit >= 0) return c->fused_fit;
@@ -437,18 +451,19 @@ static int enqueue_step(lbrmt_ctx* c, long long n, hipStream_t main_s, bool firs
     hipEvent_t ev_bulk = c->ev_bulk[ek];
     hipEvent_t prev_join = c->ev_join[ep], prev_bulk = c->ev_bulk[ep];
     if (c->nsolid > 0) {
+        // the extrapolation in one launch (its tile list comes from the
+        // distance transform)
+        const int ff = fused_threads(c);
+        const bool fused = ff > 0 && fused_fit_ok(g);
+        const bool along = bulk_along(c, fused);
         hipStream_t band = main_s;
-        if (c->overlap) {
+        if (c->overlap && !along) {
             if (first) {
                 HIPCHK(c, hipEventRecord(ev_fork, main_s));
                 HIPCHK(c, hipStreamWaitEvent(c->side, ev_fork, 0));
             }
             band = c->side;
         }
-        // the extrapolation in one launch (its tile list comes from the
-        // distance transform)
-        const int ff = fused_threads(c);
-        const bool fused = ff > 0 && fused_fit_ok(g);
         {
             // advection and the layers of the extrapolation zone (one pass)
             Bracket b(c, 0, band);
@@ -472,17 +487,20 @@ static int enqueue_step(lbrmt_ctx* c, long long n, hipStream_t main_s, bool firs
         // step's is ordered by the fork).  Not before the extrapolation: the
         // wait delays its launch until the bulk update has filled the
         // compute units (FP64 step 0.179 -> 0.213 ms)
-        if (c->overlap && !first) HIPCHK(c, hipStreamWaitEvent(band, prev_bulk, 0));
+        if (c->overlap && !along && !first)
+            HIPCHK(c, hipStreamWaitEvent(band, prev_bulk, 0));
         {
             // relabel and the stress divergence (one pass); with overlap also
             // the lattice update of the window's nodes
             Bracket b(c, 3, band);
             const LbFuse lf{c->lat[s.cur], c->lat[s.nxt], c->Fx[s.nxt], c->Fy[s.nxt], s.wprev,
-                            ox, oy, c->bb.ticket, s.wnext};
+                            ox, oy, c->bb.ticket, s.wnext,
+                            along ? lb_along_tiles(g, prec) : 0, 0};
             HIPCHK(c, launch_force(g, c->body, c->bb, s, c->Fx[s.cur], c->Fy[s.cur], c->drho,
                                    band, c->overlap ? &lf : nullptr));
             b.done();
         }
+        if (along) return LBRMT_OK;
         if (c->overlap) {
             // prev_join and prev_bulk are the previous step's events
             // the early tiles of a held bulk update: the tile rows of its
@@ -511,8 +529,8 @@ static int enqueue_step(lbrmt_ctx* c, long long n, hipStream_t main_s, bool firs
                 HIPCHK(c, launch_lb(g, prec, c->lb_variant, c->lat[s.cur], c->lat[s.nxt], c->Fx[s.nxt],
                                     c->Fy[s.nxt], c->Fx[s.cur], c->Fy[s.cur], c->drho, c->bb.win,
                                     s.wprev, s.wcur, ox, oy, 3, c->bb.health, main_s,
-                                    c->bulk_blocks, nullptr, 0, nullptr, 0, early, 1000,
-                                    early > 0 ? 2 : 0));
+                                    c->bulk_blocks, nullptr, 0, nullptr, 0,
+                                    early, 1000, early > 0 ? 2 : 0));
                 b.done();
             }
             if (last) HIPCHK(c, hipStreamWaitEvent(main_s, ev_join, 0));

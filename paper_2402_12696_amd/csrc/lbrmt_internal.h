@@ -77,6 +77,10 @@ constexpr int MB_RECENTRE_MARGIN = 4;
 // health[6] (the early launch may then have updated nodes of the window)
 constexpr int BULK_EARLY_GAP = 2;
 
+// largest lattice (bytes read and written by one update) whose bulk update the
+// force pass takes along
+constexpr long long BULK_ALONG_BYTES = 72000000;
+
 // Axis-aligned box of the interior solid nodes of one body (i0 > i1: empty).
 // The working window of a step is this box dilated by `layers` nodes.
 struct Win {
@@ -599,7 +603,12 @@ struct LbFuse {
     double fpo_x, fpo_y;
     unsigned* ticket;  // arrival counter of the blocks, 0 between launches
     int wnext;         // ring slot of the new solid box
+    int along;         // blocks beyond the pass's own that update the lattice
+                       // outside the window (0: none, another launch does)
+    int nown;          // the pass's own blocks (set by its launch)
 };
+// tiles of the lattice update that the force pass takes along (LbTile)
+int lb_along_tiles(const GridP& g, int precision);
 // lf null: relabel and force only (the lattice update of the window follows
 // in a lattice kernel), the new solid box left as partial boxes in bb.boxpart
 // (RELABEL_BLOCKS of them); else it goes into ring slot lf->wnext.
