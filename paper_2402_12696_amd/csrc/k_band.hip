@@ -28,6 +28,7 @@
 // inversion of grad xi where det < kappa_J.
 #include "lb_node.h"
 #include "fit_window.h"
+#include "mb_recentre.h"
 
 namespace lbrmt {
 
@@ -524,7 +525,7 @@ constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
 // previous window} is read from the level set, the tile's solid nodes are
 // tagged and advected (Sec. 3.1) in the same pass, and the tags of the window
 // are all written here.
-template <int LC, int TH, bool ADV, typename S, bool LATCHK = false, bool SPLIT = false>
+template <int LC, int TH, bool ADV, typename S, bool LATCHK = false>
 __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ win, int wslot,
                                              int wprev, int8_t* tag, int* lists, int* lcount,
                                              unsigned* health, const S* __restrict__ A,
@@ -542,31 +543,33 @@ __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ wi
     const int L = LC > 0 ? LC : g.layers;
     const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
     const int ntx = (w + DTX - 1) / DTX, nty = (h + TH - 1) / TH;
-    // SPLIT (one solid): when the grid has at least ADV_MIN_WORKERS blocks
-    // beyond the tiles, block t < ntile takes tile t without its advection,
-    // and the blocks beyond advect the solid nodes of the window, 256 nodes
-    // of it (row-major over its interior part) at a time, one per thread:
-    // interior tiles no longer advect 512 nodes each while boundary tiles
-    // idle.  The solid set is the same (interior, phi^n < 0, inside D), and
-    // each node's advection is the same arithmetic, so the bits are too.
+    // When the grid has enough blocks beyond the tiles (ADV_MIN_WORKERS, or
+    // one thread for each node of the solid set's box), block t < ntile takes
+    // tile t without its advection, and the blocks beyond advect the solid
+    // nodes of that box, 256 nodes of it (row-major) at a time, one per
+    // thread: interior tiles no longer advect their nodes in turn while
+    // boundary tiles idle.  The solid set is the same (interior, phi^n < 0,
+    // inside D), and each node's advection is the same arithmetic, so the
+    // bits are too.
     const int ntile = ntx * nty;
     bool adv_here = ADV;
-    if (SPLIT && ADV && (int)gridDim.x - ntile >= ADV_MIN_WORKERS) {
-        adv_here = false;
-        if ((int)blockIdx.x >= ntile) {
-            const int i0 = max(W.i0, 0), i1 = min(W.i1, g.nx - 1);
-            const int j0 = max(W.j0, 0), j1 = min(W.j1, g.ny - 1);
-            if (i0 > i1 || j0 > j1) return;
-            const int ww = i1 - i0 + 1;
-            const long long nn = (long long)ww * (j1 - j0 + 1);
-            const int nwork = gridDim.x - ntile;
-            for (long long e = (long long)(blockIdx.x - ntile) * blockDim.x + threadIdx.x; e < nn;
-                 e += (long long)nwork * blockDim.x) {
-                const int x = i0 + (int)(e % ww), y = j0 + (int)(e / ww);
-                if (D.has(x, y) && phi[pidx(g, x, y)] < S(0))
-                    advect_node<S, LATCHK>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, x, y, health);
+    if (ADV) {
+        const Win B = win[wslot];  // (a box of interior nodes)
+        const int bw = B.i1 - B.i0 + 1;
+        const long long nn = (long long)bw * (B.j1 - B.j0 + 1);
+        const int nwork = (int)gridDim.x - ntile;
+        if (nwork >= ADV_MIN_WORKERS || (nwork > 0 && nwork * 256ll >= nn)) {
+            adv_here = false;
+            if ((int)blockIdx.x >= ntile) {
+                for (long long e = (long long)(blockIdx.x - ntile) * blockDim.x + threadIdx.x;
+                     e < nn; e += (long long)nwork * blockDim.x) {
+                    const int x = B.i0 + (int)(e % bw), y = B.j0 + (int)(e / bw);
+                    if (D.has(x, y) && phi[pidx(g, x, y)] < S(0))
+                        advect_node<S, LATCHK>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, x, y,
+                                               health);
+                }
+                return;
             }
-            return;
         }
     }
     __shared__ int cnt[MAX_LAYERS + 1];
@@ -634,9 +637,8 @@ __device__ __forceinline__ void dt_tile_body(GridP g, const Win* __restrict__ wi
             unsigned long long d = lane < rh ? rows[lane] : 0ull;
             const unsigned ps = (unsigned)(d >> L);
             unsigned pl[NP] = {}, any = 0;
-#pragma unroll
-            for (int l = 1; l <= (LC > 0 ? LC : DT_MASK_LAYERS); l++) {
-                if (LC == 0 && l > L) break;
+#pragma unroll LC > 0 ? LC : 1
+            for (int l = 1; l <= L; l++) {
                 const unsigned long long n = d | d << 1 | d >> 1 | row_shift<DPP_WAVE_SHL1>(d) |
                                              row_shift<DPP_WAVE_SHR1>(d);
                 const unsigned fresh = (unsigned)((n & ~d) >> L);
@@ -787,7 +789,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 5 : 1, 8))) void k_advect_dt
     // a SIMD first (2048^2 step FP64 155 -> 151 us, FP32 103 -> 93, with the
     // whole bulk update behind this pass)
     __builtin_amdgcn_s_setprio(3);
-    dt_tile_body<LC, TH, true, S, true, true>(g, win, wcur, wprev, tag, lists, lcount, health, A,
+    dt_tile_body<LC, TH, true, S, true>(g, win, wcur, wprev, tag, lists, lcount, health, A,
                                               fpx, fpy, X, Y, phi, X1, Y1, ff_list, ff_n);
 }
 
@@ -795,9 +797,13 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 5 : 1, 8))) void k_advect_dt
 // fewer rounds (FP32 step 0.634 -> 0.619 ms; FP64 0.998 -> 0.994)
 template <int LC, int TH, typename S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void kb_advect_dt(
-    const AdvectArgs* __restrict__ args, const int* __restrict__ ord)
+    const AdvectArgs* __restrict__ args, const int* __restrict__ ord,
+    const long long* __restrict__ dstep, long long* dcur)
 {
     const AdvectArgs& a = args[ord ? ord[blockIdx.y] : blockIdx.y];
+    // several solids: this step's number for the passes that follow (the
+    // counter itself moves on before the step ends)
+    if (dcur && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *dcur = *dstep;
     dt_tile_body<LC, TH, true, S>(a.g, a.win, a.wcur, a.wprev, a.tag, a.lists, a.lcount, a.health,
                                   (const S*)a.A, a.fpx, a.fpy, (const S*)a.X, (const S*)a.Y,
                                   (const S*)a.phi, (S*)a.X1, (S*)a.Y1, a.ff_list, a.ff_n);
@@ -1432,19 +1438,21 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
 // fits, layer by layer from the first to the last, every target that lies in
 // a stopped tile at or after the layer where that tile stopped (found by the
 // tile's tags; full scan windows up to r_max, the per-layer path's fit).
+// cut_tiles null: every tile of the window (nc of them), from layer cut_all.
 // lst: FF_TILE^2 entries of LDS, cn one
 template <typename T, int NT>
 __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* tag,
                          const T* __restrict__ phin, T* X1, T* Y1, unsigned* health,
-                         const int* cut_tiles, int nc, int* lst, int* cn)
+                         const int* cut_tiles, int nc, int cut_all, int* lst, int* cn)
 {
     constexpr int NG = NT / FIT_LANES;
     const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
     const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
     for (int l = 1; l <= g.layers; l++) {
         for (int c = 0; c < nc; c++) {
-            const int t = cut_tiles[c] & FF_CUT_TILE;
-            if (cut_tiles[c] >> FF_CUT_SHIFT > l) continue;
+            const int ct = cut_tiles ? cut_tiles[c] : c | cut_all << FF_CUT_SHIFT;
+            const int t = ct & FF_CUT_TILE;
+            if (ct >> FF_CUT_SHIFT > l) continue;
             const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
             if (threadIdx.x == 0) *cn = 0;
             __syncthreads();
@@ -1495,22 +1503,16 @@ __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* t
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
 // margin, and every tile with more than 64 targets in layers 1 and 2 before
 // its first layer (fit_rest then fits most of the zone: a check of it).
-template <typename T, int NT, int LC>
-__device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
-                                               int wcur, int wprev, int8_t* tag,
-                                               const T* __restrict__ phin, T* X1, T* Y1,
-                                               unsigned* health, int* cut_tiles, int* ncut,
-                                               const int* __restrict__ ff_list, int* ff_n,
-                                               unsigned* ticket, int* wide, int reach)
+template <typename T, int NT, int LC, int NODES, int LN>
+__device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN>& s, const GridP& g, const Rect& W,
+                                          const Rect& D, int8_t* tag, const T* __restrict__ phin,
+                                          T* X1, T* Y1, unsigned* health, int* cut_tiles,
+                                          int* ncut, const int* __restrict__ ff_list, int ntile,
+                                          int t0, int* ff_n, unsigned* ticket, int* wide,
+                                          int reach)
 {
     constexpr int RW = FF_REGION;
-    __shared__ FitLds<T, RW * RW, FF_LAYER> s;
-    // (the first tile is read together with the count: the list holds at
-    // least as many entries as there are blocks)
-    const int ntile = *ff_n, t0 = ff_list[blockIdx.x];
-    const Rect W = window_of(win, wcur, g);
-    const Rect D = window_of(win, wprev, g);
-    if ((int)blockIdx.x >= ntile || !W.ok) return;
+    static_assert(RW * RW <= NODES, "a tile with its margin");
     const int L = LC > 0 ? LC : g.layers;
     const int S = 2 * (L - 1) + 2, rw = FF_TILE + 2 * S;  // margin of the copy, its width
     const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
@@ -1518,8 +1520,8 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
         const int t = k == (int)blockIdx.x ? t0 : ff_list[k];
         const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
         const FitRegion R{x0 - S, y0 - S, rw, rw, x0, y0, FF_TILE, FF_TILE, 2};
-        fit_region<T, NT, RW * RW, FF_LAYER, LC == FF_LAYERS ? RW : 0>(s, g, W, D, L, R, tag, phin,
-                                                                       X1, Y1, reach);
+        fit_region<T, NT, NODES, LN, LC == FF_LAYERS ? RW : 0>(s, g, W, D, L, R, tag, phin, X1,
+                                                               Y1, reach);
         if (threadIdx.x == 0 && s.cut <= L)
             through(&cut_tiles[atomicAdd(ncut, 1)], t | s.cut << FF_CUT_SHIFT);
     }
@@ -1528,13 +1530,74 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     if (nc > 0) {
         __threadfence();
         static_assert(sizeof(s.rec) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
-        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, (int*)s.rec, s.cnt);
+        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.rec, s.cnt);
     }
     if (threadIdx.x == 0) {
         *ncut = 0;
         *ff_n = 0;
         *wide = nc;
     }
+}
+
+template <typename T, int NT, int LC>
+__device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
+                                               int wcur, int wprev, int8_t* tag,
+                                               const T* __restrict__ phin, T* X1, T* Y1,
+                                               unsigned* health, int* cut_tiles, int* ncut,
+                                               const int* __restrict__ ff_list, int* ff_n,
+                                               unsigned* ticket, int* wide, int reach)
+{
+    __shared__ FitLds<T, FF_REGION * FF_REGION, FF_LAYER> s;
+    // (the first tile is read together with the count: the list holds at
+    // least as many entries as there are blocks)
+    const int ntile = *ff_n, t0 = ff_list[blockIdx.x];
+    const Rect W = window_of(win, wcur, g);
+    const Rect D = window_of(win, wprev, g);
+    if ((int)blockIdx.x >= ntile || !W.ok) return;
+    fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut, ff_list, ntile,
+                         t0, ff_n, ticket, wide, reach);
+}
+
+// Several solids: solid row y (ord[y], the largest first).  A solid whose
+// window (dilated by 2) fits one block's copy is one block's, unless tiles is
+// set (few solids: whole-solid blocks would leave most of the chip idle);
+// any other's listed tiles are shared by the row's blocks.
+template <typename T, int NT, int LC>
+__global__ __launch_bounds__(NT) void kb_fit_mb(const FitArgs* __restrict__ args,
+                                                 const int* __restrict__ ord, int tiles)
+{
+    __shared__ FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB> s;
+    const FitArgs& a = args[ord[blockIdx.y]];
+    const GridP& g = a.g;
+    const Rect W = window_of(a.win, a.wcur, g);
+    const Rect D = window_of(a.win, a.wprev, g);
+    if (!W.ok) return;
+    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
+    const int ntile = *a.ff_n;
+    if (!tiles && (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
+        !(g.py && h + 4 > g.ny)) {
+        if (blockIdx.x != 0) return;
+        const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
+        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0>(s, g, W, D, g.layers, R, a.tag,
+                                                           (const T*)a.phin, (T*)a.X1,
+                                                           (T*)a.Y1, 2);
+        const int l0 = s.cut;
+        if (l0 <= g.layers) {
+            // the layers that the copy cannot serve
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            __threadfence();
+            const int nt = ((w + FF_TILE - 1) / FF_TILE) * ((h + FF_TILE - 1) / FF_TILE);
+            fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
+                            nullptr, nt, l0, (int*)s.rec, s.cnt);
+        }
+        if (threadIdx.x == 0) *a.ff_n = 0;
+        return;
+    }
+    if ((int)blockIdx.x >= ntile) return;
+    fit_tiles<T, NT, LC>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
+                        a.cut_tiles, a.ncut, a.ff_list, ntile, a.ff_list[blockIdx.x], a.ff_n,
+                        a.ticket, a.ff_wide, 2);
 }
 
 template <typename T, int NT, int LC>
@@ -1955,13 +2018,119 @@ __global__ __launch_bounds__(256) void k_edges(GridP g, BodyP b, Win* win, int w
                         o2, lcount, health, lf);
 }
 
+// window index of lattice column c (row r) in solid grid g; along a
+// sub-window axis the offset from the window origin, in [-PAD, lnx - PAD)
+__device__ __forceinline__ int win_col(const GridP& g, int c)
+{
+    if (!g.wx) return c;
+    const int d = wrap_axis(c - g.ox, g.lnx);
+    return d >= g.lnx - PAD ? d - g.lnx : d;
+}
+__device__ __forceinline__ int win_row(const GridP& g, int r)
+{
+    if (!g.wy) return r;
+    const int d = wrap_axis(r - g.oy, g.lny);
+    return d >= g.lny - PAD ? d - g.lny : d;
+}
+
+// rectangle V of a solid's window as lattice nodes {x, dx, y, dy}: columns
+// x .. x + dx (x wrapped, the range may run over a periodic seam), rows
+// likewise; dx < 0 or dy < 0: empty
+__device__ int4 mb_region(const GridP& g, const Rect& V)
+{
+    int4 r = make_int4(0, -1, 0, -1);
+    if (!V.ok) return r;
+    if (g.wx) {
+        r.x = wrap_axis(V.i0 + g.ox, g.lnx);
+        r.y = V.i1 - V.i0;
+    } else {
+        r.x = max(V.i0, 0);
+        r.y = min(V.i1, g.nx - 1) - r.x;
+    }
+    if (g.wy) {
+        r.z = wrap_axis(V.j0 + g.oy, g.lny);
+        r.w = V.j1 - V.j0;
+    } else {
+        r.z = max(V.j0, 0);
+        r.w = min(V.j1, g.ny - 1) - r.z;
+    }
+    return r;
+}
+
+// do [a, a + la] and [b, b + lb] meet (on a circle of n nodes if periodic)?
+__device__ __forceinline__ bool ranges_meet(int a, int la, int b, int lb, int n, int periodic)
+{
+    if (!periodic) return a <= b + lb && b <= a + la;
+    return wrap_axis(b - a, n) <= la || wrap_axis(a - b, n) <= lb;
+}
+
+// One block, solid k: the relabel's partial boxes (SAME: of this launch, by
+// the solid's last block) into ring slot wnext, the solid's force region, and
+// the force blocks it meets stamped and listed.
+template <bool SAME>
+__device__ __forceinline__ void mb_mark(const MbMark& m, int k, int nbox, unsigned* health)
+{
+    MbBody& B = m.bodies[k];
+    const int sval = m.dcur ? (int)(*m.dcur + 1) : m.sval;
+    __shared__ Win feps, fbox;
+    if (nbox > 0) {
+        const Win r = reduce_boxes<SAME>(B.boxpart, nbox, &B.win[m.wnext], nullptr);
+        if (threadIdx.x == 0) fbox = r;
+        reduce_boxes<SAME>(B.boxpart + 4 * nbox, nbox, &feps, nullptr);
+    }
+    __shared__ int4 reg;
+    if (threadIdx.x == 0) {
+        const GridP& g = B.g;
+        Rect R;
+        if (nbox > 0) {
+            check_zone(g, fbox, health);
+            // the force region of this step: the nodes with phi < eps and
+            // their neighbours (elsewhere every solid fraction is zero on the
+            // node and its edges, and the force is the uniform one), inside
+            // the working window
+            const Win e = feps;
+            const Rect V = window_of(B.win, m.wcur, g);
+            R.i0 = max(e.i0 - 1, V.i0);
+            R.i1 = min(e.i1 + 1, V.i1);
+            R.j0 = max(e.j0 - 1, V.j0);
+            R.j1 = min(e.j1 + 1, V.j1);
+            R.ok = V.ok && e.i0 <= e.i1 && R.i0 <= R.i1 && R.j0 <= R.j1;
+        } else {
+            R = window_of(B.win, m.wcur, g);
+        }
+        reg = mb_region(g, R);
+        B.reg = reg;
+    }
+    __syncthreads();
+    if (reg.y < 0 || reg.w < 0) return;
+    // sample columns x, x + FB, ..., x + dx (and rows alike): every block met
+    const int nsx = reg.y / FB + 2, nsy = reg.w / FB + 2;
+    for (int e = threadIdx.x; e < nsx * nsy; e += blockDim.x) {
+        int gx = reg.x + min((e % nsx) * FB, reg.y), gy = reg.z + min((e / nsx) * FB, reg.w);
+        if (m.lg.px) gx = wrap_axis(gx, m.lg.nx);
+        if (m.lg.py) gy = wrap_axis(gy, m.lg.ny);
+        const int blk = (gy >> FB_LOG) * m.nbx + (gx >> FB_LOG);
+        if (atomicExch(&m.stamp[blk], sval) != sval) m.list[atomicAdd(m.count, 1)] = blk;
+    }
+}
+
+// the initial regions (one block per solid)
+__global__ __launch_bounds__(256) void k_mb_mark(MbMark m)
+{
+    mb_mark<false>(m, blockIdx.x, 0, nullptr);
+}
+
 template <int MODE, typename C>
 __global__ __launch_bounds__(256) void kb_force(const EdgesArgs* __restrict__ args,
-                                                const int* __restrict__ ord)
+                                                const int* __restrict__ ord, MbMark mk)
 {
-    const EdgesArgs& a = args[ord ? ord[blockIdx.y] : blockIdx.y];
+    const int row = ord ? ord[blockIdx.y] : blockIdx.y;
+    const EdgesArgs& a = args[row];
     edges_body<MODE, C>(a.g, a.b, a.win, a.wvalid, a.boxpart, 0, (C*)a.X, (C*)a.Y, nullptr,
                         a.tag, (C*)a.phi, a.o0, a.o1, a.o2, a.lcount, a.health, LbFuse{});
+    // several solids: the solid's last block marks its region (a launch of
+    // its own, one block per solid, took 6 to 12 us)
+    if (MODE == 2 && last_arrival(a.ticket, gridDim.x)) mb_mark<true>(mk, row, gridDim.x, a.health);
 }
 
 int lb_along_tiles(const GridP& g, int precision)
@@ -2069,111 +2238,13 @@ hipError_t launch_read_refmap(const GridP& g, const BodyP& b, const BandBufs& bb
 // their summed fraction where it exceeds one, plus the contact stress of
 // every pair, Eqs. (3_6_global_stress) to (3_6_normal).
 
-// window index of lattice column c (row r) in solid grid g; along a
-// sub-window axis the offset from the window origin, in [-PAD, lnx - PAD)
-__device__ __forceinline__ int win_col(const GridP& g, int c)
+hipError_t launch_mb_mark(const MbMark& m, int nb, hipStream_t st)
 {
-    if (!g.wx) return c;
-    const int d = wrap_axis(c - g.ox, g.lnx);
-    return d >= g.lnx - PAD ? d - g.lnx : d;
-}
-__device__ __forceinline__ int win_row(const GridP& g, int r)
-{
-    if (!g.wy) return r;
-    const int d = wrap_axis(r - g.oy, g.lny);
-    return d >= g.lny - PAD ? d - g.lny : d;
-}
-
-// rectangle V of a solid's window as lattice nodes {x, dx, y, dy}: columns
-// x .. x + dx (x wrapped, the range may run over a periodic seam), rows
-// likewise; dx < 0 or dy < 0: empty
-__device__ int4 mb_region(const GridP& g, const Rect& V)
-{
-    int4 r = make_int4(0, -1, 0, -1);
-    if (!V.ok) return r;
-    if (g.wx) {
-        r.x = wrap_axis(V.i0 + g.ox, g.lnx);
-        r.y = V.i1 - V.i0;
-    } else {
-        r.x = max(V.i0, 0);
-        r.y = min(V.i1, g.nx - 1) - r.x;
-    }
-    if (g.wy) {
-        r.z = wrap_axis(V.j0 + g.oy, g.lny);
-        r.w = V.j1 - V.j0;
-    } else {
-        r.z = max(V.j0, 0);
-        r.w = min(V.j1, g.ny - 1) - r.z;
-    }
-    return r;
-}
-
-// do [a, a + la] and [b, b + lb] meet (on a circle of n nodes if periodic)?
-__device__ __forceinline__ bool ranges_meet(int a, int la, int b, int lb, int n, int periodic)
-{
-    if (!periodic) return a <= b + lb && b <= a + la;
-    return wrap_axis(b - a, n) <= la || wrap_axis(a - b, n) <= lb;
-}
-
-// one block per solid
-__global__ __launch_bounds__(256) void k_mb_mark(GridP lg, MbBody* bodies, int wcur, int wnext,
-                                                 int nbox, int* stamp, int sval, int* list,
-                                                 int* count, int nbx, unsigned* health,
-                                                 const long long* dstep)
-{
-    MbBody& B = bodies[blockIdx.x];
-    if (dstep) sval = (int)(*dstep + 1);
-    __shared__ Win feps;
-    if (nbox > 0) {
-        reduce_boxes(B.boxpart, nbox, &B.win[wnext], nullptr);
-        reduce_boxes(B.boxpart + 4 * nbox, nbox, &feps, nullptr);
-    }
-    __shared__ int4 reg;
-    if (threadIdx.x == 0) {
-        const GridP& g = B.g;
-        Rect R;
-        if (nbox > 0) {
-            check_zone(g, B.win[wnext], health);
-            // the force region of this step: the nodes with phi < eps and
-            // their neighbours (elsewhere every solid fraction is zero on the
-            // node and its edges, and the force is the uniform one), inside
-            // the working window
-            const Win e = feps;
-            const Rect V = window_of(B.win, wcur, g);
-            R.i0 = max(e.i0 - 1, V.i0);
-            R.i1 = min(e.i1 + 1, V.i1);
-            R.j0 = max(e.j0 - 1, V.j0);
-            R.j1 = min(e.j1 + 1, V.j1);
-            R.ok = V.ok && e.i0 <= e.i1 && R.i0 <= R.i1 && R.j0 <= R.j1;
-        } else {
-            R = window_of(B.win, wcur, g);
-        }
-        reg = mb_region(g, R);
-        B.reg = reg;
-    }
-    __syncthreads();
-    if (reg.y < 0 || reg.w < 0) return;
-    // sample columns x, x + FB, ..., x + dx (and rows alike): every block met
-    const int nsx = reg.y / FB + 2, nsy = reg.w / FB + 2;
-    for (int e = threadIdx.x; e < nsx * nsy; e += blockDim.x) {
-        int gx = reg.x + min((e % nsx) * FB, reg.y), gy = reg.z + min((e / nsx) * FB, reg.w);
-        if (lg.px) gx = wrap_axis(gx, lg.nx);
-        if (lg.py) gy = wrap_axis(gy, lg.ny);
-        const int blk = (gy >> FB_LOG) * nbx + (gx >> FB_LOG);
-        if (atomicExch(&stamp[blk], sval) != sval) list[atomicAdd(count, 1)] = blk;
-    }
-}
-
-hipError_t launch_mb_mark(const GridP& lg, MbBody* bodies, int nb, int wcur, int wnext,
-                          int nbox, int* stamp, int sval, int* list, int* count, int nbx,
-                          unsigned* health, hipStream_t st, const long long* dstep)
-{
-    if (nb > 0)
-        k_mb_mark<<<nb, 256, 0, st>>>(lg, bodies, wcur, wnext, nbox, stamp, sval, list, count,
-                                      nbx, health, dstep);
+    if (nb > 0) k_mb_mark<<<nb, 256, 0, st>>>(m);
     return hipGetLastError();
 }
 
+// (with solids the combine moves the counter on)
 __global__ void k_mb_tick(long long* dstep)
 {
     if (threadIdx.x == 0) *dstep += 1;
@@ -2368,10 +2439,12 @@ __global__ __launch_bounds__(256) void k_mb_combine(GridP lg, const MbBody* __re
                                                     const int* __restrict__ count,
                                                     int* count_clear, int nbx, double* fx,
                                                     double* fy, double* drho, int mode,
-                                                    unsigned* health, int nblk_all)
+                                                    unsigned* health, int nblk_all,
+                                                    const long long* dcur, long long* dstep)
 {
     static_assert(FB * FB == 256, "one thread per node of a force block");
     if (blockIdx.x == 0 && threadIdx.x == 0 && count_clear) *count_clear = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && dstep) *dstep = *dcur + 1;
     __shared__ int sl[MB_MAX_PER_BLOCK];
     __shared__ int wcnt[4];
     __shared__ int ns;
@@ -2416,16 +2489,17 @@ __global__ __launch_bounds__(256) void k_mb_combine(GridP lg, const MbBody* __re
 hipError_t launch_mb_combine(const GridP& lg, int precision, const MbBody* bodies, int nb,
                              int buf, int wcur, const int* list, const int* count,
                              int* count_clear, int nbx, double* fx, double* fy, double* drho,
-                             bool drho_only, unsigned* health, hipStream_t st)
+                             bool drho_only, unsigned* health, hipStream_t st,
+                             const long long* dcur, long long* dstep)
 {
     if (precision == 0)
         k_mb_combine<double><<<MB_COMBINE_BLOCKS, 256, 0, st>>>(
             lg, bodies, nb, buf, wcur, list, count, count_clear, nbx, fx, fy, drho,
-            drho_only ? 1 : 0, health, 0);
+            drho_only ? 1 : 0, health, 0, dcur, dstep);
     else
         k_mb_combine<float><<<MB_COMBINE_BLOCKS, 256, 0, st>>>(
             lg, bodies, nb, buf, wcur, list, count, count_clear, nbx, fx, fy, drho,
-            drho_only ? 1 : 0, health, 0);
+            drho_only ? 1 : 0, health, 0, dcur, dstep);
     return hipGetLastError();
 }
 
@@ -2436,29 +2510,12 @@ hipError_t launch_mb_read_stress(const GridP& lg, int precision, const MbBody* b
     if (precision == 0)
         k_mb_combine<double><<<MB_COMBINE_BLOCKS, 256, 0, st>>>(
             lg, bodies, nb, buf, wslot, nullptr, nullptr, nullptr, nbx, sxx, sxy, syy, 2, health,
-            nbx * nby);
+            nbx * nby, nullptr, nullptr);
     else
         k_mb_combine<float><<<MB_COMBINE_BLOCKS, 256, 0, st>>>(
             lg, bodies, nb, buf, wslot, nullptr, nullptr, nullptr, nbx, sxx, sxy, syy, 2, health,
-            nbx * nby);
+            nbx * nby, nullptr, nullptr);
     return hipGetLastError();
-}
-
-// a solid's window origin in its table entries
-__device__ void mb_set_origin(MbBody& B, const MbTabs& tabs, int k, int ox, int oy)
-{
-    B.g.ox = ox;
-    B.g.oy = oy;
-    for (int p = 0; p < 7; p++) {
-        tabs.adv[p][k].g.ox = ox;
-        tabs.adv[p][k].g.oy = oy;
-        tabs.lay[p][k].g.ox = ox;
-        tabs.lay[p][k].g.oy = oy;
-        tabs.fit[p][k].g.ox = ox;
-        tabs.fit[p][k].g.oy = oy;
-        tabs.edg[p][k].g.ox = ox;
-        tabs.edg[p][k].g.oy = oy;
-    }
 }
 
 // the region boxes and window origins of the solids from a saved copy of the
@@ -2476,89 +2533,6 @@ hipError_t launch_mb_copy_reg(const MbBody* src, MbBody* dst, int nb, const MbTa
                               hipStream_t st)
 {
     k_mb_copy_reg<<<(nb + 255) / 256, 256, 0, st>>>(src, dst, nb, tabs);
-    return hipGetLastError();
-}
-
-// the shift of one sub-window axis: 0 while the zone [lo - L, hi + L] keeps
-// MB_RECENTRE_MARGIN nodes from both ends of [0, n), else the move that puts
-// the box's middle at the window's middle
-__device__ __forceinline__ int recentre_shift(int lo, int hi, int L, int n)
-{
-    if (lo - L >= MB_RECENTRE_MARGIN && hi + L <= n - 1 - MB_RECENTRE_MARGIN) return 0;
-    const int mid2 = lo + hi;  // twice the box's middle
-    return (mid2 - (n - 1)) / 2;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_mb_recentre(MbBody* bodies, MbTabs tabs, int buf,
-                                                     int wa, int wb)
-{
-    const int k = blockIdx.x;
-    MbBody& B = bodies[k];
-    __shared__ int s_dx, s_dy;
-    if (threadIdx.x == 0) {
-        const GridP& g = B.g;
-        const Win a = B.win[wa], b = B.win[wb];
-        const bool av = a.i0 <= a.i1 && a.j0 <= a.j1, bv = b.i0 <= b.i1 && b.j0 <= b.j1;
-        int dx = 0, dy = 0;
-        if (av || bv) {
-            const int i0 = min(av ? a.i0 : b.i0, bv ? b.i0 : a.i0);
-            const int i1 = max(av ? a.i1 : b.i1, bv ? b.i1 : a.i1);
-            const int j0 = min(av ? a.j0 : b.j0, bv ? b.j0 : a.j0);
-            const int j1 = max(av ? a.j1 : b.j1, bv ? b.j1 : a.j1);
-            if (g.wx) dx = recentre_shift(i0, i1, g.layers, g.nx);
-            if (g.wy) dy = recentre_shift(j0, j1, g.layers, g.ny);
-        }
-        s_dx = dx;
-        s_dy = dy;
-    }
-    __syncthreads();
-    const int dx = s_dx, dy = s_dy;
-    if (dx == 0 && dy == 0) return;
-    const GridP& g = B.g;
-    T* X = (T*)B.X[buf];
-    T* Y = (T*)B.Y[buf];
-    T* P = (T*)B.phi[buf];
-    T* tX = (T*)B.X[1 - buf];
-    T* tY = (T*)B.Y[1 - buf];
-    T* tP = (T*)B.phi[1 - buf];
-    // padded window (-PAD .. n + PAD - 1 on each axis, row pitch pp): node
-    // (i, j) of the moved window is node (i + dx, j + dy) of the old one
-    const int wpx = g.nx + 2 * PAD, wpy = g.ny + 2 * PAD;
-    const long long N = (long long)g.pp * wpy;
-    for (long long e = threadIdx.x; e < N; e += blockDim.x) {
-        const int pi = (int)(e % g.pp), pj = (int)(e / g.pp);
-        const int si = pi + dx, sj = pj + dy;
-        const bool in = pi < wpx && si >= 0 && si < wpx && sj >= 0 && sj < wpy;
-        const long long q = in ? (long long)sj * g.pp + si : 0;
-        tX[e] = in ? X[q] : T(0);
-        tY[e] = in ? Y[q] : T(0);
-        tP[e] = in ? P[q] : T(INFINITY);
-    }
-    __syncthreads();
-    for (long long e = threadIdx.x; e < N; e += blockDim.x) {
-        X[e] = tX[e];
-        Y[e] = tY[e];
-        P[e] = tP[e];
-    }
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < 3; q++) {
-            Win& w = B.win[q];
-            if (w.i0 > w.i1 || w.j0 > w.j1) continue;
-            w.i0 -= dx;
-            w.i1 -= dx;
-            w.j0 -= dy;
-            w.j1 -= dy;
-        }
-        mb_set_origin(B, tabs, k, g.ox + dx, g.oy + dy);
-    }
-}
-
-hipError_t launch_mb_recentre(int precision, MbBody* bodies, int nb, const MbTabs& tabs, int buf,
-                              int wa, int wb, hipStream_t st)
-{
-    if (precision == 0) k_mb_recentre<double><<<nb, 256, 0, st>>>(bodies, tabs, buf, wa, wb);
-    else k_mb_recentre<float><<<nb, 256, 0, st>>>(bodies, tabs, buf, wa, wb);
     return hipGetLastError();
 }
 
@@ -2674,49 +2648,49 @@ hipError_t launch_mb_diag(int precision, const MbBody* bodies, int nb, int buf, 
 }
 
 hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int layers,
-                             hipStream_t st, bool relabel_only, int dt_blocks, int fit_blocks,
-                             int band_blocks, bool fused)
+                             hipStream_t st, int dt_blocks, int fit_blocks, int band_blocks,
+                             bool fused, const MbStep* mb)
 {
+    // the reference-map chain of every member of a batch, or (mb) of every
+    // solid of a context, which relabels and marks only
     const dim3 gb(band_blocks, nsim), gd(dt_blocks, nsim), gf(fit_blocks, nsim);
-    // fit_blocks == 0: every layer of a member in one block (kb_fit_lds);
+    const long long* dstep = mb ? mb->dstep : nullptr;
+    long long* dcur = mb ? mb->dcur : nullptr;
+#define ADB(T, LC, TH) kb_advect_dt<LC, TH, T><<<gd, 256, 0, st>>>(t.adv, t.ord, dstep, dcur)
+#define ADB_D(LC, TH) ADB(double, LC, TH)
+#define ADB_F(LC, TH) ADB(float, LC, TH)
     // fused: every layer of a member in one launch over its zone tiles (the
-    // members' advection pass lists those tiles)
-    const dim3 g1(1, nsim), gz(FF_BATCH_BLOCKS, nsim);
+    // advection pass lists those tiles); several solids: by solid or by tile
+#define CHAIN(T, MB_NT)                                                                        \
+    do {                                                                                       \
+        if (fused && mb) {                                                                     \
+            if (layers == FF_LAYERS)                                                           \
+                kb_fit_mb<T, MB_NT, FF_LAYERS><<<gf, MB_NT, 0, st>>>(t.fit, t.ord, mb->tiles); \
+            else kb_fit_mb<T, MB_NT, 0><<<gf, MB_NT, 0, st>>>(t.fit, t.ord, mb->tiles);        \
+        } else if (fused) {                                                                    \
+            if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS><<<gf, FF_THREADS, 0, st>>>(t.fit); \
+            else kb_fit_fused<T, 0><<<gf, FF_THREADS, 0, st>>>(t.fit);                         \
+        } else if (mb) {                                                                       \
+            kb_fit_lds<T, MB_NT><<<dim3(1, nsim), MB_NT, 0, st>>>(t.fit, layers, t.ord);       \
+        } else {                                                                               \
+            for (int l = 1; l <= layers; l++)                                                  \
+                if (l <= 2) kb_layer_fit<T, true><<<gf, 256, 0, st>>>(t.fit, l);               \
+                else kb_layer_fit<T, false><<<gf, 256, 0, st>>>(t.fit, l);                     \
+        }                                                                                      \
+        if (mb) kb_force<2, T><<<gb, 256, 0, st>>>(t.edg, t.ord, mb->mark);                    \
+        else kb_force<0, T><<<gb, 256, 0, st>>>(t.edg, t.ord, MbMark{});                       \
+    } while (0)
     if (precision == 0) {
-#define ADB(LC, TH) kb_advect_dt<LC, TH, double><<<gd, 256, 0, st>>>(t.adv, t.ord)
-        DT_DISPATCH(layers, fused, ADB);
-#undef ADB
-        if (fused) {
-            if (layers == FF_LAYERS) kb_fit_fused<double, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
-            else kb_fit_fused<double, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
-        } else if (fit_blocks == 0) {
-            kb_fit_lds<double, MB_FIT_THREADS_F64><<<g1, MB_FIT_THREADS_F64, 0, st>>>(t.fit, layers,
-                                                                                 t.ord);
-        } else {
-            for (int l = 1; l <= layers; l++)
-                if (l <= 2) kb_layer_fit<double, true><<<gf, 256, 0, st>>>(t.fit, l);
-                else kb_layer_fit<double, false><<<gf, 256, 0, st>>>(t.fit, l);
-        }
-        if (relabel_only) kb_force<2, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
-        else kb_force<0, double><<<gb, 256, 0, st>>>(t.edg, t.ord);
+        DT_DISPATCH(layers, fused, ADB_D);
+        CHAIN(double, MB_FIT_THREADS_F64);
     } else {
-#define ADB(LC, TH) kb_advect_dt<LC, TH, float><<<gd, 256, 0, st>>>(t.adv, t.ord)
-        DT_DISPATCH(layers, fused, ADB);
-#undef ADB
-        if (fused) {
-            if (layers == FF_LAYERS) kb_fit_fused<float, FF_LAYERS><<<gz, FF_THREADS, 0, st>>>(t.fit);
-            else kb_fit_fused<float, 0><<<gz, FF_THREADS, 0, st>>>(t.fit);
-        } else if (fit_blocks == 0) {
-            kb_fit_lds<float, MB_FIT_THREADS_F32><<<g1, MB_FIT_THREADS_F32, 0, st>>>(t.fit, layers,
-                                                                                t.ord);
-        } else {
-            for (int l = 1; l <= layers; l++)
-                if (l <= 2) kb_layer_fit<float, true><<<gf, 256, 0, st>>>(t.fit, l);
-                else kb_layer_fit<float, false><<<gf, 256, 0, st>>>(t.fit, l);
-        }
-        if (relabel_only) kb_force<2, float><<<gb, 256, 0, st>>>(t.edg, t.ord);
-        else kb_force<0, float><<<gb, 256, 0, st>>>(t.edg, t.ord);
+        DT_DISPATCH(layers, fused, ADB_F);
+        CHAIN(float, MB_FIT_THREADS_F32);
     }
+#undef CHAIN
+#undef ADB_F
+#undef ADB_D
+#undef ADB
     return hipGetLastError();
 }
 

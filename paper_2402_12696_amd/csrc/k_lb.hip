@@ -17,6 +17,7 @@
 // f_i - w_i rho_f is stored in float and the arithmetic is float, so rho =
 // rho_f + sum(df) keeps its small part.
 #include "lb_node.h"
+#include "mb_recentre.h"
 
 namespace lbrmt {
 
@@ -149,11 +150,17 @@ __global__ __launch_bounds__(LB_TX* LB_TY) void k_lb_mb(
     GridP g, const S* __restrict__ A, S* __restrict__ B, const double* __restrict__ fpx,
     const double* __restrict__ fpy, const double* __restrict__ fcx, const double* __restrict__ fcy,
     const double* __restrict__ drho, StampValid vp, StampValid vc, double fpo_x, double fpo_y,
-    unsigned* __restrict__ health, const long long* __restrict__ dstep)
+    unsigned* __restrict__ health, const long long* __restrict__ dstep, int nlb, MbRecentre rc)
 {
+    // blocks beyond the lattice's: one per solid, its window (the update reads
+    // no map; a launch of its own took 4.5 us)
+    if ((int)blockIdx.x >= nlb) {
+        mb_recentre<S>(rc, blockIdx.x - nlb);
+        return;
+    }
     constexpr int TH = LB_TY * R;
     const int ntx = (g.nx + LB_TX - 1) / LB_TX;
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    const int t = xcd_remap(blockIdx.x, nlb);
     vp.val = (int)*dstep;
     vc.val = vp.val + 1;
     lb_tile<S, 0, LB_TX, LB_TY, R, NT, StampValid, StampValid>(
@@ -313,28 +320,30 @@ template <typename S, int TX, int TY, int R, bool NT>
 static void lb_mb_one(const GridP& g, const void* A, void* B, const double* fpx,
                       const double* fpy, const double* fcx, const double* fcy,
                       const double* drho, StampValid vp, StampValid vc, double fpo_x,
-                      double fpo_y, unsigned* health, hipStream_t st, const long long* dstep)
+                      double fpo_y, unsigned* health, hipStream_t st, const long long* dstep,
+                      const MbRecentre& rc)
 {
     const int ntiles = ((g.nx + TX - 1) / TX) * ((g.ny + TY * R - 1) / (TY * R));
-    k_lb_mb<S, TX, TY, R, NT><<<ntiles, TX * TY, 0, st>>>(g, (const S*)A, (S*)B, fpx, fpy, fcx,
+    static_assert(TX * TY == 256, "the blocks that move a window");
+    k_lb_mb<S, TX, TY, R, NT><<<ntiles + rc.n, TX * TY, 0, st>>>(g, (const S*)A, (S*)B, fpx, fpy, fcx,
                                                          fcy, drho, vp, vc, fpo_x, fpo_y,
-                                                         health, dstep);
+                                                         health, dstep, ntiles, rc);
 }
 
 hipError_t launch_lb_mb(const GridP& g, int precision, int variant, const void* A, void* B,
                         const double* fpx, const double* fpy, const double* fcx,
                         const double* fcy, const double* drho, StampValid vp, StampValid vc,
                         double fpo_x, double fpo_y, unsigned* health, hipStream_t st,
-                        const long long* dstep)
+                        const long long* dstep, const MbRecentre& rc)
 {
     // the measured single-solid choices: 64 x 4 (FP64), 256 x 1 (FP32), nontemporal stores
     (void)variant;
     if (precision == 0)
         lb_mb_one<double, 64, 4, 1, true>(g, A, B, fpx, fpy, fcx, fcy, drho, vp, vc, fpo_x,
-                                          fpo_y, health, st, dstep);
+                                          fpo_y, health, st, dstep, rc);
     else
         lb_mb_one<float, 256, 1, 1, true>(g, A, B, fpx, fpy, fcx, fcy, drho, vp, vc, fpo_x,
-                                          fpo_y, health, st, dstep);
+                                          fpo_y, health, st, dstep, rc);
     return hipGetLastError();
 }
 

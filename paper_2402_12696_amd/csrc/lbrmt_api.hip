@@ -97,11 +97,18 @@ BodyLayout body_layout(const lbrmt_grid_desc* d, const MbGeom& m)
     B.off_gcol = take(m.pplane);
     B.off_lists = take((size_t)m.lcap * NSUB * 4 * (size_t)(d->layers + 1));
     B.off_lcount = take((size_t)(MAX_LAYERS + 1) * NSUB * LCOUNT_PAD * 4);
-    B.off_boxpart = take((size_t)std::max(BOX_BLOCKS, MB_BAND_BLOCKS) * 4 * 4);
+    B.off_boxpart = take((size_t)BOX_BLOCKS * 4 * 4);
     B.off_ticket = take(4);
     B.off_win = take(3 * sizeof(Win));
     B.total = o;
     return B;
+}
+
+// a solid's tile lists of the extrapolation: three counters, then the listed
+// and the stopped tiles
+size_t mfit_bytes(const MbGeom& m)
+{
+    return round_up((4 + 2 * (size_t)fused_tiles(m.nx, m.ny)) * 4, ALIGN);
 }
 
 struct Layout {
@@ -116,7 +123,7 @@ struct Layout {
     // several solids
     int nbx, nby;
     size_t off_stamp[2], off_mlist[2], off_mcount, off_dstep, off_mbtab, off_tabs, off_bsum,
-        off_mord, off_bodies, body_bytes;
+        off_mord, off_bodies, off_mfit, off_dcur, body_bytes;
 };
 
 Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
@@ -177,6 +184,7 @@ Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
         }
         L.off_mcount = take(2 * 4);
         L.off_dstep = take(8);
+        L.off_dcur = take(8);
         L.off_mbtab = take((size_t)max_solids * sizeof(MbBody));
         L.off_tabs = take(7 * ((size_t)max_solids * (sizeof(AdvectArgs) + sizeof(LayersArgs) +
                                                      sizeof(FitArgs) + sizeof(EdgesArgs)) +
@@ -185,6 +193,7 @@ Layout make_layout(const lbrmt_grid_desc* d, int max_solids = 1)
         L.off_mord = take((size_t)max_solids * 4);
         L.body_bytes = body_layout(d, mb_geom(d)).total;
         L.off_bodies = take((size_t)max_solids * L.body_bytes);
+        L.off_mfit = take((size_t)max_solids * mfit_bytes(mb_geom(d)));
     }
     L.total = o;
     return L;
@@ -259,6 +268,7 @@ struct lbrmt_ctx {
     int* mlist[2] = {nullptr, nullptr};
     int* mcount = nullptr;
     long long* dstep = nullptr;
+    long long* dcur = nullptr;  // the running step's number
     double* bsum = nullptr;
     int adj_flip = 0;  // which half of an adjoint buffer holds state n + 1
 };
@@ -348,6 +358,31 @@ static MbTabs mb_tabs(const lbrmt_ctx* c)
     return t;
 }
 
+// How the solids' layers are shared out: by tiles, each with its margin, as
+// for one solid, while all solids' tiles are a round or two of blocks; else a
+// block per solid, with more for the tiles of solids whose window is not one
+// block's.  (MI355X: a block takes a tile in about 20 us, a small solid of a
+// suspension in about 45.)
+struct MbFit {
+    int tiles, blocks;
+};
+static MbFit mb_fit(const lbrmt_ctx* c)
+{
+    long long all = 0, most = 1;
+    bool large = false;
+    for (const MbBody& m : c->mbh) {
+        const double ext = m.b.shape == 1 ? std::max(m.b.R, m.b.Rb) : m.b.R;
+        const long long side = std::min<long long>(
+            2 * ((long long)std::ceil(ext) + c->d.layers) + 1, std::max(m.g.nx, m.g.ny) + 2 * PAD);
+        const long long t = (side + FF_TILE - 1) / FF_TILE;
+        all += t * t;
+        most = std::max(most, t * t);
+        large = large || (side + 4) * (side + 4) > MB_FIT_LDS_NODES;
+    }
+    const bool tiles = all <= MB_FIT_TILES;
+    return MbFit{tiles ? 1 : 0, (int)std::min<long long>(tiles || large ? most : 1, FF_BLOCKS)};
+}
+
 // several solids, step n on stream st: the chain of every solid (relabel
 // only), the force blocks and the combined forces, the sub-windows that need
 // to follow their solids, the lattice update
@@ -357,28 +392,35 @@ static int enqueue_step_mb(lbrmt_ctx* c, long long n, hipStream_t st)
     const int p = n == 0 ? 6 : (int)(n % 6);
     const int nb = c->nsolid;
     const int prec = c->d.precision;
+    // the step's number: read from the copy the first pass makes, as the
+    // counter moves on before the last one
+    const long long* dcur = nb > 0 ? c->dcur : c->dstep;
+    MbRecentre rc{c->mbd, MbTabs{}, s.nxt, s.wcur, s.wnext, 0};
     if (nb > 0) {
-        HIPCHK(c, launch_batch_band(prec, c->mtab[p], nb, c->d.layers, st, true, MB_DT_BLOCKS,
-                                    0, MB_BAND_BLOCKS));
-        HIPCHK(c, launch_mb_mark(c->g, c->mbd, nb, s.wcur, s.wnext, MB_BAND_BLOCKS,
-                                 c->stamp[s.cur], 0, c->mlist[s.cur], &c->mcount[s.cur],
-                                 c->L.nbx, c->bb.health, st, c->dstep));
+        const bool fused = fused_fit_ok(c->mbh[0].g);  // (every window has one shape)
+        const MbFit f = mb_fit(c);
+        const MbStep mb{MbMark{c->g, c->mbd, s.wcur, s.wnext, c->stamp[s.cur], c->mlist[s.cur],
+                               &c->mcount[s.cur], c->L.nbx, 0, c->dcur},
+                        f.tiles, c->dstep, c->dcur};
+        HIPCHK(c, launch_batch_band(prec, c->mtab[p], nb, c->d.layers, st, mb_dt_blocks(nb),
+                                    f.blocks, mb_band_blocks(nb), fused, &mb));
         HIPCHK(c, launch_mb_combine(c->g, prec, c->mbd, nb, s.nxt, s.wcur, c->mlist[s.cur],
                                     &c->mcount[s.cur], &c->mcount[s.nxt], c->L.nbx,
                                     c->Fx[s.cur], c->Fy[s.cur], c->drho, false, c->bb.health,
-                                    st));
+                                    st, c->dcur, c->dstep));
         // the maps of step n + 1 are in buffer s.nxt, their boxes in slots
         // s.wcur (validity) and s.wnext (solid set)
-        if (c->mg.wx || c->mg.wy)
-            HIPCHK(c, launch_mb_recentre(prec, c->mbd, nb, mb_tabs(c), s.nxt, s.wcur, s.wnext,
-                                         st));
+        if (c->mg.wx || c->mg.wy) {
+            rc.tabs = mb_tabs(c);
+            rc.n = nb;
+        }
     }
     HIPCHK(c, launch_lb_mb(c->g, prec, c->lb_variant, c->lat[s.cur], c->lat[s.nxt],
                            c->Fx[s.nxt], c->Fy[s.nxt], c->Fx[s.cur], c->Fy[s.cur], c->drho,
                            StampValid{c->stamp[s.nxt], 0, c->L.nbx},
                            StampValid{c->stamp[s.cur], 0, c->L.nbx}, fpo_x(c, n), fpo_y(c, n),
-                           c->bb.health, st, c->dstep));
-    HIPCHK(c, launch_mb_tick(c->dstep, st));
+                           c->bb.health, st, dcur, rc));
+    if (nb == 0) HIPCHK(c, launch_mb_tick(c->dstep, st));
     return LBRMT_OK;
 }
 
@@ -752,6 +794,7 @@ static int create_impl(const lbrmt_grid_desc* d, int32_t max_solids, void* ws, s
         }
         c->mcount = (int*)(c->ws + L.off_mcount);
         c->dstep = (long long*)(c->ws + L.off_dstep);
+        c->dcur = (long long*)(c->ws + L.off_dcur);
         c->mbd = (MbBody*)(c->ws + L.off_mbtab);
         c->bsum = (double*)(c->ws + L.off_bsum);
         c->mord = (int*)(c->ws + L.off_mord);
@@ -900,11 +943,13 @@ static BandBufs mb_bufs(const lbrmt_ctx* c, int k)
     b.ticket = (unsigned*)(base + c->BL.off_ticket);
     b.win = m.win;
     b.health = c->bb.health;
-    b.cut_tiles = nullptr;  // no tiles: a solid's layers in one block
-    b.ncut = nullptr;
-    b.ff_list = nullptr;
-    b.ff_n = nullptr;
-    b.ff_wide = nullptr;
+    // (outside the solid's block, which a saved state holds as it is)
+    char* fb = c->ws + c->L.off_mfit + (size_t)k * mfit_bytes(c->mg);
+    b.ncut = (int*)fb;
+    b.ff_n = b.ncut + 1;
+    b.ff_wide = b.ncut + 2;
+    b.ff_list = b.ncut + 4;
+    b.cut_tiles = b.ff_list + fused_tiles(c->mg.nx, c->mg.ny);
     return b;
 }
 
@@ -952,6 +997,7 @@ static int mb_tables(lbrmt_ctx* c)
     // block rows take the solids by decreasing semi-axis sum (each solid's
     // work is its own, so the order changes no result)
     std::vector<int> ord(nb);
+    const bool fused = fused_fit_ok(c->mbh[0].g);
     for (int k = 0; k < nb; k++) ord[k] = k;
     auto size_of = [&](int k) {
         const BodyP& b = c->mbh[k].b;
@@ -968,13 +1014,15 @@ static int mb_tables(lbrmt_ctx* c)
             const GridP& g = c->mbh[k].g;
             adv[k] = AdvectArgs{g, c->lat[s.cur], c->Fx[s.nxt], c->Fy[s.nxt], b.X[s.cur],
                                 b.Y[s.cur], b.phi[s.cur], b.X[s.nxt], b.Y[s.nxt], b.tag, b.win,
-                                s.wprev, s.wcur, b.lists, b.lcount, b.health};
+                                s.wprev, s.wcur, b.lists, b.lcount, b.health,
+                                fused ? b.ff_list : nullptr, fused ? b.ff_n : nullptr};
             lay[k] = LayersArgs{g, b.win, s.wcur, b.tag, b.gcol, b.lists, b.lcount, b.health};
             fit[k] = FitArgs{g, b.win, s.wcur, s.wprev, b.tag, b.lists, b.lcount, b.phi[s.cur],
-                             b.X[s.nxt], b.Y[s.nxt], b.health};
+                             b.X[s.nxt], b.Y[s.nxt], b.health, b.cut_tiles, b.ncut,
+                             b.ff_list, b.ff_n, b.ticket, b.ff_wide};
             edg[k] = EdgesArgs{g, c->mbh[k].b, b.win, s.wcur, b.boxpart, b.X[s.nxt], b.Y[s.nxt],
                                b.tag, b.phi[s.nxt], nullptr, nullptr, nullptr, b.lcount,
-                               b.health};
+                               b.health, b.ticket};
         }
         const BatchTables& T = c->mtab[p];
         HIPCHK(c, hipMemcpyAsync(T.adv, adv.data(), nb * sizeof(AdvectArgs), hipMemcpyHostToDevice, c->st));
@@ -990,6 +1038,17 @@ static int mb_tables(lbrmt_ctx* c)
     return LBRMT_OK;
 }
 
+// the fused extrapolation's tile lists start empty (each launch leaves them so)
+static hipError_t clear_cut_tiles(lbrmt_ctx* c, hipStream_t st)
+{
+    if (c->multi)
+        return hipMemsetAsync(c->ws + c->L.off_mfit, 0, (size_t)c->nsolid * mfit_bytes(c->mg), st);
+    hipError_t e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
+    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_n, 0, 4, st);
+    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_wide, 0, 4, st);
+    return e;
+}
+
 // several solids: every solid's initial map on its window (as for one solid),
 // then the density excess of the mixture, then f = f^eq
 static int init_mb(lbrmt_ctx* c, const double* d_u0)
@@ -1000,6 +1059,7 @@ static int init_mb(lbrmt_ctx* c, const double* d_u0)
     HIPCHK(c, hipMemsetAsync(c->mcount, 0, 2 * 4, st));
     HIPCHK(c, hipMemsetAsync(c->dstep, 0, 8, st));
     const int nb = c->nsolid;
+    HIPCHK(c, clear_cut_tiles(c, st));
     for (int k = 0; k < nb; k++) {
         const BandBufs b = mb_bufs(c, k);
         const GridP& g = c->mbh[k].g;
@@ -1016,8 +1076,9 @@ static int init_mb(lbrmt_ctx* c, const double* d_u0)
     if (rc != LBRMT_OK) return rc;
     if (nb > 0) {
         // the blocks of the initial regions (stamp -1, which no step uses)
-        HIPCHK(c, launch_mb_mark(c->g, c->mbd, nb, 0, 0, 0, c->stamp[1], -1, c->mlist[1],
-                                 &c->mcount[1], c->L.nbx, c->bb.health, st));
+        HIPCHK(c, launch_mb_mark(MbMark{c->g, c->mbd, 0, 0, c->stamp[1], c->mlist[1],
+                                        &c->mcount[1], c->L.nbx, -1, nullptr},
+                                 nb, st));
         HIPCHK(c, launch_mb_combine(c->g, c->d.precision, c->mbd, nb, 0, 0, c->mlist[1],
                                     &c->mcount[1], &c->mcount[0], c->L.nbx, c->Fx[0], c->Fy[0],
                                     c->drho, true, c->bb.health, st));
@@ -1028,16 +1089,6 @@ static int init_mb(lbrmt_ctx* c, const double* d_u0)
     c->step = 0;
     c->inited = true;
     return LBRMT_OK;
-}
-
-// the fused extrapolation's tile lists start empty (each launch leaves them so)
-static hipError_t clear_cut_tiles(lbrmt_ctx* c, hipStream_t st)
-{
-    if (c->multi) return hipSuccess;  // several solids: no fused extrapolation
-    hipError_t e = hipMemsetAsync(c->bb.ncut, 0, 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_n, 0, 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(c->bb.ff_wide, 0, 4, st);
-    return e;
 }
 
 int lbrmt_init(lbrmt_ctx* c, const double* d_u0)
@@ -1699,6 +1750,7 @@ int lbrmt_load_state(lbrmt_ctx* c, const void* buf)
     if (c->multi) {
         int rc = state_copy_mb(c, (char*)b, off, true);
         if (rc != LBRMT_OK) return rc;
+        HIPCHK(c, clear_cut_tiles(c, c->st));
         c->inited = true;
         return LBRMT_OK;
     }
@@ -2163,8 +2215,10 @@ int batch_enqueue(lbrmt_batch* b, long long n, hipStream_t st)
 {
     const int p = n == 0 ? 6 : (int)(n % 6);
     const BatchTables& T = b->tab[p];
-    BCHK(b, launch_batch_band(b->precision, T, b->n, b->layers, st, false, BATCH_DT_BLOCKS,
-                              BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS, batch_fused(b)));
+    const bool fused = batch_fused(b);
+    BCHK(b, launch_batch_band(b->precision, T, b->n, b->layers, st, BATCH_DT_BLOCKS,
+                              fused ? FF_BATCH_BLOCKS : BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS,
+                              fused));
     BCHK(b, launch_lb_batch(b->precision, b->lb_variant, T.lb, b->tile_sim, b->total_tiles, st));
     return LBRMT_OK;
 }

@@ -51,16 +51,24 @@ constexpr int FF_BATCH_BLOCKS = 64;   // fused extrapolation of a batch: blocks 
 // a block holds valid force planes at step n when its stamp equals n + 1.
 constexpr int FB_LOG = 4;
 constexpr int FB = 1 << FB_LOG;
-// advection and distance transform of several solids: blocks per solid (a
-// multiple of NSUB); 8 (each block taking about two tiles of a solid's
-// window): 4096^2 suspension of 400 solids FP32 step 0.590 -> 0.540 ms
-// against 16 (24: 0.546)
-constexpr int MB_DT_BLOCKS = 8;
-// relabel of several solids: two partial boxes per block, 8 blocks per
-// solid (4096^2 suspension of 400 solids: FP32 step 0.6157 -> 0.6120 ms
-// against 16, 0.637 at 32; 4 as fast as 8)
-constexpr int MB_BAND_BLOCKS = 8;
-// one block per solid runs all its layers
+// Several solids, blocks per solid: 1024 over the solids for the advection and
+// distance transform (within 8 .. 64, a multiple of NSUB), 640 for the relabel
+// (within 4 .. 32; two partial boxes per block), so that a few solids fill the
+// chip and many leave no block idle.  us/step on MI355X with (advection,
+// relabel) blocks: 5 solids in 384 x 320 FP64 (8, 8) 100, (64, 64) 69.8, (128,
+// 64) 73.2, (128, 32) 71.7; 25 solids in 1024^2 FP64 (80, 40) 106.8, (80, 24)
+// 106.3, (40, 40) 102.4; 400 solids in 4096^2 FP32 (8, 8) 442, (8, 4) 432, (16,
+// 4) 444, (32, 4) 490
+inline int mb_share(int total, int nb, int least, int most)
+{
+    const int n = total / (nb > 0 ? nb : 1) / least * least;
+    return n < least ? least : n < most ? n : most;
+}
+inline int mb_dt_blocks(int nb) { return mb_share(1024, nb, NSUB, 64); }
+inline int mb_band_blocks(int nb) { return mb_share(640, nb, 4, 32); }
+// few solids, at most this many tiles in all: extrapolation by tiles
+constexpr int MB_FIT_TILES = 512;
+// threads of a block that runs all layers of a solid, or of its tiles
 constexpr int MB_FIT_THREADS_F64 = 512;
 constexpr int MB_FIT_THREADS_F32 = 512;
 // nodes of a several-solid fit block's LDS copy (its window dilated by 2)
@@ -303,6 +311,7 @@ struct EdgesArgs {
     double *o0, *o1, *o2;
     int* lcount;
     unsigned* health;
+    unsigned* ticket;  // several solids: arrival counter of the solid's blocks
 };
 struct LbArgs {
     GridP g;
@@ -452,6 +461,45 @@ struct MbBody {
                           // the nodes with phi < eps and their neighbours
 };
 
+// Where the solids mark the force blocks they meet: stamped with this step's
+// number plus one (*dcur + 1, or sval when dcur is null), the newly stamped
+// ones listed
+struct MbMark {
+    GridP lg;
+    MbBody* bodies;
+    int wcur, wnext;
+    int *stamp, *list, *count;
+    int nbx, sval;
+    const long long* dcur;
+};
+// a step's chain over several solids
+struct MbStep {
+    MbMark mark;
+    int tiles;              // extrapolation by tiles for every solid
+    const long long* dstep; // the step counter, copied to dcur by the first pass
+    long long* dcur;
+};
+
+// the chain's per-phase argument tables of a several-solid context (each
+// entry holds a copy of its solid's window geometry)
+struct MbTabs {
+    AdvectArgs* adv[7];
+    LayersArgs* lay[7];
+    FitArgs* fit[7];
+    EdgesArgs* edg[7];
+};
+// A step's last pass moves the sub-window of every solid whose zone (its boxes
+// in ring slots wa and wb, dilated by the layers) comes within
+// MB_RECENTRE_MARGIN nodes of the window's border, so that the boxes are
+// centred: the maps of buffer buf move within the window (through the other
+// buffer, free between steps), the ring boxes shift, and the origin changes in
+// the solid table and the argument tables; every node keeps its lattice
+// position and value.  n: the solids, 0 with no sub-window axis.
+struct MbRecentre {
+    MbBody* bodies;
+    MbTabs tabs;
+    int buf, wa, wb, n;
+};
 
 // ---- adjoint (k_adjoint.hip; FP64, one solid)
 
@@ -510,14 +558,13 @@ struct LossCoef {
 // Every launcher enqueues on `st` and returns hipGetLastError().
 
 // lattice Boltzmann (k_lb.hip)
-// relabel_only: the force kernel relabels and writes partial boxes only
-// (several solids: the forces come from launch_mb_combine); blocks per member
-// of the distance transform, one extrapolation layer (0: all layers of a
-// member in one block) and the force kernel
+// blocks per member of the distance transform, of the extrapolation (one
+// layer, or fused: every layer) and of the force kernel; mb: the members are
+// the solids of a context, which relabel and mark only (the forces come from
+// launch_mb_combine)
 hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int layers,
-                             hipStream_t st, bool relabel_only = false,
-                             int dt_blocks = BATCH_DT_BLOCKS, int fit_blocks = BATCH_FIT_BLOCKS,
-                             int band_blocks = BATCH_BAND_BLOCKS, bool fused = false);
+                             hipStream_t st, int dt_blocks, int fit_blocks, int band_blocks,
+                             bool fused, const MbStep* mb = nullptr);
 hipError_t launch_lb_batch(int precision, int variant, const LbArgs* args, const int* tile_sim,
                            int total_tiles, hipStream_t st);
 // PART 0 / 2 launches with nbox > 0 also reduce the force pass's partial
@@ -553,12 +600,13 @@ hipError_t launch_read_force(const GridP& g, const double* fpx, const double* fp
                              hipStream_t st, StampValid sv = StampValid{nullptr, 0, 0});
 // lattice update of a several-solid context: every tile, force planes where
 // the stamps say so
-// (the stamp values are *dstep for vp and *dstep + 1 for vc)
+// (the stamp values are *dstep for vp and *dstep + 1 for vc); rc: the windows
+// to move
 hipError_t launch_lb_mb(const GridP& g, int precision, int variant, const void* A, void* B,
                         const double* fpx, const double* fpy, const double* fcx,
                         const double* fcy, const double* drho, StampValid vp, StampValid vc,
                         double fpo_x, double fpo_y, unsigned* health, hipStream_t st,
-                        const long long* dstep);
+                        const long long* dstep, const MbRecentre& rc);
 hipError_t launch_poke(const GridP& g, int precision, void* A, long long node, double value,
                        hipStream_t st);
 
@@ -620,51 +668,31 @@ hipError_t launch_read_stress(const GridP& g, const BodyP& b, const BandBufs& bb
 hipError_t launch_read_refmap(const GridP& g, const BodyP& b, const BandBufs& bb, int buf, int wvalid, double* X,
                               double* Y, double* phi, hipStream_t st);
 
-// several solids (k_band.hip).  mark: per solid, reduce the relabel's partial
-// boxes into ring slot wnext, flag a window that comes too close to its
-// border, and stamp (value sval) the force blocks of its region of slot wcur,
-// listing each newly stamped block once (list / count).
-// dstep != nullptr: the stamp value is *dstep + 1 (the device step counter,
-// so that replayed graphs stamp with the running step)
-hipError_t launch_mb_mark(const GridP& lg, MbBody* bodies, int nb, int wcur, int wnext,
-                          int nbox, int* stamp, int sval, int* list, int* count, int nbx,
-                          unsigned* health, hipStream_t st, const long long* dstep = nullptr);
-// advances the device step counter
+// several solids (k_band.hip).  mark: the force blocks of every solid's
+// initial region stamped and listed (a step's force pass does this itself)
+hipError_t launch_mb_mark(const MbMark& m, int nb, hipStream_t st);
+// advances the device step counter (a context without solids)
 hipError_t launch_mb_tick(long long* dstep, hipStream_t st);
 // combine: over the listed blocks, the global stress of every half-edge
 // (blend of the solids normalised by their summed fraction, plus contact),
 // its divergence, buoyancy and the fluid force into fx, fy; the density
 // excess into drho.  Zeroes *count_clear (the next step's list counter).
-// drho_only: the density excess only (initialisation).
+// drho_only: the density excess only (initialisation).  dstep: the step
+// counter, moved on to *dcur + 1.
 hipError_t launch_mb_combine(const GridP& lg, int precision, const MbBody* bodies, int nb,
                              int buf, int wcur, const int* list, const int* count,
                              int* count_clear, int nbx, double* fx, double* fy, double* drho,
-                             bool drho_only, unsigned* health, hipStream_t st);
+                             bool drho_only, unsigned* health, hipStream_t st,
+                             const long long* dcur = nullptr, long long* dstep = nullptr);
 // node averages of the global half-edge solid stresses of the state whose
 // maps are in buffer buf over window slot wslot, into [ny][nx] planes
 hipError_t launch_mb_read_stress(const GridP& lg, int precision, const MbBody* bodies, int nb,
                                  int buf, int wslot, int nbx, int nby, double* sxx, double* sxy,
                                  double* syy, unsigned* health, hipStream_t st);
-// the chain's per-phase argument tables of a several-solid context (each
-// entry holds a copy of its solid's window geometry)
-struct MbTabs {
-    AdvectArgs* adv[7];
-    LayersArgs* lay[7];
-    FitArgs* fit[7];
-    EdgesArgs* edg[7];
-};
 // the region boxes and window origins of the solid table dst (and of the
 // argument tables) from a saved copy src (device)
 hipError_t launch_mb_copy_reg(const MbBody* src, MbBody* dst, int nb, const MbTabs& tabs,
                               hipStream_t st);
-// moves the sub-window of every solid whose zone (its boxes in ring slots wa
-// and wb, dilated by the layers) comes within MB_RECENTRE_MARGIN nodes of the
-// window's border, so that the boxes are centred: the maps of buffer buf
-// move within the window (through the other buffer, free between steps),
-// the ring boxes shift, and the origin changes in the solid table and the
-// argument tables; every node keeps its lattice position and value
-hipError_t launch_mb_recentre(int precision, MbBody* bodies, int nb, const MbTabs& tabs, int buf,
-                              int wa, int wb, hipStream_t st);
 hipError_t launch_mb_read_refmap(const GridP& lg, int precision, const MbBody* bodies, int k,
                                  int buf, int wvalid, double* X, double* Y, double* phi,
                                  hipStream_t st);
