@@ -26,6 +26,8 @@
 // (it decides the solid set), the normal matrix of the fit and its
 // well-posedness test (exact sums of powers of two on a few nodes), and the
 // inversion of grad xi where det < kappa_J.
+#include <type_traits>
+
 #include "lb_node.h"
 #include "fit_window.h"
 #include "mb_recentre.h"
@@ -1119,10 +1121,12 @@ struct Vec2<float> {
     using V = float2;
 };
 
-template <typename T, int NODES, int LN>
+// REC uint4: a record of the layers 3 and up holds the mask of valid nodes and
+// the normal matrix; unsigned: the mask alone
+template <typename T, int NODES, int LN, typename REC = uint4>
 struct FitLds {
     typename Vec2<T>::V val[NODES + 1];  // values of node e at e + 1; the first stays zero
-    uint4 rec[(FF_LAYERS - 2) * LN];     // layers >= 3: mask, cofactors, determinant
+    REC rec[(FF_LAYERS - 2) * LN];       // layers >= 3
     unsigned short lst[FF_LAYERS * LN];  // targets of layer l (places in the copy) from (l - 1) LN
     unsigned char st[NODES];             // tags; 255 where there is none
     int cnt[FF_LAYERS + 1];
@@ -1135,8 +1139,8 @@ struct FitRegion {
     int x0, y0, rw, rh, ox, oy, ow, oh, mstep;
 };
 
-template <typename T, int NT, int NODES, int LN, int RWC>
-__device__ __forceinline__ void fit_region(FitLds<T, NODES, LN>& s, const GridP& g,
+template <typename T, int NT, int NODES, int LN, int RWC, typename REC>
+__device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const GridP& g,
                                            const Rect& W, const Rect& D, int L,
                                            const FitRegion& R, const int8_t* tag,
                                            const T* __restrict__ phin, T* X1, T* Y1, int reach)
@@ -1255,9 +1259,12 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN>& s, const GridP&
                 m |= s.st[q + C2::off_b(0, k) * rw + C2::off_a(0, k)] < l ? 1u << k : 0u;
         const Geo2 G = geo2(m, g.det_rel);
         if (!G.ok) atomicMin(&s.cut, l);
-        s.rec[(l - 3) * LN + e] =
-            make_uint4(m, (unsigned)(G.m00 | G.m11 << 8 | (G.m01 & 0xff) << 16),
-                       (unsigned)((G.m02 & 0xff) | (G.m12 & 0xff) << 8), (unsigned)G.det);
+        if constexpr (sizeof(REC) == 4)
+            s.rec[(l - 3) * LN + e] = m;
+        else
+            s.rec[(l - 3) * LN + e] =
+                make_uint4(m, (unsigned)(G.m00 | G.m11 << 8 | (G.m01 & 0xff) << 16),
+                           (unsigned)((G.m02 & 0xff) | (G.m12 & 0xff) << 8), (unsigned)G.det);
     };
     // layer 1 + set: set 1 takes its weights while set 0 fits layer 1, and
     // weighs the values after the barrier
@@ -1336,17 +1343,24 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN>& s, const GridP&
     auto prep = [&](int l, int a, int n) {
         pq = -1;
         if (a >= n) return;
-        const uint4 r = s.rec[(l - 3) * LN + a];
+        const REC r = s.rec[(l - 3) * LN + a];
         pq = s.lst[(l - 1) * LN + a] + 1;
-        pg.m00 = (int)(r.y & 0xff);
-        pg.m11 = (int)(r.y >> 8 & 0xff);
-        pg.m01 = (int)(r.y << 8) >> 24;
-        pg.m02 = (int)(r.z << 24) >> 24;
-        pg.m12 = (int)(r.z << 16) >> 24;
-        pg.det = (int)r.w;
+        unsigned m;
+        if constexpr (sizeof(REC) == 4) {
+            m = r;
+            pg = geo2(m, g.det_rel);
+        } else {
+            m = r.x;
+            pg.m00 = (int)(r.y & 0xff);
+            pg.m11 = (int)(r.y >> 8 & 0xff);
+            pg.m01 = (int)(r.y << 8) >> 24;
+            pg.m02 = (int)(r.z << 24) >> 24;
+            pg.m12 = (int)(r.z << 16) >> 24;
+            pg.det = (int)r.w;
+        }
 #pragma unroll
         for (int k = 0; k < NS; k++)
-            adr[k] = ((int)(r.x << (31 - k)) >> 31) &
+            adr[k] = ((int)(m << (31 - k)) >> 31) &
                      (pq + C2::off_b(0, k) * rw + C2::off_a(0, k));
     };
     auto finish = [&]() {
@@ -1503,8 +1517,8 @@ __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* t
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
 // margin, and every tile with more than 64 targets in layers 1 and 2 before
 // its first layer (fit_rest then fits most of the zone: a check of it).
-template <typename T, int NT, int LC, int NODES, int LN>
-__device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN>& s, const GridP& g, const Rect& W,
+template <typename T, int NT, int LC, int NODES, int LN, typename REC>
+__device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN, REC>& s, const GridP& g, const Rect& W,
                                           const Rect& D, int8_t* tag, const T* __restrict__ phin,
                                           T* X1, T* Y1, unsigned* health, int* cut_tiles,
                                           int* ncut, const int* __restrict__ ff_list, int ntile,
@@ -1539,7 +1553,7 @@ __device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN>& s, const GridP& 
     }
 }
 
-template <typename T, int NT, int LC>
+template <typename T, int NT, int LC, typename REC = uint4>
 __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
                                                int wcur, int wprev, int8_t* tag,
                                                const T* __restrict__ phin, T* X1, T* Y1,
@@ -1547,7 +1561,7 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
                                                const int* __restrict__ ff_list, int* ff_n,
                                                unsigned* ticket, int* wide, int reach)
 {
-    __shared__ FitLds<T, FF_REGION * FF_REGION, FF_LAYER> s;
+    __shared__ FitLds<T, FF_REGION * FF_REGION, FF_LAYER, REC> s;
     // (the first tile is read together with the count: the list holds at
     // least as many entries as there are blocks)
     const int ntile = *ff_n, t0 = ff_list[blockIdx.x];
@@ -1562,10 +1576,11 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
 // window (dilated by 2) fits one block's copy is one block's, unless tiles is
 // set (few solids: whole-solid blocks would leave most of the chip idle);
 // any other's listed tiles are shared by the row's blocks.
-template <typename T, int NT, int LC>
-__global__ __launch_bounds__(NT) void kb_fit_mb(const FitArgs* __restrict__ args,
-                                                 const int* __restrict__ ord, int tiles)
+template <typename T, int LC>
+__global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restrict__ args,
+                                                        const int* __restrict__ ord, int tiles)
 {
+    constexpr int NT = FF_THREADS;
     __shared__ FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB> s;
     const FitArgs& a = args[ord[blockIdx.y]];
     const GridP& g = a.g;
@@ -1613,14 +1628,25 @@ __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict
                               ff_list, ff_n, ticket, wide, reach);
 }
 
-// a batch: member blockIdx.y
+// A batch: member blockIdx.y.  Its tiles are many rounds of blocks, and a
+// block is bound by its chain of layers: in FP32 two blocks of 256 threads
+// share a compute unit, their records short enough (masks alone, the matrices
+// counted again) for both copies to fit (96 cavities of 96^2 .. 768^2, 2900
+// tiles: 234 -> 168 us; one block a solid of a suspension, 400 of them, is
+// little more than a round, and slower two to a unit: 47 -> 56 us).  FP64
+// copies do not fit twice.
+template <typename T>
+struct BatchFit {
+    static constexpr int NT = sizeof(T) == 4 ? 256 : FF_THREADS;
+    using Rec = typename std::conditional<sizeof(T) == 4, unsigned, uint4>::type;
+};
 template <typename T, int LC>
-__global__ __launch_bounds__(FF_THREADS) void kb_fit_fused(const FitArgs* __restrict__ args)
+__global__ __launch_bounds__(BatchFit<T>::NT) void kb_fit_fused(const FitArgs* __restrict__ args)
 {
     const FitArgs& a = args[blockIdx.y];
-    fit_fused_body<T, FF_THREADS, LC>(a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin,
-                                      (T*)a.X1, (T*)a.Y1, a.health, a.cut_tiles, a.ncut,
-                                      a.ff_list, a.ff_n, a.ticket, a.ff_wide, 2);
+    fit_fused_body<T, BatchFit<T>::NT, LC, typename BatchFit<T>::Rec>(
+        a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
+        a.cut_tiles, a.ncut, a.ff_list, a.ff_n, a.ticket, a.ff_wide, 2);
 }
 
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
@@ -2665,11 +2691,11 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
     do {                                                                                       \
         if (fused && mb) {                                                                     \
             if (layers == FF_LAYERS)                                                           \
-                kb_fit_mb<T, MB_NT, FF_LAYERS><<<gf, MB_NT, 0, st>>>(t.fit, t.ord, mb->tiles); \
-            else kb_fit_mb<T, MB_NT, 0><<<gf, MB_NT, 0, st>>>(t.fit, t.ord, mb->tiles);        \
+                kb_fit_mb<T, FF_LAYERS><<<gf, FF_THREADS, 0, st>>>(t.fit, t.ord, mb->tiles);   \
+            else kb_fit_mb<T, 0><<<gf, FF_THREADS, 0, st>>>(t.fit, t.ord, mb->tiles);          \
         } else if (fused) {                                                                    \
-            if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS><<<gf, FF_THREADS, 0, st>>>(t.fit); \
-            else kb_fit_fused<T, 0><<<gf, FF_THREADS, 0, st>>>(t.fit);                         \
+            if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit); \
+            else kb_fit_fused<T, 0><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit);                    \
         } else if (mb) {                                                                       \
             kb_fit_lds<T, MB_NT><<<dim3(1, nsim), MB_NT, 0, st>>>(t.fit, layers, t.ord);       \
         } else {                                                                               \
