@@ -374,8 +374,13 @@ __device__ __forceinline__ bool upwind_d(C vel, C X0, C Y0, bool okm1, bool okm2
 // pull gather reads must lie in D (with the chain beside the bulk update,
 // the nodes of D are the ones the previous step's force pass updated); a
 // solid node on D's rim is counted as an advection miss and keeps its value.
-template <typename S, bool LATCHK = false>
-__device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict__ A,
+// INNER: every stencil node lies in D, and the lattice node off the lattice's
+// border, so that all addresses are fixed offsets from the node's (the same
+// loads and arithmetic, without the tests: about a third fewer instructions,
+// which bound the pass where a solid is large; MI355X, 2048^2 cavity FP64 22 ->
+// 18 us, 96 batch members FP32 94 -> 80).
+template <typename S, bool LATCHK, bool INNER>
+__device__ __forceinline__ void advect_at(const GridP& g, const S* __restrict__ A,
                                             const double* __restrict__ fpx,
                                             const double* __restrict__ fpy,
                                             const S* __restrict__ X, const S* __restrict__ Y,
@@ -385,25 +390,28 @@ __device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict_
     using C = S;
     constexpr bool DISP = sizeof(S) == 4;
     const long long P = g.plane;
-    const long long k = pidx(g, i, j);
+    const int k = (int)pidx(g, i, j);  // (a map has fewer than 2^26 nodes)
     // stencil nodes: x-1, x-2, x+1, x+2, y-1, y-2, y+1, y+2
     const int di[8] = {-1, -2, 1, 2, 0, 0, 0, 0};
     const int dj[8] = {0, 0, 0, 0, -1, -2, 1, 2};
-    long long ks[8];
+    int ks[8];
 #pragma unroll
-    for (int q = 0; q < 8; q++) ks[q] = ref_index(g, D, i + di[q], j + dj[q]);
+    for (int q = 0; q < 8; q++)
+        ks[q] = INNER ? k + dj[q] * g.pp + di[q] : (int)ref_index(g, D, i + di[q], j + dj[q]);
     // populations of the pull gather (the node is interior), at the node's
     // lattice position (a solid's window may be a sub-range of the lattice)
     const int li = lat_col(g, i), lj = lat_row(g, j);
-    const bool bw = !g.lpx && li == 0, be = !g.lpx && li == g.lnx - 1;
-    const bool bs = !g.lpy && lj == 0, bn = !g.lpy && lj == g.lny - 1;
+    const bool bw = !INNER && !g.lpx && li == 0, be = !INNER && !g.lpx && li == g.lnx - 1;
+    const bool bs = !INNER && !g.lpy && lj == 0, bn = !INNER && !g.lpy && lj == g.lny - 1;
     int im = li - 1, ip = li + 1, jm = lj - 1, jp = lj + 1;
-    im = im < 0 ? (g.lpx ? g.lnx - 1 : 0) : im;
-    ip = ip >= g.lnx ? (g.lpx ? 0 : g.lnx - 1) : ip;
-    jm = jm < 0 ? (g.lpy ? g.lny - 1 : 0) : jm;
-    jp = jp >= g.lny ? (g.lpy ? 0 : g.lny - 1) : jp;
+    if (!INNER) {
+        im = im < 0 ? (g.lpx ? g.lnx - 1 : 0) : im;
+        ip = ip >= g.lnx ? (g.lpx ? 0 : g.lnx - 1) : ip;
+        jm = jm < 0 ? (g.lpy ? g.lny - 1 : 0) : jm;
+        jp = jp >= g.lny ? (g.lpy ? 0 : g.lny - 1) : jp;
+    }
     bool lat_ok = true;
-    if (LATCHK) {
+    if (LATCHK && !INNER) {
         // D is a rectangle holding (i, j): the four axis neighbours decide
         int iw = i - 1, ie = i + 1, js = j - 1, jn = j + 1;
         if (g.px) {
@@ -421,28 +429,27 @@ __device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict_
             jm = jp = lj;
         }
     }
-    const long long r0 = (long long)lj * g.pitch, rm = (long long)jm * g.pitch,
-                    rp = (long long)jp * g.pitch, n = r0 + li;
+    const int r0 = lj * g.pitch, rm = jm * g.pitch, rp = jp * g.pitch, n = r0 + li;
     // ---- all loads
     const C X0 = X[k], Y0 = Y[k];
     C ps[8], xs[8], ys[8];
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        const long long kq = ks[q] >= 0 ? ks[q] : k;
+        const int kq = INNER || ks[q] >= 0 ? ks[q] : k;
         ps[q] = phi[kq];
         xs[q] = X[kq];
         ys[q] = Y[kq];
     }
     C f[NQ];
     f[0] = A[n];
-    f[1] = bw ? A[3 * P + n] : A[1 * P + r0 + im];
-    f[2] = bs ? A[4 * P + n] : A[2 * P + rm + li];
-    f[3] = be ? A[1 * P + n] : A[3 * P + r0 + ip];
-    f[4] = bn ? A[2 * P + n] : A[4 * P + rp + li];
-    f[5] = (bw || bs) ? A[7 * P + n] : A[5 * P + rm + im];
-    f[6] = (be || bs) ? A[8 * P + n] : A[6 * P + rm + ip];
-    f[7] = (be || bn) ? A[5 * P + n] : A[7 * P + rp + ip];
-    f[8] = (bw || bn) ? A[6 * P + n] : A[8 * P + rp + im];
+    f[1] = bw ? (A + 3 * P)[n] : (A + 1 * P)[r0 + im];
+    f[2] = bs ? (A + 4 * P)[n] : (A + 2 * P)[rm + li];
+    f[3] = be ? (A + 1 * P)[n] : (A + 3 * P)[r0 + ip];
+    f[4] = bn ? (A + 2 * P)[n] : (A + 4 * P)[rp + li];
+    f[5] = (bw || bs) ? (A + 7 * P)[n] : (A + 5 * P)[rm + im];
+    f[6] = (be || bs) ? (A + 8 * P)[n] : (A + 6 * P)[rm + ip];
+    f[7] = (be || bn) ? (A + 5 * P)[n] : (A + 7 * P)[rp + ip];
+    f[8] = (bw || bn) ? (A + 6 * P)[n] : (A + 8 * P)[rp + im];
     const C Fx = C(fpx[n]), Fy = C(fpy[n]);
     // ---- arithmetic: half-force velocity of Eq. (2_2_lbm_moments_force); the
     // FP32 mode stores f_i - w_i rho_f (sum w_i = 1, sum w_i c_i = 0)
@@ -452,7 +459,7 @@ __device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict_
     const C v = (f[2] + f[5] + f[6] - f[4] - f[7] - f[8]) / rho + Fy / (C(2) * rho);
     bool okq[8];
 #pragma unroll
-    for (int q = 0; q < 8; q++) okq[q] = ks[q] >= 0 && ps[q] < C(INFINITY);
+    for (int q = 0; q < 8; q++) okq[q] = (INNER || ks[q] >= 0) && ps[q] < C(INFINITY);
     C dXx, dYx, dXy, dYy;
     const bool okx = upwind_d<C>(u, X0, Y0, okq[0], okq[1], xs[0], ys[0], xs[1], ys[1], okq[2],
                                  okq[3], xs[2], ys[2], xs[3], ys[3], dXx, dYx);
@@ -472,6 +479,22 @@ __device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict_
     }
 }
 
+template <typename S, bool LATCHK = false>
+__device__ __forceinline__ void advect_node(const GridP& g, const S* __restrict__ A,
+                                            const double* __restrict__ fpx,
+                                            const double* __restrict__ fpy,
+                                            const S* __restrict__ X, const S* __restrict__ Y,
+                                            const S* __restrict__ phi, S* X1, S* Y1,
+                                            const Rect& D, int i, int j, unsigned* health)
+{
+    const int li = lat_col(g, i), lj = lat_row(g, j);
+    const bool inner = i - 2 >= D.i0 && i + 2 <= D.i1 && j - 2 >= D.j0 && j + 2 <= D.j1 &&
+                       li > 0 && li < g.lnx - 1 && lj > 0 && lj < g.lny - 1;
+    if (__all(inner))
+        advect_at<S, LATCHK, true>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, i, j, health);
+    else
+        advect_at<S, LATCHK, false>(g, A, fpx, fpy, X, Y, phi, X1, Y1, D, i, j, health);
+}
 
 // ---------------------------------------------------------------- layers
 
