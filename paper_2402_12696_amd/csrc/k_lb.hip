@@ -126,9 +126,9 @@ __global__ __launch_bounds__(LB_TX* LB_TY) void k_lb(
 // takes tile t = xcd_remap(b) of member tile_sim[t].
 template <typename S, int LB_TX, int LB_TY, int R, bool NT>
 __global__ __launch_bounds__(LB_TX* LB_TY) void kb_lb(const LbArgs* __restrict__ args,
-                                                     const int* __restrict__ tile_sim)
+                                                     const int* __restrict__ tile_sim, int t0)
 {
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    const int t = t0 + xcd_remap(blockIdx.x, gridDim.x);
     const LbArgs& a = args[tile_sim[t]];
     const int local = t - a.tile_base;
     // the member's first tile reduces the force pass's partial boxes
@@ -287,10 +287,10 @@ hipError_t launch_lb(const GridP& g, int precision, int variant, const void* A, 
 }
 
 template <typename S>
-static void lb_batch_variant(int v, const LbArgs* args, const int* tile_sim, int total,
+static void lb_batch_variant(int v, const LbArgs* args, const int* tile_sim, int t0, int total,
                              hipStream_t st)
 {
-#define LBB(TX, TY, R, NT) kb_lb<S, TX, TY, R, NT><<<total, TX * TY, 0, st>>>(args, tile_sim)
+#define LBB(TX, TY, R, NT) kb_lb<S, TX, TY, R, NT><<<total, TX * TY, 0, st>>>(args, tile_sim, t0)
     switch (v) {
     case 1: LBB(128, 2, 1, false); break;
     case 2: LBB(256, 1, 1, false); break;
@@ -348,11 +348,11 @@ hipError_t launch_lb_mb(const GridP& g, int precision, int variant, const void* 
 }
 
 hipError_t launch_lb_batch(int precision, int variant, const LbArgs* args, const int* tile_sim,
-                           int total_tiles, hipStream_t st)
+                           int t0, int total_tiles, hipStream_t st)
 {
     if (total_tiles <= 0) return hipSuccess;
-    if (precision == 0) lb_batch_variant<double>(variant, args, tile_sim, total_tiles, st);
-    else lb_batch_variant<float>(variant, args, tile_sim, total_tiles, st);
+    if (precision == 0) lb_batch_variant<double>(variant, args, tile_sim, t0, total_tiles, st);
+    else lb_batch_variant<float>(variant, args, tile_sim, t0, total_tiles, st);
     return hipGetLastError();
 }
 

@@ -2050,7 +2050,8 @@ int lbrmt_autotune_steps(lbrmt_ctx* c, int32_t steps, int32_t* best_fused, doubl
 // Independent members of different sizes stepped together: every kernel of
 // the step is one launch over all members (the reference-map kernels take the
 // member from blockIdx.y, the lattice update runs over the concatenated tile
-// lists), so one step costs 17 launches whatever the member count.  Members
+// lists), so one step costs 4 launches whatever the member count (14 layer by
+// layer; twice as many when it runs as two groups).  Members
 // are ordinary contexts on slices of the batch workspace; their argument
 // tables for the six phases n mod 6 (and n = 0) live in the workspace too.
 struct lbrmt_batch {
@@ -2058,6 +2059,9 @@ struct lbrmt_batch {
     int precision = 0, layers = 0;
     std::vector<lbrmt_ctx*> m;
     hipStream_t st = nullptr, cap = nullptr;
+    // the second group of members in a captured sequence
+    hipStream_t side = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_lb = nullptr, ev_join = nullptr;
     char* ws = nullptr;
     BatchTables tab[7];
     int* tile_sim = nullptr;
@@ -2211,15 +2215,63 @@ int batch_tables(lbrmt_batch* b)
     return LBRMT_OK;
 }
 
-int batch_enqueue(lbrmt_batch* b, long long n, hipStream_t st)
+// one step of members k0 .. k1 - 1 (lattice tiles t0 .. t1 - 1): their
+// reference-map chain and lattice update
+int batch_members(lbrmt_batch* b, long long n, int k0, int k1, int t0, int t1, hipStream_t st)
 {
     const int p = n == 0 ? 6 : (int)(n % 6);
-    const BatchTables& T = b->tab[p];
+    BatchTables T = b->tab[p];
+    T.adv += k0;
+    T.fit += k0;
+    T.edg += k0;
     const bool fused = batch_fused(b);
-    BCHK(b, launch_batch_band(b->precision, T, b->n, b->layers, st, BATCH_DT_BLOCKS,
-                              fused ? FF_BATCH_BLOCKS : BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS,
-                              fused));
-    BCHK(b, launch_lb_batch(b->precision, b->lb_variant, T.lb, b->tile_sim, b->total_tiles, st));
+    // no more blocks than the largest member's grid has tiles
+    long long tiles = 1;
+    for (int k = k0; k < k1; k++)
+        tiles = std::max(tiles, fused_tiles(b->m[k]->d.nx, b->m[k]->d.ny));
+    const int fit = (int)std::min<long long>(tiles, FF_BATCH_BLOCKS);
+    BCHK(b, launch_batch_band(b->precision, T, k1 - k0, b->layers, st, BATCH_DT_BLOCKS,
+                              fused ? fit : BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS, fused));
+    if (st == b->cap) BCHK(b, hipEventRecord(b->ev_lb, st));  // (captured)
+    BCHK(b, launch_lb_batch(b->precision, b->lb_variant, T.lb, b->tile_sim, t0, t1 - t0, st));
+    return LBRMT_OK;
+}
+
+int batch_enqueue(lbrmt_batch* b, long long n, hipStream_t st)
+{
+    return batch_members(b, n, 0, b->n, 0, b->total_tiles, st);
+}
+
+// GRAPH_STEPS steps on the capture stream.  Large batches run as two groups of
+// members side by side, the second a chain behind the first, so that one
+// group's lattice update (bound by HBM) meets the other's reference-map chain
+// (bound by latency and issue): members depend on nothing of each other.
+int batch_sequence(lbrmt_batch* b)
+{
+    int k1 = 0, t1 = 0;
+    while (k1 < b->n && 2ll * t1 < b->total_tiles)
+        t1 += (int)batch_tile_count(b->m[k1++]->d, b->lb_variant);
+    const bool two = k1 > 0 && k1 < b->n && (b->nodes >= BATCH_GROUP_NODES || b->n >= BATCH_GROUP_MEMBERS);
+    if (two) {
+        BCHK(b, hipEventRecord(b->ev_fork, b->cap));
+        BCHK(b, hipStreamWaitEvent(b->side, b->ev_fork, 0));
+    }
+    for (int k = 0; k < GRAPH_STEPS; k++) {
+        int rc = LBRMT_OK;
+        if (!two) {
+            rc = batch_enqueue(b, 6 + k, b->cap);
+        } else {
+            rc = batch_members(b, 6 + k, 0, k1, 0, t1, b->cap);
+            if (rc == LBRMT_OK && k == 0) BCHK(b, hipStreamWaitEvent(b->side, b->ev_lb, 0));
+            if (rc == LBRMT_OK)
+                rc = batch_members(b, 6 + k, k1, b->n, t1, b->total_tiles, b->side);
+        }
+        if (rc != LBRMT_OK) return rc;
+    }
+    if (two) {
+        BCHK(b, hipEventRecord(b->ev_join, b->side));
+        BCHK(b, hipStreamWaitEvent(b->cap, b->ev_join, 0));
+    }
     return LBRMT_OK;
 }
 
@@ -2227,8 +2279,7 @@ int batch_graph(lbrmt_batch* b)
 {
     hipGraph_t graph = nullptr;
     BCHK(b, hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    int rc = LBRMT_OK;
-    for (int k = 0; k < GRAPH_STEPS && rc == LBRMT_OK; k++) rc = batch_enqueue(b, 6 + k, b->cap);
+    const int rc = batch_sequence(b);
     hipError_t e = hipStreamEndCapture(b->cap, &graph);
     if (rc != LBRMT_OK) {
         if (graph) (void)hipGraphDestroy(graph);
@@ -2315,6 +2366,9 @@ int lbrmt_batch_create(const lbrmt_grid_desc* descs, const lbrmt_solid_desc* sol
     }
     if (rc == LBRMT_OK) {
         hipError_t e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+        for (hipEvent_t* v : {&b->ev_fork, &b->ev_lb, &b->ev_join})
+            if (e == hipSuccess) e = hipEventCreateWithFlags(v, hipEventDisableTiming);
         if (e != hipSuccess) rc = bfail(b, "stream creation", e);
     }
     if (rc != LBRMT_OK) {
@@ -2333,6 +2387,9 @@ void lbrmt_batch_destroy(lbrmt_batch* b)
     if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
     if (b->gsrc) (void)hipGraphDestroy(b->gsrc);
     if (b->cap) (void)hipStreamDestroy(b->cap);
+    if (b->side) (void)hipStreamDestroy(b->side);
+    for (hipEvent_t v : {b->ev_fork, b->ev_lb, b->ev_join})
+        if (v) (void)hipEventDestroy(v);
     for (auto c : b->m) lbrmt_destroy(c);
     delete b;
 }
@@ -2442,10 +2499,10 @@ int lbrmt_batch_autotune(lbrmt_batch* b, int32_t reps, int32_t* best_variant, do
         b->lb_variant = v;
         int rc = batch_tables(b);  // tile list of this shape
         if (rc != LBRMT_OK) return rc;
-        BCHK(b, launch_lb_batch(b->precision, v, b->tab[p].lb, b->tile_sim, b->total_tiles, b->st));
+        BCHK(b, launch_lb_batch(b->precision, v, b->tab[p].lb, b->tile_sim, 0, b->total_tiles, b->st));
         BCHK(b, hipEventRecord(e0, b->st));
         for (int r = 0; r < reps; r++)
-            BCHK(b, launch_lb_batch(b->precision, v, b->tab[p].lb, b->tile_sim, b->total_tiles,
+            BCHK(b, launch_lb_batch(b->precision, v, b->tab[p].lb, b->tile_sim, 0, b->total_tiles,
                                     b->st));
         BCHK(b, hipEventRecord(e1, b->st));
         BCHK(b, hipEventSynchronize(e1));

@@ -337,6 +337,12 @@ struct BatchTables {
     // passes takes (null: row y)
     const int* ord = nullptr;
 };
+// A batch of so many nodes or members runs its captured steps as two groups of
+// members (us/step on MI355X, one group -> two, FP32: 24 members of 96^2 ..
+// 768^2 206 -> 185, 64 of 64^2 110 -> 104, 256 of 64^2 305 -> 274, 8 of 1024^2
+// 195 -> 189; but 8 of 64^2 60 -> 71, 16 of 256^2 89 -> 92, 2 of 1024^2 90 -> 100)
+constexpr long long BATCH_GROUP_NODES = 4000000;
+constexpr int BATCH_GROUP_MEMBERS = 24;
 // blocks per member of the batched reference-map kernels (the distance
 // transform count is a multiple of NSUB and at most DT_BLOCKS, which the list
 // capacity assumes; relabel's partial boxes number BATCH_BAND_BLOCKS)
@@ -565,8 +571,9 @@ struct LossCoef {
 hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int layers,
                              hipStream_t st, int dt_blocks, int fit_blocks, int band_blocks,
                              bool fused, const MbStep* mb = nullptr);
+// (the lattice tiles t0 .. t0 + tiles - 1 of the concatenated list)
 hipError_t launch_lb_batch(int precision, int variant, const LbArgs* args, const int* tile_sim,
-                           int total_tiles, hipStream_t st);
+                           int t0, int tiles, hipStream_t st);
 // PART 0 / 2 launches with nbox > 0 also reduce the force pass's partial
 // boxes (boxpart) into ring slot wnext of win.  PART 3 updates the tiles
 // [frac0, frac1) / 1000 of the grid's tiles (none if that range is empty);
