@@ -2311,14 +2311,14 @@ template <typename C>
 __device__ __forceinline__ void mb_load3(const MbBody& B, const Rect& V, int buf, int wi, int wj,
                                          C* sX, C* sY, C* sP)
 {
-    const C* X = (const C*)B.X[buf];
-    const C* Y = (const C*)B.Y[buf];
-    const C* P = (const C*)B.phi[buf];
+    // (pointers read from memory: to device memory, not to any)
+    using G = const __attribute__((address_space(1))) C*;
+    G X = (G)B.X[buf], Y = (G)B.Y[buf], P = (G)B.phi[buf];
 #pragma unroll
     for (int e = 0; e < 9; e++) {
         int ci = wi + e % 3 - 1, cj = wj + e / 3 - 1;
         const bool in = canon(B.g, ci, cj) && V.has(ci, cj);
-        const long long k = in ? pidx(B.g, ci, cj) : 0;
+        const int k = in ? (int)pidx(B.g, ci, cj) : 0;
         const C xv = X[k], yv = Y[k], p = P[k];
         const bool set = in && p < C(INFINITY);
         sX[e] = set ? xv : C(NAN);
@@ -2330,7 +2330,7 @@ __device__ __forceinline__ void mb_load3(const MbBody& B, const Rect& V, int buf
 // the half-edges of a node in the 3 x 3 stencil: L, R, B, T as (a, b, s1..s4,
 // dir) with a before b along the normal and s1 + s2 - s3 - s4 the tangential
 // difference (the stencil of the single-solid force kernel)
-__constant__ int MB_EDGE[4][7] = {{3, 4, 7, 6, 1, 0, 0},
+constexpr int MB_EDGE[4][7] = {{3, 4, 7, 6, 1, 0, 0},
                                   {4, 5, 8, 7, 2, 1, 0},
                                   {1, 4, 5, 2, 3, 0, 1},
                                   {4, 7, 8, 5, 6, 3, 1}};
@@ -2494,40 +2494,34 @@ __global__ __launch_bounds__(256) void k_mb_combine(GridP lg, const MbBody* __re
     static_assert(FB * FB == 256, "one thread per node of a force block");
     if (blockIdx.x == 0 && threadIdx.x == 0 && count_clear) *count_clear = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0 && dstep) *dstep = *dcur + 1;
-    __shared__ int sl[MB_MAX_PER_BLOCK];
-    __shared__ int wcnt[4];
-    __shared__ int ns;
+    __shared__ int sl[MB_MAX_PER_BLOCK], hit[MB_HITS], nh;
     const int nblk = list ? *count : nblk_all;
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
     for (int t = blockIdx.x; t < nblk; t += gridDim.x) {
         const int blk = list ? list[t] : t;
         const int bx0 = (blk % nbx) * FB, by0 = (blk / nbx) * FB;
-        if (threadIdx.x == 0) ns = 0;
+        if (threadIdx.x == 0) nh = 0;
         __syncthreads();
-        // the solids whose region meets this block, in index order
-        for (int base = 0; base < nb; base += blockDim.x) {
-            const int k = base + threadIdx.x;
-            bool hit = false;
-            if (k < nb) {
-                const int4 r = bodies[k].reg;
-                hit = r.y >= 0 && r.w >= 0 &&
-                      ranges_meet(r.x, r.y, bx0, FB - 1, lg.nx, lg.px) &&
-                      ranges_meet(r.z, r.w, by0, FB - 1, lg.ny, lg.py);
+        // the solids whose region meets this block, as they are found
+        for (int k = threadIdx.x; k < nb; k += blockDim.x) {
+            const int4 r = bodies[k].reg;
+            if (r.y >= 0 && r.w >= 0 && ranges_meet(r.x, r.y, bx0, FB - 1, lg.nx, lg.px) &&
+                ranges_meet(r.z, r.w, by0, FB - 1, lg.ny, lg.py)) {
+                const int u = atomicAdd(&nh, 1);
+                if (u < MB_HITS) hit[u] = k;
             }
-            const unsigned long long m = __ballot(hit);
-            if (lane == 0) wcnt[w] = __popcll(m);
-            __syncthreads();
-            int off = ns + __popcll(m & ((1ull << lane) - 1ull));
-            for (int u = 0; u < w; u++) off += wcnt[u];
-            if (hit) {
-                if (off < MB_MAX_PER_BLOCK) sl[off] = k;
-                else if (mode != 2) atomicAdd(&health[7], 1u);
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) ns = min(ns + wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3],
-                                           MB_MAX_PER_BLOCK);
-            __syncthreads();
         }
+        __syncthreads();
+        // in index order: a solid's place is the number of those before it
+        const int all = min(nh, MB_HITS), ns = min(all, MB_MAX_PER_BLOCK);
+        if ((int)threadIdx.x < all) {
+            const int k = hit[threadIdx.x];
+            int place = 0;
+            for (int u = 0; u < all; u++) place += hit[u] < k ? 1 : 0;
+            if (place < MB_MAX_PER_BLOCK) sl[place] = k;
+        }
+        if (threadIdx.x == 0 && nh > MB_MAX_PER_BLOCK && mode != 2)
+            atomicAdd(&health[7], (unsigned)(nh - MB_MAX_PER_BLOCK));
+        __syncthreads();
         const int gi = bx0 + threadIdx.x % FB, gj = by0 + threadIdx.x / FB;
         if (gi < lg.nx && gj < lg.ny)
             mb_node<C>(lg, bodies, sl, ns, buf, wcur, gi, gj, fx, fy, drho, mode, health);

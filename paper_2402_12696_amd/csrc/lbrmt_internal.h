@@ -74,6 +74,7 @@ constexpr int MB_FIT_THREADS_F32 = 512;
 // nodes of a several-solid fit block's LDS copy (its window dilated by 2)
 constexpr int MB_FIT_LDS_NODES = 7168;
 constexpr int MB_MAX_PER_BLOCK = 32;  // solids overlapping one force block
+constexpr int MB_HITS = 256;          // of them found at once (more: the first found)
 // force combine of several solids: blocks striding over the stamped force
 // blocks (4096: suspension FP32 step 0.5416 -> 0.5370 ms against 2048)
 constexpr int MB_COMBINE_BLOCKS = 4096;
