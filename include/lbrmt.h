@@ -335,11 +335,11 @@ int lbrmt_kernel_time(lbrmt_ctx* ctx, const char* name, double* avg_ms, int64_t*
  *                         leaves the registers), each taking a tile of the window
  *                         with the margin its later layers read; tiles whose
  *                         targets need wider scan windows than the margin
- *                         holds are finished by a second, one-block launch.
+ *                         holds are finished by the launch's last block.
  *                         0: one launch per layer; 1: 512 threads with the
- *                         margin check one node tighter, so that the second
- *                         launch finishes most tiles (a check of that
- *                         launch); -1 (default): 512, or 0 when LBRMT_OPT_BULK_BLOCKS caps
+ *                         margin check one node tighter, so that the last
+ *                         block finishes most tiles (a check of that
+ *                         pass); -1 (default): 512, or 0 when LBRMT_OPT_BULK_BLOCKS caps
  *                         the bulk update.  With
  *                         overlap and no cap, the bulk lattice update then
  *                         starts when the advection pass has finished, so
@@ -363,8 +363,9 @@ int lbrmt_kernel_time(lbrmt_ctx* ctx, const char* name, double* avg_ms, int64_t*
  *                         previous step's bulk update has ended, beside the
  *                         end of that step's chain and this step's
  *                         advection pass; the held launch takes the other
- *                         tiles.  -1 (default): 300 on grids of 2048 x 2048
- *                         nodes or more, else 0.  Ignored while kernel timing
+ *                         tiles.  -1 (default): 0, and on lattices of up to
+ *                         72 MB read and written per update the force pass
+ *                         takes the bulk update along instead.  Ignored while kernel timing
  *                         is on.  Results are bitwise identical.  (A solid
  *                         box whose lower edge moves down by more than 2
  *                         rows in one step is counted in LBRMT_H_WINDOW_CLIP.)
@@ -417,8 +418,9 @@ int lbrmt_autotune_steps(lbrmt_ctx* ctx, int32_t steps, int32_t* best_fused, dou
 /* ---------------------------------------------------------------- batches
  * Many independent simulations (members) of any sizes stepped together: each
  * kernel of the step is one launch over all members, so a step costs the same
- * 17 launches whatever the member count, and blocks of six steps replay one
- * HIP graph.  Every member follows exactly the arithmetic of a single context
+ * 4 launches whatever the member count, and blocks of six steps replay one
+ * HIP graph (24 members or 4 million nodes and more: as two groups of members
+ * side by side).  Every member follows exactly the arithmetic of a single context
  * with the same description: results are bitwise identical to stepping each
  * member alone.  All members share the precision and the layer count; each
  * holds zero or one solid.  The batch carves one caller-owned device

@@ -9,10 +9,11 @@
 // a device ring of three boxes (previous, current, next step) so no host round
 // trip is needed.  A node outside a window holds no reference map.
 //
-// One step runs: advect (tags: solid / none) -> two-pass Manhattan distance
-// transform (exact layer numbers and one node list per layer) -> one fit
-// kernel per layer -> relabel (per-block boxes) -> force (LDS-tiled half
-// edges; reduces the boxes).
+// One step runs: advect (tags: solid / none, exact Manhattan layer numbers of
+// the zone, its tiles or one node list per layer) -> fits of every layer in one
+// launch, or one per layer -> force (relabel with per-block boxes, LDS-tiled
+// half edges, the lattice update of the window's nodes; the last block reduces
+// the boxes).
 //
 // These kernels take every discrete decision of the method (solid set, layers,
 // window growth of the fit, singular Jacobians); this file is compiled without

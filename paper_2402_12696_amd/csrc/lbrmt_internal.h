@@ -626,9 +626,9 @@ hipError_t launch_init_tags(const GridP& g, const BodyP& b, const BandBufs& bb, 
                             hipStream_t st);
 hipError_t launch_layers(const GridP& g, const BandBufs& bb, int wslot, hipStream_t st);
 // fused_threads 256 / 512 / 1024: all layers in one k_fit_fused launch of
-// that block size (walled axes, at most FF_LAYERS layers; else, and for 0,
-// one launch per layer); 1: 1024 threads with the fits' reach narrowed by one
-// node, so that the one-block pass over stopped tiles takes most of them
+// that block size (1024: 512; at most FF_LAYERS layers and no short periodic
+// axis; else, and for 0, one launch per layer); 1: 512 threads with the fits'
+// reach narrowed by one node, so that the last block takes most tiles
 hipError_t launch_extrapolate(const GridP& g, const BandBufs& bb, const StepSlots& s,
                               hipStream_t st, int fused_threads);
 // (a periodic axis wraps inside a block's copy, which holds no node twice when
