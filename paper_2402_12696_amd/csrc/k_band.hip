@@ -1463,7 +1463,9 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
         fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0>(s, g, W, D, layers, R, a.tag, (const T*)a.phin,
                                                (T*)a.X1, (T*)a.Y1, 2);
         l0 = s.cut;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
+        if (l0 <= layers) __threadfence();  // (the copy's results went through the caches)
     }
     for (int l = l0; l <= layers; l++) {
         layer_fit_body<T, true>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
