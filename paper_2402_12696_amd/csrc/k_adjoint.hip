@@ -566,7 +566,9 @@ __global__ __launch_bounds__(256) void k_adj_fit(GridP g, BodyP b, AdjSnap s, Ad
 // 2 L + 2 nodes (a margin's targets are recomputed by each block that needs
 // them).  Only the tile's solid nodes are written: what the zone's nodes hold
 // is spent after this, and k_adj_advect clears it, so no block reads what
-// another writes.  Bound by a chain of L dependent layers in LDS; launches of
+// another writes.  A node is a tile's own where it lies in the window without
+// wrapping: the last tile of a periodic axis may run over the seam, where it
+// holds nodes of the window's first tile.  Bound by a chain of L dependent layers in LDS; launches of
 // their own each scanned the window's tags again (256^2, solid of radius 40:
 // 12 launches, ~75 us a step -> one, 43 us).
 // s.wide: some target of the step has a wider scan window (or none): then one
@@ -745,7 +747,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
                 const double Xb = xb[q], Yb = yb[q];
                 if (Xb == 0.0 && Yb == 0.0) continue;
                 const int i0 = x0 + q % rw, j0 = y0 + q / rw;
-                const bool own = dist(q) <= 0;
+                const bool own = dist(q) <= 0 && W.has(i0, j0);
                 int i = i0, j = j0;
                 canon(g, i, j);
                 // xi^{n+1} of the scan nodes, all in flight together
@@ -785,7 +787,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
         }
         for (int e = tid; e < AT * AT; e += AT_THREADS) {
             const int q = (m + e / AT) * rw + m + e % AT;
-            if (st[q] != TAG_SOLID) continue;
+            if (st[q] != TAG_SOLID || !W.has(x0 + q % rw, y0 + q / rw)) continue;
             const double x = xb[q], y = yb[q];
             if (x == 0.0 && y == 0.0) continue;
             const long long k = global_of(q);
