@@ -2525,16 +2525,21 @@ __global__ __launch_bounds__(256) void k_mb_combine(GridP lg, const MbBody* __re
         const int bx0 = (blk % nbx) * FB, by0 = (blk / nbx) * FB;
         if (threadIdx.x == 0) nh = 0;
         __syncthreads();
-        // the solids whose region meets this block, as they are found
-        for (int k = threadIdx.x; k < nb; k += blockDim.x) {
-            const int4 r = bodies[k].reg;
-            if (r.y >= 0 && r.w >= 0 && ranges_meet(r.x, r.y, bx0, FB - 1, lg.nx, lg.px) &&
-                ranges_meet(r.z, r.w, by0, FB - 1, lg.ny, lg.py)) {
-                const int u = atomicAdd(&nh, 1);
-                if (u < MB_HITS) hit[u] = k;
+        // the solids whose region meets this block, as they are found among
+        // MB_CHUNK solids at a time: a list that ends holds the first in index
+        // order that the block takes
+        for (int k0 = 0; k0 < nb; k0 += MB_CHUNK) {
+            const int k = k0 + threadIdx.x;
+            if (k < nb && (int)threadIdx.x < MB_CHUNK) {
+                const int4 r = bodies[k].reg;
+                if (r.y >= 0 && r.w >= 0 && ranges_meet(r.x, r.y, bx0, FB - 1, lg.nx, lg.px) &&
+                    ranges_meet(r.z, r.w, by0, FB - 1, lg.ny, lg.py)) {
+                    const int u = atomicAdd(&nh, 1);
+                    if (u < MB_HITS) hit[u] = k;
+                }
             }
+            __syncthreads();
         }
-        __syncthreads();
         // in index order: a solid's place is the number of those before it
         const int all = min(nh, MB_HITS), ns = min(all, MB_MAX_PER_BLOCK);
         if ((int)threadIdx.x < all) {

@@ -74,7 +74,11 @@ constexpr int MB_FIT_THREADS_F32 = 512;
 // nodes of a several-solid fit block's LDS copy (its window dilated by 2)
 constexpr int MB_FIT_LDS_NODES = 7168;
 constexpr int MB_MAX_PER_BLOCK = 32;  // solids overlapping one force block
-constexpr int MB_HITS = 256;          // of them found at once (more: the first found)
+// of them listed (one thread of a force block's 256 each) to be put in index
+// order, and the solids looked at between two barriers: while the list has
+// fewer entries than the block takes, the next of these fit into it
+constexpr int MB_HITS = 256;
+constexpr int MB_CHUNK = MB_HITS - MB_MAX_PER_BLOCK;
 // force combine of several solids: blocks striding over the stamped force
 // blocks (4096: suspension FP32 step 0.5416 -> 0.5370 ms against 2048)
 constexpr int MB_COMBINE_BLOCKS = 4096;
