@@ -1996,7 +1996,8 @@ int lbrmt_autotune_steps(lbrmt_ctx* c, int32_t steps, int32_t* best_fused, doubl
 {
     if (!c || steps < 1) return LBRMT_EINVAL;
     if (!c->inited || c->member || c->multi) return LBRMT_ESTATE;
-    if (c->nsolid == 0 || !fused_fit_ok(c->g)) {
+    // (on a periodic axis the call never steps, whichever path the fits take)
+    if (c->nsolid == 0 || c->g.px || c->g.py || !fused_fit_ok(c->g)) {
         if (best_fused) *best_fused = c->fused_fit;
         if (best_ms) *best_ms = 0.0;
         return LBRMT_OK;
