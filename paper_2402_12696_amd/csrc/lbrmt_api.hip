@@ -2071,10 +2071,9 @@ struct lbrmt_batch {
     int lb_variant = 3;
     long long nodes = 0;  // interior nodes of all members (the autotune key)
     bool graph = true;
-    // the option as set: 1024, 0 (one launch per layer) or -1; not set or -1:
-    // one extrapolation launch if every member can
-    int fused_fit = 0;
-    bool fused_set = false;
+    // 0: one launch per layer; -1 (default) or 1024: one extrapolation launch
+    // if every member can
+    int fused_fit = -1;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t gsrc = nullptr;  // the captured graph of gexec
     long long step = 0;
@@ -2148,7 +2147,7 @@ int bfail(lbrmt_batch* b, const char* what, hipError_t e)
 // and 93
 bool batch_fused(const lbrmt_batch* b)
 {
-    if (b->fused_set && b->fused_fit == 0) return false;
+    if (b->fused_fit == 0) return false;
     for (const lbrmt_ctx* c : b->m)
         if (c->nsolid == 0 || !fused_fit_ok(c->g)) return false;
     return true;
@@ -2463,7 +2462,6 @@ int lbrmt_batch_set_option(lbrmt_batch* b, int32_t option, int64_t value)
     case LBRMT_OPT_FUSED_FIT:
         if (value != -1 && value != 0 && value != 1024) return LBRMT_EINVAL;
         b->fused_fit = (int)value;
-        b->fused_set = value != -1;
         break;
     default:
         return LBRMT_EINVAL;
