@@ -1588,9 +1588,9 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
                                                unsigned* ticket, int* wide, int reach)
 {
     __shared__ FitLds<T, FF_REGION * FF_REGION, FF_LAYER, REC> s;
-    // (the first tile is read together with the count: the list holds at
-    // least as many entries as there are blocks)
-    const int ntile = *ff_n, t0 = ff_list[blockIdx.x];
+    // (the first tile is read together with the count; a block beyond the
+    // list's room reads its last entry, and leaves)
+    const int ntile = *ff_n, t0 = ff_list[ff_first(blockIdx.x, g.nx, g.ny)];
     const Rect W = window_of(win, wcur, g);
     const Rect D = window_of(win, wprev, g);
     if ((int)blockIdx.x >= ntile || !W.ok) return;

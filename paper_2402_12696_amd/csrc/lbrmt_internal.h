@@ -646,6 +646,13 @@ __host__ __device__ inline long long fused_tiles(int nx, int ny)
     return (long long)((nx + 2 * PAD + FF_TILE - 1) / FF_TILE) *
            ((ny + 2 * PAD + FF_TILE - 1) / FF_TILE);
 }
+// the place in the tile list of a grid (room for each of its tiles) that block
+// b of an extrapolation launch reads first
+__host__ __device__ inline int ff_first(int b, int nx, int ny)
+{
+    const int room = (int)fused_tiles(nx, ny);
+    return b < room ? b : room - 1;
+}
 hipError_t launch_init_fill(const GridP& g, const BodyP& b, const BandBufs& bb, int wslot,
                             hipStream_t st);
 hipError_t launch_advect_layers(const GridP& g, int precision, const BandBufs& bb,
