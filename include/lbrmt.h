@@ -319,7 +319,10 @@ int lbrmt_kernel_time(lbrmt_ctx* ctx, const char* name, double* avg_ms, int64_t*
  *   LBRMT_OPT_LB_VARIANT  tile shape of the lattice Boltzmann update, 0 ..
  *                         LBRMT_OPT_LB_VARIANT_COUNT - 1, default 3 for FP64 and
  *                         5 for FP32 (results are bitwise identical across
- *                         variants; only speed differs).
+ *                         variants; only speed differs).  Set to another than
+ *                         the default, the update of the tiles away from the
+ *                         solid is a launch of its own on small lattices too
+ *                         (see LBRMT_OPT_BULK_EARLY).
  *   LBRMT_OPT_GRAPH       1 (default): whole blocks of six steps replay one
  *                         captured HIP graph; 0: every kernel is launched
  *                         eagerly (results are bitwise identical).
@@ -365,7 +368,11 @@ int lbrmt_kernel_time(lbrmt_ctx* ctx, const char* name, double* avg_ms, int64_t*
  *                         advection pass; the held launch takes the other
  *                         tiles.  -1 (default): 0, and on lattices of up to
  *                         72 MB read and written per update the force pass
- *                         takes the bulk update along instead.  Ignored while kernel timing
+ *                         takes the bulk update along instead, in tiles of
+ *                         the default LBRMT_OPT_LB_VARIANT (not with this
+ *                         option, LBRMT_OPT_LB_VARIANT or
+ *                         LBRMT_OPT_BULK_BLOCKS set, LBRMT_OPT_HOLD_BULK 0, or
+ *                         one launch per layer).  Ignored while kernel timing
  *                         is on.  Results are bitwise identical.  (A solid
  *                         box whose lower edge moves down by more than 2
  *                         rows in one step is counted in LBRMT_H_WINDOW_CLIP.)
@@ -398,7 +405,10 @@ int lbrmt_band_nodes(lbrmt_ctx* ctx, int64_t* band_nodes, int64_t* window_nodes)
  * the next step overwrites, so the state is unchanged.  The choice is
  * remembered for the process per (nx, ny, precision): contexts created later
  * with the same grid start with it (lbrmt_batch_autotune: per member count,
- * total nodes and precision, for batches).  best_variant / best_ms
+ * total nodes and precision, for batches).  It shapes the update where that is
+ * a launch of its own: a choice made here does not keep the force pass of a
+ * small lattice from taking the update along (see LBRMT_OPT_BULK_EARLY), as
+ * LBRMT_OPT_LB_VARIANT does when it is set.  best_variant / best_ms
  * (nullable): the choice and its time per launch.  Synchronises the stream.
  * ESTATE before init or on a batch member. */
 int lbrmt_autotune(lbrmt_ctx* ctx, int32_t reps, int32_t* best_variant, double* best_ms);

@@ -228,6 +228,8 @@ struct lbrmt_ctx {
     bool inited = false;
     bool overlap = true;  // the chain on an internal stream beside the bulk lattice update
     int lb_variant = 3;    // set per precision by lbrmt_create
+    // a tile shape other than the default was asked for by option
+    bool lb_asked = false;
     hipGraphExec_t gexec = nullptr;
     // steps 6 + p .. 6 + p + r - 1 (r < 6): replayed for step runs that do not
     // start or end on a six-step boundary, captured on first use
@@ -447,11 +449,12 @@ static int bulk_early(const lbrmt_ctx* c) { return c->bulk_early >= 0 ? c->bulk_
 // -> 55.8, 1024^2 62.7 -> 69.6; FP32 64^2 46.5 -> 40.4, 768^2 49.6 -> 46.1,
 // 1024^2 53.8 -> 53.5, 1300^2 59.5 -> 65.8: the lines cross near 75 MB read
 // and written.  An option that shapes the launch beside the chain keeps that
-// launch, as timing does.
+// launch, as timing does; the tile shape that an autotuner chose for it does
+// not (it gains less than the two dependencies cost).
 static bool bulk_along(const lbrmt_ctx* c, bool fused)
 {
     if (!c->overlap || !fused || c->timing || c->bulk_blocks > 0 || c->hold_bulk == 0 ||
-        c->bulk_early >= 0)
+        c->bulk_early >= 0 || c->lb_asked)
         return false;
     const long long bytes = (long long)c->d.nx * c->d.ny * 18 * (c->d.precision == 0 ? 8 : 4);
     return bytes <= BULK_ALONG_BYTES;
@@ -717,9 +720,9 @@ static int create_impl(const lbrmt_grid_desc* d, int32_t max_solids, void* ws, s
     if (bytes < L.total) return LBRMT_EWORKSPACE;
     lbrmt_ctx* c = new lbrmt_ctx();
     c->d = *d;
-    // measured fastest tile shapes: 64 x 4 (FP64), 256 x 1 (FP32), nontemporal
-    // stores; or the variant an earlier lbrmt_autotune chose for this shape
-    c->lb_variant = d->precision == LBRMT_FP64 ? 3 : 5;
+    // the default tile shape, or the one an earlier lbrmt_autotune chose for
+    // this grid
+    c->lb_variant = lb_default_variant(d->precision);
     if (!member) c->lb_variant = tuned_variant(0, d->nx, d->ny, d->precision, c->lb_variant);
     c->L = L;
     c->max_solids = max_solids;
@@ -1845,6 +1848,7 @@ int lbrmt_set_option(lbrmt_ctx* c, int32_t option, int64_t value)
     case LBRMT_OPT_LB_VARIANT:
         if (value < 0 || value >= lb_variant_count()) return LBRMT_EINVAL;
         c->lb_variant = (int)value;
+        c->lb_asked = value != lb_default_variant(c->d.precision);
         break;
     case LBRMT_OPT_GRAPH:
         if (value != 0 && value != 1) return LBRMT_EINVAL;
@@ -1984,8 +1988,11 @@ int lbrmt_autotune(lbrmt_ctx* c, int32_t reps, int32_t* best_variant, double* be
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
-    int rc = lbrmt_set_option(c, LBRMT_OPT_LB_VARIANT, best);
-    if (rc != LBRMT_OK) return rc;
+    if (best != c->lb_variant) {
+        c->lb_variant = best;
+        int rc = drop_graphs(c);  // they bake the shape in
+        if (rc != LBRMT_OK) return rc;
+    }
     remember_variant(0, c->d.nx, c->d.ny, c->d.precision, best);
     if (best_variant) *best_variant = best;
     if (best_ms) *best_ms = best_t / reps;
@@ -2337,7 +2344,7 @@ int lbrmt_batch_create(const lbrmt_grid_desc* descs, const lbrmt_solid_desc* sol
     b->n = n;
     b->precision = descs[0].precision;
     b->layers = descs[0].layers;
-    b->lb_variant = b->precision == LBRMT_FP64 ? 3 : 5;
+    b->lb_variant = lb_default_variant(b->precision);
     for (int k = 0; k < n; k++) b->nodes += (long long)descs[k].nx * descs[k].ny;
     b->lb_variant = tuned_variant(1, n, b->nodes, b->precision, b->lb_variant);
     b->st = (hipStream_t)stream;

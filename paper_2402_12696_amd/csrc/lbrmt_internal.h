@@ -595,6 +595,9 @@ hipError_t launch_lb(const GridP& g, int precision, int variant, const void* A, 
                      Win* winw = nullptr, int wnext = 0, int frac0 = 0, int frac1 = 1000,
                      int split = 0);
 int lb_variant_count();
+// the tile shape measured fastest: 64 x 4 (FP64), 256 x 1 (FP32), one node per
+// thread, nontemporal stores (LbTile is the same)
+inline int lb_default_variant(int precision) { return precision == 0 ? 3 : 5; }
 void lb_variant_tile(int v, int* tx, int* ty);
 // drho0 (several solids): the density excess of every node, instead of the
 // single solid's level set
