@@ -509,43 +509,36 @@ __device__ __forceinline__ void adj_relabel_node(const BodyP& b, const AdjSnap& 
     y += pb * gy;
 }
 
-// The targets of layer l of the window, nt threads of which this is number t,
-// on the adjoint fields in memory.  RELABEL: each target's relabel first (only
-// its own thread touches a node of layer l in this pass).
+// Target (i, j) of layer l, node kt, on the adjoint fields in memory.  RELABEL:
+// its relabel first (only its own thread touches a node of layer l in this
+// pass).
 template <bool RELABEL>
-__device__ __forceinline__ void adj_fit_layer(const GridP& g, const BodyP& b, const AdjSnap& s,
-                                              const AdjBufs& a, const Rect& W, const Rect& D,
-                                              int l, long long t, long long nt)
+__device__ __forceinline__ void adj_fit_node(const GridP& g, const BodyP& b, const AdjSnap& s,
+                                             const AdjBufs& a, const Rect& W, const Rect& D, int l,
+                                             int i, int j, long long kt)
 {
-    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
-    for (long long e = t; e < (long long)w * h; e += nt) {
-        int i = W.i0 + (int)(e % w), j = W.j0 + (int)(e / w);
-        if (!canon(g, i, j)) continue;
-        const long long kt = pidx(g, i, j);
-        if (s.tag[kt] != l) continue;  // not this layer, or its fit failed
-        // (past the CU's own cache: the block may have added to it)
-        double Xb = __hip_atomic_load(&a.xbar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        double Yb = __hip_atomic_load(&a.ybar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (RELABEL) adj_relabel_node(b, s, kt, a.pbar1[kt], Xb, Yb);
-        if (Xb == 0.0 && Yb == 0.0) continue;
-        adj_fit_target<0>(
-            g, D, s, a, l, i, j, Xb, Yb, true,
-            [&](int aa, int bb) -> long long {
-                int x = i + aa, y = j + bb;
-                if (!canon(g, x, y) || !W.has(x, y)) return -1;
-                const long long k = pidx(g, x, y);
-                const int t = s.tag[k];
-                return t == TAG_SOLID || (t > 0 && t < l) ? k : -1;
-            },
-            [&](long long k, int, int, double& xv, double& yv) {
-                xv = s.X1[k];
-                yv = s.Y1[k];
-            },
-            [&](long long k, double vx, double vy) {
-                atomicAdd(&a.xbar1[k], vx);
-                atomicAdd(&a.ybar1[k], vy);
-            });
-    }
+    // (past the caches: any block may have added to it in this launch)
+    double Xb = __hip_atomic_load(&a.xbar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    double Yb = __hip_atomic_load(&a.ybar1[kt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (RELABEL) adj_relabel_node(b, s, kt, a.pbar1[kt], Xb, Yb);
+    if (Xb == 0.0 && Yb == 0.0) return;
+    adj_fit_target<0>(
+        g, D, s, a, l, i, j, Xb, Yb, true,
+        [&](int aa, int bb) -> long long {
+            int x = i + aa, y = j + bb;
+            if (!canon(g, x, y) || !W.has(x, y)) return -1;
+            const long long k = pidx(g, x, y);
+            const int t = s.tag[k];
+            return t == TAG_SOLID || (t > 0 && t < l) ? k : -1;
+        },
+        [&](long long k, int, int, double& xv, double& yv) {
+            xv = s.X1[k];
+            yv = s.Y1[k];
+        },
+        [&](long long k, double vx, double vy) {
+            atomicAdd(&a.xbar1[k], vx);
+            atomicAdd(&a.ybar1[k], vy);
+        });
 }
 
 // one launch per layer, last layer first
@@ -554,8 +547,86 @@ __global__ __launch_bounds__(256) void k_adj_fit(GridP g, BodyP b, AdjSnap s, Ad
     const Rect W = window_of(s.win, 1, g);
     const Rect D = window_of(s.win, 0, g);
     if (!W.ok) return;
-    adj_fit_layer<false>(g, b, s, a, W, D, l, blockIdx.x * (long long)blockDim.x + threadIdx.x,
-                         (long long)gridDim.x * blockDim.x);
+    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
+    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < (long long)w * h;
+         e += (long long)gridDim.x * blockDim.x) {
+        int i = W.i0 + (int)(e % w), j = W.j0 + (int)(e / w);
+        if (!canon(g, i, j)) continue;
+        const long long kt = pidx(g, i, j);
+        if (s.tag[kt] != l) continue;  // not this layer, or its fit failed
+        adj_fit_node<false>(g, b, s, a, W, D, l, i, j, kt);
+    }
+}
+
+// Every layer on the fields in memory, by all blocks of a launch, where a fit
+// has a wider scan window than a tile's copy serves.  The layers' shares of the
+// window (last layer first) are numbered, and a block takes the next number by
+// an atomic: a share waits for those of the layer before it, whose numbers are
+// smaller, so that running blocks hold them all and the wait ends however few
+// blocks run at a time (a block works its numbers off in their order).  What
+// one share adds and another reads goes through atomics, complete before the
+// share counts as done.  a.work: 0 between launches; the numbers taken, the
+// blocks that have left, each layer's shares done.  Bound by what a layer's
+// targets do one after the other, ~18 us a layer.  One block alone scanned the
+// window once per layer; thin solids, us per reverse step, 256^2 / 768^2: one
+// block 1311 / 5953, this 271 / 448 (a launch per layer, which every other step
+// would pay for, 238 / 387).
+__device__ __forceinline__ void adj_fit_shared(const GridP& g, const BodyP& b, const AdjSnap& s,
+                                               const AdjBufs& a, const Rect& W, const Rect& D,
+                                               int L)
+{
+    __shared__ unsigned number[2];
+    const int w = W.i1 - W.i0 + 1, nt = blockDim.x;
+    const long long n = (long long)w * (W.j1 - W.j0 + 1);
+    // nodes per thread of a share, 32 at most (bits of hit): a share to half the
+    // blocks that run at a time, one on each of the chip's 256 units, so that
+    // the others look through the next layer's meanwhile
+    const int half = max(1, min((int)gridDim.x, 256) / 2);
+    const int rounds = (int)min((n + half * nt - 1) / (half * nt), 32ll);
+    const unsigned shares = (unsigned)((n + rounds * nt - 1) / (rounds * nt)), all = shares * L;
+    unsigned *taken = a.work, *left = a.work + 1, *done = a.work + 2;
+    if (threadIdx.x == 0) number[0] = atomicAdd(taken, 1u);
+    __syncthreads();
+    for (int turn = 0;; turn ^= 1) {
+        const unsigned q = number[turn];
+        if (q >= all) break;
+        const int k = q / shares, l = L - k;
+        const long long e0 = (long long)(q % shares) * (rounds * nt) + threadIdx.x;
+        // (which of the thread's nodes are targets, and the next number: before the wait)
+        unsigned hit = 0;
+        for (int u0 = 0; u0 < rounds; u0 += 4) {
+            int tv[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int e = (int)min(e0 + (u0 + u) * nt, n - 1);
+                tv[u] = s.tag[pidx(g, W.i0 + e % w, W.j0 + e / w)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                if (tv[u] == l && u0 + u < rounds && e0 + (u0 + u) * nt < n) hit |= 1u << (u0 + u);
+        }
+        if (threadIdx.x == 0) {
+            number[turn ^ 1] = atomicAdd(taken, 1u);
+            if (k > 0)
+                while (__hip_atomic_load(&done[k - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                       shares)
+                    __builtin_amdgcn_s_sleep(1);
+        }
+        __syncthreads();
+        while (hit) {
+            const int e = (int)e0 + (__ffs(hit) - 1) * nt;  // (a window has fewer than 2^26 nodes)
+            hit &= hit - 1;
+            const int i = W.i0 + e % w, j = W.j0 + e / w;
+            adj_fit_node<true>(g, b, s, a, W, D, l, i, j, pidx(g, i, j));
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) atomicAdd(&done[k], 1u);
+    }
+    if (threadIdx.x == 0 && atomicAdd(left, 1u) == gridDim.x - 1) {
+        __threadfence();
+        for (int k = 0; k < ADJ_WORK; k++) a.work[k] = 0u;
+    }
 }
 
 // Relabel and every layer backwards in one launch (up to FF_LAYERS layers).
@@ -571,8 +642,8 @@ __global__ __launch_bounds__(256) void k_adj_fit(GridP g, BodyP b, AdjSnap s, Ad
 // holds nodes of the window's first tile.  Bound by a chain of L dependent layers in LDS; launches of
 // their own each scanned the window's tags again (256^2, solid of radius 40:
 // 12 launches, ~75 us a step -> one, 43 us).
-// s.wide: some target of the step has a wider scan window (or none): then one
-// block runs the layers on the fields in memory.
+// s.wide: some target of the step has a wider scan window (or none): then the
+// blocks run the layers on the fields in memory (adj_fit_shared).
 constexpr int AT = FF_TILE, AT_THREADS = 512;
 constexpr int AT_R = AT + 4 * FF_LAYERS + 4;  // side of the copy at FF_LAYERS layers
 // LC: the layer count (FF_LAYERS), or 0 (the grid's)
@@ -590,12 +661,7 @@ __global__ __launch_bounds__(AT_THREADS) void k_adj_fits(GridP g, BodyP b, AdjSn
     if (!W.ok) return;
     const int L = LC > 0 ? LC : g.layers;
     if (*s.wide != 0) {
-        if (blockIdx.x != 0) return;
-        for (int l = L; l >= 1; l--) {
-            adj_fit_layer<true>(g, b, s, a, W, D, l, threadIdx.x, blockDim.x);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-        }
+        adj_fit_shared(g, b, s, a, W, D, L);
         return;
     }
     const int m = 2 * L + 2, rw = LC == FF_LAYERS ? AT_R : AT + 2 * m;

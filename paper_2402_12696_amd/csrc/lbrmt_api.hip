@@ -1468,7 +1468,7 @@ AdjLayout adj_layout(const lbrmt_ctx* c)
         A.Fx[k] = take(N * 8);
         A.Fy[k] = take(N * 8);
     }
-    A.acc = take(2 * 8);
+    A.acc = take(2 * 8 + ADJ_WORK * 4);  // the sums, then the counters
     A.total = o;
     return A;
 }
@@ -1492,6 +1492,7 @@ AdjBufs adj_bufs(const lbrmt_ctx* c, void* adj)
     a.Fpbar_x = (double*)(b + L.Fx[h]);
     a.Fpbar_y = (double*)(b + L.Fy[h]);
     a.acc = (double*)(b + L.acc);
+    a.work = (unsigned*)(a.acc + 2);
     return a;
 }
 

@@ -557,7 +557,9 @@ struct AdjBufs {
     double *Fcbar_x, *Fcbar_y;
     double *Fpbar_x, *Fpbar_y;
     double* acc;
+    unsigned* work;  // ADJ_WORK counters of adj_fit_shared, 0 between launches
 };
+constexpr int ADJ_WORK = 2 + FF_LAYERS;
 
 // loss coefficients of one state: centroid c, mean displacement d, and
 // gc = dL/dc / sum lambda, gd = dL/dd / sum lambda
