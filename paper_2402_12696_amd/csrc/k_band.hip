@@ -1133,7 +1133,17 @@ __global__ __launch_bounds__(256) void kb_layer_fit(const FitArgs* __restrict__ 
 //
 // A target that the copy cannot serve (its fit needs a scan window wider than
 // half-width 2, or fails for good) sets s.cut to its layer: the layers before
-// it stand, the caller sees to the others.
+// it stand, the caller sees to the others (FIT_TILE).
+// A whole window's copy holds every node there is, so it can serve wider scan
+// windows too: FIT_WIDE lists such targets (up to FF_WIDE) and searches them in
+// the copy as on the maps, eight lanes each, when the others of their layer are
+// done; one that fails for good cuts the layers after its own, whose records
+// take it for valid.  (60 solids of 44 x 1.8 nodes, us/step FP64 with the layers
+// from the first such target on fitted from the maps 207, searched in the copy
+// 101; FP32 184, 88.)  The search in its layers costs a solid without such
+// targets 2 us a step, so FIT_WHOLE goes first and leaves before its third layer
+// with nothing written if there are any.
+enum FitMode { FIT_TILE, FIT_WHOLE, FIT_WIDE };
 template <typename T>
 struct Vec2;
 template <>
@@ -1153,7 +1163,9 @@ struct FitLds {
     REC rec[(FF_LAYERS - 2) * LN];       // layers >= 3
     unsigned short lst[FF_LAYERS * LN];  // targets of layer l (places in the copy) from (l - 1) LN
     unsigned char st[NODES];             // tags; 255 where there is none
+    unsigned short wide[FF_WIDE];        // targets without a fit at half-width 2
     int cnt[FF_LAYERS + 1];
+    int nwide, wlayers;                  // their number, and their layers (a bit each)
     int cut;
 };
 
@@ -1163,12 +1175,15 @@ struct FitRegion {
     int x0, y0, rw, rh, ox, oy, ow, oh, mstep;
 };
 
-template <typename T, int NT, int NODES, int LN, int RWC, typename REC>
+template <typename T, int NT, int NODES, int LN, int RWC, FitMode MODE, typename REC>
 __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const GridP& g,
                                            const Rect& W, const Rect& D, int L,
-                                           const FitRegion& R, const int8_t* tag,
-                                           const T* __restrict__ phin, T* X1, T* Y1, int reach)
+                                           const FitRegion& R, int8_t* tag,
+                                           const T* __restrict__ phin, T* X1, T* Y1,
+                                           unsigned* health, int reach)
 {
+    constexpr bool WIDE = MODE == FIT_WIDE;
+    static_assert(!WIDE || sizeof(REC) > 4, "a record without a fit is marked in its determinant");
     using C2 = Win2<T, 8>;
     constexpr int NS = C2::NS;
     constexpr int NIT = (NODES + NT - 1) / NT;  // staged nodes per thread
@@ -1211,6 +1226,7 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
     }
     __syncthreads();  // the previous region's shared state is no longer read
     if (tid <= FF_LAYERS) s.cnt[tid] = 0;
+    if (WIDE && tid == FF_LAYERS + 1) s.nwide = s.wlayers = 0;
     if (tid == 0) {
         s.cut = L + 1;
         s.val[0].x = s.val[0].y = T(0);
@@ -1264,6 +1280,69 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
         __syncthreads();
         return;
     }
+    // target q of layer l has no fit at half-width 2
+    auto defer = [&](int q, int l) {
+        if constexpr (WIDE) {
+            const int u = atomicAdd(&s.nwide, 1);
+            if (u < FF_WIDE) {
+                s.wide[u] = (unsigned short)q;
+                atomicOr(&s.wlayers, 1 << l);
+                return;
+            }
+        }
+        atomicMin(&s.cut, l);
+    };
+    // layer l's of them, the rest of the layer being done (as fit_target, the
+    // nodes read from the copy); nobody lists meanwhile
+    auto search = [&](int l) {
+        const int nw = min(s.nwide, FF_WIDE), sub = tid % FIT_LANES;
+#pragma unroll 1
+        for (int u = tid / FIT_LANES; u < nw; u += NT / FIT_LANES) {
+            const int q = s.wide[u];
+            if (s.st[q] != l) continue;  // whole groups leave together
+            const int i = R.x0 + q % rw, j = R.y0 + q / rw;
+            double nxh, nyh;
+            const bool use_n = target_normal<T>(g, D, l, i, j, sub, phin, nxh, nyh);
+            T xo = T(0), yo = T(0);
+            bool ok = false;
+#pragma unroll 1
+            for (int r = 3; r <= g.r_max && !ok; r++) {
+                const int side = 2 * r + 1;
+                int count = 0, a = sub % side - r, b = sub / side - r;
+                Fit<T> f;
+                f.zero();
+#pragma unroll 1
+                for (int k = sub; k < side * side; k += FIT_LANES) {
+                    int x = i + a, y = j + b;
+                    if (canon(g, x, y) && W.has(x, y)) {
+                        const int e = (y - R.y0) * rw + x - R.x0;
+                        if (s.st[e] < l) {
+                            count++;
+                            f.add(a, b, use_n, nxh, nyh, s.val[e + 1].x, s.val[e + 1].y);
+                        }
+                    }
+                    a += FIT_LANES;
+                    while (a > r) {
+                        a -= side;
+                        b += 1;
+                    }
+                }
+                ok = fit_finish<T>(g.det_rel, f, count, xo, yo);
+            }
+            if (sub == 0) {
+                if (ok) {
+                    s.val[q + 1].x = xo;
+                    s.val[q + 1].y = yo;
+                } else {
+                    s.st[q] = (unsigned char)(l | TAG_FAIL);
+                    tag[pidx(g, i, j)] = (int8_t)(l | TAG_FAIL);
+                    atomicAdd(&health[1], 1u);
+                    atomicMin(&s.cut, l + 1);
+                }
+            }
+        }
+        __syncthreads();
+    };
     // ---- layers 1 and 2 (sets 0 and 1), with the normal of phi^n at the
     // target; the records of the others (sets 2 and 3)
     auto record = [&](int e) {
@@ -1282,13 +1361,14 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
             if (C2::in(0, k))
                 m |= s.st[q + C2::off_b(0, k) * rw + C2::off_a(0, k)] < l ? 1u << k : 0u;
         const Geo2 G = geo2(m, g.det_rel);
-        if (!G.ok) atomicMin(&s.cut, l);
+        if (!G.ok) defer(q, l);
         if constexpr (sizeof(REC) == 4)
             s.rec[(l - 3) * LN + e] = m;
         else
             s.rec[(l - 3) * LN + e] =
                 make_uint4(m, (unsigned)(G.m00 | G.m11 << 8 | (G.m01 & 0xff) << 16),
-                           (unsigned)((G.m02 & 0xff) | (G.m12 & 0xff) << 8), (unsigned)G.det);
+                           (unsigned)((G.m02 & 0xff) | (G.m12 & 0xff) << 8),
+                           !WIDE || G.ok ? (unsigned)G.det : 0u);
     };
     // layer 1 + set: set 1 takes its weights while set 0 fits layer 1, and
     // weighs the values after the barrier
@@ -1348,7 +1428,7 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
                         s.val[q + 1].x = xo;
                         s.val[q + 1].y = yo;
                     } else {
-                        atomicMin(&s.cut, l);
+                        defer(q, l);
                     }
                     have = false;
                 }
@@ -1359,6 +1439,7 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
                 for (; e < stop; e += NT - 2 * SW) record(e);
             }
             __syncthreads();
+            if (WIDE && (s.wlayers >> (ph + 1) & 1)) search(ph + 1);
         }
     }
     // ---- layers 3 and up
@@ -1375,6 +1456,10 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
             pg = geo2(m, g.det_rel);
         } else {
             m = r.x;
+            if (WIDE && r.w == 0) {
+                pq = -1;
+                return;
+            }
             pg.m00 = (int)(r.y & 0xff);
             pg.m11 = (int)(r.y >> 8 & 0xff);
             pg.m01 = (int)(r.y << 8) >> 24;
@@ -1401,7 +1486,9 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
         s.val[pq].x = xo;
         s.val[pq].y = yo;
     };
-    const int last = min(L, s.cut - 1);  // (the same in every thread: no cut follows)
+    const int wl = WIDE ? __builtin_amdgcn_readfirstlane(s.wlayers) : 0;
+    int last = min(L, s.cut - 1);  // (the same in every thread)
+    if (MODE == FIT_WHOLE && last < L) return;
     int lm = 3 + set, n = s.cnt[min(lm, FF_LAYERS)];  // the set's next layer
     if (lm <= last) prep(lm, lane, n);
 #pragma unroll 1
@@ -1418,6 +1505,10 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
             }
         }
         __syncthreads();
+        if (WIDE && (wl >> l & 1)) {
+            search(l);
+            last = min(last, s.cut - 1);
+        }
         if (mine) {
             lm += NSET;
             n = s.cnt[min(lm, FF_LAYERS)];
@@ -1437,14 +1528,47 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
     }
 }
 
-// Every layer of one solid in one block (several solids: a solid's layers are
-// short) on a copy of its window dilated by 2, laid out in unwrapped
-// coordinates, each node holding what its periodic image holds, so it is kept
-// only while no two of its nodes are images of one node (the copy no wider
-// than a period).  The layers that the copy cannot serve, and every layer of
-// a solid whose copy would exceed MB_FIT_LDS_NODES nodes or a period, are
-// fitted on the maps (layer_fit_body: the same bits).  Block row y takes table
-// row ord[y] (row y when ord is null).
+// Can a block's copy hold a whole window (dilated by 2; no two of its nodes
+// images of one node)?
+__device__ __forceinline__ bool fits_whole(const GridP& g, const Rect& W)
+{
+    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
+    return (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
+           !(g.py && h + 4 > g.ny);
+}
+
+// Every layer of one solid in one block on such a copy, laid out in unwrapped
+// coordinates, each node holding what its periodic image holds.  Returns the
+// first layer that the copy could not serve (the block sees what it wrote of
+// the others), layers + 1 if none.  wide: there are targets without a fit at
+// half-width 2.
+template <typename T, int NT>
+__device__ __forceinline__ int fit_whole(FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB>& s,
+                                         const GridP& g, const Rect& W, const Rect& D,
+                                         const FitArgs& a, bool wide)
+{
+    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
+    const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
+    if (!wide)
+        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0, FIT_WHOLE>(
+            s, g, W, D, g.layers, R, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, 2);
+    if (wide || s.cut <= g.layers)
+        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0, FIT_WIDE>(
+            s, g, W, D, g.layers, R, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, 2);
+    const int l0 = s.cut;
+    if (l0 <= g.layers) {
+        // (the copy's results went through the caches)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        __threadfence();
+    }
+    return l0;
+}
+
+// Several solids without the one-launch extrapolation: one block per solid
+// (its layers are short), on a copy where that can be.  The layers that the
+// copy cannot serve are fitted on the maps (layer_fit_body: the same bits).
+// Block row y takes table row ord[y] (row y when ord is null).
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ args, int layers,
                                                   const int* __restrict__ ord)
@@ -1455,18 +1579,7 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
     const Rect W = window_of(a.win, a.wcur, g);
     const Rect D = window_of(a.win, a.wprev, g);
     if (!W.ok) return;
-    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
-    int l0 = 1;
-    if (layers <= FF_LAYERS && (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
-        !(g.py && h + 4 > g.ny)) {
-        const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
-        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0>(s, g, W, D, layers, R, a.tag, (const T*)a.phin,
-                                               (T*)a.X1, (T*)a.Y1, 2);
-        l0 = s.cut;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (l0 <= layers) __threadfence();  // (the copy's results went through the caches)
-    }
+    const int l0 = layers <= FF_LAYERS && fits_whole(g, W) ? fit_whole<T, NT>(s, g, W, D, a, false) : 1;
     for (int l = l0; l <= layers; l++) {
         layer_fit_body<T, true>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
                                 (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
@@ -1535,21 +1648,20 @@ __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* t
 // windows read solid nodes only, which the copy holds across the margin.  Only
 // the tile's own targets are written back.  A tile that the copy cannot serve
 // from some layer on (a fit that needs a wider scan window, or fails for good;
-// more than FF_LAYER targets
-// in a layer) is listed, with the layer; the block that ends last finishes
-// the listed tiles layer by layer (fit_rest) and empties both lists.  (A
-// launch of its own for that took 4 us a step, with nothing to do but at rare
-// steps; the ticket of the blocks takes ~1 us.)
+// more than FF_LAYER targets in a layer) is listed, with the layer; the block
+// that ends last finishes the listed tiles layer by layer (fit_rest) and
+// empties both lists.  (A launch of its own for that took 4 us a step, with
+// nothing to do but at rare steps; the ticket of the blocks takes ~1 us.)
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
 // margin, and every tile with more than 64 targets in layers 1 and 2 before
 // its first layer (fit_rest then fits most of the zone: a check of it).
+// Returns the number of listed tiles in the last block, -1 in the others.
 template <typename T, int NT, int LC, int NODES, int LN, typename REC>
-__device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN, REC>& s, const GridP& g, const Rect& W,
-                                          const Rect& D, int8_t* tag, const T* __restrict__ phin,
-                                          T* X1, T* Y1, unsigned* health, int* cut_tiles,
-                                          int* ncut, const int* __restrict__ ff_list, int ntile,
-                                          int t0, int* ff_n, unsigned* ticket, int* wide,
-                                          int reach)
+__device__ __forceinline__ int fit_tiles(FitLds<T, NODES, LN, REC>& s, const GridP& g, const Rect& W,
+                                         const Rect& D, int8_t* tag, const T* __restrict__ phin,
+                                         T* X1, T* Y1, unsigned* health, int* cut_tiles,
+                                         int* ncut, const int* __restrict__ ff_list, int ntile,
+                                         int t0, unsigned* ticket, int reach)
 {
     constexpr int RW = FF_REGION;
     static_assert(RW * RW <= NODES, "a tile with its margin");
@@ -1560,23 +1672,16 @@ __device__ __forceinline__ void fit_tiles(FitLds<T, NODES, LN, REC>& s, const Gr
         const int t = k == (int)blockIdx.x ? t0 : ff_list[k];
         const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
         const FitRegion R{x0 - S, y0 - S, rw, rw, x0, y0, FF_TILE, FF_TILE, 2};
-        fit_region<T, NT, NODES, LN, LC == FF_LAYERS ? RW : 0>(s, g, W, D, L, R, tag, phin, X1,
-                                                               Y1, reach);
+        fit_region<T, NT, NODES, LN, LC == FF_LAYERS ? RW : 0, FIT_TILE>(
+            s, g, W, D, L, R, tag, phin, X1, Y1, health, reach);
         if (threadIdx.x == 0 && s.cut <= L)
             through(&cut_tiles[atomicAdd(ncut, 1)], t | s.cut << FF_CUT_SHIFT);
     }
-    if (!last_arrival(ticket, min(ntile, (int)gridDim.x))) return;
+    static_assert(sizeof(s.rec) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
+    if (!last_arrival(ticket, min(ntile, (int)gridDim.x))) return -1;
     const int nc = seen(ncut);
-    if (nc > 0) {
-        __threadfence();
-        static_assert(sizeof(s.rec) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
-        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.rec, s.cnt);
-    }
-    if (threadIdx.x == 0) {
-        *ncut = 0;
-        *ff_n = 0;
-        *wide = nc;
-    }
+    if (nc > 0) __threadfence();
+    return nc;
 }
 
 template <typename T, int NT, int LC, typename REC = uint4>
@@ -1594,14 +1699,24 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     const Rect W = window_of(win, wcur, g);
     const Rect D = window_of(win, wprev, g);
     if ((int)blockIdx.x >= ntile || !W.ok) return;
-    fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut, ff_list, ntile,
-                         t0, ff_n, ticket, wide, reach);
+    const int nc = fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut,
+                                        ff_list, ntile, t0, ticket, reach);
+    if (nc < 0) return;
+    if (nc > 0)
+        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.rec, s.cnt);
+    if (threadIdx.x == 0) {
+        *ncut = 0;
+        *ff_n = 0;
+        *wide = nc;
+    }
 }
 
 // Several solids: solid row y (ord[y], the largest first).  A solid whose
-// window (dilated by 2) fits one block's copy is one block's, unless tiles is
-// set (few solids: whole-solid blocks would leave most of the chip idle);
-// any other's listed tiles are shared by the row's blocks.
+// window fits one block's copy is one block's, unless tiles is set (few
+// solids: whole-solid blocks would leave most of the chip idle); any other's
+// listed tiles are shared by the row's blocks.  Of the tiles that their copies
+// cannot serve, the last block finishes the whole solid where it can, which
+// the layers on the maps take longer than.
 template <typename T, int LC>
 __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restrict__ args,
                                                         const int* __restrict__ ord, int tiles)
@@ -1613,32 +1728,34 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
     const Rect W = window_of(a.win, a.wcur, g);
     const Rect D = window_of(a.win, a.wprev, g);
     if (!W.ok) return;
-    const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
     const int ntile = *a.ff_n;
-    if (!tiles && (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
-        !(g.py && h + 4 > g.ny)) {
+    const bool whole = fits_whole(g, W);
+    const int* cut_tiles = nullptr;  // the tiles left to the maps, and from which layer
+    int nc = 0, l0 = 0;
+    if (whole && !tiles) {
         if (blockIdx.x != 0) return;
-        const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
-        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0>(s, g, W, D, g.layers, R, a.tag,
-                                                           (const T*)a.phin, (T*)a.X1,
-                                                           (T*)a.Y1, 2);
-        const int l0 = s.cut;
-        if (l0 <= g.layers) {
-            // the layers that the copy cannot serve
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            __threadfence();
-            const int nt = ((w + FF_TILE - 1) / FF_TILE) * ((h + FF_TILE - 1) / FF_TILE);
-            fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
-                            nullptr, nt, l0, (int*)s.rec, s.cnt);
-        }
-        if (threadIdx.x == 0) *a.ff_n = 0;
-        return;
+        nc = 1;
+    } else {
+        if ((int)blockIdx.x >= ntile) return;
+        nc = fit_tiles<T, NT, LC>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1,
+                                  a.health, a.cut_tiles, a.ncut, a.ff_list, ntile,
+                                  a.ff_list[blockIdx.x], a.ticket, 2);
+        if (nc < 0) return;
+        cut_tiles = a.cut_tiles;
     }
-    if ((int)blockIdx.x >= ntile) return;
-    fit_tiles<T, NT, LC>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
-                        a.cut_tiles, a.ncut, a.ff_list, ntile, a.ff_list[blockIdx.x], a.ff_n,
-                        a.ticket, a.ff_wide, 2);
+    if (__builtin_expect(nc > 0 && whole, 0)) {
+        l0 = fit_whole<T, NT>(s, g, W, D, a, tiles != 0);
+        cut_tiles = nullptr;
+        nc = l0 > g.layers ? 0
+                           : ((W.i1 - W.i0 + FF_TILE) / FF_TILE) * ((W.j1 - W.j0 + FF_TILE) / FF_TILE);
+    }
+    if (nc > 0)
+        fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, cut_tiles,
+                        nc, l0, (int*)s.rec, s.cnt);
+    if (threadIdx.x == 0) {
+        *a.ncut = 0;
+        *a.ff_n = 0;
+    }
 }
 
 template <typename T, int NT, int LC>

@@ -42,6 +42,8 @@ constexpr int FF_REGION = FF_TILE + 4 * (FF_LAYERS - 1) + 4;
 // whole solid: up to 220 for a disc that fits the copy)
 constexpr int FF_LAYER = 192;
 constexpr int FF_LAYER_MB = 224;
+// most targets that a whole solid's copy searches in wider scan windows
+constexpr int FF_WIDE = 512;
 // fused extrapolation: threads of a block (two halves of 128 targets a pass;
 // up to 256 registers a lane, where 1024 threads would leave 128 and spill)
 constexpr int FF_THREADS = 512;
