@@ -1592,48 +1592,88 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
 // a stopped tile at or after the layer where that tile stopped (found by the
 // tile's tags; full scan windows up to r_max, the per-layer path's fit).
 // cut_tiles null: every tile of the window (nc of them), from layer cut_all.
-// lst: FF_TILE^2 entries of LDS, cn one
+// The tiles' tags are read twice, to count each layer's targets and to list
+// them, for as many layers at a time as the list has room for (lst, room: LDS;
+// a layer of its own larger than that goes by shares of the tiles).  (Two solids
+// of 200 x 2.4 nodes, us/step FP64 with each tile's tags read in each layer 378,
+// so 223; FP32 347, 202.)
 template <typename T, int NT>
 __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* tag,
                          const T* __restrict__ phin, T* X1, T* Y1, unsigned* health,
-                         const int* cut_tiles, int nc, int cut_all, int* lst, int* cn)
+                         const int* cut_tiles, int nc, int cut_all, int* lst, int room)
 {
-    constexpr int NG = NT / FIT_LANES;
+    constexpr int NG = NT / FIT_LANES, TN = FF_TILE * FF_TILE, U = 4;
+    __shared__ int cnt[FF_LAYERS + 1], at[FF_LAYERS + 1];
     const int sub = threadIdx.x % FIT_LANES, grp = threadIdx.x / FIT_LANES;
     const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
-    for (int l = 1; l <= g.layers; l++) {
-        for (int c = 0; c < nc; c++) {
-            const int ct = cut_tiles ? cut_tiles[c] : c | cut_all << FF_CUT_SHIFT;
-            const int t = ct & FF_CUT_TILE;
-            if (ct >> FF_CUT_SHIFT > l) continue;
-            const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
-            if (threadIdx.x == 0) *cn = 0;
-            __syncthreads();
-            for (int e = threadIdx.x; e < FF_TILE * FF_TILE; e += NT) {
-                const int x = x0 + e % FF_TILE, y = y0 + e / FF_TILE;
-                const int kt = (int)pidx(g, min(x, W.i1), min(y, W.j1));
-                if (tag[kt] == l && W.has(x, y)) lst[atomicAdd(cn, 1)] = kt;
+    // f(layer, node) of the targets of layers la .. lb in tiles c0 .. c1 - 1
+    auto targets = [&](int c0, int c1, int la, int lb, auto f) {
+        for (int e0 = c0 * TN + threadIdx.x; e0 < c1 * TN; e0 += NT * U) {
+            int kt[U], tv[U], ct[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int e = min(e0 + u * NT, c1 * TN - 1), c = e / TN, o = e % TN;
+                ct[u] = cut_tiles ? cut_tiles[c] : c | cut_all << FF_CUT_SHIFT;
+                const int t = ct[u] & FF_CUT_TILE;
+                const int x = W.i0 + (t % ntx) * FF_TILE + o % FF_TILE;
+                const int y = W.j0 + (t / ntx) * FF_TILE + o / FF_TILE;
+                kt[u] = (int)pidx(g, min(x, W.i1), min(y, W.j1));
+                tv[u] = tag[kt[u]];
+                if (e0 + u * NT >= c1 * TN || !W.has(x, y)) tv[u] = TAG_NONE;
             }
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                if (tv[u] >= la && tv[u] <= lb && tv[u] >= ct[u] >> FF_CUT_SHIFT) f(tv[u], kt[u]);
+        }
+    };
+    for (int la = 1; la <= g.layers;) {
+        __syncthreads();
+        if (threadIdx.x <= FF_LAYERS) cnt[threadIdx.x] = 0;
+        __syncthreads();
+        targets(0, nc, la, g.layers, [&](int l, int) { atomicAdd(&cnt[l], 1); });
+        __syncthreads();
+        int lb = la, n = cnt[la];  // (the same in every thread)
+        while (lb < g.layers && n + cnt[lb + 1] <= room) n += cnt[++lb];
+        // tiles at a time: all, or (one layer, beyond the room) what surely fits
+        const int step = n <= room ? nc : room / TN;
+        for (int c0 = 0; c0 < nc; c0 += step) {
+            const int c1 = min(nc, c0 + step);
             __syncthreads();
-            const int n = *cn;
-            for (int a = grp; a < n; a += NG) {
-                const int kt = lst[a];
-                const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
-                T xo = T(0), yo = T(0);
-                const bool done =
-                    fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin, X1, Y1, xo, yo);
-                if (sub == 0) {
-                    if (done) {
-                        X1[kt] = xo;
-                        Y1[kt] = yo;
-                    } else {
-                        tag[kt] = (int8_t)(l | TAG_FAIL);
-                        atomicAdd(&health[1], 1u);
-                    }
+            if (threadIdx.x == 0) {
+                int o = 0;
+                for (int l = la; l <= lb; l++) {
+                    at[l] = o;
+                    o += cnt[l];
                 }
             }
             __syncthreads();
+            // (at[l] runs to the end of layer l's entries)
+            targets(c0, c1, la, lb, [&](int l, int kt) { lst[atomicAdd(&at[l], 1)] = kt; });
+            __syncthreads();
+            int from = 0;
+            for (int l = la; l <= lb; l++) {
+                const int end = at[l];
+                for (int a = from + grp; a < end; a += NG) {
+                    const int kt = lst[a];
+                    const int i = kt % g.pp - PAD, j = kt / g.pp - PAD;
+                    T xo = T(0), yo = T(0);
+                    const bool done =
+                        fit_target<T, true>(g, W, D, l, kt, i, j, sub, tag, phin, X1, Y1, xo, yo);
+                    if (sub == 0) {
+                        if (done) {
+                            X1[kt] = xo;
+                            Y1[kt] = yo;
+                        } else {
+                            tag[kt] = (int8_t)(l | TAG_FAIL);
+                            atomicAdd(&health[1], 1u);
+                        }
+                    }
+                }
+                from = end;
+                __syncthreads();
+            }
         }
+        la = lb + 1;
     }
 }
 
@@ -1677,7 +1717,7 @@ __device__ __forceinline__ int fit_tiles(FitLds<T, NODES, LN, REC>& s, const Gri
         if (threadIdx.x == 0 && s.cut <= L)
             through(&cut_tiles[atomicAdd(ncut, 1)], t | s.cut << FF_CUT_SHIFT);
     }
-    static_assert(sizeof(s.rec) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
+    static_assert(sizeof(s.val) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
     if (!last_arrival(ticket, min(ntile, (int)gridDim.x))) return -1;
     const int nc = seen(ncut);
     if (nc > 0) __threadfence();
@@ -1702,8 +1742,11 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     const int nc = fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut,
                                         ff_list, ntile, t0, ticket, reach);
     if (nc < 0) return;
-    if (nc > 0)
-        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.rec, s.cnt);
+    // (told unlikely, it costs a launch without such tiles nothing; else 0.3 us at
+    // 256^2 FP32)
+    if (__builtin_expect(nc > 0, 0))
+        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.val,
+                        (int)(sizeof(s.val) / sizeof(int)));
     if (threadIdx.x == 0) {
         *ncut = 0;
         *ff_n = 0;
@@ -1749,9 +1792,9 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
         nc = l0 > g.layers ? 0
                            : ((W.i1 - W.i0 + FF_TILE) / FF_TILE) * ((W.j1 - W.j0 + FF_TILE) / FF_TILE);
     }
-    if (nc > 0)
+    if (__builtin_expect(nc > 0, 0))
         fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, cut_tiles,
-                        nc, l0, (int*)s.rec, s.cnt);
+                        nc, l0, (int*)s.val, (int)(sizeof(s.val) / sizeof(int)));
     if (threadIdx.x == 0) {
         *a.ncut = 0;
         *a.ff_n = 0;
