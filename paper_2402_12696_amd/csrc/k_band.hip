@@ -1695,21 +1695,22 @@ __device__ void fit_rest(const GridP& g, const Rect& W, const Rect& D, int8_t* t
 // reach = 2; reach = 1 stops every tile with a target on the rim of its
 // margin, and every tile with more than 64 targets in layers 1 and 2 before
 // its first layer (fit_rest then fits most of the zone: a check of it).
-// Returns the number of listed tiles in the last block, -1 in the others.
+// Block b of nb.  Returns the number of listed tiles in the last block, -1 in
+// the others.
 template <typename T, int NT, int LC, int NODES, int LN, typename REC>
 __device__ __forceinline__ int fit_tiles(FitLds<T, NODES, LN, REC>& s, const GridP& g, const Rect& W,
                                          const Rect& D, int8_t* tag, const T* __restrict__ phin,
                                          T* X1, T* Y1, unsigned* health, int* cut_tiles,
                                          int* ncut, const int* __restrict__ ff_list, int ntile,
-                                         int t0, unsigned* ticket, int reach)
+                                         int t0, unsigned* ticket, int reach, int b, int nb)
 {
     constexpr int RW = FF_REGION;
     static_assert(RW * RW <= NODES, "a tile with its margin");
     const int L = LC > 0 ? LC : g.layers;
     const int S = 2 * (L - 1) + 2, rw = FF_TILE + 2 * S;  // margin of the copy, its width
     const int ntx = (W.i1 - W.i0 + FF_TILE) / FF_TILE;
-    for (int k = blockIdx.x; k < ntile; k += gridDim.x) {
-        const int t = k == (int)blockIdx.x ? t0 : ff_list[k];
+    for (int k = b; k < ntile; k += nb) {
+        const int t = k == b ? t0 : ff_list[k];
         const int x0 = W.i0 + (t % ntx) * FF_TILE, y0 = W.j0 + (t / ntx) * FF_TILE;
         const FitRegion R{x0 - S, y0 - S, rw, rw, x0, y0, FF_TILE, FF_TILE, 2};
         fit_region<T, NT, NODES, LN, LC == FF_LAYERS ? RW : 0, FIT_TILE>(
@@ -1718,7 +1719,7 @@ __device__ __forceinline__ int fit_tiles(FitLds<T, NODES, LN, REC>& s, const Gri
             through(&cut_tiles[atomicAdd(ncut, 1)], t | s.cut << FF_CUT_SHIFT);
     }
     static_assert(sizeof(s.val) >= sizeof(int) * FF_TILE * FF_TILE, "fit_rest's list");
-    if (!last_arrival(ticket, min(ntile, (int)gridDim.x))) return -1;
+    if (!last_arrival(ticket, min(ntile, nb))) return -1;
     const int nc = seen(ncut);
     if (nc > 0) __threadfence();
     return nc;
@@ -1740,7 +1741,8 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     const Rect D = window_of(win, wprev, g);
     if ((int)blockIdx.x >= ntile || !W.ok) return;
     const int nc = fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut,
-                                        ff_list, ntile, t0, ticket, reach);
+                                        ff_list, ntile, t0, ticket, reach, blockIdx.x,
+                                        gridDim.x);
     if (nc < 0) return;
     // (told unlikely, it costs a launch without such tiles nothing; else 0.3 us at
     // 256^2 FP32)
@@ -1762,11 +1764,15 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
 // the layers on the maps take longer than.
 template <typename T, int LC>
 __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restrict__ args,
-                                                        const int* __restrict__ ord, int tiles)
+                                                        const int* __restrict__ ord, MbFit f)
 {
     constexpr int NT = FF_THREADS;
     __shared__ FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB> s;
-    const FitArgs& a = args[ord[blockIdx.y]];
+    // row and block of it
+    const int many = f.rows * f.blocks, id = blockIdx.x;
+    const int row = id < many ? id / f.blocks : f.rows + id - many;
+    const int b = id < many ? id % f.blocks : 0, nb = id < many ? f.blocks : 1;
+    const FitArgs& a = args[ord[row]];
     const GridP& g = a.g;
     const Rect W = window_of(a.win, a.wcur, g);
     const Rect D = window_of(a.win, a.wprev, g);
@@ -1775,19 +1781,19 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
     const bool whole = fits_whole(g, W);
     const int* cut_tiles = nullptr;  // the tiles left to the maps, and from which layer
     int nc = 0, l0 = 0;
-    if (whole && !tiles) {
-        if (blockIdx.x != 0) return;
+    if (whole && !f.tiles) {
+        if (b != 0) return;
         nc = 1;
     } else {
-        if ((int)blockIdx.x >= ntile) return;
+        if (b >= ntile) return;
         nc = fit_tiles<T, NT, LC>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1,
                                   a.health, a.cut_tiles, a.ncut, a.ff_list, ntile,
-                                  a.ff_list[blockIdx.x], a.ticket, 2);
+                                  a.ff_list[b], a.ticket, 2, b, nb);
         if (nc < 0) return;
         cut_tiles = a.cut_tiles;
     }
     if (__builtin_expect(nc > 0 && whole, 0)) {
-        l0 = fit_whole<T, NT>(s, g, W, D, a, tiles != 0);
+        l0 = fit_whole<T, NT>(s, g, W, D, a, f.tiles != 0);
         cut_tiles = nullptr;
         nc = l0 > g.layers ? 0
                            : ((W.i1 - W.i0 + FF_TILE) / FF_TILE) * ((W.j1 - W.j0 + FF_TILE) / FF_TILE);
@@ -2886,6 +2892,8 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
     // the reference-map chain of every member of a batch, or (mb) of every
     // solid of a context, which relabels and marks only
     const dim3 gb(band_blocks, nsim), gd(dt_blocks, nsim), gf(fit_blocks, nsim);
+    const MbFit mf = mb ? mb->fit : MbFit{};
+    const int gm = mf.rows * mf.blocks + nsim - mf.rows;  // blocks of kb_fit_mb
     const long long* dstep = mb ? mb->dstep : nullptr;
     long long* dcur = mb ? mb->dcur : nullptr;
 #define ADB(T, LC, TH) kb_advect_dt<LC, TH, T><<<gd, 256, 0, st>>>(t.adv, t.ord, dstep, dcur)
@@ -2897,8 +2905,8 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
     do {                                                                                       \
         if (fused && mb) {                                                                     \
             if (layers == FF_LAYERS)                                                           \
-                kb_fit_mb<T, FF_LAYERS><<<gf, FF_THREADS, 0, st>>>(t.fit, t.ord, mb->tiles);   \
-            else kb_fit_mb<T, 0><<<gf, FF_THREADS, 0, st>>>(t.fit, t.ord, mb->tiles);          \
+                kb_fit_mb<T, FF_LAYERS><<<gm, FF_THREADS, 0, st>>>(t.fit, t.ord, mf);          \
+            else kb_fit_mb<T, 0><<<gm, FF_THREADS, 0, st>>>(t.fit, t.ord, mf);                 \
         } else if (fused) {                                                                    \
             if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit); \
             else kb_fit_fused<T, 0><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit);                    \

@@ -365,24 +365,34 @@ static MbTabs mb_tabs(const lbrmt_ctx* c)
 // block per solid, with more for the tiles of solids whose window is not one
 // block's.  (MI355X: a block takes a tile in about 20 us, a small solid of a
 // suspension in about 45.)
-struct MbFit {
-    int tiles, blocks;
-};
+// The rows of large solids come first in the solids' order (mb_tables); the
+// others get one block each, as blocks without work still take a unit's LDS for
+// some us (60 discs of R 22 with 3 of R 38, FP32, us/step with 16 blocks to every
+// row 204, so 111).
+static long long mb_side(const lbrmt_ctx* c, const MbBody& m)
+{
+    const double ext = m.b.shape == 1 ? std::max(m.b.R, m.b.Rb) : m.b.R;
+    return std::min<long long>(2 * ((long long)std::ceil(ext) + c->d.layers) + 1,
+                               std::max(m.g.nx, m.g.ny) + 2 * PAD);
+}
+static bool mb_large(const lbrmt_ctx* c, const MbBody& m)
+{
+    const long long side = mb_side(c, m);
+    return (side + 4) * (side + 4) > MB_FIT_LDS_NODES;
+}
 static MbFit mb_fit(const lbrmt_ctx* c)
 {
     long long all = 0, most = 1;
-    bool large = false;
+    int large = 0;
     for (const MbBody& m : c->mbh) {
-        const double ext = m.b.shape == 1 ? std::max(m.b.R, m.b.Rb) : m.b.R;
-        const long long side = std::min<long long>(
-            2 * ((long long)std::ceil(ext) + c->d.layers) + 1, std::max(m.g.nx, m.g.ny) + 2 * PAD);
-        const long long t = (side + FF_TILE - 1) / FF_TILE;
+        const long long t = (mb_side(c, m) + FF_TILE - 1) / FF_TILE;
         all += t * t;
         most = std::max(most, t * t);
-        large = large || (side + 4) * (side + 4) > MB_FIT_LDS_NODES;
+        large += mb_large(c, m) ? 1 : 0;
     }
     const bool tiles = all <= MB_FIT_TILES;
-    return MbFit{tiles ? 1 : 0, (int)std::min<long long>(tiles || large ? most : 1, FF_BLOCKS)};
+    return MbFit{tiles ? 1 : 0, (int)std::min<long long>(most, FF_BLOCKS),
+                 tiles ? c->nsolid : large};
 }
 
 // several solids, step n on stream st: the chain of every solid (relabel
@@ -403,9 +413,9 @@ static int enqueue_step_mb(lbrmt_ctx* c, long long n, hipStream_t st)
         const MbFit f = mb_fit(c);
         const MbStep mb{MbMark{c->g, c->mbd, s.wcur, s.wnext, c->stamp[s.cur], c->mlist[s.cur],
                                &c->mcount[s.cur], c->L.nbx, 0, c->dcur},
-                        f.tiles, c->dstep, c->dcur};
-        HIPCHK(c, launch_batch_band(prec, c->mtab[p], nb, c->d.layers, st, mb_dt_blocks(nb),
-                                    f.blocks, mb_band_blocks(nb), fused, &mb));
+                        f, c->dstep, c->dcur};
+        HIPCHK(c, launch_batch_band(prec, c->mtab[p], nb, c->d.layers, st, mb_dt_blocks(nb), 1,
+                                    mb_band_blocks(nb), fused, &mb));
         HIPCHK(c, launch_mb_combine(c->g, prec, c->mbd, nb, s.nxt, s.wcur, c->mlist[s.cur],
                                     &c->mcount[s.cur], &c->mcount[s.nxt], c->L.nbx,
                                     c->Fx[s.cur], c->Fy[s.cur], c->drho, false, c->bb.health,
@@ -997,14 +1007,15 @@ static int mb_tables(lbrmt_ctx* c)
     // the advection and extrapolation passes (a group of blocks, or one
     // block, per solid; more than the GPU holds at once) start the largest
     // solids first, so that the last blocks to start are the shortest: their
-    // block rows take the solids by decreasing semi-axis sum (each solid's
-    // work is its own, so the order changes no result)
+    // block rows take the solids by decreasing semi-axis sum, those that are
+    // large for the fits (mb_fit) ahead of the others (each solid's work is
+    // its own, so the order changes no result)
     std::vector<int> ord(nb);
     const bool fused = fused_fit_ok(c->mbh[0].g);
     for (int k = 0; k < nb; k++) ord[k] = k;
     auto size_of = [&](int k) {
         const BodyP& b = c->mbh[k].b;
-        return b.R + (b.shape == 1 ? b.Rb : b.R);
+        return std::make_pair(mb_large(c, c->mbh[k]), b.R + (b.shape == 1 ? b.Rb : b.R));
     };
     std::stable_sort(ord.begin(), ord.end(),
                      [&](int x, int y) { return size_of(x) > size_of(y); });

@@ -485,10 +485,16 @@ struct MbMark {
     int nbx, sval;
     const long long* dcur;
 };
+// How several solids' layers are shared out: by tiles for every solid, or a
+// block per solid; the first rows of their order get blocks blocks, the others
+// one
+struct MbFit {
+    int tiles, blocks, rows;
+};
 // a step's chain over several solids
 struct MbStep {
     MbMark mark;
-    int tiles;              // extrapolation by tiles for every solid
+    MbFit fit;
     const long long* dstep; // the step counter, copied to dcur by the first pass
     long long* dcur;
 };
