@@ -45,6 +45,8 @@ CASES = {
         dict(cx=35.0, cy=30.0 + 50.0 * k, R=27.5, G=0.005, rho_s=1.0, shape="ellipse", b=1.1,
              theta=0.05) for k in range(2)]),
     "more layers than one launch": _many(5, layers=13),
+    "twenty layers, round": _many(5, R=12.0, b=12.0, layers=20),
+    "thirteen layers, r_max 2": _many(5, R=15.0, layers=13, r_max=2),
 }
 
 
