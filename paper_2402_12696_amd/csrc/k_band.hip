@@ -1183,7 +1183,6 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
                                            unsigned* health, int reach)
 {
     constexpr bool WIDE = MODE == FIT_WIDE;
-    static_assert(!WIDE || sizeof(REC) > 4, "a record without a fit is marked in its determinant");
     using C2 = Win2<T, 8>;
     constexpr int NS = C2::NS;
     constexpr int NIT = (NODES + NT - 1) / NT;  // staged nodes per thread
@@ -1362,8 +1361,9 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
                 m |= s.st[q + C2::off_b(0, k) * rw + C2::off_a(0, k)] < l ? 1u << k : 0u;
         const Geo2 G = geo2(m, g.det_rel);
         if (!G.ok) defer(q, l);
+        // (a record without a fit: no node, or determinant 0)
         if constexpr (sizeof(REC) == 4)
-            s.rec[(l - 3) * LN + e] = m;
+            s.rec[(l - 3) * LN + e] = !WIDE || G.ok ? m : 0u;
         else
             s.rec[(l - 3) * LN + e] =
                 make_uint4(m, (unsigned)(G.m00 | G.m11 << 8 | (G.m01 & 0xff) << 16),
@@ -1453,6 +1453,10 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
         unsigned m;
         if constexpr (sizeof(REC) == 4) {
             m = r;
+            if (WIDE && m == 0) {
+                pq = -1;
+                return;
+            }
             pg = geo2(m, g.det_rel);
         } else {
             m = r.x;
@@ -1530,10 +1534,10 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
 
 // Can a block's copy hold a whole window (dilated by 2; no two of its nodes
 // images of one node)?
-__device__ __forceinline__ bool fits_whole(const GridP& g, const Rect& W)
+__device__ __forceinline__ bool fits_whole(const GridP& g, const Rect& W, int nodes)
 {
     const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
-    return (long long)(w + 4) * (h + 4) <= MB_FIT_LDS_NODES && !(g.px && w + 4 > g.nx) &&
+    return (long long)(w + 4) * (h + 4) <= nodes && !(g.px && w + 4 > g.nx) &&
            !(g.py && h + 4 > g.ny);
 }
 
@@ -1542,20 +1546,19 @@ __device__ __forceinline__ bool fits_whole(const GridP& g, const Rect& W)
 // holds.  Returns the first layer that the copy did not serve (the block sees
 // what it wrote of the others).  wide: there are targets without a fit at
 // half-width 2.
-template <typename T, int NT>
-__device__ __forceinline__ int fit_whole(FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB>& s,
-                                         const GridP& g, const Rect& W, const Rect& D,
-                                         const FitArgs& a, bool wide)
+template <typename T, int NT, int NODES, int LN, typename REC>
+__device__ __forceinline__ int fit_whole(FitLds<T, NODES, LN, REC>& s, const GridP& g,
+                                         const Rect& W, const Rect& D, int8_t* tag,
+                                         const T* __restrict__ phin, T* X1, T* Y1,
+                                         unsigned* health, bool wide)
 {
     const int w = W.i1 - W.i0 + 1, h = W.j1 - W.j0 + 1;
     const FitRegion R{W.i0 - 2, W.j0 - 2, w + 4, h + 4, W.i0, W.j0, w, h, 0};
     const int L = min(g.layers, FF_LAYERS);
     if (!wide)
-        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0, FIT_WHOLE>(
-            s, g, W, D, L, R, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, 2);
+        fit_region<T, NT, NODES, LN, 0, FIT_WHOLE>(s, g, W, D, L, R, tag, phin, X1, Y1, health, 2);
     if (wide || s.cut <= L)
-        fit_region<T, NT, MB_FIT_LDS_NODES, FF_LAYER_MB, 0, FIT_WIDE>(
-            s, g, W, D, L, R, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, 2);
+        fit_region<T, NT, NODES, LN, 0, FIT_WIDE>(s, g, W, D, L, R, tag, phin, X1, Y1, health, 2);
     const int l0 = s.cut;
     if (l0 <= g.layers) {
         // (the copy's results went through the caches)
@@ -1582,7 +1585,10 @@ __global__ __launch_bounds__(NT) void kb_fit_lds(const FitArgs* __restrict__ arg
     const Rect W = window_of(a.win, a.wcur, g);
     const Rect D = window_of(a.win, a.wprev, g);
     if (!W.ok) return;
-    const int l0 = fits_whole(g, W) ? fit_whole<T, NT>(s, g, W, D, a, false) : 1;
+    int l0 = 1;
+    if (fits_whole(g, W, MB_FIT_LDS_NODES))
+        l0 = fit_whole<T, NT>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
+                              false);
     for (int l = l0; l <= layers; l++) {
         layer_fit_body<T, true>(g, a.win, a.wcur, a.wprev, l, a.tag, a.lists, a.lcount,
                                 (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health);
@@ -1728,7 +1734,22 @@ __device__ __forceinline__ int fit_tiles(FitLds<T, NODES, LN, REC>& s, const Gri
     return nc;
 }
 
-template <typename T, int NT, int LC, typename REC = uint4>
+// The tiles left to the maps when fit_whole has returned l0: none, every tile of
+// the window from that layer on, or, where it served no layer, the listed ones.
+__device__ __forceinline__ int left_tiles(const GridP& g, const Rect& W, int l0, int nc,
+                                          const int*& cut_tiles)
+{
+    if (l0 > g.layers) return 0;
+    if (l0 == 1 && cut_tiles) return nc;
+    cut_tiles = nullptr;
+    return ((W.i1 - W.i0 + FF_TILE) / FF_TILE) * ((W.j1 - W.j0 + FF_TILE) / FF_TILE);
+}
+
+// WHOLE: of the tiles that their copies cannot serve, the last block finishes
+// the whole solid where its copy holds the window, which takes less than the
+// layers on the maps (8 members of 64^2, thin, us/step FP64 113 -> 77, FP32 135 ->
+// 91; 32 of 128^2 190 -> 161, 215 -> 171).
+template <typename T, int NT, int LC, bool WHOLE, typename REC = uint4>
 __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __restrict__ win,
                                                int wcur, int wprev, int8_t* tag,
                                                const T* __restrict__ phin, T* X1, T* Y1,
@@ -1736,26 +1757,32 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
                                                const int* __restrict__ ff_list, int* ff_n,
                                                unsigned* ticket, int* wide, int reach)
 {
-    __shared__ FitLds<T, FF_REGION * FF_REGION, FF_LAYER, REC> s;
+    __shared__ FitLds<T, FF_REGION * FF_REGION, WHOLE ? FF_LAYER_BATCH : FF_LAYER, REC> s;
     // (the first tile is read together with the count; a block beyond the
     // list's room reads its last entry, and leaves)
     const int ntile = *ff_n, t0 = ff_list[ff_first(blockIdx.x, g.nx, g.ny)];
     const Rect W = window_of(win, wcur, g);
     const Rect D = window_of(win, wprev, g);
     if ((int)blockIdx.x >= ntile || !W.ok) return;
-    const int nc = fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut,
-                                        ff_list, ntile, t0, ticket, reach, blockIdx.x,
-                                        gridDim.x);
+    int nc = fit_tiles<T, NT, LC>(s, g, W, D, tag, phin, X1, Y1, health, cut_tiles, ncut, ff_list,
+                                  ntile, t0, ticket, reach, blockIdx.x, gridDim.x);
     if (nc < 0) return;
+    const int cut = nc;
+    const int* left = cut_tiles;
+    int l0 = 0;
+    if (WHOLE && __builtin_expect(nc > 0 && fits_whole(g, W, FF_REGION * FF_REGION), 0)) {
+        l0 = fit_whole<T, NT>(s, g, W, D, tag, phin, X1, Y1, health, true);
+        nc = left_tiles(g, W, l0, nc, left);
+    }
     // (told unlikely, it costs a launch without such tiles nothing; else 0.3 us at
     // 256^2 FP32)
     if (__builtin_expect(nc > 0, 0))
-        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, cut_tiles, nc, 0, (int*)s.val,
+        fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, left, nc, l0, (int*)s.val,
                         (int)(sizeof(s.val) / sizeof(int)));
     if (threadIdx.x == 0) {
         *ncut = 0;
         *ff_n = 0;
-        *wide = nc;
+        *wide = cut;
     }
 }
 
@@ -1781,7 +1808,7 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
     const Rect D = window_of(a.win, a.wprev, g);
     if (!W.ok) return;
     const int ntile = *a.ff_n;
-    const bool whole = fits_whole(g, W);
+    const bool whole = fits_whole(g, W, MB_FIT_LDS_NODES);
     const int* cut_tiles = nullptr;  // the tiles left to the maps, and from which layer
     int nc = 0, l0 = 0;
     if (whole && !f.tiles) {
@@ -1796,10 +1823,9 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
         cut_tiles = a.cut_tiles;
     }
     if (__builtin_expect(nc > 0 && whole, 0)) {
-        l0 = fit_whole<T, NT>(s, g, W, D, a, f.tiles != 0);
-        cut_tiles = nullptr;
-        nc = l0 > g.layers ? 0
-                           : ((W.i1 - W.i0 + FF_TILE) / FF_TILE) * ((W.j1 - W.j0 + FF_TILE) / FF_TILE);
+        l0 = fit_whole<T, NT>(s, g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
+                              f.tiles != 0);
+        nc = left_tiles(g, W, l0, nc, cut_tiles);
     }
     if (__builtin_expect(nc > 0, 0))
         fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, cut_tiles,
@@ -1819,7 +1845,7 @@ __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict
                                                   unsigned* ticket, int* wide, int reach)
 {
     __builtin_amdgcn_s_setprio(3);
-    fit_fused_body<T, NT, LC>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_tiles, ncut,
+    fit_fused_body<T, NT, LC, false>(g, win, wcur, wprev, tag, phin, X1, Y1, health, cut_tiles, ncut,
                               ff_list, ff_n, ticket, wide, reach);
 }
 
@@ -1839,7 +1865,7 @@ template <typename T, int LC>
 __global__ __launch_bounds__(BatchFit<T>::NT) void kb_fit_fused(const FitArgs* __restrict__ args)
 {
     const FitArgs& a = args[blockIdx.y];
-    fit_fused_body<T, BatchFit<T>::NT, LC, typename BatchFit<T>::Rec>(
+    fit_fused_body<T, BatchFit<T>::NT, LC, true, typename BatchFit<T>::Rec>(
         a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
         a.cut_tiles, a.ncut, a.ff_list, a.ff_n, a.ticket, a.ff_wide, 2);
 }

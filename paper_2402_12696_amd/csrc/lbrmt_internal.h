@@ -39,8 +39,10 @@ constexpr int FF_CUT_SHIFT = 26, FF_CUT_TILE = (1 << FF_CUT_SHIFT) - 1;
 // side of a tile with its margin (2 (FF_LAYERS - 1) + 2 nodes around it)
 constexpr int FF_REGION = FF_TILE + 4 * (FF_LAYERS - 1) + 4;
 // most targets of a layer in a block's copy (a tile: typically 50 to 90; a
-// whole solid: up to 220 for a disc that fits the copy)
+// whole solid: up to 220 for a disc that fits the copy of several solids, up to
+// twice its length for a thin solid)
 constexpr int FF_LAYER = 192;
+constexpr int FF_LAYER_BATCH = 320;
 constexpr int FF_LAYER_MB = 224;
 // most targets that a whole solid's copy searches in wider scan windows
 constexpr int FF_WIDE = 512;

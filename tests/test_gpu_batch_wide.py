@@ -1,0 +1,46 @@
+"""Batch members whose fits need wide scan windows, or fail for good: finished on
+the block's copy of the whole window, on windows the copy does not hold, with
+more targets in a layer than it has room for, beside members without any.
+Against each member alone with one launch per layer: the same bits, and as many
+fits that fail."""
+import pytest
+
+import workloads
+from test_gpu_fused_fit import _equal, _state
+
+pytestmark = pytest.mark.gpu
+
+
+def _cfg(nx, ny, R, b=None, theta=0.3, **kw):
+    shape = {} if b is None else dict(shape="ellipse", b=b, theta=theta)
+    return workloads.make(nx=nx, ny=ny, tau=0.8, lid_ux=0.05,
+                          solid=dict(cx=0.48 * nx, cy=0.55 * ny, R=R, G=0.01, rho_s=1.2, **shape),
+                          **kw)
+
+
+BATCHES = {
+    "thin": [_cfg(64, 64, 20.0, 1.0), _cfg(128, 128, 40.0, 1.2), _cfg(96, 80, 14.0),
+             _cfg(90, 64, 30.0, 0.8, 0.02, periodic_x=True)],
+    "beyond the copy": [_cfg(260, 200, 90.0, 1.2), _cfg(200, 64, 90.0, 1.0, 0.05),
+                        _cfg(64, 64, 12.0)],
+    "fits that fail": [_cfg(96, 80, 30.0, 0.9, r_max=2), _cfg(70, 64, 20.0, 0.45, r_max=3)],
+    "five layers": [_cfg(96, 80, 30.0, 0.9, layers=5), _cfg(64, 64, 12.0, layers=5)],
+}
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("name", BATCHES)
+def test_members_are_bitwise_the_per_layer_path(name, prec):
+    from paper_2402_12696_amd import Batch, Sim, lbrmt as B
+    cfgs = BATCHES[name]
+    b = Batch(cfgs, precision=prec, device="cuda:0")
+    b.init()
+    b.step(20)
+    for k, c in enumerate(cfgs):
+        one = Sim(device="cuda:0", precision=prec, **c)
+        one.set_option(B.LBRMT_OPT_FUSED_FIT, 0)
+        one.init()
+        one.step(20)
+        assert _equal(_state(b.member(k)), _state(one)), (name, k)
+        one.close()
+    b.close()
