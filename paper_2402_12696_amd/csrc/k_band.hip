@@ -1778,7 +1778,7 @@ __device__ __forceinline__ void fit_fused_body(const GridP& g, const Win* __rest
     // 256^2 FP32)
     if (__builtin_expect(nc > 0, 0))
         fit_rest<T, NT>(g, W, D, tag, phin, X1, Y1, health, left, nc, l0, (int*)s.val,
-                        (int)(sizeof(s.val) / sizeof(int)));
+                        (int)(sizeof(s.val) / (sizeof(int))));
     if (threadIdx.x == 0) {
         *ncut = 0;
         *ff_n = 0;
@@ -1829,7 +1829,7 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
     }
     if (__builtin_expect(nc > 0, 0))
         fit_rest<T, NT>(g, W, D, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health, cut_tiles,
-                        nc, l0, (int*)s.val, (int)(sizeof(s.val) / sizeof(int)));
+                        nc, l0, (int*)s.val, (int)(sizeof(s.val) / (sizeof(int))));
     if (threadIdx.x == 0) {
         *a.ncut = 0;
         *a.ff_n = 0;
@@ -1849,23 +1849,23 @@ __global__ __launch_bounds__(NT) void k_fit_fused(GridP g, const Win* __restrict
                               ff_list, ff_n, ticket, wide, reach);
 }
 
-// A batch: member blockIdx.y.  Its tiles are many rounds of blocks, and a
-// block is bound by its chain of layers: in FP32 two blocks of 256 threads
-// share a compute unit, their records short enough (masks alone, the matrices
-// counted again) for both copies to fit (96 cavities of 96^2 .. 768^2, 2900
-// tiles: 234 -> 168 us; one block a solid of a suspension, 400 of them, is
-// little more than a round, and slower two to a unit: 47 -> 56 us).  FP64
-// copies do not fit twice.
-template <typename T>
+// A batch: member blockIdx.y.  Where its tiles are many rounds of blocks, and a
+// block is bound by its chain of layers, two blocks of 256 threads share a
+// compute unit in FP32 (PAIRS), their records short enough (masks alone, the
+// matrices counted again) for both copies to fit (96 cavities of 96^2 .. 768^2,
+// 2900 tiles: 234 -> 168 us; one block a solid of a suspension, 400 of them, is
+// little more than a round, and slower two to a unit: 47 -> 56 us; the line lies
+// at BATCH_FIT_TILES).  FP64 copies do not fit twice.
+template <bool PAIRS>
 struct BatchFit {
-    static constexpr int NT = sizeof(T) == 4 ? 256 : FF_THREADS;
-    using Rec = typename std::conditional<sizeof(T) == 4, unsigned, uint4>::type;
+    static constexpr int NT = PAIRS ? 256 : FF_THREADS;
+    using Rec = typename std::conditional<PAIRS, unsigned, uint4>::type;
 };
-template <typename T, int LC>
-__global__ __launch_bounds__(BatchFit<T>::NT) void kb_fit_fused(const FitArgs* __restrict__ args)
+template <typename T, int LC, bool PAIRS>
+__global__ __launch_bounds__(BatchFit<PAIRS>::NT) void kb_fit_fused(const FitArgs* __restrict__ args)
 {
     const FitArgs& a = args[blockIdx.y];
-    fit_fused_body<T, BatchFit<T>::NT, LC, true, typename BatchFit<T>::Rec>(
+    fit_fused_body<T, BatchFit<PAIRS>::NT, LC, true, typename BatchFit<PAIRS>::Rec>(
         a.g, a.win, a.wcur, a.wprev, a.tag, (const T*)a.phin, (T*)a.X1, (T*)a.Y1, a.health,
         a.cut_tiles, a.ncut, a.ff_list, a.ff_n, a.ticket, a.ff_wide, 2);
 }
@@ -2916,7 +2916,7 @@ hipError_t launch_mb_diag(int precision, const MbBody* bodies, int nb, int buf, 
 
 hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int layers,
                              hipStream_t st, int dt_blocks, int fit_blocks, int band_blocks,
-                             bool fused, const MbStep* mb)
+                             bool fused, bool pairs, const MbStep* mb)
 {
     // the reference-map chain of every member of a batch, or (mb) of every
     // solid of a context, which relabels and marks only
@@ -2937,8 +2937,15 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
                 kb_fit_mb<T, FF_LAYERS><<<gm, FF_THREADS, 0, st>>>(t.fit, t.ord, mf);          \
             else kb_fit_mb<T, 0><<<gm, FF_THREADS, 0, st>>>(t.fit, t.ord, mf);                 \
         } else if (fused) {                                                                    \
-            if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit); \
-            else kb_fit_fused<T, 0><<<gf, BatchFit<T>::NT, 0, st>>>(t.fit);                    \
+            constexpr bool P = sizeof(T) == 4;                                                 \
+            if (P && pairs) {                                                                  \
+                if (layers == FF_LAYERS) kb_fit_fused<T, FF_LAYERS, P><<<gf, 256, 0, st>>>(t.fit); \
+                else kb_fit_fused<T, 0, P><<<gf, 256, 0, st>>>(t.fit);                         \
+            } else if (layers == FF_LAYERS) {                                                  \
+                kb_fit_fused<T, FF_LAYERS, false><<<gf, FF_THREADS, 0, st>>>(t.fit);           \
+            } else {                                                                           \
+                kb_fit_fused<T, 0, false><<<gf, FF_THREADS, 0, st>>>(t.fit);                   \
+            }                                                                                  \
         } else if (mb) {                                                                       \
             kb_fit_lds<T, MB_NT><<<dim3(1, nsim), MB_NT, 0, st>>>(t.fit, layers, t.ord);       \
         } else {                                                                               \

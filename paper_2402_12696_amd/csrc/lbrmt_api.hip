@@ -369,15 +369,21 @@ static MbTabs mb_tabs(const lbrmt_ctx* c)
 // others get one block each, as blocks without work still take a unit's LDS for
 // some us (60 discs of R 22 with 3 of R 38, FP32, us/step with 16 blocks to every
 // row 204, so 111).
-static long long mb_side(const lbrmt_ctx* c, const MbBody& m)
+// side of the window of solid b however it is turned, and its tiles
+static long long zone_side(const BodyP& b, const GridP& g)
 {
-    const double ext = m.b.shape == 1 ? std::max(m.b.R, m.b.Rb) : m.b.R;
-    return std::min<long long>(2 * ((long long)std::ceil(ext) + c->d.layers) + 1,
-                               std::max(m.g.nx, m.g.ny) + 2 * PAD);
+    const double ext = b.shape == 1 ? std::max(b.R, b.Rb) : b.R;
+    return std::min<long long>(2 * ((long long)std::ceil(ext) + g.layers) + 1,
+                               std::max(g.nx, g.ny) + 2 * PAD);
 }
-static bool mb_large(const lbrmt_ctx* c, const MbBody& m)
+static long long zone_tiles(const BodyP& b, const GridP& g)
 {
-    const long long side = mb_side(c, m);
+    const long long t = (zone_side(b, g) + FF_TILE - 1) / FF_TILE;
+    return t * t;
+}
+static bool mb_large(const MbBody& m)
+{
+    const long long side = zone_side(m.b, m.g);
     return (side + 4) * (side + 4) > MB_FIT_LDS_NODES;
 }
 static MbFit mb_fit(const lbrmt_ctx* c)
@@ -385,10 +391,10 @@ static MbFit mb_fit(const lbrmt_ctx* c)
     long long all = 0, most = 1;
     int large = 0;
     for (const MbBody& m : c->mbh) {
-        const long long t = (mb_side(c, m) + FF_TILE - 1) / FF_TILE;
-        all += t * t;
-        most = std::max(most, t * t);
-        large += mb_large(c, m) ? 1 : 0;
+        const long long t = zone_tiles(m.b, m.g);
+        all += t;
+        most = std::max(most, t);
+        large += mb_large(m) ? 1 : 0;
     }
     const bool tiles = all <= MB_FIT_TILES;
     return MbFit{tiles ? 1 : 0, (int)std::min<long long>(most, FF_BLOCKS),
@@ -415,7 +421,7 @@ static int enqueue_step_mb(lbrmt_ctx* c, long long n, hipStream_t st)
                                &c->mcount[s.cur], c->L.nbx, 0, c->dcur},
                         f, c->dstep, c->dcur};
         HIPCHK(c, launch_batch_band(prec, c->mtab[p], nb, c->d.layers, st, mb_dt_blocks(nb), 1,
-                                    mb_band_blocks(nb), fused, &mb));
+                                    mb_band_blocks(nb), fused, false, &mb));
         HIPCHK(c, launch_mb_combine(c->g, prec, c->mbd, nb, s.nxt, s.wcur, c->mlist[s.cur],
                                     &c->mcount[s.cur], &c->mcount[s.nxt], c->L.nbx,
                                     c->Fx[s.cur], c->Fy[s.cur], c->drho, false, c->bb.health,
@@ -1015,7 +1021,7 @@ static int mb_tables(lbrmt_ctx* c)
     for (int k = 0; k < nb; k++) ord[k] = k;
     auto size_of = [&](int k) {
         const BodyP& b = c->mbh[k].b;
-        return std::make_pair(mb_large(c, c->mbh[k]), b.R + (b.shape == 1 ? b.Rb : b.R));
+        return std::make_pair(mb_large(c->mbh[k]), b.R + (b.shape == 1 ? b.Rb : b.R));
     };
     std::stable_sort(ord.begin(), ord.end(),
                      [&](int x, int y) { return size_of(x) > size_of(y); });
@@ -2244,13 +2250,20 @@ int batch_members(lbrmt_batch* b, long long n, int k0, int k1, int t0, int t1, h
     T.fit += k0;
     T.edg += k0;
     const bool fused = batch_fused(b);
-    // no more blocks than the largest member's grid has tiles
-    long long tiles = 1;
-    for (int k = k0; k < k1; k++)
-        tiles = std::max(tiles, fused_tiles(b->m[k]->d.nx, b->m[k]->d.ny));
-    const int fit = (int)std::min<long long>(tiles, FF_BATCH_BLOCKS);
+    // no more blocks than the largest member's zone has tiles at first (they
+    // stride over the list; blocks without work still take a unit's LDS), and
+    // an odd number, so that the members' blocks of one number, of like work,
+    // are spread over the eight XCDs
+    long long most = 1, all = 0;
+    for (int k = 0; k < b->n; k++) {
+        const long long t = zone_tiles(b->m[k]->body, b->m[k]->g);
+        all += t;
+        if (k >= k0 && k < k1) most = std::max(most, t);
+    }
+    const int fit = (int)std::min<long long>(most, FF_BATCH_BLOCKS) | 1;
     BCHK(b, launch_batch_band(b->precision, T, k1 - k0, b->layers, st, BATCH_DT_BLOCKS,
-                              fused ? fit : BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS, fused));
+                              fused ? fit : BATCH_FIT_BLOCKS, BATCH_BAND_BLOCKS, fused,
+                              all > BATCH_FIT_TILES));
     if (st == b->cap) BCHK(b, hipEventRecord(b->ev_lb, st));  // (captured)
     BCHK(b, launch_lb_batch(b->precision, b->lb_variant, T.lb, b->tile_sim, t0, t1 - t0, st));
     return LBRMT_OK;

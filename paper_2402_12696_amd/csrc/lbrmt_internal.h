@@ -50,6 +50,12 @@ constexpr int FF_WIDE = 512;
 // up to 256 registers a lane, where 1024 threads would leave 128 and spill)
 constexpr int FF_THREADS = 512;
 constexpr int FF_BATCH_BLOCKS = 64;   // fused extrapolation of a batch: blocks per member
+// members of at most this many tiles in all: blocks of FF_THREADS threads in FP32
+// too, which are the faster ones while the tiles are a round or two of blocks
+// (us/step, two blocks of 256 threads on a unit -> one of 512: 16 members of 256^2,
+// 256 tiles, 84 -> 73; 32 of them 111 -> 109; 64 of 128^2, 576 tiles, 124 -> 129;
+// 64 of 256^2 187 -> 202)
+constexpr int BATCH_FIT_TILES = 512;
 
 // Several solids: the lattice is cut into force blocks of FB x FB nodes;
 // a block holds valid force planes at step n when its stamp equals n + 1.
@@ -582,12 +588,13 @@ struct LossCoef {
 
 // lattice Boltzmann (k_lb.hip)
 // blocks per member of the distance transform, of the extrapolation (one
-// layer, or fused: every layer) and of the force kernel; mb: the members are
+// layer, or fused: every layer) and of the force kernel; pairs: in FP32 two
+// smaller fused blocks share a unit (BatchFit); mb: the members are
 // the solids of a context, which relabel and mark only (the forces come from
 // launch_mb_combine)
 hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int layers,
                              hipStream_t st, int dt_blocks, int fit_blocks, int band_blocks,
-                             bool fused, const MbStep* mb = nullptr);
+                             bool fused, bool pairs, const MbStep* mb = nullptr);
 // (the lattice tiles t0 .. t0 + tiles - 1 of the concatenated list)
 hipError_t launch_lb_batch(int precision, int variant, const LbArgs* args, const int* tile_sim,
                            int t0, int tiles, hipStream_t st);
