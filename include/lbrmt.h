@@ -459,11 +459,12 @@ int32_t lbrmt_batch_size(const lbrmt_batch* batch);
  * lbrmt_set_option on it return ESTATE.  Owned by the batch. */
 lbrmt_ctx* lbrmt_batch_member(lbrmt_batch* batch, int32_t k);
 /* LBRMT_OPT_LB_VARIANT (one tile shape for the whole batch),
- * LBRMT_OPT_GRAPH and LBRMT_OPT_FUSED_FIT (-1, default, or 1024: every
- * member's extrapolation layers in one launch, member per grid row, when every
- * member has one solid, at most 11 layers and periodic axes of at least 76
- * nodes, else one launch per layer over all members; 0: one launch per layer;
- * results are bitwise identical); get also reads
+ * LBRMT_OPT_GRAPH and LBRMT_OPT_FUSED_FIT (1024: every member's extrapolation
+ * layers in one launch, member per grid row, when every member has one solid,
+ * at most 11 layers and periodic axes of at least 76 nodes, else one launch per
+ * layer over all members; -1, default: the same, but one launch per layer when
+ * most of the members' zones are those of long thin solids; 0: one launch per
+ * layer; results are bitwise identical); get also reads
  * LBRMT_OPT_LB_VARIANT_COUNT. */
 int lbrmt_batch_set_option(lbrmt_batch* batch, int32_t option, int64_t value);
 int lbrmt_batch_get_option(const lbrmt_batch* batch, int32_t option, int64_t* value);

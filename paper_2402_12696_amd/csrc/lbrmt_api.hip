@@ -2096,8 +2096,8 @@ struct lbrmt_batch {
     int lb_variant = 3;
     long long nodes = 0;  // interior nodes of all members (the autotune key)
     bool graph = true;
-    // 0: one launch per layer; -1 (default) or 1024: one extrapolation launch
-    // if every member can
+    // 0: one launch per layer; 1024: one extrapolation launch if every member
+    // can; -1 (default): as batch_fused finds
     int fused_fit = -1;
     hipGraphExec_t gexec = nullptr;
     hipGraph_t gsrc = nullptr;  // the captured graph of gexec
@@ -2167,15 +2167,32 @@ int bfail(lbrmt_batch* b, const char* what, hipError_t e)
 
 // One extrapolation launch over every member's zone tiles, unless the option
 // asks for one launch per layer, or a member cannot (no solid, more than
-// FF_LAYERS layers, a short periodic axis): 96 cavities in FP32
-// 763 us per step layer by layer, 723 in one launch; 8 cavities in FP64 132
-// and 93
+// FF_LAYERS layers, a short periodic axis): 96 cavities in FP32 763 us per step
+// layer by layer, 629 in one launch; 8 cavities in FP64 113 and 56.
+// Not by default where most of the tiles are of long sharp solids,
+// whose tips need wide scan windows, too large for a block's copy: one block
+// of each member would finish them on the maps (32 members of 256^2, 180 x 2.4
+// nodes, us/step FP64 320 in one launch, 283 layer by layer; FP32 332, 220).
+bool long_and_sharp(const BodyP& b, const GridP& g)
+{
+    const double a = std::max(b.R, b.Rb), s = std::min(b.R, b.Rb);
+    // (the tips' radius of curvature s^2 / a below a scan window's half-width;
+    // the window's extents as the solid lies)
+    const double hx = std::hypot(b.R * b.ct, b.Rb * b.st), hy = std::hypot(b.R * b.st, b.Rb * b.ct);
+    const double w = 2.0 * (hx + g.layers) + 5.0, h = 2.0 * (hy + g.layers) + 5.0;
+    return b.shape == 1 && s * s < 2.0 * a && w * h > (double)FF_REGION * FF_REGION;
+}
 bool batch_fused(const lbrmt_batch* b)
 {
     if (b->fused_fit == 0) return false;
-    for (const lbrmt_ctx* c : b->m)
+    long long sharp = 0, all = 0;
+    for (const lbrmt_ctx* c : b->m) {
         if (c->nsolid == 0 || !fused_fit_ok(c->g)) return false;
-    return true;
+        const long long t = zone_tiles(c->body, c->g);
+        all += t;
+        if (long_and_sharp(c->body, c->g)) sharp += t;
+    }
+    return b->fused_fit == 1024 || 2 * sharp <= all;
 }
 
 // argument tables of phase p (p = n mod 6 for n >= 1; p = 6 for n = 0)

@@ -1,6 +1,7 @@
 """Batch members whose fits need wide scan windows, or fail for good: finished on
 the block's copy of the whole window, on windows the copy does not hold, with
-more targets in a layer than it has room for, beside members without any.
+more targets in a layer than it has room for, beside members without any; by
+default (long thin members layer by layer) and in one launch.
 Against each member alone with one launch per layer: the same bits, and as many
 fits that fail."""
 import pytest
@@ -29,11 +30,13 @@ BATCHES = {
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("mode", [-1, 1024])
 @pytest.mark.parametrize("name", BATCHES)
-def test_members_are_bitwise_the_per_layer_path(name, prec):
+def test_members_are_bitwise_the_per_layer_path(name, mode, prec):
     from paper_2402_12696_amd import Batch, Sim, lbrmt as B
     cfgs = BATCHES[name]
     b = Batch(cfgs, precision=prec, device="cuda:0")
+    b.set_option(B.LBRMT_OPT_FUSED_FIT, mode)
     b.init()
     b.step(20)
     for k, c in enumerate(cfgs):
