@@ -1,7 +1,7 @@
 // Weighted least-squares fits of the extrapolation zone (Sec. 3.2 step (ii))
 // on gfx950: the fit itself, for one target shared by eight lanes (values read
-// from the maps) or by two (values read from a block's copy in LDS), with the
-// same bits either way.  Included by the reference-map kernels only, and built
+// from the maps) or held by one (values read from a block's copy in LDS), with
+// the same bits either way.  Included by the reference-map kernels only, and built
 // without floating-point contraction like them.
 #pragma once
 

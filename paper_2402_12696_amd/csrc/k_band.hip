@@ -208,8 +208,6 @@ __device__ void block_box(int i0, int i1, int j0, int j1, int* out4)
     __syncthreads();
 }
 
-// reduce n partial boxes into one window slot (called by a whole block)
-
 // ---------------------------------------------------------------- window ring
 
 __global__ void k_win_reset(Win* win, int slot)
@@ -2029,11 +2027,11 @@ __device__ __forceinline__ double relabel_phi(const GridP& g, const BodyP& b, in
 // per node.  MODE 0 also relabels (Alg. 1): phi^{n+1} = phi0(xi^{n+1}) is
 // evaluated for every staged node from its tag and map, written for the
 // tile's own nodes (with the map cleared where none is held), and for the
-// window's nodes outside the interior by a strided pass (MODE 2: all of them); each block writes
-// the partial box of the new interior solid set it saw, which the next
-// lattice update (MODE 3: the last block) reduces into the next ring slot.  MODE 2 is MODE 0 without
-// the stresses (one solid of several: the forces are combined over all
-// solids afterwards).  MODE 3 is MODE 0 followed, for each of the tile's own
+// window's nodes outside the interior by a strided pass; each block writes the
+// partial box of the new interior solid set it saw, which the next lattice
+// update (MODE 3: the last block) reduces into the next ring slot.  MODE 2 is
+// the relabel alone, node by node (one solid of several: the forces are
+// combined over all solids afterwards).  MODE 3 is MODE 0 followed, for each of the tile's own
 // nodes, by its lattice Boltzmann update with the force just computed (the
 // window's nodes; the lattice update of every other node does not depend on
 // the solid's force of this step).
@@ -2046,11 +2044,8 @@ __device__ __forceinline__ void edges_body(GridP g, BodyP b, Win* win, int wvali
 {
     // the force pass ends the reference-map chain of a step: clear the layer
     // counters of the next step's distance transform
-    constexpr bool RELABEL = MODE == 0 || MODE == 2 || MODE == 3;
+    constexpr bool RELABEL = MODE != 1;
     if (RELABEL) clear_lcount(lcount);
-    __shared__ C sX[SY * SX], sY[SY * SX], sP[SY * SX];
-    __shared__ C ex[FTY][FTX + 1][3];
-    __shared__ C ey[FTY + 1][FTX][3];
     const Rect V = window_of(win, wvalid, g);
     const Rect WP = MODE == 3 ? window_of(win, lf.wprev, g) : Rect{0, -1, 0, -1, false};
     int bi0 = 0x3fffffff, bi1 = -0x3fffffff, bj0 = 0x3fffffff, bj1 = -0x3fffffff;
@@ -2095,6 +2090,9 @@ __device__ __forceinline__ void edges_body(GridP g, BodyP b, Win* win, int wvali
         block_box(ei0, ei1, ej0, ej1, boxpart + 4 * (gridDim.x + blockIdx.x));
         return;
     }
+    __shared__ C sX[SY * SX], sY[SY * SX], sP[SY * SX];
+    __shared__ C ex[FTY][FTX + 1][3];
+    __shared__ C ey[FTY + 1][FTX][3];
     Rect Rg;
     if (whole_grid) {
         Rg.i0 = 0; Rg.i1 = g.nx - 1; Rg.j0 = 0; Rg.j1 = g.ny - 1;

@@ -1,10 +1,10 @@
 // Host side of the gfx950 LBRMT library: the C ABI of include/lbrmt.h.
 //
-// One step (Alg. 1) is a fixed launch sequence.  The reference-map chain
-// (advect, 11 extrapolation layers, relabel, force) runs on an internal side
-// stream while the lattice Boltzmann update of every tile outside the band
-// region runs on the caller's stream; the band tiles are updated after the
-// chain has produced this step's force.  Buffer parities repeat every 6 steps
+// One step (Alg. 1) is a fixed launch sequence.  The reference-map chain (advect
+// with the layers, extrapolation, relabel and force with the lattice update of
+// the window's nodes) runs on an internal side stream while the lattice Boltzmann
+// update of every other node runs on the caller's; on small lattices the force
+// pass takes that along, on one stream.  Buffer parities repeat every 6 steps
 // (lattice / xi / force double buffers, 3-slot window ring), so 6 steps are
 // captured once into a hipGraph and replayed.
 #include <hip/hip_runtime.h>

@@ -46,8 +46,8 @@ constexpr int FF_LAYER_BATCH = 320;
 constexpr int FF_LAYER_MB = 224;
 // most targets that a whole solid's copy searches in wider scan windows
 constexpr int FF_WIDE = 512;
-// fused extrapolation: threads of a block (two halves of 128 targets a pass;
-// up to 256 registers a lane, where 1024 threads would leave 128 and spill)
+// fused extrapolation: threads of a block (four sets of 128 targets a pass; up
+// to 256 registers a lane, where 1024 threads would leave 128 and spill)
 constexpr int FF_THREADS = 512;
 constexpr int FF_BATCH_BLOCKS = 64;   // fused extrapolation of a batch: blocks per member
 // members of at most this many tiles in all: blocks of FF_THREADS threads in FP32
@@ -751,7 +751,7 @@ hipError_t launch_adjoint_loss(const GridP& g, const BodyP& b, const AdjSnap& s,
                                const AdjBufs& a, int which, const LossCoef& c, hipStream_t st);
 hipError_t launch_adjoint_init(const GridP& g, const BodyP& b, const AdjSnap& s,
                                const AdjBufs& a, double* u0bar, hipStream_t st);
-// dst[0] = x, dst[1] = y (device, stream-ordered)
+// a snapshot's pieces, windows, uniform force and wide-window flag in one launch
 hipError_t launch_snapshot(const SnapCopy& c, int pieces, hipStream_t st);
 
 // reductions (k_diag.hip); partial: scratch of diag_partial_doubles() doubles
