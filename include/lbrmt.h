@@ -429,7 +429,7 @@ int lbrmt_autotune_steps(lbrmt_ctx* ctx, int32_t steps, int32_t* best_fused, dou
  * Many independent simulations (members) of any sizes stepped together: each
  * kernel of the step is one launch over all members, so a step costs the same
  * 4 launches whatever the member count, and blocks of six steps replay one
- * HIP graph (24 members or 4 million nodes and more: as two groups of members
+ * HIP graph (48 members or 4 million nodes and more: as two groups of members
  * side by side).  Every member follows exactly the arithmetic of a single context
  * with the same description: results are bitwise identical to stepping each
  * member alone.  All members share the precision and the layer count; each

@@ -354,10 +354,11 @@ struct BatchTables {
 };
 // A batch of so many nodes or members runs its captured steps as two groups of
 // members (us/step on MI355X, one group -> two, FP32: 24 members of 96^2 ..
-// 768^2 206 -> 185, 64 of 64^2 110 -> 104, 256 of 64^2 305 -> 274, 8 of 1024^2
-// 195 -> 189; but 8 of 64^2 60 -> 71, 16 of 256^2 89 -> 92, 2 of 1024^2 90 -> 100)
+// 768^2 184 -> 177, 64 of 64^2 111 -> 97, 256 of 64^2 305 -> 272, 8 of 1024^2 218 ->
+// 218, FP64 378 -> 360; but 24 of 64^2 58 -> 67, 32 of 128^2 73 -> 75, 16 of 256^2
+// 72 -> 75, 2 of 1024^2 97 -> 110)
 constexpr long long BATCH_GROUP_NODES = 4000000;
-constexpr int BATCH_GROUP_MEMBERS = 24;
+constexpr int BATCH_GROUP_MEMBERS = 48;
 // blocks per member of the batched reference-map kernels (the distance
 // transform count is a multiple of NSUB and at most DT_BLOCKS, which the list
 // capacity assumes; relabel's partial boxes number BATCH_BAND_BLOCKS)
