@@ -1798,8 +1798,8 @@ __global__ __launch_bounds__(FF_THREADS) void kb_fit_mb(const FitArgs* __restric
     __shared__ FitLds<T, MB_FIT_LDS_NODES, FF_LAYER_MB> s;
     // row and block of it
     const int many = f.rows * f.blocks, id = blockIdx.x;
-    const int row = id < many ? id / f.blocks : f.rows + id - many;
-    const int b = id < many ? id % f.blocks : 0, nb = id < many ? f.blocks : 1;
+    const int nb = id < many ? f.blocks : f.few, at = id < many ? id : id - many;
+    const int row = at / nb + (id < many ? 0 : f.rows), b = at % nb;
     const FitArgs& a = args[ord[row]];
     const GridP& g = a.g;
     const Rect W = window_of(a.win, a.wcur, g);
@@ -2920,7 +2920,7 @@ hipError_t launch_batch_band(int precision, const BatchTables& t, int nsim, int 
     // solid of a context, which relabels and marks only
     const dim3 gb(band_blocks, nsim), gd(dt_blocks, nsim), gf(fit_blocks, nsim);
     const MbFit mf = mb ? mb->fit : MbFit{};
-    const int gm = mf.rows * mf.blocks + nsim - mf.rows;  // blocks of kb_fit_mb
+    const int gm = mf.rows * mf.blocks + (nsim - mf.rows) * mf.few;  // blocks of kb_fit_mb
     const long long* dstep = mb ? mb->dstep : nullptr;
     long long* dcur = mb ? mb->dcur : nullptr;
 #define ADB(T, LC, TH) kb_advect_dt<LC, TH, T><<<gd, 256, 0, st>>>(t.adv, t.ord, dstep, dcur)

@@ -366,9 +366,10 @@ static MbTabs mb_tabs(const lbrmt_ctx* c)
 // block's.  (MI355X: a block takes a tile in about 20 us, a small solid of a
 // suspension in about 45.)
 // The rows of large solids come first in the solids' order (mb_tables); the
-// others get one block each, as blocks without work still take a unit's LDS for
-// some us (60 discs of R 22 with 3 of R 38, FP32, us/step with 16 blocks to every
-// row 204, so 111).
+// others get one block each, or by tiles as many as the largest of them has, as
+// blocks without work still take a unit's LDS for some us (60 discs of R 22 with
+// 3 of R 38, FP32, us/step with 16 blocks to every row 204, so 111; 200 of R 3
+// with one of R 150, by tiles, FP64 529, 396).
 // side of the window of solid b however it is turned, and its tiles
 static long long zone_side(const BodyP& b, const GridP& g)
 {
@@ -388,17 +389,21 @@ static bool mb_large(const MbBody& m)
 }
 static MbFit mb_fit(const lbrmt_ctx* c)
 {
-    long long all = 0, most = 1;
+    long long all = 0, most = 1, few = 1;
     int large = 0;
     for (const MbBody& m : c->mbh) {
         const long long t = zone_tiles(m.b, m.g);
         all += t;
-        most = std::max(most, t);
-        large += mb_large(m) ? 1 : 0;
+        if (mb_large(m)) {
+            most = std::max(most, t);
+            large++;
+        } else {
+            few = std::max(few, t);
+        }
     }
     const bool tiles = all <= MB_FIT_TILES;
-    return MbFit{tiles ? 1 : 0, (int)std::min<long long>(most, FF_BLOCKS),
-                 tiles ? c->nsolid : large};
+    return MbFit{tiles ? 1 : 0, (int)std::min<long long>(most, FF_BLOCKS), large,
+                 tiles ? (int)few : 1};
 }
 
 // several solids, step n on stream st: the chain of every solid (relabel

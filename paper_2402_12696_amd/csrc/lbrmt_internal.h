@@ -495,10 +495,10 @@ struct MbMark {
     const long long* dcur;
 };
 // How several solids' layers are shared out: by tiles for every solid, or a
-// block per solid; the first rows of their order get blocks blocks, the others
-// one
+// block per solid; the first rows of their order get blocks blocks each, the
+// others few
 struct MbFit {
-    int tiles, blocks, rows;
+    int tiles, blocks, rows, few;
 };
 // a step's chain over several solids
 struct MbStep {

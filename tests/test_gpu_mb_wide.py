@@ -35,6 +35,10 @@ CASES = {
         dict(cx=455.0, cy=60.0, R=40.0, G=0.005, rho_s=1.0, shape="ellipse", b=1.2, theta=1.2),
         dict(cx=440.0, cy=180.0, R=38.0, G=0.005, rho_s=1.0),
         dict(cx=452.0, cy=330.0, R=90.0, G=0.005, rho_s=1.0, shape="ellipse", b=1.1, theta=1.5)]),
+    "by tiles, a large one among small": dict(nx=400, ny=300, solids=[
+        dict(cx=20.0 + 30.0 * k, cy=30.0, R=4.0, G=0.005, rho_s=1.0) for k in range(5)] + [
+        dict(cx=220.0, cy=170.0, R=80.0, G=0.005, rho_s=1.0),
+        dict(cx=90.0, cy=120.0, R=40.0, G=0.005, rho_s=1.0, shape="ellipse", b=1.0, theta=1.4)]),
     "beyond the copy": dict(nx=300, ny=260, solids=[
         dict(cx=150.0, cy=90.0, R=100.0, G=0.005, rho_s=1.0, shape="ellipse", b=1.2, theta=0.1),
         dict(cx=140.0, cy=190.0, R=90.0, G=0.005, rho_s=1.0, shape="ellipse", b=0.8, theta=0.9)]),
