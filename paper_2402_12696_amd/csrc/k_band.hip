@@ -1290,9 +1290,11 @@ __device__ __forceinline__ void fit_region(FitLds<T, NODES, LN, REC>& s, const G
         atomicMin(&s.cut, l);
     };
     // layer l's of them, the rest of the layer being done (as fit_target, the
-    // nodes read from the copy); nobody lists meanwhile
+    // nodes read from the copy); nobody lists meanwhile.  Not those of a layer
+    // that is cut (its targets were listed with nodes that have failed since,
+    // or not all of them were): the caller's
     auto search = [&](int l) {
-        const int nw = min(s.nwide, FF_WIDE), sub = tid % FIT_LANES;
+        const int nw = s.cut <= l ? 0 : min(s.nwide, FF_WIDE), sub = tid % FIT_LANES;
 #pragma unroll 1
         for (int u = tid / FIT_LANES; u < nw; u += NT / FIT_LANES) {
             const int q = s.wide[u];

@@ -34,6 +34,8 @@ def _same(got, ref):
     _thin(517, 413, 180.0, b=2.0),
     _thin(128, 128, 30.0, r_max=2),
     _thin(160, 90, 40.0, periodic_x=True),
+    _thin(150, 131, 30.0, b=None, det_rel=0.33),
+    _thin(139, 133, 30.0, b=None, det_rel=0.3, r_max=2),
 ], ids=lambda c: f"{c['nx']}x{c['ny']}")
 def test_shared_layers_match_launches_per_layer(cfg):
     _same(_gradient(cfg, 512), _gradient(cfg, 0))

@@ -25,6 +25,11 @@ BATCHES = {
     "beyond the copy": [_cfg(260, 200, 90.0, 1.2), _cfg(200, 64, 90.0, 1.0, 0.05),
                         _cfg(64, 64, 12.0)],
     "fits that fail": [_cfg(96, 80, 30.0, 0.9, r_max=2), _cfg(70, 64, 20.0, 0.45, r_max=3)],
+    "half of the fits wide": [_cfg(96, 80, 20.0, det_rel=0.33), _cfg(128, 128, 24.0, det_rel=0.25)],
+    "all wide: more than the list holds": [_cfg(96, 80, 20.0, det_rel=0.6),
+                                           _cfg(200, 150, 55.0, det_rel=0.6)],
+    "half of the fits fail": [_cfg(96, 80, 20.0, det_rel=0.3, r_max=2),
+                              _cfg(200, 150, 55.0, det_rel=0.3, r_max=2)],
     "five layers": [_cfg(96, 80, 30.0, 0.9, layers=5), _cfg(64, 64, 12.0, layers=5)],
 }
 

@@ -35,6 +35,9 @@ def _run(cfg, prec, opt):
     ("seven layers", _long(180, 64, 70.0, 1.0, 0.1, layers=7), 512),
     ("a few layers at a time", _long(1500, 64, 700.0, 1.5), 1),
     ("a few layers, wide windows", _long(1400, 200, 660.0, 1.0, 0.1), 512),
+    ("half of a disc's fits wide", _long(128, 120, 40.0, 40.0, det_rel=0.33), 512),
+    ("all of a disc's fits wide", _long(128, 120, 40.0, 40.0, det_rel=0.6), 256),
+    ("half of a disc's fits fail", _long(128, 120, 40.0, 40.0, det_rel=0.3, r_max=2), 512),
     ("a layer by shares (FP32: 11554 entries)", _long(6100, 64, 2960.0, 1.5), 1),
 ])
 def test_left_tiles_are_bitwise_the_per_layer_path(name, cfg, opt, prec):

@@ -49,6 +49,15 @@ CASES = {
         dict(cx=35.0, cy=30.0 + 50.0 * k, R=27.5, G=0.005, rho_s=1.0, shape="ellipse", b=1.1,
              theta=0.05) for k in range(2)]),
     "more layers than one launch": _many(5, layers=13),
+    # (a disc's fits at half-width 2 have det / (sum w)^3 between 0.2 and 0.5)
+    "few, some fits wide": _many(5, b=22.0, det_rel=0.25),
+    "few, half of the fits wide": _many(5, b=22.0, det_rel=0.33),
+    "many, half of the fits wide": _many(60, b=22.0, det_rel=0.33),
+    "few, all wide: more than the list holds": _many(5, b=22.0, det_rel=0.6),
+    "many, all wide: more than the list holds": _many(60, b=22.0, det_rel=0.6),
+    "few, half of the fits fail": _many(5, b=22.0, det_rel=0.3, r_max=2),
+    "many, half of the fits fail": _many(60, b=22.0, det_rel=0.3, r_max=2),
+    "few, thirteen layers, half fail": _many(4, R=15.0, b=15.0, layers=13, det_rel=0.3, r_max=2),
     "twenty layers, round": _many(5, R=12.0, b=12.0, layers=20),
     "thirteen layers, r_max 2": _many(5, R=15.0, layers=13, r_max=2),
 }
